@@ -64,6 +64,12 @@ int auto_window(uint32_t max_len) {
     return 0;
 }
 
+// Band kernel: the first window tried for a batch's longest sequence.  A
+// window of W diagonals is exact for about W score steps, and a pair that
+// needs more is aligned again in the next window, so the rule aims at the
+// window most pairs of that length stay within at a few percent of edits.
+int band_window(uint32_t max_len) { return max_len <= 400 ? 32 : max_len <= 1200 ? 64 : 128; }
+
 template <class F>
 int capture_graph(hipStream_t s, F&& body, hipGraph_t* graph, hipGraphExec_t* exec) {
     *graph = nullptr;
@@ -560,6 +566,35 @@ int engine_align_device(Engine* e, const BatchIO& io, hipStream_t user_stream,
             sp.lds_per_block = lane_lds_bytes(pen, lcap, cigar, lbt);
         }
     }
+    // Otherwise the band kernel, when it is built for the penalties and no
+    // short-kernel shape was asked for.  Ends-free: the window holds the free
+    // start and end diagonals and leaves room for a few edits beside them.
+    bool band = false;
+    BandPlan bp;
+    if (use_short && !lane && !e->opt.window && !e->opt.lanes_per_pair) {
+        int bw = band_window(max_len);
+        if (!global) {
+            const uint32_t reach = std::max(
+                std::max(std::min<uint32_t>((uint32_t)e->ends.pb, st.max_p),
+                         std::min<uint32_t>((uint32_t)e->ends.tb, st.max_t)),
+                std::max(std::min<uint32_t>((uint32_t)e->ends.pe, st.max_p),
+                         std::min<uint32_t>((uint32_t)e->ends.te, st.max_t)));
+            while (bw < 128 && (uint32_t)bw < 2 * reach + 8 + max_len / 32) bw *= 2;
+            if ((uint32_t)bw < 2 * reach + 8 + max_len / 32) bw = 0;
+        }
+        if (bw && band_plan(pen, cigar, bw, e->opt.step_cap, max_len, e->opt.block_threads, !global, &bp)) {
+            band = true;
+            window = bp.window;
+            lanes = bp.lanes;
+            sp = ShortPlan{};
+            sp.window = bp.window;
+            sp.lanes = bp.lanes;
+            sp.cap = bp.cap;
+            sp.slot_cap = bp.slot_cap;
+            sp.block_threads = bp.block_threads;
+            sp.lds_per_block = bp.lds_per_block;
+        }
+    }
     const bool persistent = use_short && schedule != WFA_SCHED_PLAIN;
     const bool bucket = persistent && e->opt.bucket >= 0;
     // graphs: by default for the persistent schedule; the plain one only on request
@@ -610,14 +645,16 @@ int engine_align_device(Engine* e, const BatchIO& io, hipStream_t user_stream,
         // pairs per workgroup: lane groups of the short kernel, or one per lane
         const int gpb = lane ? sp.block_threads : short_groups_per_block(lanes, sp.block_threads);
         if (persistent) {
-            int bpc = lane ? lane_max_blocks_per_cu(pen, sp.cap, cigar, sp.block_threads)
-                           : short_max_blocks_per_cu(window, lanes, cigar, sp.block_threads,
+            int bpc = lane   ? lane_max_blocks_per_cu(pen, sp.cap, cigar, sp.block_threads)
+                      : band ? band_max_blocks_per_cu(pen, bp, cigar, !global)
+                             : short_max_blocks_per_cu(window, lanes, cigar, sp.block_threads,
                                                      sp.lds_per_block, sp.row_bytes);
             if (bpc < 1) bpc = 1;
             grid = e->num_cus * bpc;
             if (std::getenv("WFA_DEBUG"))
                 std::fprintf(stderr, "libwfa plan: %s, %d threads per block, %d blocks per CU, "
-                                     "%d B LDS per block\n", lane ? "lane kernel" : "short kernel",
+                                     "%d B LDS per block\n",
+                             lane ? "lane kernel" : band ? "band kernel" : "short kernel",
                              sp.block_threads, bpc, sp.lds_per_block);
             const size_t needed = (N + gpb - 1) / gpb;
             if ((size_t)grid > needed) grid = (int)needed;
@@ -633,8 +670,28 @@ int engine_align_device(Engine* e, const BatchIO& io, hipStream_t user_stream,
     if (lane && cigar)  // one history region per wavefront of the launch
         RCCHK(ws.ensure(ws.lane_hist, (size_t)grid * (sp.block_threads / 64) *
                                           lane_hist_bytes_per_wave(pen, sp.cap, true, sp.slot_cap)));
-    if (lane && persistent) RCCHK(ws.ensure(ws.lane_queues, LANE_QUEUES * 32 * 4));
+    if ((lane || band) && persistent) RCCHK(ws.ensure(ws.lane_queues, LANE_QUEUES * 32 * 4));
     flags = ws.flags.as<DevFlags>();
+
+    // the band kernel's arguments but for its queue, run slots and hand-over list
+    auto band_args = [&](const BandPlan& p) -> BandArgs {
+        BandArgs a{};
+        a.pairs = d.pairs;
+        a.pw = d.pw;
+        a.tw = d.tw;
+        a.npairs = (uint32_t)N;
+        a.ends = e->ends;
+        a.g = pen.g;
+        a.cap = p.cap;
+        a.seq_words = p.seq_words;
+        a.hist_words = p.hist_words;
+        a.group_bytes = p.group_bytes;
+        a.slot_cap = p.slot_cap;
+        a.scores = d.scores;
+        a.nruns = ws.nruns.as<uint32_t>();
+        a.run_src = ws.run_src.as<uint64_t>();
+        return a;
+    };
 
     // ---- device phase (graph-capturable) ----------------------------------
     // Three phases; in graph mode the first and last are captured graphs and
@@ -650,7 +707,7 @@ int engine_align_device(Engine* e, const BatchIO& io, hipStream_t user_stream,
         fill.add((uint32_t*)flags, 2, ~0u);
         fill.add((uint32_t*)flags + 2, sizeof(DevFlags) / 4 - 2, 0u);
         fill.add(ws.nruns.as<uint32_t>(), N, 0u);
-        if (lane && persistent) fill.add(ws.lane_queues.as<uint32_t>(), LANE_QUEUES * 32, 0u);
+        if ((lane || band) && persistent) fill.add(ws.lane_queues.as<uint32_t>(), LANE_QUEUES * 32, 0u);
         if (use_short && bucket) fill.add(hist, 2 * BUCKET_KEYS, 0u);
         HIPCHK(launch_fill_multi(fill, q));
         if (ascii) {
@@ -693,6 +750,16 @@ int engine_align_device(Engine* e, const BatchIO& io, hipStream_t user_stream,
             a.ovf_list = ws.ovf_list.as<uint32_t>();
             a.ovf_count = &flags->ovf_count;
             HIPCHK(launch_lane(a, sp.cap, cigar, persistent, sp.block_threads, grid, q));
+        } else if (band) {
+            BandArgs a = band_args(bp);
+            a.order = bucket ? ws.order.as<uint32_t>() : nullptr;
+            a.num = (uint32_t)N;
+            a.queue = ws.lane_queues.as<uint32_t>();
+            a.persistent = persistent ? 1 : 0;
+            a.slots = ws.slots.as<uint32_t>();
+            a.ovf_list = ws.ovf_list.as<uint32_t>();
+            a.ovf_count = &flags->ovf_count;
+            HIPCHK(launch_band(a, pen, bp, cigar, grid, q));
         } else if (use_short) {
             ShortArgs a{};
             a.pairs = d.pairs;
@@ -758,7 +825,7 @@ int engine_align_device(Engine* e, const BatchIO& io, hipStream_t user_stream,
                               // the packing's word counts (packed input: none)
                               ascii ? (int)st.max_p : 0, ascii ? (int)st.max_t : 0, grid,
                               (int)(bucket ? 1 : 0) | (stride_p ? 4 : 0) | (stride_t ? 8 : 0) |
-                                  (persistent ? 16 : 0) | (sp.block_threads << 8),
+                                  (persistent ? 16 : 0) | (band ? 32 : 0) | (sp.block_threads << 8),
                               e->ends.pb, e->ends.pe, e->ends.tb, e->ends.te, queue_chunk,
                               sp.slot_cap};
         for (int i = 0; i < 18; i++) key.ints[i] = ints[i];
@@ -849,15 +916,64 @@ int engine_align_device(Engine* e, const BatchIO& io, hipStream_t user_stream,
         Buf* lists[2] = {&ws.ovf_list, &ws.ovf_list2};
         int in_list = 0;
         uint64_t slots2_used = 0;  // words of slots2 taken by earlier passes
+        bool banded = false;
+        // after a pass's launch: what it handed over, and to which list
+        auto pass_done = [&](uint64_t slot_words, int w2) -> int {
+            HIPCHK(hipEventRecord(e->ev[11], s));
+            uint32_t n_out = 0;
+            HIPCHK(hipMemcpyAsync(&n_out, &flags->ovf_count2, 4, hipMemcpyDeviceToHost, s));
+            HIPCHK(hipStreamSynchronize(s));
+            ms_cascade += ev_ms(e->ev[10], e->ev[11]);
+            if (cigar) slots2_used += slot_words;
+            ovf_final = n_out;
+            in_list = 1 - in_list;
+            ovf_buf = lists[in_list];
+            window2 = w2;
+            requeued += n_out;
+            return WFA_OK;
+        };
         // the cascade's windows: 64, 128, 256 above the first window
         for (int w2 = 64; w2 <= wmax && ovf_final > 0; w2 *= 2) {
             if (w2 <= window) continue;
+            const uint32_t n2 = ovf_final;
+            BandPlan bp2;
+            const bool shaped = e->opt.window || e->opt.lanes_per_pair;
+            if (!shaped && w2 <= 128 &&
+                band_plan(pen, cigar, w2, 0, max_len, 0, !global, &bp2)) {
+                if (cigar)
+                    RCCHK(ws.grow_keep(ws.slots2, (slots2_used + (uint64_t)n2 * bp2.slot_cap) * 4,
+                                       slots2_used * 4, s));
+                int bpc2 = band_max_blocks_per_cu(pen, bp2, cigar, !global);
+                if (bpc2 < 1) bpc2 = 1;
+                const int gpb2 = short_groups_per_block(bp2.lanes, bp2.block_threads);
+                const int grid2 = (int)std::min<size_t>((size_t)e->num_cus * bpc2, (n2 + gpb2 - 1) / gpb2);
+                RCCHK(ws.ensure(ws.lane_queues, LANE_QUEUES * 32 * 4));
+                BandArgs a = band_args(bp2);
+                a.order = lists[in_list]->as<uint32_t>();
+                a.num = n2;
+                a.queue = ws.lane_queues.as<uint32_t>();
+                a.persistent = 1;
+                a.run_src_add = SLOTS2_BIT + slots2_used;
+                a.slots = cigar ? ws.slots2.as<uint32_t>() + slots2_used : nullptr;
+                a.ovf_list = lists[1 - in_list]->as<uint32_t>();
+                a.ovf_count = &flags->ovf_count2;
+                FillOps fill{};
+                fill.add(&flags->ovf_count2, 1, 0u);
+                fill.add(a.queue, LANE_QUEUES * 32, 0u);
+                HIPCHK(launch_fill_multi(fill, s));
+                HIPCHK(hipEventRecord(e->ev[10], s));
+                HIPCHK(launch_band(a, pen, bp2, cigar, grid2, s));
+                RCCHK(pass_done((uint64_t)n2 * bp2.slot_cap, w2));
+                banded = true;
+                continue;
+            }
+            // the band of 128 holds as many steps as a window of 256
+            if (w2 > 128 && (banded || band)) break;
             const int l2 = default_lanes(w2);
             ShortPlan sp2;
             if (!short_shape_supported(w2, l2) ||
                 short_plan(e, pen, cigar, w2, l2, default_cap(pen, w2), max_len, &sp2) != WFA_OK)
                 break;
-            const uint32_t n2 = ovf_final;
             if (cigar)
                 RCCHK(ws.grow_keep(ws.slots2, (slots2_used + (uint64_t)n2 * sp2.slot_cap) * 4,
                                    slots2_used * 4, s));
@@ -898,17 +1014,7 @@ int engine_align_device(Engine* e, const BatchIO& io, hipStream_t user_stream,
             HIPCHK(launch_fill_u32(&flags->ovf_count2, 0u, 2, s));  // ovf_count2, queue2
             HIPCHK(hipEventRecord(e->ev[10], s));
             HIPCHK(launch_short(a, w2, l2, cigar, true, sp2.block_threads, grid2, s));
-            HIPCHK(hipEventRecord(e->ev[11], s));
-            uint32_t n_out = 0;
-            HIPCHK(hipMemcpyAsync(&n_out, &flags->ovf_count2, 4, hipMemcpyDeviceToHost, s));
-            HIPCHK(hipStreamSynchronize(s));
-            ms_cascade += ev_ms(e->ev[10], e->ev[11]);
-            if (cigar) slots2_used += (uint64_t)n2 * sp2.slot_cap;
-            ovf_final = n_out;
-            in_list = 1 - in_list;
-            ovf_buf = lists[in_list];
-            window2 = w2;
-            requeued += n_out;
+            RCCHK(pass_done((uint64_t)n2 * sp2.slot_cap, w2));
         }
     }
 

@@ -110,6 +110,38 @@ struct LaneArgs {
     uint32_t* ovf_count;
 };
 
+// Arguments of the band kernel (all device pointers).
+struct BandArgs {
+    const PairDesc* pairs;
+    const uint64_t* pw;         // packed pattern words
+    const uint64_t* tw;         // packed text words
+    const uint32_t* order;      // queue position -> pair index (NULL: identity)
+    uint32_t num;               // pairs in the queue
+    uint32_t npairs;            // pairs of the batch (bound of the indices in `order`)
+    Ends ends;                  // free ends (all zero: global alignment)
+    uint32_t* queue;            // persistent: LANE_QUEUES claim counters, 32 words apart
+    int persistent;
+    int g;                      // score units per step
+    int cap;                    // last step a pair may reach
+    int seq_words;              // 64-bit words of LDS per sequence
+    int hist_words;             // CIGAR: dwords of records per group
+    int group_bytes;            // LDS bytes per lane group
+    int slot_cap;               // most runs a pair may have in the kernel
+    int32_t* scores;            // [pairs]
+    uint32_t* nruns;            // [pairs] runs written
+    uint64_t* run_src;          // [pairs] where the reversed runs live
+    uint64_t run_src_add;       // added to run_src (a cascade pass: SLOTS2_BIT + its offset in slots2)
+    uint32_t* slots;            // [pairs * slot_cap] reversed runs, packed per wave
+    uint32_t* ovf_list;         // pairs the kernel could not hold
+    uint32_t* ovf_count;
+};
+
+// Launch shape of the band kernel.
+struct BandPlan {
+    int window = 0, lanes = 0, cap = 0, seq_words = 0, hist_words = 0, group_bytes = 0;
+    int slot_cap = 0, block_threads = 256, lds_per_block = 0;
+};
+
 // What the general kernel's forward pass hands to its CIGAR walk, per job.
 struct GenJobState {
     long long bump;     // end of the history rows (or checkpoints) in the slice
@@ -213,7 +245,17 @@ int short_groups_per_block(int lanes, int block_threads);
 int short_max_blocks_per_cu(int window, int lanes, bool cigar, int block_threads,
                             int lds_per_block, int row_bytes);
 
-// Claim counters of the persistent one-lane-per-pair kernel (each on its own
+// Band kernel: built for some scaled penalties and windows of 32, 64 and 128
+// diagonals.  band_plan fills the launch shape (step_cap 0: every step the
+// window is exact for); false if the kernel does not hold the batch.
+bool band_supported(const Pen& pen, int window);
+bool band_plan(const Pen& pen, bool cigar, int window, int step_cap, uint32_t max_len,
+               int block_threads, bool ends, BandPlan* bp);
+int band_max_blocks_per_cu(const Pen& pen, const BandPlan& bp, bool cigar, bool ends);
+hipError_t launch_band(const BandArgs& a, const Pen& pen, const BandPlan& bp, bool cigar, int grid,
+                       hipStream_t s);
+
+// Claim counters of the persistent one-lane-per-pair and band kernels (each on its own
 // 128-byte line: LANE_QUEUES * 32 words, zeroed before a launch).
 constexpr int LANE_QUEUES = 64;
 

@@ -1,0 +1,289 @@
+// Wavefront rows in registers, shared by the band kernel (k_band.hip) and the
+// front kernel (k_front.hip).
+//
+// A lane owns C neighbouring diagonals; a row of offsets is C / 2 registers of
+// two 16-bit offsets each, so the recurrences run two cells per instruction
+// (v_pk_max_i16 and friends) and the M, I and D rows a step reads back live in
+// registers for compile-time scaled penalties (X, OE, E).  Neighbouring lanes
+// exchange one column per step with DPP moves.
+//
+// Offsets are stored shifted left by SH (0 or 1).  With SH = 1 an offset is
+// twice the base position, i.e. the bit position in the 2-bit sequence: the
+// funnel shift of a 16-base window takes it as it stands.  SH = 1 holds
+// sequences up to 16383 bases, SH = 0 up to 32766.  NULL is any negative
+// value: NUL16P when stored by the extension, drifting up by 1 << SH per step
+// along a chain of I or D cells, so a kernel stops before 16384 >> SH steps.
+//
+// Candidates past the matrix (offset above L = min(m, n + k) on diagonal k) are
+// dropped from M after the maximum and stay in the I and D rows.  That changes
+// no result of an exact alignment: an I candidate past the last text column
+// has passed, on a lower diagonal and at a lower score, an M cell on that
+// column, from which the remaining deletions cost less than any way on from
+// this diagonal; D past the last pattern row and a mismatch past either are
+// the same argument.  So the cells such a candidate hides lie on no optimal
+// alignment, and every cell on one keeps its offset and its tie-break.
+// (The WF-adaptive reduction measures cells off the optimal paths too and
+// keeps to the general kernel.)
+#pragma once
+#include <hip/hip_runtime.h>
+#include <stdint.h>
+
+namespace wfa {
+namespace rows {
+
+constexpr uint32_t NUL16P = 0xC000C000u;  // two NULL offsets (-16384)
+enum { EV_X = 0, EV_I = 1, EV_D = 2 };    // walk events: len << 2 | kind
+
+typedef short s16x2 __attribute__((ext_vector_type(2)));
+typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
+template <class T>
+using lds_p = __attribute__((address_space(3))) T*;
+
+__device__ __forceinline__ s16x2 as_s(uint32_t a) { return __builtin_bit_cast(s16x2, a); }
+__device__ __forceinline__ u16x2 as_u(uint32_t a) { return __builtin_bit_cast(u16x2, a); }
+__device__ __forceinline__ uint32_t bits(s16x2 a) { return __builtin_bit_cast(uint32_t, a); }
+__device__ __forceinline__ uint32_t bits(u16x2 a) { return __builtin_bit_cast(uint32_t, a); }
+__device__ __forceinline__ uint32_t pk_max(uint32_t a, uint32_t b) {
+    return bits(__builtin_elementwise_max(as_s(a), as_s(b)));
+}
+__device__ __forceinline__ uint32_t pk_add(uint32_t a, uint32_t b) { return bits(as_u(a) + as_u(b)); }
+__device__ __forceinline__ uint32_t pk_sub(uint32_t a, uint32_t b) { return bits(as_u(a) - as_u(b)); }
+// The next three are written as instructions: from vector code the compiler
+// takes the halves apart again (a compare, a select and a permute for each).
+__device__ __forceinline__ uint32_t pk_minu(uint32_t a, uint32_t b) {
+    uint32_t r;
+    asm("v_pk_min_u16 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
+    return r;
+}
+// 0xffff in each half whose sign bit is set
+__device__ __forceinline__ uint32_t pk_sign(uint32_t a) {
+    uint32_t r;
+    asm("v_pk_ashrrev_i16 %0, 15, %1 op_sel_hi:[0,1]" : "=v"(r) : "v"(a));
+    return r;
+}
+// 1 in each half where a != b
+__device__ __forceinline__ uint32_t pk_ne(uint32_t a, uint32_t b) {
+    uint32_t r;
+    asm("v_pk_min_u16 %0, %1, 1 op_sel_hi:[1,0]" : "=v"(r) : "v"(a ^ b));
+    return r;
+}
+// a wave-uniform mask of the lanes where c holds
+__device__ __forceinline__ uint64_t lanes_where(bool c) { return __builtin_amdgcn_ballot_w64(c); }
+__device__ __forceinline__ uint32_t pk_pair(int lo, int hi) {
+    return (uint32_t)(lo & 0xffff) | ((uint32_t)hi << 16);
+}
+
+// the value of the lane before / after (whole wavefront; the end lane keeps `end`)
+__device__ __forceinline__ uint32_t wave_prev(uint32_t end, uint32_t x) {
+    return (uint32_t)__builtin_amdgcn_update_dpp((int)end, (int)x, 0x138, 0xF, 0xF, false);
+}
+__device__ __forceinline__ uint32_t wave_next(uint32_t end, uint32_t x) {
+    return (uint32_t)__builtin_amdgcn_update_dpp((int)end, (int)x, 0x130, 0xF, 0xF, false);
+}
+// the same within groups of G lanes (`first` / `last`: this lane is at the
+// group's end); the group's end lane reads NULL
+template <int G>
+__device__ __forceinline__ uint32_t group_prev(uint32_t x, bool first) {
+    if constexpr (G == 64) {
+        return wave_prev(NUL16P, x);
+    } else if constexpr (G == 16) {
+        return (uint32_t)__builtin_amdgcn_update_dpp((int)NUL16P, (int)x, 0x111, 0xF, 0xF, false);
+    } else if constexpr (G < 16) {
+        const uint32_t y = (uint32_t)__builtin_amdgcn_update_dpp((int)NUL16P, (int)x, 0x111, 0xF, 0xF, false);
+        return first ? NUL16P : y;
+    } else {
+        const uint32_t y = wave_prev(NUL16P, x);
+        return first ? NUL16P : y;
+    }
+}
+template <int G>
+__device__ __forceinline__ uint32_t group_next(uint32_t x, bool last) {
+    if constexpr (G == 64) {
+        return wave_next(NUL16P, x);
+    } else if constexpr (G == 16) {
+        return (uint32_t)__builtin_amdgcn_update_dpp((int)NUL16P, (int)x, 0x101, 0xF, 0xF, false);
+    } else if constexpr (G < 16) {
+        const uint32_t y = (uint32_t)__builtin_amdgcn_update_dpp((int)NUL16P, (int)x, 0x101, 0xF, 0xF, false);
+        return last ? NUL16P : y;
+    } else {
+        const uint32_t y = wave_next(NUL16P, x);
+        return last ? NUL16P : y;
+    }
+}
+
+// The rows of one lane.  M[j], I[j], D[j] hold step s - 1 - j.
+template <int X, int OE, int E, int C, int SH, bool CIGAR>
+struct Rows {
+    static constexpr int P = C / 2;
+    static constexpr int RM = X > OE ? X : OE;
+    static constexpr uint32_t ONE = SH ? 0x00020002u : 0x00010001u;
+    uint32_t M[RM][P], I[E][P], D[E][P];
+    uint32_t acc[P];  // decision records of up to four steps
+
+    __device__ __forceinline__ void clear() {
+#pragma unroll
+        for (int p = 0; p < P; p++) {
+#pragma unroll
+            for (int j = 0; j < RM; j++) M[j][p] = NUL16P;
+#pragma unroll
+            for (int j = 0; j < E; j++) I[j][p] = D[j][p] = NUL16P;
+            acc[p] = 0;
+        }
+    }
+    // what a step hands to the next diagonal up (the best source of an
+    // insertion) and down (of a deletion)
+    __device__ __forceinline__ void sources(uint32_t (&a)[P], uint32_t (&b)[P]) const {
+#pragma unroll
+        for (int p = 0; p < P; p++) {
+            a[p] = pk_max(M[OE - 1][p], I[E - 1][p]);
+            b[p] = pk_max(M[OE - 1][p], D[E - 1][p]);
+        }
+    }
+    // The cells of a step before extension: m (M), i, d, from sources a, b and
+    // the neighbour lanes' columns (ap: the last register of a one lane down,
+    // bn: the first of b one lane up).  CIGAR: four record bits per cell are
+    // shifted into acc: M is not a mismatch / not the end of an insertion
+    // (ties: mismatch, then insertion, then deletion), the insertion into the
+    // next diagonal up extends one / the deletion into the next one down does
+    // (ties: open).  The two gap bits stand at their source's diagonal.  acc
+    // holds four steps; `fresh` starts the next four.
+    __device__ __forceinline__ void cells(const uint32_t (&a)[P], const uint32_t (&b)[P], uint32_t ap,
+                                          uint32_t bn, uint32_t (&m)[P], uint32_t (&i)[P],
+                                          uint32_t (&d)[P], bool fresh) {
+#pragma unroll
+        for (int p = 0; p < P; p++) {
+            i[p] = pk_add(__builtin_amdgcn_alignbit(a[p], p ? a[p - 1] : ap, 16), ONE);
+            d[p] = __builtin_amdgcn_alignbit(p < P - 1 ? b[p + 1] : bn, b[p], 16);
+            const uint32_t x = pk_add(M[X - 1][p], ONE);
+            m[p] = pk_max(pk_max(x, i[p]), d[p]);
+            if constexpr (CIGAR) {
+                const uint32_t nx = pk_ne(m[p], x), ni = pk_ne(m[p], i[p]);
+                const uint32_t ai = pk_ne(a[p], M[OE - 1][p]), ad = pk_ne(b[p], M[OE - 1][p]);
+                acc[p] = (fresh ? 0u : acc[p] << 4) | nx | (ni << 1) | (ai << 2) | (ad << 3);
+            }
+        }
+    }
+    __device__ __forceinline__ void push(const uint32_t (&m)[P], const uint32_t (&i)[P],
+                                         const uint32_t (&d)[P]) {
+#pragma unroll
+        for (int p = 0; p < P; p++) {
+#pragma unroll
+            for (int j = RM - 1; j > 0; j--) M[j][p] = M[j - 1][p];
+#pragma unroll
+            for (int j = E - 1; j > 0; j--) {
+                I[j][p] = I[j - 1][p];
+                D[j][p] = D[j - 1][p];
+            }
+            M[0][p] = m[p];
+            I[0][p] = i[p];
+            D[0][p] = d[p];
+        }
+    }
+};
+
+// Where a lane's cells sit: packed limits (L << SH; -1 for a diagonal outside
+// the matrix) and, for cells with no offset, a packed offset inside the text
+// whose compares read staged bases; k2: twice each diagonal.
+template <int C>
+struct Place {
+    static constexpr int P = C / 2;
+    uint32_t lim[P], safe[P];
+    int k2[C];
+    template <int SH>
+    __device__ __forceinline__ void set(int n, int m, int k0) {
+#pragma unroll
+        for (int c = 0; c < C; c++) {
+            k2[c] = 2 * (k0 + c);
+            // four registers, not one and an add per cell and step
+            asm volatile("" : "+v"(k2[c]));
+        }
+#pragma unroll
+        for (int p = 0; p < P; p++) {
+            int l[2], z[2];
+#pragma unroll
+            for (int u = 0; u < 2; u++) {
+                const int k = k0 + 2 * p + u;
+                l[u] = (k < -n || k > m) ? -1 : min(m, n + k) << SH;
+                z[u] = min(max(k, 0), m) << SH;
+            }
+            lim[p] = pk_pair(l[0], l[1]);
+            safe[p] = pk_pair(z[0], z[1]);
+        }
+    }
+};
+
+// 16 bases from bit position `b` (twice the base) of a sequence whose dwords
+// start at LDS byte `base`; q = b >> 5
+__device__ __forceinline__ uint32_t win16q(uint32_t base, int q, uint32_t b) {
+    asm("" : "+v"(q));  // keeps q << 2 and the base in one instruction
+    lds_p<const uint32_t> w = (lds_p<const uint32_t>)(uintptr_t)(base + ((uint32_t)q << 2));
+    return __builtin_amdgcn_alignbit(w[1], w[0], b);
+}
+__device__ __forceinline__ uint32_t win16(uint32_t base, int b) { return win16q(base, b >> 5, (uint32_t)b); }
+
+// Extend the cells m of one step along matches (sequences in LDS at byte
+// addresses tb, pb) and drop those past the matrix.  Sixteen bases first;
+// a wavefront goes on only while one of its lanes still matches.
+template <int C, int SH>
+__device__ __forceinline__ void extend(uint32_t (&m)[C / 2], const Place<C>& pl, uint32_t tb,
+                                       uint32_t pb) {
+    constexpr int P = C / 2;
+    uint32_t bad[P], hv[P], rm[P], x[C], r[C];
+#pragma unroll
+    for (int p = 0; p < P; p++) {
+        const uint32_t u = pk_sub(pl.lim[p], m[p]);
+        bad[p] = pk_sign(m[p] | u);
+        hv[p] = (pl.safe[p] & bad[p]) | (m[p] & ~bad[p]);
+        rm[p] = u & ~bad[p];  // what is left before the matrix ends
+    }
+    // bit position of column c in the text, bits left
+    auto pos = [&](int c) -> uint32_t {
+        return ((c & 1) ? hv[c / 2] >> 16 : hv[c / 2] & 0xffffu) << (1 - SH);
+    };
+    auto left = [&](int c) -> uint32_t {
+        return ((c & 1) ? rm[c / 2] >> 16 : rm[c / 2] & 0xffffu) << (1 - SH);
+    };
+    uint32_t lo = ~0u;
+#pragma unroll
+    for (int c = 0; c < C; c++) {
+        const int v = (int)pos(c) - pl.k2[c];
+        // the dword of the position straight from the packed offsets
+        const uint32_t q = (c & 1) ? hv[c / 2] >> (20 + SH)
+                                   : __builtin_amdgcn_ubfe(hv[c / 2], 4 + SH, 12 - SH);
+        x[c] = win16q(tb, (int)q, pos(c)) ^ win16(pb, v);
+        uint32_t z;
+        asm("v_ffbl_b32 %0, %1" : "=v"(z) : "v"(x[c]));  // ~0 for a zero word
+        r[c] = min(z, left(c));  // bits; an odd one rounds down below
+        lo = min(lo, x[c]);
+    }
+    if (lanes_where(lo == 0)) {
+#pragma unroll
+        for (int c = 0; c < C; c++) {
+            if (x[c] == 0 && left(c) > 32) {
+                const int h = (int)pos(c), v = h - pl.k2[c];
+                uint32_t done = 32, z;
+                do {
+                    const uint32_t y = win16(tb, h + (int)done) ^ win16(pb, v + (int)done);
+                    asm("v_ffbl_b32 %0, %1" : "=v"(z) : "v"(y));
+                    done += min(z, 32u);
+                } while (z >= 32 && done < left(c));
+                r[c] = min(done, left(c));
+            }
+        }
+    }
+#pragma unroll
+    for (int p = 0; p < P; p++) {
+        const uint32_t rr = SH ? (r[2 * p] | (r[2 * p + 1] << 16)) & 0xFFFEFFFEu
+                               : (r[2 * p] >> 1) | ((r[2 * p + 1] >> 1) << 16);
+        m[p] = ((hv[p] + rr) & ~bad[p]) | (NUL16P & bad[p]);
+    }
+}
+
+// The record of cell (s, column) among the stored words: four steps of a
+// register pair of columns to a dword, the first of the four on top.
+__device__ __forceinline__ uint32_t record_of(uint32_t word, int s, int col) {
+    return (word >> (16 * (col & 1) + 4 * (3 - (s & 3)))) & 15u;
+}
+
+}  // namespace rows
+}  // namespace wfa
