@@ -106,6 +106,258 @@ struct Dev {
     uint64_t capacity;
 };
 
+// Lengths of pairs (the descriptors live on the device): pattern and text of
+// pending[i] at 2 i and 2 i + 1.
+int pair_lengths(Engine* e, const Dev& d, const std::vector<uint32_t>& pending, hipStream_t s,
+                 std::vector<uint32_t>* lens) {
+    Workspace& ws = e->ws;
+    RCCHK(ws.ensure(ws.jobs, pending.size() * 4));
+    RCCHK(ws.ensure(ws.gen_tmp, pending.size() * 8));
+    HIPCHK(hipMemcpyAsync(ws.jobs.ptr, pending.data(), pending.size() * 4, hipMemcpyHostToDevice, s));
+    HIPCHK(launch_pair_lengths(d.pairs, ws.jobs.as<uint32_t>(), pending.size(), ws.gen_tmp.as<uint32_t>(),
+                               s));
+    lens->resize(2 * pending.size());
+    HIPCHK(hipMemcpyAsync(lens->data(), ws.gen_tmp.ptr, lens->size() * 4, hipMemcpyDeviceToHost, s));
+    HIPCHK(hipStreamSynchronize(s));
+    return WFA_OK;
+}
+
+// Runs of a launch's jobs (their order: ws.jobs) out of the arena, behind the
+// `gen_used` runs gathered so far.
+int gather_runs(Engine* e, size_t nj, uint64_t& gen_used, hipStream_t s) {
+    Workspace& ws = e->ws;
+    HIPCHK(launch_scan(SCAN_U32, ws.job_nruns.ptr, nj, ws.job_offsets.as<uint64_t>(), ws.scan_tmp.ptr, s));
+    uint64_t runs = 0;
+    HIPCHK(hipMemcpyAsync(&runs, ws.job_offsets.as<uint64_t>() + nj, 8, hipMemcpyDeviceToHost, s));
+    HIPCHK(hipStreamSynchronize(s));
+    RCCHK(ws.grow_keep(ws.gen_runs, (gen_used + runs + 1) * 4, gen_used * 4, s));
+    HIPCHK(launch_gather_general(ws.jobs.as<uint32_t>(), nj, ws.job_nruns.as<uint32_t>(),
+                                 ws.run_src.as<uint64_t>(), ws.arena.as<uint8_t>(), 0,
+                                 ws.job_offsets.as<uint64_t>(), gen_used, ws.gen_runs.as<uint32_t>(), s));
+    gen_used += runs;
+    return WFA_OK;
+}
+
+// Stable order of `n` items by a small key, largest first.
+template <class Key>
+void order_by(size_t n, uint32_t keys, Key&& key, std::vector<uint32_t>* order) {
+    std::vector<uint32_t> first(keys + 1, 0);
+    for (size_t i = 0; i < n; i++) first[keys - key(i)]++;
+    uint32_t at = 0;
+    for (uint32_t& f : first) {
+        const uint32_t c = f;
+        f = at;
+        at += c;
+    }
+    order->resize(n);
+    for (size_t i = 0; i < n; i++) (*order)[first[keys - key(i)]++] = (uint32_t)i;
+}
+
+// Pairs in `pending` on the front kernel (global alignment, exact, penalties
+// it is built for); what it does not hold stays in `pending` for the general
+// kernel.  The host reads the score bounds back to size every pair's rows,
+// records and workgroup.
+int run_front(Engine* e, const Pen& pen, bool cigar, const Dev& d, std::vector<uint32_t>& pending,
+              uint64_t& gen_used, hipStream_t s, uint64_t* done) {
+    Workspace& ws = e->ws;
+    std::vector<uint32_t> lens;
+    RCCHK(pair_lengths(e, d, pending, s, &lens));
+    const size_t np = pending.size();
+    auto n_of = [&](size_t i) { return lens[2 * i]; };
+    auto m_of = [&](size_t i) { return lens[2 * i + 1]; };
+    // longest pairs first (by classes of 64 bases of n + m), pairs past 16383
+    // bases before all others, pairs past the kernel's lengths last
+    constexpr uint32_t LEN_CLASSES = 1024;
+    auto len_class = [&](size_t i) -> uint32_t {
+        if (!front_fits(n_of(i), m_of(i))) return 0;
+        const uint32_t c = 1 + std::min((n_of(i) + m_of(i)) / 64, LEN_CLASSES - 2);
+        return std::max(n_of(i), m_of(i)) > 16383 ? c + LEN_CLASSES : c;
+    };
+    std::vector<uint32_t> order;
+    order_by(np, 2 * LEN_CLASSES, len_class, &order);
+    size_t nf = np, n16 = 0;
+    while (nf > 0 && len_class(order[nf - 1]) == 0) nf--;
+    while (n16 < nf && len_class(order[n16]) >= LEN_CLASSES) n16++;
+    // the fixed region of the allocation-free entry point cannot hold an arena
+    // for either kernel: a batch with pairs for both is the general kernel's
+    if (!nf || (ws.fixed_base && nf < np)) return WFA_OK;
+    std::vector<uint32_t> rest;
+    for (size_t i = nf; i < np; i++) rest.push_back(pending[order[i]]);
+    auto longest = [&](const uint32_t* idx, size_t cnt, uint32_t* n, uint32_t* m) {
+        *n = *m = 0;
+        for (size_t i = 0; i < cnt; i++) {
+            *n = std::max(*n, n_of(idx[i]));
+            *m = std::max(*m, m_of(idx[i]));
+        }
+    };
+    FrontArgs a{};
+    a.pairs = d.pairs;
+    a.pw = d.pw;
+    a.tw = d.tw;
+    a.g = pen.g;
+    a.scores = d.scores;
+    a.nruns = ws.nruns.as<uint32_t>();
+    a.run_src = ws.run_src.as<uint64_t>();
+    uint32_t n, m;
+
+    // ---- score bounds ------------------------------------------------------
+    std::vector<int32_t> bounds(nf);
+    std::vector<uint32_t> ids(nf);
+    for (size_t i = 0; i < nf; i++) ids[i] = pending[order[i]];
+    RCCHK(ws.ensure(ws.gen_state, nf * 4));
+    HIPCHK(hipMemcpyAsync(ws.jobs.ptr, ids.data(), nf * 4, hipMemcpyHostToDevice, s));
+    a.ids = ws.jobs.as<uint32_t>();
+    a.bounds = ws.gen_state.as<int32_t>();
+    longest(order.data(), n16, &n, &m);
+    HIPCHK(launch_bound(a, pen, 0, (int)n16, n, m, s));
+    a.ids += n16;
+    a.bounds += n16;
+    longest(order.data() + n16, nf - n16, &n, &m);
+    HIPCHK(launch_bound(a, pen, 1, (int)(nf - n16), n, m, s));
+    HIPCHK(hipMemcpyAsync(bounds.data(), ws.gen_state.ptr, nf * 4, hipMemcpyDeviceToHost, s));
+    HIPCHK(hipStreamSynchronize(s));
+
+    // ---- shapes --------------------------------------------------------------
+    // Row forms.  Two blocks of diagonals per wavefront when the pairs fill
+    // the chip; one when they do not, where the longest pair's chain of steps
+    // sets the time.  Then also all pairs go in one launch, so that they run
+    // side by side: in the widest form any of them needs.
+    struct Job {
+        FrontShapeInfo f;
+        FrontForm form;
+        uint32_t idx;  // position in `pending`
+        int nblk, waves;
+        uint64_t words;  // CIGAR: records, events and runs in the arena
+    };
+    std::vector<Job> held;
+    held.reserve(nf);
+    const bool few = nf <= (size_t)e->num_cus;
+    FrontForm all{1, 2, 1};
+    for (size_t i = 0; i < nf; i++) {
+        Job j{};
+        j.idx = order[i];
+        if (!front_shape(pen, n_of(j.idx), m_of(j.idx), bounds[i], &j.f)) {
+            rest.push_back(pending[j.idx]);
+            continue;
+        }
+        if (j.f.width > 16 * 2 * 64 * 2) j.form = {j.f.sh, 4, 2};
+        else j.form = {j.f.sh, 2, few && j.f.width <= 16 * 64 * 2 ? 1 : 2};
+        all.sh = std::min(all.sh, j.form.sh);
+        all.cols = std::max(all.cols, j.form.cols);
+        all.blocks = std::max(all.blocks, j.form.blocks);
+        held.push_back(j);
+    }
+    if (held.empty() || (ws.fixed_base && !rest.empty())) return WFA_OK;
+    uint64_t want = 0, most = 0;
+    for (Job& j : held) {
+        if (few) j.form = all;
+        j.nblk = front_blocks(j.f.width, j.form.cols);
+        j.waves = (j.nblk + j.form.blocks - 1) / j.form.blocks;
+        j.words = (uint64_t)(j.f.bound / 4 + 1) * j.nblk * 32 * j.form.cols + j.f.ev_words + j.f.run_words;
+        want += j.words * 4;
+        most = std::max(most, j.words * 4);
+    }
+    // the pairs with the most work first; a launch takes pairs of one row form
+    auto same_form = [](const FrontForm& x, const FrontForm& y) {
+        return x.sh == y.sh && x.cols == y.cols && x.blocks == y.blocks;
+    };
+    std::vector<uint32_t> by_work;
+    order_by(held.size(), 8 * 32, [&](size_t i) -> uint32_t {
+        const Job& j = held[i];
+        return ((1 - j.form.sh) * 4 + (j.form.cols == 4 ? 2 : 0) + (j.form.blocks - 1)) * 32 + j.waves;
+    }, &by_work);
+    if (cigar) {  // the arena keeps its size across calls; see run_general
+        const size_t others = ws.total - ws.arena.bytes;
+        const size_t cap = ws.budget > others ? (ws.budget - others) / 4 * 3 : 0;
+        const size_t target = std::min<size_t>(want, cap);
+        if (ws.arena.bytes < target) {
+            ws.release(ws.arena);
+            size_t t = target;
+            int rc = ws.ensure(ws.arena, t);
+            while (rc != WFA_OK && t / 2 >= most) {
+                t /= 2;
+                rc = ws.ensure(ws.arena, t);
+            }
+            if (rc != WFA_OK) return WFA_OK;  // the general kernel needs less
+        }
+        if (ws.arena.bytes < most) return WFA_OK;
+    }
+    if (std::getenv("WFA_DEBUG")) {
+        double sum = 0;
+        for (const Job& j : held) sum += j.f.bound;
+        std::fprintf(stderr, "libwfa front: %zu pairs, mean bound %.1f steps, records %.2f GiB\n",
+                     held.size(), sum / held.size(), want / 1073741824.0);
+    }
+
+    std::vector<FrontJob> fj;
+    for (size_t off = 0; off < held.size();) {
+        // the pairs whose records fit the arena
+        fj.clear();
+        ids.clear();
+        uint64_t used = 0;
+        size_t end = off;
+        for (; end < held.size(); end++) {
+            const Job& j = held[by_work[end]];
+            const uint64_t w = cigar ? j.words : 0;
+            if ((used + w) * 4 > ws.arena.bytes && cigar) break;
+            fj.push_back({pending[j.idx], j.f.bound, j.f.kbase, j.nblk, j.form.cols, used,
+                          j.words - j.f.ev_words - j.f.run_words, (int32_t)j.f.ev_words,
+                          (int32_t)j.f.run_words, 0});
+            ids.push_back(pending[j.idx]);
+            used += w;
+        }
+        const size_t nj = end - off;
+        RCCHK(ws.ensure(ws.jobs, nj * 4));
+        RCCHK(ws.ensure(ws.gen_slices, nj * sizeof(FrontJob)));
+        RCCHK(ws.ensure(ws.job_nruns, nj * 4));
+        RCCHK(ws.ensure(ws.job_offsets, (nj + 1) * 8));
+        RCCHK(ws.ensure(ws.fail_list, nj * 4));
+        RCCHK(ws.ensure(ws.scan_tmp, scan_temp_bytes(nj) + 64));
+        DevFlags* flags = ws.flags.as<DevFlags>();
+        HIPCHK(hipMemcpyAsync(ws.jobs.ptr, ids.data(), nj * 4, hipMemcpyHostToDevice, s));
+        HIPCHK(hipMemcpyAsync(ws.gen_slices.ptr, fj.data(), nj * sizeof(FrontJob), hipMemcpyHostToDevice, s));
+        FillOps fill{};
+        fill.add(ws.job_nruns.as<uint32_t>(), nj, 0u);
+        fill.add(&flags->fail_count, 1, 0u);
+        HIPCHK(launch_fill_multi(fill, s));
+        a.arena = cigar ? ws.arena.as<uint32_t>() : nullptr;
+        a.fail_list = ws.fail_list.as<uint32_t>();
+        a.fail_count = &flags->fail_count;
+        for (size_t i = 0; i < nj;) {
+            // a launch: workgroups of one size.  Smaller pairs join while the
+            // group would not fill the chip, or lacks few wavefronts.
+            const Job& f = held[by_work[off + i]];
+            size_t k = i;
+            n = m = 0;
+            for (; k < nj; k++) {
+                const Job& g = held[by_work[off + k]];
+                if (!same_form(g.form, f.form)) break;
+                if (4 * g.waves <= 3 * f.waves && k - i >= 2 * (size_t)e->num_cus) break;
+                n = std::max(n, n_of(g.idx));
+                m = std::max(m, m_of(g.idx));
+            }
+            a.jobs = ws.gen_slices.as<FrontJob>() + i;
+            a.job_nruns = ws.job_nruns.as<uint32_t>() + i;
+            HIPCHK(launch_front(a, pen, cigar, f.form, (int)(k - i), f.waves, n, m, s));
+            i = k;
+        }
+        uint32_t nfail = 0;
+        HIPCHK(hipMemcpyAsync(&nfail, &flags->fail_count, 4, hipMemcpyDeviceToHost, s));
+        if (cigar) RCCHK(gather_runs(e, nj, gen_used, s));
+        HIPCHK(hipStreamSynchronize(s));
+        if (nfail) {
+            std::vector<uint32_t> f(nfail);
+            HIPCHK(hipMemcpy(f.data(), ws.fail_list.ptr, nfail * 4ull, hipMemcpyDeviceToHost));
+            rest.insert(rest.end(), f.begin(), f.end());
+        }
+        *done += nj - nfail;
+        off = end;
+    }
+    std::sort(rest.begin(), rest.end());
+    pending.swap(rest);
+    return WFA_OK;
+}
+
 // Pairs in `pending` on the workgroup-per-pair kernel, chunked by the budget;
 // pairs whose slice is too small are retried with a 4x slice.
 // A pair the kernel gives up on ends the call with WFA_E_LIMIT and its index
@@ -119,23 +371,8 @@ int run_general(Engine* e, const Pen& pen, bool cigar, const Dev& d, const Batch
     RCCHK(ws.ensure(ws.flags, sizeof(DevFlags)));
     DevFlags* flags = ws.flags.as<DevFlags>();
 
-    // lengths of the pending pairs (the descriptors live on the device)
-    std::vector<uint32_t> plen(pending.size()), tlen(pending.size());
-    {
-        RCCHK(ws.ensure(ws.jobs, pending.size() * 4));
-        RCCHK(ws.ensure(ws.gen_tmp, pending.size() * 8));
-        HIPCHK(hipMemcpyAsync(ws.jobs.ptr, pending.data(), pending.size() * 4,
-                              hipMemcpyHostToDevice, s));
-        HIPCHK(launch_pair_lengths(d.pairs, ws.jobs.as<uint32_t>(), pending.size(),
-                                   ws.gen_tmp.as<uint32_t>(), s));
-        std::vector<uint32_t> lens(2 * pending.size());
-        HIPCHK(hipMemcpyAsync(lens.data(), ws.gen_tmp.ptr, lens.size() * 4, hipMemcpyDeviceToHost, s));
-        HIPCHK(hipStreamSynchronize(s));
-        for (size_t i = 0; i < pending.size(); i++) {
-            plen[i] = lens[2 * i];
-            tlen[i] = lens[2 * i + 1];
-        }
-    }
+    std::vector<uint32_t> lens;
+    RCCHK(pair_lengths(e, d, pending, s, &lens));
     // Longest pairs first: a launch then holds pairs of similar size, its
     // slices are sized for its own longest pair (short pairs run many at a
     // time), and the long pairs start early.
@@ -143,7 +380,7 @@ int run_general(Engine* e, const Pen& pen, bool cigar, const Dev& d, const Batch
         uint32_t pair, n, m;
     };
     std::vector<Job> jobs(pending.size());
-    for (size_t i = 0; i < pending.size(); i++) jobs[i] = {pending[i], plen[i], tlen[i]};
+    for (size_t i = 0; i < pending.size(); i++) jobs[i] = {pending[i], lens[2 * i], lens[2 * i + 1]};
     std::stable_sort(jobs.begin(), jobs.end(), [](const Job& a, const Job& b) {
         return (uint64_t)a.n + a.m > (uint64_t)b.n + b.m;
     });
@@ -358,18 +595,7 @@ int run_general(Engine* e, const Pen& pen, bool cigar, const Dev& d, const Batch
             *general_done += nj - nfail;
             if (cigar) {
                 // gather this chunk's runs out of the arena before it is reused
-                HIPCHK(launch_scan(SCAN_U32, ws.job_nruns.ptr, nj, ws.job_offsets.as<uint64_t>(),
-                                   ws.scan_tmp.ptr, s));
-                uint64_t chunk_runs = 0;
-                HIPCHK(hipMemcpyAsync(&chunk_runs, ws.job_offsets.as<uint64_t>() + nj, 8,
-                                      hipMemcpyDeviceToHost, s));
-                HIPCHK(hipStreamSynchronize(s));
-                RCCHK(ws.grow_keep(ws.gen_runs, (gen_used + chunk_runs + 1) * 4, gen_used * 4, s));
-                HIPCHK(launch_gather_general(ws.jobs.as<uint32_t>(), nj, ws.job_nruns.as<uint32_t>(),
-                                             ws.run_src.as<uint64_t>(), ws.arena.as<uint8_t>(), 0,
-                                             ws.job_offsets.as<uint64_t>(), gen_used,
-                                             ws.gen_runs.as<uint32_t>(), s));
-                gen_used += chunk_runs;
+                RCCHK(gather_runs(e, nj, gen_used, s));
             }
             off += nj;
         }
@@ -1032,6 +1258,17 @@ int engine_align_device(Engine* e, const BatchIO& io, hipStream_t user_stream,
     // offsets and runs are written, so nothing more runs on the device
     const bool tail = !pending.empty() || !use_short || fl.ovf_count > 0;
     if (tail) HIPCHK(hipEventRecord(e->ev[2], s));
+    // The front kernel first, unless the caller chose a form of the general
+    // kernel's memory or a step limit.
+    if (!pending.empty() && global && e->heur.mwl == 0 && front_supported(pen) &&
+        e->opt.general_step_limit == 0 && e->opt.general_checkpoint == 0 &&
+        e->opt.general_slice_kib == 0 && e->opt.general_pairs == 0) {
+        const int rf = run_front(e, pen, cigar, d, pending, gen_used, s, &general_done);
+        if (rf != WFA_OK) {
+            (void)finish_user();
+            return rf;
+        }
+    }
     if (!pending.empty()) {
         int64_t gave_up = -1;
         const int rg = run_general(e, pen, cigar, d, st, pending, gen_used, s, &general_done,

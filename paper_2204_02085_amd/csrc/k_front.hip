@@ -1,0 +1,539 @@
+// Front kernel: long and divergent pairs, a workgroup per pair, wavefront rows
+// in registers (rows.h).
+//
+// Two kernels per batch of pairs:
+//
+//   k_bound       one wavefront per pair aligns greedily in a band of 128
+//                 diagonals that follows the furthest point.  Its score U is
+//                 that of an alignment, so no optimal one costs more.
+//   k_front       one workgroup per pair.  A cell on diagonal k at step s lies
+//                 on an optimal alignment only if a gap back to the end
+//                 diagonal still fits, s + e |k - kt| <= U, and only if a gap
+//                 from diagonal 0 has reached it.  Both cut the triangle of
+//                 cells to a diamond, half of it when U is the score.  Every
+//                 lane owns C neighbouring diagonals for the whole pair, so
+//                 the rows stay in registers; neighbouring lanes exchange a
+//                 column by DPP, neighbouring wavefronts through LDS, with one
+//                 barrier per step.  In CIGAR mode the first wavefront then
+//                 walks the decision records back (see walk).
+//
+// What bounds it: VALU issue and the chain of a step (the neighbour's column
+// from LDS, the recurrences, two windows of each sequence from LDS, the barrier),
+// hidden by the other workgroups of a CU: about 60 instructions per step and
+// 128 diagonals, 0.6 to 0.85 of the issue slots by the workgroups' size.
+// Measured on whole calls against the general kernel, whose rows cross L2 and
+// HBM and fill the whole triangle: 20 k pairs of 1-10 kbp at 5-10 % with CIGARs
+// 29.4 ms (108.3), 5 k of them score-only 7.3 ms (25.5), 24 pairs of 10-20 kbp
+// 11.3 ms (66.5).  Of the 20 k pairs' time k_bound takes 2.1 ms; its bound was
+// the score itself for every pair looked at.  The record walk in a kernel of its
+// own took 2.8 ms more.
+//
+// Cells a pruned cell would have fed never beat those of an optimal
+// alignment: a missing candidate only lowers offsets off the optimal paths,
+// and a cell on one has all its sources on one.  So scores and tie-breaks are
+// those of the full wavefronts.
+#include <hip/hip_runtime.h>
+#include <stdint.h>
+
+#include <algorithm>
+
+#include "kernels.h"
+#include "rows.h"
+
+namespace wfa {
+
+namespace {
+
+using namespace rows;
+
+__device__ __forceinline__ void wave_fence() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// Both sequences into LDS: the text's words, then the pattern's, each followed
+// by a zero word.  The pattern starts at least four words in, so a compare a
+// little before its first base (a cell off the matrix) stays in the block.
+__device__ __forceinline__ int text_words(int m) { return max((m + 31) / 32 + 1, 8); }
+__device__ __forceinline__ void stage(lds_p<uint64_t> dst, const uint64_t* pw, const uint64_t* tw,
+                                      const PairDesc& d, int tid, int bt) {
+    const int nwt = ((int)d.t_len + 31) >> 5, nwp = ((int)d.p_len + 31) >> 5;
+    const int tws = text_words((int)d.t_len);
+    for (int w = tid; w < tws; w += bt) dst[w] = w < nwt ? tw[d.t_start + w] : 0ull;
+    for (int w = tid; w <= nwp; w += bt) dst[tws + w] = w < nwp ? pw[d.p_start + w] : 0ull;
+}
+
+// 16-bit value of a packed register at a wave-uniform lane and half
+__device__ __forceinline__ int half_at(uint32_t reg, int lane, int half) {
+    const uint32_t w = (uint32_t)__builtin_amdgcn_readlane((int)reg, lane);
+    return (int)(short)(w >> (16 * half));
+}
+
+// largest of the lanes' values, in every lane
+__device__ __forceinline__ int wave_max(int v) {
+    v = max(v, __builtin_amdgcn_update_dpp(v, v, 0x111, 0xF, 0xF, false));  // row_shr:1
+    v = max(v, __builtin_amdgcn_update_dpp(v, v, 0x112, 0xF, 0xF, false));
+    v = max(v, __builtin_amdgcn_update_dpp(v, v, 0x114, 0xF, 0xF, false));
+    v = max(v, __builtin_amdgcn_update_dpp(v, v, 0x118, 0xF, 0xF, false));
+    v = max(v, __builtin_amdgcn_update_dpp(v, v, 0x142, 0xA, 0xF, false));  // row_bcast:15
+    v = max(v, __builtin_amdgcn_update_dpp(v, v, 0x143, 0xC, 0xF, false));  // row_bcast:31
+    return __builtin_amdgcn_readlane(v, 63);
+}
+
+template <int X, int OE, int E, int SH>
+__global__ __launch_bounds__(64) void k_bound(FrontArgs a) {
+    constexpr int C = 2;
+    extern __shared__ __align__(16) unsigned char lds[];
+    const uint32_t pair = a.ids[blockIdx.x];
+    const PairDesc d = a.pairs[pair];
+    const int n = (int)d.p_len, m = (int)d.t_len, kt = m - n;
+    const int lane = threadIdx.x;
+    stage((lds_p<uint64_t>)lds, a.pw, a.tw, d, lane, 64);
+    wave_fence();
+    const uint32_t tb = (uint32_t)(uintptr_t)(lds_p<unsigned char>)lds;
+    const uint32_t pb = tb + 8 * text_words(m);
+    // every base mismatched and the length difference in one gap
+    int U = X * min(n, m) + (kt ? (OE - E) + E * abs(kt) : 0);
+    int kmin = -64;
+    Place<C> pl;
+    pl.template set<SH>(n, m, kmin + C * lane);
+    Rows<X, OE, E, C, SH, false> row;
+    row.clear();
+    for (int s = 0; s < U; s += 4) {
+        bool end = false;
+#pragma unroll
+        for (int u = 0; u < 4; u++) {
+            if (end) break;
+            uint32_t sa[1], sb[1], cm[1], ci[1], cd[1];
+            row.sources(sa, sb);
+            row.cells(sa, sb, wave_prev(NUL16P, sa[0]), wave_next(NUL16P, sb[0]), cm, ci, cd, false);
+            if (u == 0 && s == 0) {
+                cm[0] = lane == 32 ? 0xC0000000u : NUL16P;  // M_0[0] = 0
+                ci[0] = cd[0] = NUL16P;
+            }
+            extend<C, SH>(cm, pl, tb, pb);
+            row.push(cm, ci, cd);
+            const int col = kt - kmin;
+            if (col >= 0 && col < 128 && half_at(cm[0], col >> 1, col & 1) == m << SH) {
+                U = min(U, s + u);
+                end = true;
+            }
+        }
+        if (end) break;
+        // follow the furthest point (2 h - k), a lane or two at a time
+        const int k0 = kmin + C * lane;
+        const int h0 = (int)(short)row.M[0][0] << (1 - SH), h1 = (int)(short)(row.M[0][0] >> 16) << (1 - SH);
+        const int top = wave_max((max(h0 - k0, h1 - k0 - 1) << 6) | lane);
+        int shift = top < 0 ? 0 : (top & 63) - 32;  // (below 0: no cell at this step)
+        shift = shift > 8 ? 2 : shift > 2 ? 1 : shift < -8 ? -2 : shift < -2 ? -1 : 0;
+        if (shift) {
+            for (; shift > 0; shift--, kmin += C) {
+#pragma unroll
+                for (int j = 0; j < Rows<X, OE, E, C, SH, false>::RM; j++)
+                    row.M[j][0] = wave_next(NUL16P, row.M[j][0]);
+#pragma unroll
+                for (int j = 0; j < E; j++) {
+                    row.I[j][0] = wave_next(NUL16P, row.I[j][0]);
+                    row.D[j][0] = wave_next(NUL16P, row.D[j][0]);
+                }
+            }
+            for (; shift < 0; shift++, kmin -= C) {
+#pragma unroll
+                for (int j = 0; j < Rows<X, OE, E, C, SH, false>::RM; j++)
+                    row.M[j][0] = wave_prev(NUL16P, row.M[j][0]);
+#pragma unroll
+                for (int j = 0; j < E; j++) {
+                    row.I[j][0] = wave_prev(NUL16P, row.I[j][0]);
+                    row.D[j][0] = wave_prev(NUL16P, row.D[j][0]);
+                }
+            }
+            pl.template set<SH>(n, m, kmin + C * lane);
+        }
+    }
+    if (lane == 0) a.bounds[blockIdx.x] = U;
+}
+
+constexpr int WALK_QUADS = 64;  // quads of steps of the record window in LDS
+constexpr int WALK_DW = 8;      // its dwords (16 diagonals) per quad
+
+// One pair's walk, by one wavefront: the records back to the list of edits,
+// 256 steps of them in LDS at a time, then the edits from the start along
+// matches, 1024 bases per compare.  Everything but the loads and stores is
+// wave-uniform.  Sequences at LDS bytes tb and pb, `win` the record window.
+template <int X, int OE, int E>
+__device__ void walk(const FrontArgs& a, const FrontJob& job, int S, int n, int m, int lane,
+                     lds_p<uint32_t> win, uint32_t tb, uint32_t pb) {
+    typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+    const int rowdw = job.nw * 32 * job.cols;  // dwords per quad of steps
+    const uint32_t* hist = a.arena + job.hist;
+    uint32_t* evs = a.arena + job.hist + job.hist_words;
+    uint32_t* runs_end = evs + job.ev_words + job.run_words;
+
+    // ---- the edits, last to first; lane i keeps event i of the current 64
+    int qtop = -1, c0 = 0;
+    bool bad = false;
+    auto record = [&](int s, int k) -> uint32_t {
+        const int q = s >> 2, col = k - job.kbase, dw = col >> 1;
+        if (col < 0 || dw >= rowdw) {
+            bad = true;
+            return 0;
+        }
+        if (q > qtop || q <= qtop - WALK_QUADS || dw < c0 || dw >= c0 + WALK_DW) {
+            qtop = q;
+            c0 = min(max((dw - WALK_DW / 2) & ~3, 0), rowdw - WALK_DW);
+            wave_fence();
+            if (q - lane >= 0) {
+                const u32x4* from = (const u32x4*)(hist + (uint64_t)(q - lane) * rowdw + c0);
+                lds_p<u32x4> to = (lds_p<u32x4>)(win + lane * WALK_DW);
+#pragma unroll
+                for (int i = 0; i < WALK_DW / 4; i++) to[i] = from[i];
+            }
+            wave_fence();
+        }
+        const uint32_t word = (uint32_t)__builtin_amdgcn_readfirstlane((int)win[(qtop - q) * WALK_DW + dw - c0]);
+        return record_of(word, s, col);
+    };
+    int s = S, k = m - n, ne = 0;
+    uint32_t evreg = 0;
+    while (s > 0 && !bad) {
+        const uint32_t f = record(s, k);
+        int kind = EV_X, len = 1;
+        if (!(f & 1)) {
+            s -= X;
+        } else {
+            const bool ins = !(f & 2);
+            kind = ins ? EV_I : EV_D;
+            const uint32_t more = ins ? 4u : 8u;
+            len = 0;
+            for (;;) {
+                len++;
+                k += ins ? -1 : 1;
+                if (s <= 0) bad = true;
+                if (bad) break;
+                const bool ext = (record(s, k) & more) != 0;
+                s -= ext ? E : OE;
+                if (!ext) break;
+            }
+        }
+        evreg = lane == (ne & 63) ? (uint32_t)(len << 2 | kind) : evreg;
+        ne++;
+        if (ne > job.ev_words) bad = true;
+        if (!bad && (ne & 63) == 0) evs[ne - 64 + lane] = evreg;
+    }
+    if (s != 0 || k != 0) bad = true;
+
+    // ---- replay; runs are stored downwards from the end, so that they stand
+    // last to first
+    int h = 0, v = 0, nr = 0, cop = -1, clen = 0;
+    uint32_t rreg = 0;
+    auto put = [&]() {
+        rreg = lane == (nr & 63) ? ((uint32_t)clen << 4) | (uint32_t)cop : rreg;
+        nr++;
+        if (nr > job.run_words) bad = true;
+        if (!bad && (nr & 63) == 0) runs_end[-(nr - 64) - 1 - lane] = rreg;
+    };
+    auto emit = [&](int op, int len) {
+        if (len <= 0) return;
+        if (op == cop) {
+            clen += len;
+        } else {
+            if (cop >= 0) put();
+            cop = op;
+            clen = len;
+        }
+    };
+    for (int i = ne - 1; !bad; i--) {
+        int left = min(n - v, m - h), mm = 0;
+        while (left > 0) {  // lane l compares 16 bases, 16 l on
+            uint32_t x = 1;
+            if (16 * lane < left)
+                x = win16(tb, 2 * (h + mm + 16 * lane)) ^ win16(pb, 2 * (v + mm + 16 * lane));
+            const uint64_t stop = lanes_where(x != 0);
+            int z = 1024;
+            if (stop) {
+                const int fl = __builtin_ctzll(stop);
+                const uint32_t y = (uint32_t)__builtin_amdgcn_readlane((int)x, fl);
+                z = 16 * fl + (__builtin_ctz(y) >> 1);
+            }
+            z = min(z, left);
+            mm += z;
+            left -= z;
+            if (z < 1024) break;
+        }
+        emit(0, mm);
+        h += mm;
+        v += mm;
+        if (i < 0) break;
+        if ((i & 63) == 63 && i != ne - 1) evreg = evs[i - 63 + lane];
+        const uint32_t ev = (uint32_t)__builtin_amdgcn_readlane((int)evreg, i & 63);
+        const int len = (int)(ev >> 2), kind = (int)(ev & 3);
+        emit(1 + kind, len);
+        if (kind != EV_D) h += len;
+        if (kind != EV_I) v += len;
+        if (h > m || v > n) bad = true;
+    }
+    if (h != m || v != n) bad = true;
+    if (cop >= 0) put();
+    if (!bad && (nr & 63) && lane < (nr & 63)) runs_end[-(nr & ~63) - 1 - lane] = rreg;
+    if (lane == 0) {
+        if (bad) {
+            a.fail_list[atomicAdd(a.fail_count, 1u)] = job.pair;
+        } else {
+            a.scores[job.pair] = S * a.g;
+            a.nruns[job.pair] = (uint32_t)nr;
+            a.job_nruns[blockIdx.x] = (uint32_t)nr;
+            a.run_src[job.pair] = (uint64_t)(runs_end - a.arena) - nr;  // arena words
+        }
+    }
+}
+
+// The rows of one block of 64 C diagonals, and where it stands.
+template <int X, int OE, int E, int C, int SH, bool CIGAR>
+struct Block {
+    static constexpr int P = C / 2;
+    Rows<X, OE, E, C, SH, CIGAR> row;
+    Place<C> pl;
+    uint32_t sa[P], sb[P];           // sources of the next step
+    lds_p<uint32_t> xin, xout;       // the columns next to it
+    int k0;                          // this lane's first diagonal
+};
+
+// NB blocks of diagonals per wavefront: block b is wavefront b mod nwv's, nwv
+// the pair's wavefronts.  With NB = 2 a wavefront holds one block of either
+// half of the diamond's diagonals, of which about one is active at a time, so
+// no wavefront is idle for half of the pair's steps.
+template <int X, int OE, int E, int C, int NB, int SH, bool CIGAR>
+__global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(C * NB <= 4 ? 8 : 4)))
+void k_front(FrontArgs a) {
+    constexpr int P = C / 2, WC = 64 * C;  // columns of a block
+    using B = Block<X, OE, E, C, SH, CIGAR>;
+    extern __shared__ __align__(16) unsigned char lds[];
+    const FrontJob job = a.jobs[blockIdx.x];
+    const PairDesc d = a.pairs[job.pair];
+    const int n = (int)d.p_len, m = (int)d.t_len, kt = m - n;
+    const int lane = threadIdx.x & 63;
+    const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const int nbb = NB * (blockDim.x >> 6);
+    // LDS: the step the pair ended at, two buffers of the columns blocks
+    // exchange (a block of NULL on either side), the window of the walk, the
+    // sequences
+    lds_p<int> done = (lds_p<int>)lds;
+    lds_p<uint32_t> xch = (lds_p<uint32_t>)(done + 4);
+    const int xb = 2 * (nbb + 2);  // words per buffer: {up, down} per block
+    lds_p<uint32_t> win = xch + 2 * xb;
+    lds_p<uint64_t> seq = (lds_p<uint64_t>)(win + (CIGAR ? WALK_QUADS * WALK_DW : 0));
+    stage(seq, a.pw, a.tw, d, threadIdx.x, blockDim.x);
+    for (int i = threadIdx.x; i < 2 * xb; i += blockDim.x) xch[i] = NUL16P;
+    if (threadIdx.x == 0) *done = -1;
+    const uint32_t tb = (uint32_t)(uintptr_t)seq, pb = tb + 8 * text_words(m);
+    int edge = lane == 0 || lane == 63;  // lanes that hand a column to the next block
+    asm("" : "+v"(edge));
+
+    const int U = job.bound, kbase = job.kbase, nwv = (job.nw + NB - 1) / NB;
+    const int ct = kt - kbase;  // column of the end diagonal
+    B blk[NB];
+#pragma unroll
+    for (int i = 0; i < NB; i++) {
+        const int b = w + i * nwv;
+        blk[i].k0 = kbase + b * WC + lane * C;
+        blk[i].pl.template set<SH>(n, m, blk[i].k0);
+        blk[i].row.clear();
+#pragma unroll
+        for (int p = 0; p < P; p++) blk[i].sa[p] = blk[i].sb[p] = NUL16P;
+        // lane 0 takes the column below from the block before, lane 63 the one
+        // above from the block after; the same lanes hand theirs out
+        const int bx = min(b, nbb - 1);
+        blk[i].xin = xch + (lane == 63 ? 2 * (bx + 2) + 1 : 2 * bx);
+        blk[i].xout = xch + 2 * (bx + 1) + (lane == 63 ? 0 : 1);
+    }
+    // the block, lane and column of the end cell
+    const int eb = ct / WC, elane = (ct % WC) / C, ecol = ct % C;
+    int S = -1;
+    // one step of block i (u: its place in the quad)
+    auto step = [&](B& q, int s, int u, bool owner) {
+        const uint32_t xv = q.xin[(u & 1) * xb];
+        uint32_t cm[P], ci[P], cd[P];
+        q.row.cells(q.sa, q.sb, wave_prev(xv, q.sa[P - 1]), wave_next(xv, q.sb[0]), cm, ci, cd, u == 0);
+        if (u == 0 && s == 0) {  // M_0[0] = 0
+#pragma unroll
+            for (int p = 0; p < P; p++) {
+                cm[p] = pk_pair(q.k0 + 2 * p == 0 ? 0 : -16384, q.k0 + 2 * p + 1 == 0 ? 0 : -16384);
+                ci[p] = cd[p] = NUL16P;
+            }
+        }
+        extend<C, SH>(cm, q.pl, tb, pb);
+        q.row.push(cm, ci, cd);
+        q.row.sources(q.sa, q.sb);
+        if (edge) q.xout[((u + 1) & 1) * xb] = lane == 63 ? q.sa[P - 1] : q.sb[0];
+        if (owner && S < 0) {
+            uint32_t reg = cm[0];
+#pragma unroll
+            for (int p = 1; p < P; p++) reg = (ecol >> 1) == p ? cm[p] : reg;
+            if (half_at(reg, elane, ecol & 1) == m << SH) S = s + u;
+        }
+    };
+    auto flush = [&](B& q, int s, int b) {
+        if (CIGAR) {
+            uint32_t* h = a.arena + job.hist + ((uint64_t)(s >> 2) * job.nw + b) * (64 * P) + lane * P;
+#pragma unroll
+            for (int p = 0; p < P; p++) h[p] = q.row.acc[p];
+        }
+    };
+    __syncthreads();
+    for (int s = 0;; s += 4) {
+        if (__builtin_amdgcn_readfirstlane(*done) >= 0 || s > U) break;
+        // diagonals of these four steps' cells, with one to spare on each side
+        const int reach = s + 3 >= OE ? 1 + (s + 3 - OE) / E : 0;
+        const int back = (U - s) / E;
+        const int dlo = max(-reach, kt - back) - 1, dhi = min(reach, kt + back) + 1;
+        bool act[NB], own[NB];
+#pragma unroll
+        for (int i = 0; i < NB; i++) {
+            const int b = w + i * nwv, lo = kbase + b * WC;
+            act[i] = w < nwv && b < job.nw && lo + WC - 1 >= dlo && lo <= dhi;
+            own[i] = b == eb;
+        }
+        auto quad = [&](bool first, bool second) {
+#pragma unroll
+            for (int u = 0; u < 4; u++) {
+                if (first) step(blk[0], s, u, own[0]);
+                if (second) step(blk[NB - 1], s, u, own[NB - 1]);
+                if (u == 3) {
+                    if (first) flush(blk[0], s, w);
+                    if (second) flush(blk[NB - 1], s, w + nwv);
+                    if (S >= 0 && lane == 0) *done = S;
+                }
+                __syncthreads();
+            }
+        };
+        if (NB == 1) {
+            if (act[0]) quad(true, false);
+        } else {
+            if (act[0] && act[NB - 1]) quad(true, true);
+            else if (act[0]) quad(true, false);
+            else if (act[NB - 1]) quad(false, true);
+        }
+        bool any = act[0];
+#pragma unroll
+        for (int i = 1; i < NB; i++) any = any || act[i];
+        if (!any) {
+#pragma unroll
+            for (int u = 0; u < 4; u++) __syncthreads();
+        }
+    }
+    const int S2 = __builtin_amdgcn_readfirstlane(*done);
+    if (S2 < 0) {  // the bound did not hold (an internal error): the general kernel takes the pair
+        if (threadIdx.x == 0) a.fail_list[atomicAdd(a.fail_count, 1u)] = job.pair;
+        return;
+    }
+    if (!CIGAR) {
+        if (threadIdx.x == 0) {
+            a.scores[job.pair] = S2 * a.g;
+            a.nruns[job.pair] = 0;
+        }
+        return;
+    }
+    // every wavefront's records are written; one wavefront walks them while
+    // the others' slots go to the next workgroup
+    __threadfence_block();
+    __syncthreads();
+    if (w == 0) walk<X, OE, E>(a, job, S2, n, m, lane, win, tb, pb);
+}
+
+// Scaled penalties (x, o + e, e) the rows are built for.
+#define WFA_FRONT_PENS(F) \
+    F(2, 4, 1)            \
+    F(1, 1, 1)            \
+    F(2, 5, 1)
+
+template <int X, int OE, int E>
+struct FrontShape {
+    template <int C, int NB, int SH>
+    static hipError_t fwd(const FrontArgs& a, bool cigar, int jobs, int waves, int lds, hipStream_t s) {
+        if (cigar)
+            hipLaunchKernelGGL((k_front<X, OE, E, C, NB, SH, true>), dim3(jobs), dim3(64 * waves), lds, s, a);
+        else
+            hipLaunchKernelGGL((k_front<X, OE, E, C, NB, SH, false>), dim3(jobs), dim3(64 * waves), lds, s, a);
+        return hipGetLastError();
+    }
+    static hipError_t launch(const FrontArgs& a, const FrontForm& f, bool cigar, int jobs, int waves,
+                             int lds, hipStream_t s) {
+        if (f.cols == 2 && f.blocks == 1)
+            return f.sh ? fwd<2, 1, 1>(a, cigar, jobs, waves, lds, s) : fwd<2, 1, 0>(a, cigar, jobs, waves, lds, s);
+        if (f.cols == 2 && f.blocks == 2)
+            return f.sh ? fwd<2, 2, 1>(a, cigar, jobs, waves, lds, s) : fwd<2, 2, 0>(a, cigar, jobs, waves, lds, s);
+        if (f.cols == 4 && f.blocks == 2)
+            return f.sh ? fwd<4, 2, 1>(a, cigar, jobs, waves, lds, s) : fwd<4, 2, 0>(a, cigar, jobs, waves, lds, s);
+        return hipErrorInvalidValue;
+    }
+};
+
+int seq_lds_bytes(uint32_t n, uint32_t m) {
+    // a tail for compares past the pattern's end by cells off the matrix
+    return 8 * (int)(std::max((m + 31) / 32 + 1, 8u) + (n + 31) / 32 + 1) + 256;
+}
+
+}  // namespace
+
+bool front_supported(const Pen& pen) {
+#define WFA_CASE(PX, POE, PE) \
+    if (pen.x == PX && pen.oe == POE && pen.e == PE) return true;
+    WFA_FRONT_PENS(WFA_CASE)
+#undef WFA_CASE
+    return false;
+}
+
+bool front_fits(uint32_t n, uint32_t m) { return std::max(n, m) <= FRONT_MAX_LEN; }
+
+bool front_shape(const Pen& pen, uint32_t n, uint32_t m, int bound, FrontShapeInfo* f) {
+    f->bound = bound;
+    f->sh = std::max(n, m) <= 16383 ? 1 : 0;
+    // NULL offsets drift up by 1 << sh per step and stay negative
+    if (bound > (f->sh ? 8000 : 16000)) return false;
+    const long long kt = (long long)m - n, og = pen.oe - pen.e;
+    // the diamond's outermost diagonals: where the reach from diagonal 0 and
+    // the way back to kt meet, with one to spare
+    long long hi = (bound + pen.e * kt - og) / (2 * pen.e) + 2;
+    long long lo = -((bound - pen.e * kt - og) / (2 * pen.e) + 2);
+    hi = std::min<long long>(std::max<long long>(hi, std::max<long long>(kt, 0)), m);
+    lo = std::max<long long>(std::min<long long>(lo, std::min<long long>(kt, 0)), -(long long)n);
+    f->kbase = (int)lo;
+    f->width = (int)(hi - lo + 1);
+    f->ev_words = (uint32_t)(bound / std::min(pen.x, pen.oe) + 64) & ~63u;
+    f->run_words = 2 * f->ev_words + 64;
+    return f->width <= FRONT_MAX_WIDTH;
+}
+
+int front_blocks(int width, int cols) { return (width + 64 * cols - 1) / (64 * cols); }
+
+hipError_t launch_bound(const FrontArgs& a, const Pen& pen, int sh, int jobs, uint32_t n, uint32_t m,
+                        hipStream_t s) {
+    if (!jobs) return hipSuccess;
+    const int lds = seq_lds_bytes(n, m);
+#define WFA_CASE(PX, POE, PE)                                                                        \
+    if (pen.x == PX && pen.oe == POE && pen.e == PE) {                                               \
+        if (sh) hipLaunchKernelGGL((k_bound<PX, POE, PE, 1>), dim3(jobs), dim3(64), lds, s, a);      \
+        else hipLaunchKernelGGL((k_bound<PX, POE, PE, 0>), dim3(jobs), dim3(64), lds, s, a);         \
+        return hipGetLastError();                                                                    \
+    }
+    WFA_FRONT_PENS(WFA_CASE)
+#undef WFA_CASE
+    return hipErrorInvalidValue;
+}
+
+hipError_t launch_front(const FrontArgs& a, const Pen& pen, bool cigar, const FrontForm& f, int jobs,
+                        int waves, uint32_t n, uint32_t m, hipStream_t s) {
+    if (!jobs) return hipSuccess;
+    if (waves < 1 || waves > 16) return hipErrorInvalidValue;
+    const int lds = 16 + 16 * (waves * f.blocks + 2) + (cigar ? WALK_QUADS * WALK_DW * 4 : 0) +
+                    seq_lds_bytes(n, m);
+#define WFA_CASE(PX, POE, PE)                       \
+    if (pen.x == PX && pen.oe == POE && pen.e == PE) \
+        return FrontShape<PX, POE, PE>::launch(a, f, cigar, jobs, waves, lds, s);
+    WFA_FRONT_PENS(WFA_CASE)
+#undef WFA_CASE
+    return hipErrorInvalidValue;
+}
+
+}  // namespace wfa

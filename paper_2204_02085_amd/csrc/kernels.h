@@ -142,6 +142,50 @@ struct BandPlan {
     int slot_cap = 0, block_threads = 256, lds_per_block = 0;
 };
 
+// One pair of a front-kernel launch.
+struct FrontJob {
+    uint32_t pair;
+    int32_t bound;        // no optimal alignment needs more score steps
+    int32_t kbase;        // diagonal of column 0
+    int32_t nw;           // blocks of 64 * cols diagonals
+    int32_t cols;         // diagonals per lane (2 or 4)
+    uint64_t hist;        // CIGAR: the pair's words in the arena: records,
+    uint64_t hist_words;  // events, runs
+    int32_t ev_words, run_words, pad;
+};
+
+// Arguments of the front kernels (all device pointers).
+struct FrontArgs {
+    const PairDesc* pairs;
+    const uint64_t* pw;         // packed pattern words
+    const uint64_t* tw;         // packed text words
+    const uint32_t* ids;        // k_bound: pair per workgroup
+    int32_t* bounds;            // k_bound: score steps no optimal alignment exceeds
+    const FrontJob* jobs;       // k_front: one per workgroup
+    int g;                      // score units per step
+    uint32_t* arena;            // CIGAR: records, events and runs of the jobs
+    int32_t* scores;            // [pairs]
+    uint32_t* nruns;            // [pairs]
+    uint64_t* run_src;          // [pairs] arena words
+    uint32_t* job_nruns;        // [jobs] runs (zeroed before the launch)
+    uint32_t* fail_list;        // pairs handed to the general kernel
+    uint32_t* fail_count;
+};
+
+// What a pair needs on the front kernel.
+struct FrontShapeInfo {
+    int sh;               // offsets stored doubled (1) or as they are
+    int bound, kbase, width;  // step bound, lowest diagonal, diagonals
+    uint32_t ev_words, run_words;
+};
+// Row form of a launch: offsets' shift, diagonals per lane, blocks of 64 * cols
+// diagonals per wavefront ({2, 1}, {2, 2} and {4, 2} are built).
+struct FrontForm {
+    int sh, cols, blocks;
+};
+constexpr int FRONT_MAX_WIDTH = 16 * 2 * 64 * 4;  // 16 wavefronts of the widest form
+constexpr uint32_t FRONT_MAX_LEN = 32766;  // offsets are 16-bit
+
 // What the general kernel's forward pass hands to its CIGAR walk, per job.
 struct GenJobState {
     long long bump;     // end of the history rows (or checkpoints) in the slice
@@ -270,6 +314,20 @@ int lane_max_blocks_per_cu(const Pen& pen, int cap, bool cigar, int block_thread
 size_t lane_hist_bytes_per_wave(const Pen& pen, int cap, bool cigar, int slot_cap);
 hipError_t launch_lane(const LaneArgs& a, int cap, bool cigar, bool persistent, int block_threads,
                        int grid, hipStream_t s);
+
+// Front kernel (global, exact): built for some scaled penalties.  launch_bound
+// writes an upper bound of every pair's score steps; front_shape turns it into
+// what the pair needs (false: the front kernel does not hold the pair).  A
+// launch takes pairs of one form, `waves` wavefronts each, n and m the longest
+// sequences; offsets stored as they are (sh 0) hold every pair.
+bool front_supported(const Pen& pen);
+bool front_fits(uint32_t n, uint32_t m);
+bool front_shape(const Pen& pen, uint32_t n, uint32_t m, int bound, FrontShapeInfo* f);
+int front_blocks(int width, int cols);
+hipError_t launch_bound(const FrontArgs& a, const Pen& pen, int sh, int jobs, uint32_t n, uint32_t m,
+                        hipStream_t s);
+hipError_t launch_front(const FrontArgs& a, const Pen& pen, bool cigar, const FrontForm& f, int jobs,
+                        int waves, uint32_t n, uint32_t m, hipStream_t s);
 
 // rows16: 16-bit ring rows (every text of the launch shorter than 32767 bases)
 hipError_t launch_general(const GeneralArgs& a, int block_threads, bool seq_in_lds,

@@ -48,8 +48,9 @@ __device__ __forceinline__ uint32_t pk_max(uint32_t a, uint32_t b) {
 }
 __device__ __forceinline__ uint32_t pk_add(uint32_t a, uint32_t b) { return bits(as_u(a) + as_u(b)); }
 __device__ __forceinline__ uint32_t pk_sub(uint32_t a, uint32_t b) { return bits(as_u(a) - as_u(b)); }
-// The next three are written as instructions: from vector code the compiler
-// takes the halves apart again (a compare, a select and a permute for each).
+// The next ones are written as instructions: from vector code the compiler
+// takes the halves apart again (a compare, a select and a permute for each) or
+// spreads a mask over several operations.
 __device__ __forceinline__ uint32_t pk_minu(uint32_t a, uint32_t b) {
     uint32_t r;
     asm("v_pk_min_u16 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
@@ -65,6 +66,19 @@ __device__ __forceinline__ uint32_t pk_sign(uint32_t a) {
 __device__ __forceinline__ uint32_t pk_ne(uint32_t a, uint32_t b) {
     uint32_t r;
     asm("v_pk_min_u16 %0, %1, 1 op_sel_hi:[1,0]" : "=v"(r) : "v"(a ^ b));
+    return r;
+}
+// (mask & a) | (~mask & b)
+__device__ __forceinline__ uint32_t bit_select(uint32_t mask, uint32_t a, uint32_t b) {
+    uint32_t r;
+    asm("v_bfi_b32 %0, %1, %2, %3" : "=v"(r) : "v"(mask), "v"(a), "v"(b));
+    return r;
+}
+// (a << n) | b
+template <int N>
+__device__ __forceinline__ uint32_t shl_or(uint32_t a, uint32_t b) {
+    uint32_t r;
+    asm("v_lshl_or_b32 %0, %1, %2, %3" : "=v"(r) : "v"(a), "n"(N), "v"(b));
     return r;
 }
 // a wave-uniform mask of the lanes where c holds
@@ -159,7 +173,8 @@ struct Rows {
             if constexpr (CIGAR) {
                 const uint32_t nx = pk_ne(m[p], x), ni = pk_ne(m[p], i[p]);
                 const uint32_t ai = pk_ne(a[p], M[OE - 1][p]), ad = pk_ne(b[p], M[OE - 1][p]);
-                acc[p] = (fresh ? 0u : acc[p] << 4) | nx | (ni << 1) | (ai << 2) | (ad << 3);
+                const uint32_t rec = shl_or<1>(shl_or<1>(shl_or<1>(ad, ai), ni), nx);
+                acc[p] = fresh ? rec : shl_or<4>(acc[p], rec);
             }
         }
     }
@@ -212,14 +227,19 @@ struct Place {
     }
 };
 
-// 16 bases from bit position `b` (twice the base) of a sequence whose dwords
-// start at LDS byte `base`; q = b >> 5
-__device__ __forceinline__ uint32_t win16q(uint32_t base, int q, uint32_t b) {
+// dwords q and q + 1 of a sequence at LDS byte `base`
+__device__ __forceinline__ void two_dwords(uint32_t base, int q, uint32_t& w0, uint32_t& w1) {
     asm("" : "+v"(q));  // keeps q << 2 and the base in one instruction
     lds_p<const uint32_t> w = (lds_p<const uint32_t>)(uintptr_t)(base + ((uint32_t)q << 2));
-    return __builtin_amdgcn_alignbit(w[1], w[0], b);
+    w0 = w[0];
+    w1 = w[1];
 }
-__device__ __forceinline__ uint32_t win16(uint32_t base, int b) { return win16q(base, b >> 5, (uint32_t)b); }
+// 16 bases from bit position `b` (twice the base) on
+__device__ __forceinline__ uint32_t win16(uint32_t base, int b) {
+    uint32_t w0, w1;
+    two_dwords(base, b >> 5, w0, w1);
+    return __builtin_amdgcn_alignbit(w1, w0, (uint32_t)b);
+}
 
 // Extend the cells m of one step along matches (sequences in LDS at byte
 // addresses tb, pb) and drop those past the matrix.  Sixteen bases first;
@@ -233,8 +253,9 @@ __device__ __forceinline__ void extend(uint32_t (&m)[C / 2], const Place<C>& pl,
     for (int p = 0; p < P; p++) {
         const uint32_t u = pk_sub(pl.lim[p], m[p]);
         bad[p] = pk_sign(m[p] | u);
-        hv[p] = (pl.safe[p] & bad[p]) | (m[p] & ~bad[p]);
+        hv[p] = bit_select(bad[p], pl.safe[p], m[p]);
         rm[p] = u & ~bad[p];  // what is left before the matrix ends
+        asm("" : "+v"(rm[p]));
     }
     // bit position of column c in the text, bits left
     auto pos = [&](int c) -> uint32_t {
@@ -243,14 +264,25 @@ __device__ __forceinline__ void extend(uint32_t (&m)[C / 2], const Place<C>& pl,
     auto left = [&](int c) -> uint32_t {
         return ((c & 1) ? rm[c / 2] >> 16 : rm[c / 2] & 0xffffu) << (1 - SH);
     };
-    uint32_t lo = ~0u;
+    // every column's loads go out before the first is used (left to itself the
+    // compiler waits for each pair in turn)
+    uint32_t t0[C], t1[C], p0[C], p1[C];
+    int v[C];
 #pragma unroll
     for (int c = 0; c < C; c++) {
-        const int v = (int)pos(c) - pl.k2[c];
+        v[c] = (int)pos(c) - pl.k2[c];
         // the dword of the position straight from the packed offsets
         const uint32_t q = (c & 1) ? hv[c / 2] >> (20 + SH)
                                    : __builtin_amdgcn_ubfe(hv[c / 2], 4 + SH, 12 - SH);
-        x[c] = win16q(tb, (int)q, pos(c)) ^ win16(pb, v);
+        two_dwords(tb, (int)q, t0[c], t1[c]);
+        two_dwords(pb, v[c] >> 5, p0[c], p1[c]);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    uint32_t lo = ~0u;
+#pragma unroll
+    for (int c = 0; c < C; c++) {
+        x[c] = __builtin_amdgcn_alignbit(t1[c], t0[c], pos(c)) ^
+               __builtin_amdgcn_alignbit(p1[c], p0[c], (uint32_t)v[c]);
         uint32_t z;
         asm("v_ffbl_b32 %0, %1" : "=v"(z) : "v"(x[c]));  // ~0 for a zero word
         r[c] = min(z, left(c));  // bits; an odd one rounds down below
@@ -260,10 +292,10 @@ __device__ __forceinline__ void extend(uint32_t (&m)[C / 2], const Place<C>& pl,
 #pragma unroll
         for (int c = 0; c < C; c++) {
             if (x[c] == 0 && left(c) > 32) {
-                const int h = (int)pos(c), v = h - pl.k2[c];
+                const int h = (int)pos(c);
                 uint32_t done = 32, z;
                 do {
-                    const uint32_t y = win16(tb, h + (int)done) ^ win16(pb, v + (int)done);
+                    const uint32_t y = win16(tb, h + (int)done) ^ win16(pb, v[c] + (int)done);
                     asm("v_ffbl_b32 %0, %1" : "=v"(z) : "v"(y));
                     done += min(z, 32u);
                 } while (z >= 32 && done < left(c));
@@ -275,7 +307,7 @@ __device__ __forceinline__ void extend(uint32_t (&m)[C / 2], const Place<C>& pl,
     for (int p = 0; p < P; p++) {
         const uint32_t rr = SH ? (r[2 * p] | (r[2 * p + 1] << 16)) & 0xFFFEFFFEu
                                : (r[2 * p] >> 1) | ((r[2 * p + 1] >> 1) << 16);
-        m[p] = ((hv[p] + rr) & ~bad[p]) | (NUL16P & bad[p]);
+        m[p] = bit_select(bad[p], NUL16P, hv[p] + rr);
     }
 }
 
