@@ -153,6 +153,187 @@ void order_by(size_t n, uint32_t keys, Key&& key, std::vector<uint32_t>* order) 
     for (size_t i = 0; i < n; i++) (*order)[first[keys - key(i)]++] = (uint32_t)i;
 }
 
+// The pairs of `pending` the 16-bit kernels can hold, longest first (by classes
+// of 64 bases of n + m), those past 16383 bases (`past` of them) before all
+// others; positions in `pending`.  The rest follow at the end.
+struct ByLength {
+    std::vector<uint32_t> lens, order;
+    size_t held = 0, past = 0;
+    uint32_t n(size_t i) const { return lens[2 * i]; }
+    uint32_t m(size_t i) const { return lens[2 * i + 1]; }
+    void longest(size_t from, size_t to, uint32_t* pn, uint32_t* pm) const {
+        *pn = *pm = 0;
+        for (size_t i = from; i < to; i++) {
+            *pn = std::max(*pn, n(order[i]));
+            *pm = std::max(*pm, m(order[i]));
+        }
+    }
+};
+int order_by_length(Engine* e, const Dev& d, const std::vector<uint32_t>& pending, hipStream_t s,
+                    ByLength* b) {
+    RCCHK(pair_lengths(e, d, pending, s, &b->lens));
+    constexpr uint32_t CLASSES = 1024;
+    auto len_class = [&](size_t i) -> uint32_t {
+        if (!front_fits(b->n(i), b->m(i))) return 0;
+        const uint32_t c = 1 + std::min((b->n(i) + b->m(i)) / 64, CLASSES - 2);
+        return std::max(b->n(i), b->m(i)) > 16383 ? c + CLASSES : c;
+    };
+    order_by(pending.size(), 2 * CLASSES, len_class, &b->order);
+    b->held = pending.size();
+    while (b->held > 0 && len_class(b->order[b->held - 1]) == 0) b->held--;
+    while (b->past < b->held && len_class(b->order[b->past]) >= CLASSES) b->past++;
+    return WFA_OK;
+}
+
+// Grow the arena to `want` bytes, or to what the budget leaves (at least
+// `most`): false if not even that.  It keeps its size across calls; see
+// run_general.
+bool grow_arena(Workspace& ws, uint64_t want, uint64_t most) {
+    const size_t others = ws.total - ws.arena.bytes;
+    const size_t cap = ws.budget > others ? (ws.budget - others) / 4 * 3 : 0;
+    const size_t target = std::min<size_t>(want, cap);
+    if (ws.arena.bytes < target) {
+        ws.release(ws.arena);
+        size_t t = target;
+        int rc = ws.ensure(ws.arena, t);
+        while (rc != WFA_OK && t / 2 >= most) {
+            t /= 2;
+            rc = ws.ensure(ws.arena, t);
+        }
+        if (rc != WFA_OK) return false;
+    }
+    return ws.arena.bytes >= most;
+}
+
+// The buffers and counters of one launch of the front or adaptive kernels over
+// `fj` (their pairs: `ids`), and its read-back: pairs that failed go to `rest`.
+int begin_jobs(Engine* e, const std::vector<FrontJob>& fj, const std::vector<uint32_t>& ids, bool cigar,
+               FrontArgs* a, hipStream_t s) {
+    Workspace& ws = e->ws;
+    const size_t nj = fj.size();
+    RCCHK(ws.ensure(ws.jobs, nj * 4));
+    RCCHK(ws.ensure(ws.gen_slices, nj * sizeof(FrontJob)));
+    RCCHK(ws.ensure(ws.job_nruns, nj * 4));
+    RCCHK(ws.ensure(ws.job_offsets, (nj + 1) * 8));
+    RCCHK(ws.ensure(ws.fail_list, nj * 4));
+    RCCHK(ws.ensure(ws.scan_tmp, scan_temp_bytes(nj) + 64));
+    DevFlags* flags = ws.flags.as<DevFlags>();
+    HIPCHK(hipMemcpyAsync(ws.jobs.ptr, ids.data(), nj * 4, hipMemcpyHostToDevice, s));
+    HIPCHK(hipMemcpyAsync(ws.gen_slices.ptr, fj.data(), nj * sizeof(FrontJob), hipMemcpyHostToDevice, s));
+    FillOps fill{};
+    fill.add(ws.job_nruns.as<uint32_t>(), nj, 0u);
+    fill.add(&flags->fail_count, 1, 0u);
+    HIPCHK(launch_fill_multi(fill, s));
+    a->jobs = ws.gen_slices.as<FrontJob>();
+    a->job_nruns = ws.job_nruns.as<uint32_t>();
+    a->arena = cigar ? ws.arena.as<uint32_t>() : nullptr;
+    a->fail_list = ws.fail_list.as<uint32_t>();
+    a->fail_count = &flags->fail_count;
+    return WFA_OK;
+}
+int end_jobs(Engine* e, size_t nj, bool cigar, uint64_t& gen_used, std::vector<uint32_t>* rest,
+             uint64_t* done, hipStream_t s) {
+    Workspace& ws = e->ws;
+    uint32_t nfail = 0;
+    HIPCHK(hipMemcpyAsync(&nfail, &ws.flags.as<DevFlags>()->fail_count, 4, hipMemcpyDeviceToHost, s));
+    if (cigar) RCCHK(gather_runs(e, nj, gen_used, s));
+    HIPCHK(hipStreamSynchronize(s));
+    if (nfail) {
+        std::vector<uint32_t> f(nfail);
+        HIPCHK(hipMemcpy(f.data(), ws.fail_list.ptr, nfail * 4ull, hipMemcpyDeviceToHost));
+        rest->insert(rest->end(), f.begin(), f.end());
+    }
+    *done += nj - nfail;
+    return WFA_OK;
+}
+
+FrontArgs front_args(Engine* e, const Pen& pen, const Dev& d) {
+    FrontArgs a{};
+    a.pairs = d.pairs;
+    a.pw = d.pw;
+    a.tw = d.tw;
+    a.g = pen.g;
+    a.scores = d.scores;
+    a.nruns = e->ws.nruns.as<uint32_t>();
+    a.run_src = e->ws.run_src.as<uint64_t>();
+    a.heur = e->heur;
+    return a;
+}
+
+// Pairs in `pending` on the adaptive kernel; what it does not hold stays for
+// the general kernel.
+int run_adapt(Engine* e, const Pen& pen, bool cigar, const Dev& d, std::vector<uint32_t>& pending,
+              uint64_t& gen_used, hipStream_t s, uint64_t* done) {
+    Workspace& ws = e->ws;
+    ByLength b;
+    RCCHK(order_by_length(e, d, pending, s, &b));
+    if (!b.held || (ws.fixed_base && b.held < pending.size())) return WFA_OK;
+    std::vector<uint32_t> rest, ids;
+    for (size_t i = b.held; i < pending.size(); i++) rest.push_back(pending[b.order[i]]);
+    // records for three quarters of a step per base: reads at 10 % with
+    // gaps take half of that, and a pair past it goes to the general
+    // kernel.  Score-only runs have none to hold: any score is below n + m
+    // bases at the dearest price each.
+    auto job_of = [&](size_t i, uint64_t at) -> FrontJob {
+        const uint32_t n = b.n(i), m = b.m(i);
+        FrontJob j{};
+        j.pair = pending[i];
+        j.hist = at;
+        if (!cigar) {
+            j.bound = (int32_t)((n + m) * (uint64_t)std::max(pen.x, pen.oe) + 2);
+            return j;
+        }
+        j.bound = (int32_t)(std::max(n, m) / 4 * 3 + 64);
+        j.hist_words = ((uint64_t)(j.bound / 4 + 2) * ADAPT_QUAD_WORDS + 63) & ~63ull;
+        j.ev_words = (j.bound / std::min(pen.x, pen.oe) + 64) & ~63;
+        j.run_words = 2 * j.ev_words + 64;
+        return j;
+    };
+    auto words_of = [](const FrontJob& j) -> uint64_t {
+        return j.hist_words + (uint64_t)j.ev_words + (uint64_t)j.run_words;
+    };
+    if (cigar) {
+        uint64_t want = 0, most = 0;
+        for (size_t i = 0; i < b.held; i++) {
+            const uint64_t w = words_of(job_of(b.order[i], 0)) * 4;
+            want += w;
+            most = std::max(most, w);
+        }
+        if (!grow_arena(ws, want, most)) return WFA_OK;
+    }
+    FrontArgs a = front_args(e, pen, d);
+    std::vector<FrontJob> fj;
+    for (size_t off = 0; off < b.held;) {
+        fj.clear();
+        ids.clear();
+        uint64_t used = 0;
+        size_t end = off;
+        for (; end < b.held; end++) {
+            const FrontJob j = job_of(b.order[end], used);
+            if (cigar && (used + words_of(j)) * 4 > ws.arena.bytes) break;
+            used += words_of(j);
+            fj.push_back(j);
+            ids.push_back(j.pair);
+        }
+        RCCHK(begin_jobs(e, fj, ids, cigar, &a, s));
+        const size_t split = std::min(std::max(b.past, off), end);  // pairs past 16383 bases end here
+        uint32_t n, m;
+        b.longest(off, split, &n, &m);
+        HIPCHK(launch_adapt(a, pen, cigar, 0, (int)(split - off), n, m, s));
+        a.jobs += split - off;
+        a.job_nruns += split - off;
+        b.longest(split, end, &n, &m);
+        HIPCHK(launch_adapt(a, pen, cigar, 1, (int)(end - split), n, m, s));
+        RCCHK(end_jobs(e, end - off, cigar, gen_used, &rest, done, s));
+        off = end;
+    }
+    std::sort(rest.begin(), rest.end());
+    pending.swap(rest);
+    if (std::getenv("WFA_DEBUG"))
+        std::fprintf(stderr, "libwfa adaptive: %zu pairs left for the general kernel\n", pending.size());
+    return WFA_OK;
+}
+
 // Pairs in `pending` on the front kernel (global alignment, exact, penalties
 // it is built for); what it does not hold stays in `pending` for the general
 // kernel.  The host reads the score bounds back to size every pair's rows,
@@ -160,44 +341,16 @@ void order_by(size_t n, uint32_t keys, Key&& key, std::vector<uint32_t>* order) 
 int run_front(Engine* e, const Pen& pen, bool cigar, const Dev& d, std::vector<uint32_t>& pending,
               uint64_t& gen_used, hipStream_t s, uint64_t* done) {
     Workspace& ws = e->ws;
-    std::vector<uint32_t> lens;
-    RCCHK(pair_lengths(e, d, pending, s, &lens));
-    const size_t np = pending.size();
-    auto n_of = [&](size_t i) { return lens[2 * i]; };
-    auto m_of = [&](size_t i) { return lens[2 * i + 1]; };
-    // longest pairs first (by classes of 64 bases of n + m), pairs past 16383
-    // bases before all others, pairs past the kernel's lengths last
-    constexpr uint32_t LEN_CLASSES = 1024;
-    auto len_class = [&](size_t i) -> uint32_t {
-        if (!front_fits(n_of(i), m_of(i))) return 0;
-        const uint32_t c = 1 + std::min((n_of(i) + m_of(i)) / 64, LEN_CLASSES - 2);
-        return std::max(n_of(i), m_of(i)) > 16383 ? c + LEN_CLASSES : c;
-    };
-    std::vector<uint32_t> order;
-    order_by(np, 2 * LEN_CLASSES, len_class, &order);
-    size_t nf = np, n16 = 0;
-    while (nf > 0 && len_class(order[nf - 1]) == 0) nf--;
-    while (n16 < nf && len_class(order[n16]) >= LEN_CLASSES) n16++;
+    ByLength b;
+    RCCHK(order_by_length(e, d, pending, s, &b));
+    const std::vector<uint32_t>& order = b.order;
+    const size_t np = pending.size(), nf = b.held, n16 = b.past;
     // the fixed region of the allocation-free entry point cannot hold an arena
     // for either kernel: a batch with pairs for both is the general kernel's
     if (!nf || (ws.fixed_base && nf < np)) return WFA_OK;
     std::vector<uint32_t> rest;
     for (size_t i = nf; i < np; i++) rest.push_back(pending[order[i]]);
-    auto longest = [&](const uint32_t* idx, size_t cnt, uint32_t* n, uint32_t* m) {
-        *n = *m = 0;
-        for (size_t i = 0; i < cnt; i++) {
-            *n = std::max(*n, n_of(idx[i]));
-            *m = std::max(*m, m_of(idx[i]));
-        }
-    };
-    FrontArgs a{};
-    a.pairs = d.pairs;
-    a.pw = d.pw;
-    a.tw = d.tw;
-    a.g = pen.g;
-    a.scores = d.scores;
-    a.nruns = ws.nruns.as<uint32_t>();
-    a.run_src = ws.run_src.as<uint64_t>();
+    FrontArgs a = front_args(e, pen, d);
     uint32_t n, m;
 
     // ---- score bounds ------------------------------------------------------
@@ -208,11 +361,11 @@ int run_front(Engine* e, const Pen& pen, bool cigar, const Dev& d, std::vector<u
     HIPCHK(hipMemcpyAsync(ws.jobs.ptr, ids.data(), nf * 4, hipMemcpyHostToDevice, s));
     a.ids = ws.jobs.as<uint32_t>();
     a.bounds = ws.gen_state.as<int32_t>();
-    longest(order.data(), n16, &n, &m);
+    b.longest(0, n16, &n, &m);
     HIPCHK(launch_bound(a, pen, 0, (int)n16, n, m, s));
     a.ids += n16;
     a.bounds += n16;
-    longest(order.data() + n16, nf - n16, &n, &m);
+    b.longest(n16, nf, &n, &m);
     HIPCHK(launch_bound(a, pen, 1, (int)(nf - n16), n, m, s));
     HIPCHK(hipMemcpyAsync(bounds.data(), ws.gen_state.ptr, nf * 4, hipMemcpyDeviceToHost, s));
     HIPCHK(hipStreamSynchronize(s));
@@ -236,7 +389,7 @@ int run_front(Engine* e, const Pen& pen, bool cigar, const Dev& d, std::vector<u
     for (size_t i = 0; i < nf; i++) {
         Job j{};
         j.idx = order[i];
-        if (!front_shape(pen, n_of(j.idx), m_of(j.idx), bounds[i], &j.f)) {
+        if (!front_shape(pen, b.n(j.idx), b.m(j.idx), bounds[i], &j.f)) {
             rest.push_back(pending[j.idx]);
             continue;
         }
@@ -266,22 +419,7 @@ int run_front(Engine* e, const Pen& pen, bool cigar, const Dev& d, std::vector<u
         const Job& j = held[i];
         return ((1 - j.form.sh) * 4 + (j.form.cols == 4 ? 2 : 0) + (j.form.blocks - 1)) * 32 + j.waves;
     }, &by_work);
-    if (cigar) {  // the arena keeps its size across calls; see run_general
-        const size_t others = ws.total - ws.arena.bytes;
-        const size_t cap = ws.budget > others ? (ws.budget - others) / 4 * 3 : 0;
-        const size_t target = std::min<size_t>(want, cap);
-        if (ws.arena.bytes < target) {
-            ws.release(ws.arena);
-            size_t t = target;
-            int rc = ws.ensure(ws.arena, t);
-            while (rc != WFA_OK && t / 2 >= most) {
-                t /= 2;
-                rc = ws.ensure(ws.arena, t);
-            }
-            if (rc != WFA_OK) return WFA_OK;  // the general kernel needs less
-        }
-        if (ws.arena.bytes < most) return WFA_OK;
-    }
+    if (cigar && !grow_arena(ws, want, most)) return WFA_OK;  // the general kernel needs less
     if (std::getenv("WFA_DEBUG")) {
         double sum = 0;
         for (const Job& j : held) sum += j.f.bound;
@@ -307,22 +445,7 @@ int run_front(Engine* e, const Pen& pen, bool cigar, const Dev& d, std::vector<u
             used += w;
         }
         const size_t nj = end - off;
-        RCCHK(ws.ensure(ws.jobs, nj * 4));
-        RCCHK(ws.ensure(ws.gen_slices, nj * sizeof(FrontJob)));
-        RCCHK(ws.ensure(ws.job_nruns, nj * 4));
-        RCCHK(ws.ensure(ws.job_offsets, (nj + 1) * 8));
-        RCCHK(ws.ensure(ws.fail_list, nj * 4));
-        RCCHK(ws.ensure(ws.scan_tmp, scan_temp_bytes(nj) + 64));
-        DevFlags* flags = ws.flags.as<DevFlags>();
-        HIPCHK(hipMemcpyAsync(ws.jobs.ptr, ids.data(), nj * 4, hipMemcpyHostToDevice, s));
-        HIPCHK(hipMemcpyAsync(ws.gen_slices.ptr, fj.data(), nj * sizeof(FrontJob), hipMemcpyHostToDevice, s));
-        FillOps fill{};
-        fill.add(ws.job_nruns.as<uint32_t>(), nj, 0u);
-        fill.add(&flags->fail_count, 1, 0u);
-        HIPCHK(launch_fill_multi(fill, s));
-        a.arena = cigar ? ws.arena.as<uint32_t>() : nullptr;
-        a.fail_list = ws.fail_list.as<uint32_t>();
-        a.fail_count = &flags->fail_count;
+        RCCHK(begin_jobs(e, fj, ids, cigar, &a, s));
         for (size_t i = 0; i < nj;) {
             // a launch: workgroups of one size.  Smaller pairs join while the
             // group would not fill the chip, or lacks few wavefronts.
@@ -333,24 +456,15 @@ int run_front(Engine* e, const Pen& pen, bool cigar, const Dev& d, std::vector<u
                 const Job& g = held[by_work[off + k]];
                 if (!same_form(g.form, f.form)) break;
                 if (4 * g.waves <= 3 * f.waves && k - i >= 2 * (size_t)e->num_cus) break;
-                n = std::max(n, n_of(g.idx));
-                m = std::max(m, m_of(g.idx));
+                n = std::max(n, b.n(g.idx));
+                m = std::max(m, b.m(g.idx));
             }
             a.jobs = ws.gen_slices.as<FrontJob>() + i;
             a.job_nruns = ws.job_nruns.as<uint32_t>() + i;
             HIPCHK(launch_front(a, pen, cigar, f.form, (int)(k - i), f.waves, n, m, s));
             i = k;
         }
-        uint32_t nfail = 0;
-        HIPCHK(hipMemcpyAsync(&nfail, &flags->fail_count, 4, hipMemcpyDeviceToHost, s));
-        if (cigar) RCCHK(gather_runs(e, nj, gen_used, s));
-        HIPCHK(hipStreamSynchronize(s));
-        if (nfail) {
-            std::vector<uint32_t> f(nfail);
-            HIPCHK(hipMemcpy(f.data(), ws.fail_list.ptr, nfail * 4ull, hipMemcpyDeviceToHost));
-            rest.insert(rest.end(), f.begin(), f.end());
-        }
-        *done += nj - nfail;
+        RCCHK(end_jobs(e, nj, cigar, gen_used, &rest, done, s));
         off = end;
     }
     std::sort(rest.begin(), rest.end());
@@ -1258,12 +1372,14 @@ int engine_align_device(Engine* e, const BatchIO& io, hipStream_t user_stream,
     // offsets and runs are written, so nothing more runs on the device
     const bool tail = !pending.empty() || !use_short || fl.ovf_count > 0;
     if (tail) HIPCHK(hipEventRecord(e->ev[2], s));
-    // The front kernel first, unless the caller chose a form of the general
-    // kernel's memory or a step limit.
-    if (!pending.empty() && global && e->heur.mwl == 0 && front_supported(pen) &&
+    // The front kernel first, or under the heuristic the adaptive one, unless
+    // the caller chose a form of the general kernel's memory or a step limit.
+    const bool heuristic = e->heur.mwl > 0;
+    if (!pending.empty() && global && (heuristic ? adapt_supported(pen) : front_supported(pen)) &&
         e->opt.general_step_limit == 0 && e->opt.general_checkpoint == 0 &&
         e->opt.general_slice_kib == 0 && e->opt.general_pairs == 0) {
-        const int rf = run_front(e, pen, cigar, d, pending, gen_used, s, &general_done);
+        const int rf = (heuristic ? run_adapt : run_front)(e, pen, cigar, d, pending, gen_used, s,
+                                                           &general_done);
         if (rf != WFA_OK) {
             (void)finish_user();
             return rf;

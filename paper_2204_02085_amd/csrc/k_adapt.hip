@@ -1,0 +1,349 @@
+// Adaptive kernel: the WF-adaptive heuristic, one wavefront per pair.
+//
+// The reduction keeps a wavefront to the diagonals near its furthest points,
+// usually a few dozen, so a pair's rows fit the registers of one wavefront: a
+// window of 128 diagonals, two per lane, that moves along with the reduced
+// ranges, and a second block of 128 beside it while they are wider.  Where k_general spent a workgroup, several barriers and row traffic
+// on every step, a step here is about 130 instructions of one wavefront, the
+// least distance by DPP and the kept range by two ballots.
+//
+// What bounds it: VALU issue, 0.75 of it over 10 k pairs of 1-10 kbp at 5-10 %
+// under the thresholds (10, 50), 4.3 ms with CIGARs (whole call 4.8 ms; 32.5 ms on
+// the general kernel).  The second block inside the same kernel: 22 of those
+// pairs outgrow 128 diagonals for a stretch, and aligning them again in a wider
+// window took another 4.7 ms, the latency of their chains.
+//
+// The reduction measures every cell, on an optimal path or not, so offsets
+// here follow the recurrences to the letter: a candidate past the matrix is
+// dropped before the maximum (as an unsigned distance below the diagonal's
+// limit, like the general kernel's), in I and D too, and the ranges of steps
+// are those of the sources widened by one and clipped to the matrix.
+//
+// A pair whose ranges outgrow the window, or that needs more steps than its
+// records hold, goes to the general kernel.
+#include <hip/hip_runtime.h>
+#include <stdint.h>
+
+#include <algorithm>
+#include <type_traits>
+
+#include "kernels.h"
+#include "rows.h"
+#include "walk.h"
+
+namespace wfa {
+
+namespace {
+
+using namespace rows;
+
+constexpr int WALK_DW = 1024;  // dwords of the walk's record window in LDS
+
+// smallest of the lanes' values, in every lane
+__device__ __forceinline__ int wave_min(int v) { return -wave_max(-v); }
+
+// The window is two blocks of 128 diagonals, two per lane and block; the second
+// is computed only while the ranges do not fit the first.
+template <int X, int OE, int E, int SH, bool CIGAR>
+__global__ __launch_bounds__(64) void k_adapt(FrontArgs a) {
+    constexpr int NB = 2, BW = 128, AW = NB * BW;
+    constexpr int RM = X > OE ? X : OE;
+    constexpr uint32_t ONE = SH ? 0x00020002u : 0x00010001u;
+    extern __shared__ __align__(16) unsigned char lds[];
+    const FrontJob job = a.jobs[blockIdx.x];
+    const PairDesc d = a.pairs[job.pair];
+    const int n = (int)d.p_len, m = (int)d.t_len, kt = m - n;
+    const int lane = threadIdx.x;
+    lds_p<uint32_t> win = (lds_p<uint32_t>)lds;
+    lds_p<uint64_t> seq = (lds_p<uint64_t>)(win + (CIGAR ? WALK_DW : 0));
+    stage(seq, a.pw, a.tw, d, lane, 64);
+    wave_fence();
+    const uint32_t tb = (uint32_t)(uintptr_t)seq, pb = tb + 8 * text_words(m);
+    const int MWL = a.heur.mwl, MDT = a.heur.mdt;
+    uint32_t* hist = CIGAR ? a.arena + job.hist : nullptr;  // per quad: the records, the window's base
+
+    int kmin = -BW / 2;
+    Place<2> pl[NB];
+    uint32_t inside[NB];  // 0xffff in the halves whose diagonal is in the matrix
+    auto place = [&]() {
+#pragma unroll
+        for (int b = 0; b < NB; b++) {
+            pl[b].template set<SH>(n, m, kmin + BW * b + 2 * lane);
+            inside[b] = ~pk_sign(pl[b].lim[0]);
+        }
+    };
+    place();
+    uint32_t M[RM][NB], I[E][NB], D[E][NB], acc[NB];
+#pragma unroll
+    for (int b = 0; b < NB; b++) {
+        acc[b] = 0;
+#pragma unroll
+        for (int j = 0; j < RM; j++) M[j][b] = NUL16P;
+#pragma unroll
+        for (int j = 0; j < E; j++) I[j][b] = D[j][b] = NUL16P;
+    }
+    auto shift_up = [&](uint32_t (&r)[NB]) {  // one lane: the window moves two diagonals up
+        r[0] = wave_next((uint32_t)__builtin_amdgcn_readlane((int)r[1], 0), r[0]);
+        r[1] = wave_next(NUL16P, r[1]);
+    };
+    auto shift_down = [&](uint32_t (&r)[NB]) {
+        r[1] = wave_prev((uint32_t)__builtin_amdgcn_readlane((int)r[0], 63), r[1]);
+        r[0] = wave_prev(NUL16P, r[0]);
+    };
+    // ranges of the last RM steps; lo > hi: no wavefront
+    constexpr int NONE = 1 << 29;
+    int lo[RM], hi[RM];
+#pragma unroll
+    for (int j = 0; j < RM; j++) {
+        lo[j] = NONE;
+        hi[j] = -NONE;
+    }
+    int S = -1;
+    // four steps on the first nb blocks
+    auto quad = [&](int s, auto blocks) {
+        constexpr int nb = decltype(blocks)::value;
+#pragma unroll
+        for (int u = 0; u < 4; u++) {
+            if (S >= 0) break;
+            // the step's range: its sources', one wider, inside the matrix
+            int l = min(min(lo[X - 1], lo[OE - 1]), lo[E - 1]);
+            int h = max(max(hi[X - 1], hi[OE - 1]), hi[E - 1]);
+            bool present = l <= h;
+            l = max(l - 1, -n);
+            h = min(h + 1, m);
+            uint32_t cm[NB], ci[NB], cd[NB], rec[NB];
+#pragma unroll
+            for (int b = 0; b < NB; b++) {
+                cm[b] = ci[b] = cd[b] = NUL16P;
+                rec[b] = 0;
+            }
+            if (u == 0 && s == 0) {
+                present = true;
+                l = h = 0;
+                if (lane == 32) cm[0] = 0xC0000000u;  // M_0[0] = 0
+                uint32_t c1[1] = {cm[0]};
+                extend<2, SH>(c1, pl[0], tb, pb);
+                cm[0] = c1[0];
+            } else if (present) {
+#pragma unroll
+                for (int b = 0; b < nb; b++) {
+                    // the columns before and after, across the blocks' border
+                    auto up = [&](const uint32_t (&r)[NB]) {
+                        const uint32_t end = b ? (uint32_t)__builtin_amdgcn_readlane((int)r[b ? b - 1 : 0], 63) : NUL16P;
+                        return __builtin_amdgcn_alignbit(r[b], wave_prev(end, r[b]), 16);
+                    };
+                    auto down = [&](const uint32_t (&r)[NB]) {
+                        const uint32_t end = b + 1 < nb ? (uint32_t)__builtin_amdgcn_readlane((int)r[b + 1 < nb ? b + 1 : b], 0) : NUL16P;
+                        return __builtin_amdgcn_alignbit(wave_next(end, r[b]), r[b], 16);
+                    };
+                    // distances below the limit: past it they wrap to huge,
+                    // NULL is past L
+                    const uint32_t L = pl[b].lim[0];
+                    const uint32_t tio = pk_sub(L, pk_add(up(M[OE - 1]), ONE)), tdo = pk_sub(L, down(M[OE - 1]));
+                    const uint32_t tx = pk_sub(L, pk_add(M[X - 1][b], ONE));
+                    const uint32_t ti = pk_minu(tio, pk_sub(L, pk_add(up(I[E - 1]), ONE)));
+                    const uint32_t td = pk_minu(tdo, pk_sub(L, down(D[E - 1])));
+                    const uint32_t tm = pk_minu(pk_minu(tx, ti), td);
+                    if (CIGAR)
+                        rec[b] = shl_or<1>(shl_or<1>(shl_or<1>(pk_ne(tdo, td), pk_ne(tio, ti)), pk_ne(ti, tm)),
+                                           pk_ne(tx, tm));
+                    ci[b] = pk_sub(L, ti);
+                    cd[b] = pk_sub(L, td);
+                    ci[b] = bit_select(pk_sign(ci[b] | ti | ~inside[b]), NUL16P, ci[b]);
+                    cd[b] = bit_select(pk_sign(cd[b] | td | ~inside[b]), NUL16P, cd[b]);
+                    uint32_t c1[1] = {bit_select(inside[b], pk_sub(L, tm), NUL16P)};
+                    extend<2, SH>(c1, pl[b], tb, pb);
+                    cm[b] = c1[0];
+                }
+            }
+            if (CIGAR) {
+#pragma unroll
+                for (int b = 0; b < nb; b++) acc[b] = u ? shl_or<4>(acc[b], rec[b]) : rec[b];
+            }
+            const int tc = kt - kmin;
+            const uint32_t treg = nb > 1 && tc >= BW ? cm[NB - 1] : cm[0];
+            if (tc >= 0 && tc < nb * BW && half_at(treg, (tc & (BW - 1)) >> 1, tc & 1) == m << SH) {
+                S = s + u;  // the step that reaches the end is not reduced
+            } else if (present && h - l + 1 >= MWL) {
+                // distances to the end: max(n + k, m) - M, in the offsets' units
+                constexpr int FAR = 1 << 28;
+                int dist[2 * NB], least = FAR;
+#pragma unroll
+                for (int c = 0; c < 2 * nb; c++) {
+                    const int v = (int)(short)(cm[c / 2] >> (16 * (c & 1)));
+                    const int k = kmin + BW * (c / 2) + 2 * lane + (c & 1);
+                    dist[c] = v >= 0 ? (max(n + k, m) << SH) - v : FAR;
+                    least = min(least, dist[c]);
+                }
+                least = wave_min(least);
+                if (least != FAR) {
+                    const int lim = min(least + (int)min((long long)MDT << SH, (long long)FAR), FAR - 1);
+                    int rl = AW, rh = -1;  // kept columns
+#pragma unroll
+                    for (int c = 0; c < 2 * nb; c++) {
+                        const uint64_t in = lanes_where(dist[c] <= lim);
+                        if (in) {
+                            rl = min(rl, BW * (c / 2) + 2 * (int)__builtin_ctzll(in) + (c & 1));
+                            rh = max(rh, BW * (c / 2) + 2 * (63 - (int)__builtin_clzll(in)) + (c & 1));
+                        }
+                    }
+                    l = kmin + rl;
+                    h = kmin + rh;
+#pragma unroll
+                    for (int b = 0; b < nb; b++) {
+                        const int c = BW * b + 2 * lane;
+                        const uint32_t keep = (c >= rl && c <= rh ? 0xffffu : 0u) |
+                                              (c + 1 >= rl && c + 1 <= rh ? 0xffff0000u : 0u);
+                        cm[b] = bit_select(keep, cm[b], NUL16P);
+                        ci[b] = bit_select(keep, ci[b], NUL16P);
+                        cd[b] = bit_select(keep, cd[b], NUL16P);
+                    }
+                }
+            }
+#pragma unroll
+            for (int j = RM - 1; j > 0; j--) {
+                lo[j] = lo[j - 1];
+                hi[j] = hi[j - 1];
+            }
+            lo[0] = present ? l : NONE;
+            hi[0] = present ? h : -NONE;
+#pragma unroll
+            for (int b = 0; b < nb; b++) {
+#pragma unroll
+                for (int j = RM - 1; j > 0; j--) M[j][b] = M[j - 1][b];
+#pragma unroll
+                for (int j = E - 1; j > 0; j--) {
+                    I[j][b] = I[j - 1][b];
+                    D[j][b] = D[j - 1][b];
+                }
+                M[0][b] = cm[b];
+                I[0][b] = ci[b];
+                D[0][b] = cd[b];
+            }
+            if (CIGAR && (u == 3 || S >= 0)) {
+                uint32_t* q = hist + (uint64_t)(s >> 2) * ADAPT_QUAD_WORDS;
+#pragma unroll
+                for (int b = 0; b < nb; b++) q[64 * b + lane] = acc[b] << (4 * (3 - u));
+                if (lane == 0) q[64 * NB] = (uint32_t)kmin;
+            }
+        }
+    };
+    for (int s = 0; S < 0; s += 4) {
+        // the rows' ranges, four steps on, inside the first block or, if they
+        // are wider, inside both
+        int ul = NONE, uh = -NONE;
+#pragma unroll
+        for (int j = 0; j < RM; j++) {
+            ul = min(ul, lo[j]);
+            uh = max(uh, hi[j]);
+        }
+        if (s == 0) ul = uh = 0;
+        const int width = uh - ul + 1 + 8;
+        if (s > job.bound || ul > uh || width + 2 > AW) break;
+        const int room = width + 2 <= BW ? BW : AW;
+        if (ul - 4 < kmin || uh + 4 > kmin + room - 1) {
+            int shift = (((ul + uh) >> 1) - room / 2 - kmin) / 2;  // lanes
+            kmin += 2 * shift;
+            for (; shift > 0; shift--) {
+#pragma unroll
+                for (int j = 0; j < RM; j++) shift_up(M[j]);
+#pragma unroll
+                for (int j = 0; j < E; j++) {
+                    shift_up(I[j]);
+                    shift_up(D[j]);
+                }
+            }
+            for (; shift < 0; shift++) {
+#pragma unroll
+                for (int j = 0; j < RM; j++) shift_down(M[j]);
+#pragma unroll
+                for (int j = 0; j < E; j++) {
+                    shift_down(I[j]);
+                    shift_down(D[j]);
+                }
+            }
+            place();
+        }
+        if (room == BW) quad(s, std::integral_constant<int, 1>{});
+        else quad(s, std::integral_constant<int, 2>{});
+    }
+    if (S < 0) {  // outgrew the window, or its records
+        if (lane == 0) a.fail_list[atomicAdd(a.fail_count, 1u)] = job.pair;
+        return;
+    }
+    if (!CIGAR) {
+        if (lane == 0) {
+            a.scores[job.pair] = S * a.g;
+            a.nruns[job.pair] = 0;
+        }
+        return;
+    }
+    // the walk, WQ quads of steps of the records in LDS at a time (what a quad
+    // left unwritten of its second block is never on the way)
+    constexpr int QW = 64 * NB, WQ = WALK_DW / QW;
+    __threadfence_block();
+    uint32_t* evs = hist + job.hist_words;
+    uint32_t* runs_end = evs + job.ev_words + job.run_words;
+    int qtop = -1;
+    uint32_t bases = 0;  // lane i: the window's base at quad qtop - i
+    auto record = [&](int s, int k, bool& bad) -> uint32_t {
+        const int q = s >> 2;
+        if (q > qtop || q <= qtop - WQ) {
+            qtop = q;
+            wave_fence();
+#pragma unroll 4
+            for (int i = 0; i < WQ * NB; i++) {
+                const int r = i / NB, w = (i % NB) * 64 + lane;
+                win[i * 64 + lane] = q - r >= 0 ? hist[(uint64_t)(q - r) * ADAPT_QUAD_WORDS + w] : 0u;
+            }
+            bases = lane < WQ && q - lane >= 0 ? hist[(uint64_t)(q - lane) * ADAPT_QUAD_WORDS + QW] : 0u;
+            wave_fence();
+        }
+        const int col = k - __builtin_amdgcn_readlane((int)bases, qtop - q);
+        if (col < 0 || col >= AW) {
+            bad = true;
+            return 0;
+        }
+        const uint32_t word = (uint32_t)__builtin_amdgcn_readfirstlane((int)win[(qtop - q) * QW + (col >> 1)]);
+        return record_of(word, s, col);
+    };
+    const int nr = walk<X, OE, E, true>(record, S, n, m, lane, evs, job.ev_words, runs_end, job.run_words,
+                                        tb, pb);
+    walk_done(a, job, S, nr, runs_end, lane);
+}
+
+// Scaled penalties (x, o + e, e) the rows are built for.
+#define WFA_ADAPT_PENS(F) \
+    F(2, 4, 1)            \
+    F(1, 1, 1)            \
+    F(2, 5, 1)
+
+}  // namespace
+
+bool adapt_supported(const Pen& pen) {
+#define WFA_CASE(PX, POE, PE) \
+    if (pen.x == PX && pen.oe == POE && pen.e == PE) return true;
+    WFA_ADAPT_PENS(WFA_CASE)
+#undef WFA_CASE
+    return false;
+}
+
+hipError_t launch_adapt(const FrontArgs& a, const Pen& pen, bool cigar, int sh, int jobs, uint32_t n,
+                        uint32_t m, hipStream_t s) {
+    if (!jobs) return hipSuccess;
+    const int lds = (cigar ? WALK_DW * 4 : 0) + seq_lds_bytes(n, m);
+#define WFA_GO(PX, POE, PE, SHF, CG) \
+    hipLaunchKernelGGL((k_adapt<PX, POE, PE, SHF, CG>), dim3(jobs), dim3(64), lds, s, a)
+#define WFA_CASE(PX, POE, PE)                                                                    \
+    if (pen.x == PX && pen.oe == POE && pen.e == PE) {                                           \
+        if (cigar) { if (sh) WFA_GO(PX, POE, PE, 1, true); else WFA_GO(PX, POE, PE, 0, true); }  \
+        else { if (sh) WFA_GO(PX, POE, PE, 1, false); else WFA_GO(PX, POE, PE, 0, false); }      \
+        return hipGetLastError();                                                                \
+    }
+    WFA_ADAPT_PENS(WFA_CASE)
+#undef WFA_CASE
+#undef WFA_GO
+    return hipErrorInvalidValue;
+}
+
+}  // namespace wfa

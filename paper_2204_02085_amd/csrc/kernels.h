@@ -170,6 +170,7 @@ struct FrontArgs {
     uint32_t* job_nruns;        // [jobs] runs (zeroed before the launch)
     uint32_t* fail_list;        // pairs handed to the general kernel
     uint32_t* fail_count;
+    Heuristic heur;             // k_adapt: the reduction
 };
 
 // What a pair needs on the front kernel.
@@ -328,6 +329,15 @@ hipError_t launch_bound(const FrontArgs& a, const Pen& pen, int sh, int jobs, ui
                         hipStream_t s);
 hipError_t launch_front(const FrontArgs& a, const Pen& pen, bool cigar, const FrontForm& f, int jobs,
                         int waves, uint32_t n, uint32_t m, hipStream_t s);
+
+// Adaptive kernel (the WF-adaptive heuristic, global): one wavefront per pair,
+// built for some scaled penalties; a job's `bound` is the last step its records
+// hold (ADAPT_QUAD_WORDS words per four steps), pairs it does not hold go to
+// the fail list.  A launch takes pairs of one `sh` (1: up to 16383 bases).
+constexpr int ADAPT_QUAD_WORDS = 2 * 64 + 1;  // both blocks' records, the window's base
+bool adapt_supported(const Pen& pen);
+hipError_t launch_adapt(const FrontArgs& a, const Pen& pen, bool cigar, int sh, int jobs, uint32_t n,
+                        uint32_t m, hipStream_t s);
 
 // rows16: 16-bit ring rows (every text of the launch shorter than 32767 bases)
 hipError_t launch_general(const GeneralArgs& a, int block_threads, bool seq_in_lds,
