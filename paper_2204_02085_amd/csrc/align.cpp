@@ -191,8 +191,11 @@ int order_by_length(Engine* e, const Dev& d, const std::vector<uint32_t>& pendin
 bool grow_arena(Workspace& ws, uint64_t want, uint64_t most) {
     const size_t others = ws.total - ws.arena.bytes;
     const size_t cap = ws.budget > others ? (ws.budget - others) / 4 * 3 : 0;
-    const size_t target = std::min<size_t>(want, cap);
-    if (ws.arena.bytes < target) {
+    // in steps of 64 MiB, so that batches of similar size seldom grow it again
+    // (a growth waits for the stream and maps the memory anew)
+    constexpr size_t STEP = (size_t)64 << 20;
+    const size_t target = std::min<size_t>(ws.fixed_base ? want : (want + STEP - 1) / STEP * STEP, cap);
+    if (ws.arena.bytes < std::min<size_t>(want, cap)) {
         ws.release(ws.arena);
         size_t t = target;
         int rc = ws.ensure(ws.arena, t);

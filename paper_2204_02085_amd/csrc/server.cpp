@@ -64,6 +64,8 @@ struct wfa_server {
     std::mutex mu;
     std::condition_variable cv_work, cv_done;
     std::deque<uint64_t> fifo;  // tickets with unadmitted pairs, arrival order
+    size_t queued_pairs = 0;    // pairs not yet admitted
+    size_t backlog = 0;         // the same when the last request came in
     std::map<uint64_t, std::unique_ptr<Request>> reqs;
     uint64_t next_ticket = 1;
     bool stop = false;
@@ -106,49 +108,94 @@ size_t pair_bytes(const wfa_server_cfg& cfg, uint32_t n, uint32_t m) {
     return io + (size_t)wf;
 }
 
-// Run one merged batch on an engine (or the user's executor).
-int run_batch(wfa_server* srv, Engine* eng, const wfa_request& rq, std::vector<int32_t>& scores,
-              std::vector<uint32_t>& runs, std::vector<uint64_t>& offsets) {
+// A worker's host buffer, kept from batch to batch and grown by doubling:
+// page-locked where the worker has an engine, so the batch's copies run by DMA
+// without staging.
+struct HostBuf {
+    void* ptr = nullptr;
+    size_t bytes = 0;
+    bool locked = false;
+    ~HostBuf() { drop(); }
+    void drop() {
+        if (locked) (void)hipHostFree(ptr);
+        else std::free(ptr);
+        ptr = nullptr;
+        bytes = 0;
+    }
+    // at least `want` bytes, contents lost when it grows; false: out of memory
+    bool ensure(size_t want, bool lock) {
+        if (bytes >= want && ptr) return true;
+        // from 2 MiB on: pinning memory stalls the device's other streams
+        const size_t size = std::max({want, 2 * bytes, (size_t)2 << 20});
+        drop();
+        locked = lock && hipHostMalloc(&ptr, size, hipHostMallocDefault) == hipSuccess;
+        if (!locked) {
+            if (lock) (void)hipGetLastError();
+            ptr = std::malloc(size);
+        }
+        bytes = ptr ? size : 0;
+        return ptr != nullptr;
+    }
+    template <class T>
+    T* as() const {
+        return (T*)ptr;
+    }
+};
+
+struct WorkerBufs {
+    HostBuf pat, txt, pairs, scores, runs, offsets;
+};
+
+// Run one merged batch on an engine (or the user's executor); the results land
+// in `w`, *needed receives the runs.
+int run_batch(wfa_server* srv, Engine* eng, const wfa_request& rq, WorkerBufs& w, size_t* needed) {
     const bool cigar = srv->cfg.mode == WFA_CIGAR;
+    const bool lock = eng != nullptr;
     const size_t n = rq.num_pairs;
-    scores.assign(n, 0);
-    offsets.assign(n + 1, 0);
+    if (!w.scores.ensure(n * 4, lock) || !w.offsets.ensure((n + 1) * 8, lock)) return WFA_E_NOMEM;
+    int32_t* scores = w.scores.as<int32_t>();
+    uint64_t* offsets = cigar ? w.offsets.as<uint64_t>() : nullptr;
+    std::fill(scores, scores + n, 0);
     // runs: at most n + m + 1 per pair; a quarter of that covers any pair
     // within ~10 % divergence, and a larger need triggers one exact re-run
-    size_t cap = 64;
-    if (cigar)
+    size_t cap = 0;
+    if (cigar) {
+        cap = 64;
         for (size_t i = 0; i < n; i++) cap += ((size_t)rq.pairs[i].p_len + rq.pairs[i].t_len) / 4 + 8;
-    else
-        cap = 0;
+        std::fill(offsets, offsets + n + 1, 0);
+    }
+    *needed = 0;
     for (int attempt = 0; attempt < 2; attempt++) {
-        runs.assign(cap ? cap : 1, 0);
-        size_t needed = 0;
+        if (!w.runs.ensure(std::max<size_t>(cap, 1) * 4, lock)) return WFA_E_NOMEM;
+        uint32_t* runs = cigar ? w.runs.as<uint32_t>() : nullptr;
         int rc;
         if (srv->cfg.executor) {
-            rc = srv->cfg.executor(srv->cfg.executor_user, &rq, scores.data(),
-                                   cigar ? runs.data() : nullptr, cap,
-                                   cigar ? offsets.data() : nullptr, &needed);
+            rc = srv->cfg.executor(srv->cfg.executor_user, &rq, scores, runs, cap, offsets, needed);
         } else {
             BatchIO io{rq.patterns, rq.texts, rq.pairs, n, WFA_ASCII, WFA_HOST, srv->cfg.pen,
-                       (wfa_mode)srv->cfg.mode, scores.data(), cigar ? runs.data() : nullptr, cap,
-                       cigar ? offsets.data() : nullptr};
+                       (wfa_mode)srv->cfg.mode, scores, runs, cap, offsets};
             int64_t bad = -1;
-            rc = engine_align(eng, io, nullptr, &needed, &bad);
+            rc = engine_align(eng, io, nullptr, needed, &bad);
         }
         if (rc == WFA_E_CAPACITY && cigar && attempt == 0) {
-            cap = needed;  // the next attempt holds every run
+            cap = *needed;  // the next attempt holds every run
             continue;
         }
-        if (rc == WFA_OK && cigar) runs.resize(needed);
         return rc;
     }
     return WFA_E_CAPACITY;
 }
 
+// A worker leaves what is queued beyond its share of the backlog to the other
+// workers, so that a burst runs on all streams at once (a burst of 32 requests of
+// 100 pairs: 7 to 8 ms, 11 to 12 when the first free worker took the rest of
+// the queue); a share is at least this many pairs.
+constexpr size_t MIN_SHARE = 512;
+
 void worker_main(wfa_server* srv, Engine* eng) {
     if (eng) (void)hipSetDevice(eng->device);
     const bool cigar = srv->cfg.mode == WFA_CIGAR;
-    const size_t max_chunk = (size_t)srv->cfg.max_chunk_pairs;
+    WorkerBufs w;
     for (;;) {
         std::vector<Piece> pieces;
         size_t est = 0;
@@ -156,6 +203,8 @@ void worker_main(wfa_server* srv, Engine* eng) {
             std::unique_lock<std::mutex> lk(srv->mu);
             for (;;) {
                 // form a batch from the head of the queue
+                const size_t share = srv->backlog / (size_t)srv->cfg.streams + 1;
+                const size_t max_chunk = std::min((size_t)srv->cfg.max_chunk_pairs, std::max(share, MIN_SHARE));
                 while (!srv->fifo.empty()) {
                     Request* r = srv->reqs[srv->fifo.front()].get();
                     size_t total = 0;
@@ -172,6 +221,7 @@ void worker_main(wfa_server* srv, Engine* eng) {
                     if (k == 0 && srv->reserved == 0 && est == 0 && pieces.empty()) k = 1;
                     if (k == 0) break;
                     pieces.push_back({r->ticket, r->next, k});
+                    srv->queued_pairs -= k;
                     est += r->est_prefix[r->next + k] - base;
                     if (r->t_admit < 0) r->t_admit = srv->now();
                     r->next += k;
@@ -194,34 +244,55 @@ void worker_main(wfa_server* srv, Engine* eng) {
             std::unique_lock<std::mutex> lk(srv->mu);
             for (auto& pc : pieces) owners.push_back(srv->reqs[pc.ticket].get());
         }
-        std::vector<uint8_t> pat, txt;
-        std::vector<wfa_pair> pairs;
-        {
+        // a piece's sequences are one range of its request's buffers (the
+        // request packed them pair after pair)
+        size_t np = 0, pat_bytes = 0, txt_bytes = 0;
+        auto range = [](const Request* r, const Piece& pc, bool text) -> std::pair<size_t, size_t> {
+            const wfa_pair& f = r->pairs[pc.first];
+            const wfa_pair& l = r->pairs[pc.first + pc.count - 1];
+            return text ? std::pair<size_t, size_t>(f.t_start, l.t_start + l.t_len)
+                        : std::pair<size_t, size_t>(f.p_start, l.p_start + l.p_len);
+        };
+        for (size_t pi = 0; pi < pieces.size(); pi++) {
+            const auto rp = range(owners[pi], pieces[pi], false), rt = range(owners[pi], pieces[pi], true);
+            np += pieces[pi].count;
+            pat_bytes += rp.second - rp.first;
+            txt_bytes += rt.second - rt.first;
+        }
+        const bool lock = eng != nullptr;
+        int rc = w.pat.ensure(pat_bytes + 1, lock) && w.txt.ensure(txt_bytes + 1, lock) &&
+                         w.pairs.ensure(np * sizeof(wfa_pair), lock)
+                     ? WFA_OK
+                     : WFA_E_NOMEM;
+        size_t needed = 0;
+        const double t_run = srv->now();
+        if (rc == WFA_OK) {
+            size_t pat_at = 0, txt_at = 0, at = 0;
+            wfa_pair* out = w.pairs.as<wfa_pair>();
             for (size_t pi = 0; pi < pieces.size(); pi++) {
                 const Piece& pc = pieces[pi];
-                Request* r = owners[pi];
+                const Request* r = owners[pi];
+                const auto rp = range(r, pc, false), rt = range(r, pc, true);
+                std::memcpy(w.pat.as<uint8_t>() + pat_at, r->pat.data() + rp.first, rp.second - rp.first);
+                std::memcpy(w.txt.as<uint8_t>() + txt_at, r->txt.data() + rt.first, rt.second - rt.first);
                 for (size_t i = pc.first; i < pc.first + pc.count; i++) {
                     const wfa_pair& q = r->pairs[i];
-                    wfa_pair d{pat.size(), txt.size(), q.p_len, q.t_len};
-                    pat.insert(pat.end(), r->pat.begin() + q.p_start,
-                               r->pat.begin() + q.p_start + q.p_len);
-                    txt.insert(txt.end(), r->txt.begin() + q.t_start,
-                               r->txt.begin() + q.t_start + q.t_len);
-                    pairs.push_back(d);
+                    out[at++] = {q.p_start - rp.first + pat_at, q.t_start - rt.first + txt_at, q.p_len,
+                                 q.t_len};
                 }
+                pat_at += rp.second - rp.first;
+                txt_at += rt.second - rt.first;
             }
+            w.pat.as<uint8_t>()[pat_at] = 0;
+            w.txt.as<uint8_t>()[txt_at] = 0;
+            wfa_request rq{w.pat.as<uint8_t>(), w.txt.as<uint8_t>(), out, np};
+            rc = run_batch(srv, eng, rq, w, &needed);
         }
-        pat.push_back(0);
-        txt.push_back(0);
-        wfa_request rq{pat.data(), txt.data(), pairs.data(), pairs.size()};
-        std::vector<int32_t> scores;
-        std::vector<uint32_t> runs;
-        std::vector<uint64_t> offsets;
-        const double t_run = srv->now();
-        const int rc = run_batch(srv, eng, rq, scores, runs, offsets);
+        const int32_t* scores = w.scores.as<int32_t>();
+        const uint32_t* runs = w.runs.as<uint32_t>();
+        const uint64_t* offsets = w.offsets.as<uint64_t>();
         if (rc != WFA_OK)
-            std::fprintf(stderr, "libwfa server: batch of %zu pairs failed: %s\n", pairs.size(),
-                         wfa_strerror(rc));
+            std::fprintf(stderr, "libwfa server: batch of %zu pairs failed: %s\n", np, wfa_strerror(rc));
         const double t_end = srv->now();
         if (eng && std::getenv("WFA_DEBUG")) {
             const wfa_stats& L = eng->last;
@@ -229,7 +300,7 @@ void worker_main(wfa_server* srv, Engine* eng) {
                          "libwfa server: batch %zu pairs, %.1f ms (engine: total %.1f, pack %.1f, "
                          "short %.1f, general %.1f, compact %.1f ms; short %llu, general %llu, "
                          "requeued %llu, chunks %d)\n",
-                         pairs.size(), (t_end - t_run) * 1e3, L.ms_total, L.ms_pack, L.ms_align,
+                         np, (t_end - t_run) * 1e3, L.ms_total, L.ms_pack, L.ms_align,
                          L.ms_general, L.ms_compact, (unsigned long long)L.short_pairs,
                          (unsigned long long)L.general_pairs, (unsigned long long)L.requeued,
                          L.host_chunks);
@@ -238,24 +309,29 @@ void worker_main(wfa_server* srv, Engine* eng) {
             std::unique_lock<std::mutex> lk(srv->mu);
             srv->busy_s += t_end - t_run;
             srv->reserved -= est;
-            srv->pairs_done += pairs.size();
+            srv->pairs_done += np;
             size_t at = 0;
             for (auto& pc : pieces) {
                 Request* r = srv->reqs[pc.ticket].get();
                 if (rc != WFA_OK) r->status = rc;
-                for (size_t i = 0; i < pc.count; i++) r->scores[pc.first + i] = scores[at + i];
-                if (cigar && rc == WFA_OK) {
+                if (scores && rc != WFA_E_NOMEM)
+                    for (size_t i = 0; i < pc.count; i++) r->scores[pc.first + i] = scores[at + i];
+                if (cigar && rc == WFA_OK && pc.count == r->pairs.size()) {
+                    // the whole request: its runs and offsets as they are
+                    r->runs.assign(runs + offsets[at], runs + offsets[at + pc.count]);
+                    r->offsets.resize(pc.count + 1);
+                    for (size_t i = 0; i <= pc.count; i++) r->offsets[i] = offsets[at + i] - offsets[at];
+                } else if (cigar && rc == WFA_OK) {
                     std::vector<uint32_t> cnt(pc.count);
                     for (size_t i = 0; i < pc.count; i++)
                         cnt[i] = (uint32_t)(offsets[at + i + 1] - offsets[at + i]);
-                    r->piece_runs[pc.first].assign(runs.begin() + offsets[at],
-                                                   runs.begin() + offsets[at + pc.count]);
+                    r->piece_runs[pc.first].assign(runs + offsets[at], runs + offsets[at + pc.count]);
                     r->piece_counts[pc.first] = std::move(cnt);
                 }
                 at += pc.count;
                 r->done_pairs += pc.count;
                 if (r->done_pairs == r->pairs.size()) {
-                    if (cigar) {
+                    if (cigar && r->offsets.empty()) {
                         r->offsets.assign(r->pairs.size() + 1, 0);
                         size_t idx = 0;
                         for (auto& kv : r->piece_runs) {
@@ -388,6 +464,8 @@ extern "C" int wfa_server_submit(wfa_server* srv, const wfa_request* req, uint64
             srv->completed++;
         } else {
             srv->fifo.push_back(r->ticket);
+            srv->queued_pairs += n;
+            srv->backlog = srv->queued_pairs;
         }
         srv->reqs[r->ticket] = std::move(r);
     }
