@@ -64,6 +64,8 @@ int auto_window(uint32_t max_len) {
     return 0;
 }
 
+constexpr int KEY_STAGED = 64;  // GraphKey: ASCII packed by the first pass itself
+
 // Band kernel: the first window tried for a batch's longest sequence.  A
 // window of W diagonals is exact for about W score steps, and a pair that
 // needs more is aligned again in the next window, so the rule aims at the
@@ -812,11 +814,12 @@ int engine_align_device(Engine* e, const BatchIO& io, hipStream_t user_stream,
     unsigned char* rb = (unsigned char*)e->readback + 128;  // the flags (with the run total)
     // Speculative start: the previous call's whole-pass graph, if this call
     // matches everything that graph was planned under except the batch facts
-    // (packed input, so no packing depends on them); kept below only if the
-    // facts lead to the same plan, else the call runs as planned and
+    // (no separate packing, whose layout depends on them); kept below only if
+    // the facts lead to the same plan, else the call runs as planned and
     // overwrites every output.
     const GraphEntry* spec_ent = nullptr;
-    if (e->spec.valid && !io.no_graph && io.enc == WFA_PACKED2) {
+    if (e->spec.valid && !io.no_graph &&
+        (io.enc == WFA_PACKED2 || (e->spec.key.ints[11] & KEY_STAGED))) {
         const GraphKey& k = e->spec.key;
         const void* ptrs[7] = {in_pairs, in_p, in_t, io.scores, io.runs, io.offsets,
                                (const void*)(uintptr_t)ws.generation};
@@ -888,8 +891,15 @@ int engine_align_device(Engine* e, const BatchIO& io, hipStream_t user_stream,
     // asks for at most 8 steps, else 16), alignment is global, and no
     // short-kernel shape was asked for.  Pairs it cannot hold go to the
     // cascade from window 64 on, as from a 32-wide first pass.
+    // A batch of at most 64 pairs per CU takes the band kernel instead, unless the
+    // lane kernel is asked for: it would leave most SIMDs without a wavefront
+    // and take the latency of its unrolled steps, 47 us (64 pairs: 98 us a call
+    // against 116; 10 k: 112 against 127; 100 k: 185 against 154, before the
+    // launches around it were cut for both).
     bool lane = false;
-    if (use_short && global && e->opt.lane_kernel >= 0 && !e->opt.window && !e->opt.lanes_per_pair &&
+    const bool tiny = N <= 64 * (size_t)e->num_cus && e->opt.lane_kernel == 0 &&
+                      e->opt.step_cap == 0 && band_supported(pen, 32);
+    if (use_short && global && !tiny && e->opt.lane_kernel >= 0 && !e->opt.window && !e->opt.lanes_per_pair &&
         e->opt.step_cap <= 16) {
         const int lcap = (e->opt.step_cap > 0 && e->opt.step_cap <= 8) ? 8 : 16;
         // a workgroup's LDS (both sequences and, with CIGAR, the history of
@@ -939,7 +949,17 @@ int engine_align_device(Engine* e, const BatchIO& io, hipStream_t user_stream,
         }
     }
     const bool persistent = use_short && schedule != WFA_SCHED_PLAIN;
-    const bool bucket = persistent && e->opt.bucket >= 0;
+    // Bucketing pays when lengths vary and a wavefront works through several
+    // rounds: it costs two passes over the descriptors (35 us at 1 M pairs), and
+    // on reads of one length it saves the lane kernel nothing (5 M pairs with
+    // CIGARs 1.55 ms either way; 1 M score-only 0.247 ms with, 0.197 without).
+    // Pairs of 50-300 bp: 50 k 0.454 ms with, 0.443 without; 100 k 0.525 and
+    // 0.551; 300 k 0.845 and 0.922; 2 M 3.72 and 4.19.
+    const uint64_t mw_p = std::max<uint64_t>((st.max_p + 31) / 32, 1);
+    const uint64_t mw_t = std::max<uint64_t>((st.max_t + 31) / 32, 1);
+    const bool even = N * (mw_p + mw_t) <= st.words_p + st.words_t + (st.words_p + st.words_t) / 16;
+    const bool bucket = persistent && (e->opt.bucket > 0 || (e->opt.bucket == 0 && !even &&
+                                                             N > 256 * (size_t)e->num_cus));
     // graphs: by default for the persistent schedule; the plain one only on request
     const bool graph = use_short && !io.no_graph && e->opt.use_graph >= 0 &&
                        (e->opt.use_graph > 0 || schedule == WFA_SCHED_AUTO ||
@@ -949,11 +969,14 @@ int engine_align_device(Engine* e, const BatchIO& io, hipStream_t user_stream,
     const bool ascii = io.enc == WFA_ASCII;
     // ASCII sides whose sequences all need about the same number of words are
     // packed at a fixed stride (no word-start scan); others by scan
-    const uint64_t mw_p = std::max<uint64_t>((st.max_p + 31) / 32, 1);
-    const uint64_t mw_t = std::max<uint64_t>((st.max_t + 31) / 32, 1);
     const bool stride_p = ascii && N * mw_p <= st.words_p + st.words_p / 4 + 64;
     const bool stride_t = ascii && N * mw_t <= st.words_t + st.words_t / 4 + 64;
-    if (ascii) {
+    // The lane and band kernels pack ASCII as they stage a pair (`staged`), so
+    // that no packed copy is written and read back; whatever kernel comes after
+    // them reads packed words, made by pack_all only if it is needed.
+    const bool staged = ascii && (lane || band);
+    bool packed = !staged;  // d holds packed words
+    auto pack_buffers = [&]() -> int {
         RCCHK(ws.ensure(ws.ws_p, (N + 1) * 8));
         RCCHK(ws.ensure(ws.ws_t, (N + 1) * 8));
         RCCHK(ws.ensure(ws.words_p, (stride_p ? N * mw_p : st.words_p) * 8 + 8));
@@ -962,6 +985,10 @@ int engine_align_device(Engine* e, const BatchIO& io, hipStream_t user_stream,
         d.pairs = ws.packed_pairs.as<PairDesc>();
         d.pw = ws.words_p.as<uint64_t>();
         d.tw = ws.words_t.as<uint64_t>();
+        return WFA_OK;
+    };
+    if (ascii && !staged) {
+        RCCHK(pack_buffers());
     } else {
         d.pairs = in_pairs;
         d.pw = (const uint64_t*)in_p;
@@ -1033,7 +1060,22 @@ int engine_align_device(Engine* e, const BatchIO& io, hipStream_t user_stream,
         a.scores = d.scores;
         a.nruns = ws.nruns.as<uint32_t>();
         a.run_src = ws.run_src.as<uint64_t>();
+        a.ascii = packed ? 0 : 1;
+        a.err_pair = &ws.flags.as<DevFlags>()->err_pair;
         return a;
+    };
+    auto launch_pack = [&](hipStream_t q) -> int {
+        if (!stride_p)
+            HIPCHK(launch_scan(SCAN_WORDS_P, in_pairs, N, ws.ws_p.as<uint64_t>(), ws.scan_tmp.ptr, q));
+        if (!stride_t)
+            HIPCHK(launch_scan(SCAN_WORDS_T, in_pairs, N, ws.ws_t.as<uint64_t>(), ws.scan_tmp.ptr, q));
+        HIPCHK(launch_pack_pairs(in_pairs, N, (const uint8_t*)in_p, (const uint8_t*)in_t,
+                                 stride_p ? nullptr : ws.ws_p.as<uint64_t>(),
+                                 stride_t ? nullptr : ws.ws_t.as<uint64_t>(), (st.max_p + 31) / 32,
+                                 (st.max_t + 31) / 32, ws.words_p.as<uint64_t>(),
+                                 ws.words_t.as<uint64_t>(), ws.packed_pairs.as<PairDesc>(),
+                                 &ws.flags.as<DevFlags>()->err_pair, q));
+        return WFA_OK;
     };
 
     // ---- device phase (graph-capturable) ----------------------------------
@@ -1053,18 +1095,7 @@ int engine_align_device(Engine* e, const BatchIO& io, hipStream_t user_stream,
         if ((lane || band) && persistent) fill.add(ws.lane_queues.as<uint32_t>(), LANE_QUEUES * 32, 0u);
         if (use_short && bucket) fill.add(hist, 2 * BUCKET_KEYS, 0u);
         HIPCHK(launch_fill_multi(fill, q));
-        if (ascii) {
-            if (!stride_p)
-                HIPCHK(launch_scan(SCAN_WORDS_P, in_pairs, N, ws.ws_p.as<uint64_t>(), ws.scan_tmp.ptr, q));
-            if (!stride_t)
-                HIPCHK(launch_scan(SCAN_WORDS_T, in_pairs, N, ws.ws_t.as<uint64_t>(), ws.scan_tmp.ptr, q));
-            HIPCHK(launch_pack_pairs(in_pairs, N, (const uint8_t*)in_p, (const uint8_t*)in_t,
-                                     stride_p ? nullptr : ws.ws_p.as<uint64_t>(),
-                                     stride_t ? nullptr : ws.ws_t.as<uint64_t>(),
-                                     (st.max_p + 31) / 32, (st.max_t + 31) / 32,
-                                     ws.words_p.as<uint64_t>(), ws.words_t.as<uint64_t>(),
-                                     ws.packed_pairs.as<PairDesc>(), &flags->err_pair, q));
-        }
+        if (ascii && !staged) RCCHK(launch_pack(q));
         if (use_short && bucket) {
             HIPCHK(launch_bucket_keys(d.pairs, N, ws.keys.as<uint32_t>(), hist, q));
             HIPCHK(launch_bucket_scatter(ws.keys.as<uint32_t>(), N, hist, taken,
@@ -1090,6 +1121,8 @@ int engine_align_device(Engine* e, const BatchIO& io, hipStream_t user_stream,
             a.run_src = ws.run_src.as<uint64_t>();
             a.slots = ws.slots.as<uint32_t>();
             a.hist = cigar ? ws.lane_hist.as<uint32_t>() : nullptr;
+            a.ascii = staged ? 1 : 0;
+            a.err_pair = &flags->err_pair;
             a.ovf_list = ws.ovf_list.as<uint32_t>();
             a.ovf_count = &flags->ovf_count;
             HIPCHK(launch_lane(a, sp.cap, cigar, persistent, sp.block_threads, grid, q));
@@ -1136,7 +1169,12 @@ int engine_align_device(Engine* e, const BatchIO& io, hipStream_t user_stream,
     };
     // post: CIGAR offsets and compaction
     auto phase_post = [&](hipStream_t q) -> int {
-        if (cigar && use_short) {
+        if (cigar && use_short && N <= FINISH_SMALL_PAIRS) {
+            HIPCHK(launch_finish_small(ws.nruns.as<uint32_t>(), ws.run_src.as<uint64_t>(),
+                                       ws.slots.as<uint32_t>(), ws.slots2.as<uint32_t>(),
+                                       ws.gen_runs.as<uint32_t>(), N, d.offsets, d.runs, d.capacity,
+                                       &flags->total_runs, q));
+        } else if (cigar && use_short) {
             HIPCHK(launch_scan(SCAN_U32, ws.nruns.ptr, N, d.offsets, ws.scan_tmp.ptr, q));
             HIPCHK(launch_compact(ws.run_src.as<uint64_t>(),
                                   ws.slots.as<uint32_t>(), ws.slots2.as<uint32_t>(),
@@ -1166,9 +1204,12 @@ int engine_align_device(Engine* e, const BatchIO& io, hipStream_t user_stream,
         const int ints[18] = {(int)io.enc, (int)io.mode, pen.x, pen.oe, pen.e, pen.g,
                               window * 256 + lanes, sp.cap,
                               // the packing's word counts (packed input: none)
-                              ascii ? (int)st.max_p : 0, ascii ? (int)st.max_t : 0, grid,
-                              (int)(bucket ? 1 : 0) | (stride_p ? 4 : 0) | (stride_t ? 8 : 0) |
-                                  (persistent ? 16 : 0) | (band ? 32 : 0) | (sp.block_threads << 8),
+                              ascii && !staged ? (int)st.max_p : 0, ascii && !staged ? (int)st.max_t : 0,
+                              grid,
+                              (int)(bucket ? 1 : 0) | (stride_p && !staged ? 4 : 0) |
+                                  (stride_t && !staged ? 8 : 0) |
+                                  (persistent ? 16 : 0) | (band ? 32 : 0) | (staged ? KEY_STAGED : 0) |
+                                  (sp.block_threads << 8),
                               e->ends.pb, e->ends.pe, e->ends.tb, e->ends.te, queue_chunk,
                               sp.slot_cap};
         for (int i = 0; i < 18; i++) key.ints[i] = ints[i];
@@ -1239,7 +1280,24 @@ int engine_align_device(Engine* e, const BatchIO& io, hipStream_t user_stream,
     uint64_t short_total = 0;
     std::memcpy(&fl, rb, sizeof(fl));
     if (cigar && use_short) short_total = fl.total_runs;
+    // Staged ASCII: the packed copy after all, for the kernels that read one;
+    // it checks every pair's bytes.
+    auto pack_all = [&]() -> int {
+        if (packed) return WFA_OK;
+        packed = true;
+        RCCHK(pack_buffers());
+        RCCHK(launch_pack(s));
+        unsigned long long err = ~0ull;
+        HIPCHK(hipMemcpyAsync(&err, &ws.flags.as<DevFlags>()->err_pair, 8, hipMemcpyDeviceToHost, s));
+        HIPCHK(hipStreamSynchronize(s));
+        if (err == ~0ull) return WFA_OK;
+        if (bad_pair) *bad_pair = (int64_t)err;
+        return WFA_E_ALPHABET;
+    };
     if (fl.err_pair != ~0ull) {
+        // a pair the first pass did not stage may come before the one it found
+        const int rp = pack_all();
+        if (rp != WFA_OK) return rp;
         if (bad_pair) *bad_pair = (int64_t)fl.err_pair;
         return WFA_E_ALPHABET;
     }
@@ -1263,9 +1321,14 @@ int engine_align_device(Engine* e, const BatchIO& io, hipStream_t user_stream,
         // after a pass's launch: what it handed over, and to which list
         auto pass_done = [&](uint64_t slot_words, int w2) -> int {
             HIPCHK(hipEventRecord(e->ev[11], s));
-            uint32_t n_out = 0;
-            HIPCHK(hipMemcpyAsync(&n_out, &flags->ovf_count2, 4, hipMemcpyDeviceToHost, s));
+            DevFlags now;
+            HIPCHK(hipMemcpyAsync(&now, flags, sizeof(now), hipMemcpyDeviceToHost, s));
             HIPCHK(hipStreamSynchronize(s));
+            if (now.err_pair != ~0ull) {  // (staged ASCII) a byte only this pass has read
+                const int rp = pack_all();
+                return rp != WFA_OK ? rp : WFA_E_ALPHABET;
+            }
+            const uint32_t n_out = now.ovf_count2;
             ms_cascade += ev_ms(e->ev[10], e->ev[11]);
             if (cigar) slots2_used += slot_words;
             ovf_final = n_out;
@@ -1312,6 +1375,7 @@ int engine_align_device(Engine* e, const BatchIO& io, hipStream_t user_stream,
             }
             // the band of 128 holds as many steps as a window of 256
             if (w2 > 128 && (banded || band)) break;
+            RCCHK(pack_all());
             const int l2 = default_lanes(w2);
             ShortPlan sp2;
             if (!short_shape_supported(w2, l2) ||
@@ -1374,6 +1438,7 @@ int engine_align_device(Engine* e, const BatchIO& io, hipStream_t user_stream,
     // the common case ends here: the first pass held every pair and its
     // offsets and runs are written, so nothing more runs on the device
     const bool tail = !pending.empty() || !use_short || fl.ovf_count > 0;
+    if (!pending.empty()) RCCHK(pack_all());
     if (tail) HIPCHK(hipEventRecord(e->ev[2], s));
     // The front kernel first, or under the heuristic the adaptive one, unless
     // the caller chose a form of the general kernel's memory or a step limit.

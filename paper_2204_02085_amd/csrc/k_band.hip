@@ -34,6 +34,7 @@
 #include <stdint.h>
 
 #include "kernels.h"
+#include "pack.h"
 #include "rows.h"
 
 namespace wfa {
@@ -127,9 +128,22 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5))) void k
             if (ks1 >= out1 || ke1 >= out1 || ks0 <= out0 || ke0 <= out0) smax = -1;
         }
         bool run = active && smax >= 0 && nwp + 1 <= a.seq_words && nwt + 1 <= a.seq_words;
-        for (int w = gl; w < a.seq_words; w += G) {
-            ST[w] = (run && w < nwt) ? a.tw[ts + w] : 0ull;
-            SP[w] = (run && w < nwp) ? a.pw[ps + w] : 0ull;
+        if (a.ascii) {  // packed on the way in: no packed copy in memory
+            bool ok = true;
+            const uint8_t* pa = (const uint8_t*)a.pw;
+            const uint8_t* ta = (const uint8_t*)a.tw;
+            for (int w = gl; w < a.seq_words; w += G) {
+                bool okt = true, okp = true;
+                ST[w] = (run && w < nwt) ? pack_word(ta, ts + 32ull * w, min(32, m - 32 * w), okt) : 0ull;
+                SP[w] = (run && w < nwp) ? pack_word(pa, ps + 32ull * w, min(32, n - 32 * w), okp) : 0ull;
+                ok = ok && okt && okp;
+            }
+            if (!ok) atomicMin(a.err_pair, (unsigned long long)pair);
+        } else {
+            for (int w = gl; w < a.seq_words; w += G) {
+                ST[w] = (run && w < nwt) ? a.tw[ts + w] : 0ull;
+                SP[w] = (run && w < nwp) ? a.pw[ps + w] : 0ull;
+            }
         }
         if (!run) {  // an idle group computes on two empty sequences
             n = m = 0;

@@ -49,6 +49,7 @@
 #include <utility>
 
 #include "kernels.h"
+#include "pack.h"
 
 namespace wfa {
 
@@ -481,7 +482,7 @@ struct LaneKernel {
 // at E = 4 % took 1.87 ms (rolled) against 2.02 ms with one register per
 // diagonal (128 VGPRs and 48 dwords per lane in scratch), and 1.88 ms at five
 // wavefronts (96 VGPRs, 30 spilled), in alternating runs on one device.
-template <int X, int OE, int E, int CAP, int LMAX, bool CIGAR>
+template <int X, int OE, int E, int CAP, int LMAX, bool CIGAR, bool ASCII>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k_lane(LaneArgs a,
                                                                                     int persistent) {
     using K = LaneKernel<X, OE, E, CAP, LMAX, CIGAR>;
@@ -555,7 +556,33 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
         ln.run = active && fits;
         ln.S = -1;
         // stage both sequences in the lane's columns (zero past their ends)
-        {
+        if constexpr (ASCII) {
+            // ASCII: packed on the way in, the words of the 64 pairs spread
+            // over the lanes (consecutive lanes on a pair's consecutive words,
+            // so their loads fall together): word w of each side of pair i is
+            // task i * NW + w
+            constexpr int NW = (K::SQ + 1) / 2;
+            const uint32_t start[4] = {(uint32_t)ps, (uint32_t)(ps >> 32), (uint32_t)ts, (uint32_t)(ts >> 32)};
+            const int lens = ln.run ? n | (m << 8) : 0;  // at most LMAX < 256 each
+            for (int t0 = 0; t0 < 64 * NW; t0 += 64) {
+                const int own = (t0 + lane) / NW, w = (t0 + lane) % NW;
+                const uint64_t p0 = (uint32_t)__shfl((int)start[0], own) | ((uint64_t)(uint32_t)__shfl((int)start[1], own) << 32);
+                const uint64_t q0 = (uint32_t)__shfl((int)start[2], own) | ((uint64_t)(uint32_t)__shfl((int)start[3], own) << 32);
+                const int nm = __shfl(lens, own);
+                const int pn = (nm & 255) - 32 * w, tn = (nm >> 8) - 32 * w;
+                bool okp = true, okt = true;
+                const uint64_t pv = pn > 0 ? pack_word((const uint8_t*)a.pw, p0 + 32 * w, min(pn, 32), okp) : 0ull;
+                const uint64_t tv = tn > 0 ? pack_word((const uint8_t*)a.tw, q0 + 32 * w, min(tn, 32), okt) : 0ull;
+                lptr<uint32_t> col = wbase - lane + own;
+                col[2 * w * 64] = (uint32_t)pv;
+                col[(K::SQ + 2 * w) * 64] = (uint32_t)tv;
+                if (2 * w + 1 < K::SQ) {
+                    col[(2 * w + 1) * 64] = (uint32_t)(pv >> 32);
+                    col[(K::SQ + 2 * w + 1) * 64] = (uint32_t)(tv >> 32);
+                }
+                if (!(okp && okt)) atomicMin(a.err_pair, (unsigned long long)(uint32_t)(a.order ? a.order[qbase + own] : qbase + own));
+            }
+        } else {
             const int nwp = ln.run ? (n + 31) >> 5 : 0, nwt = ln.run ? (m + 31) >> 5 : 0;
 #pragma unroll
             for (int w = 0; w < (K::SQ + 1) / 2; w++) {
@@ -725,25 +752,29 @@ struct LaneShape {
     static int hist_dwords(bool cigar, int slot_cap) {
         return cigar ? (LaneKernel<X, OE, E, CAP, LMAX, true>::HIST_DW + slot_cap) * 64 : 0;
     }
-    static hipError_t launch(const LaneArgs& a, bool cigar, bool persistent, int bt, int grid,
-                             hipStream_t s) {
-        const int lds = lds_bytes(cigar, bt / 64);
-        if (cigar)
-            hipLaunchKernelGGL((k_lane<X, OE, E, CAP, LMAX, true>), dim3(grid), dim3(bt), lds, s, a,
-                               persistent ? 1 : 0);
-        else
-            hipLaunchKernelGGL((k_lane<X, OE, E, CAP, LMAX, false>), dim3(grid), dim3(bt), lds, s, a,
-                               persistent ? 1 : 0);
+    template <bool CIGAR, bool ASCII>
+    static hipError_t launch_t(const LaneArgs& a, bool persistent, int bt, int grid, hipStream_t s) {
+        hipLaunchKernelGGL((k_lane<X, OE, E, CAP, LMAX, CIGAR, ASCII>), dim3(grid), dim3(bt),
+                           lds_bytes(CIGAR, bt / 64), s, a, persistent ? 1 : 0);
         return hipGetLastError();
     }
+    static hipError_t launch(const LaneArgs& a, bool cigar, bool persistent, int bt, int grid,
+                             hipStream_t s) {
+        if (cigar)
+            return a.ascii ? launch_t<true, true>(a, persistent, bt, grid, s)
+                           : launch_t<true, false>(a, persistent, bt, grid, s);
+        return a.ascii ? launch_t<false, true>(a, persistent, bt, grid, s)
+                       : launch_t<false, false>(a, persistent, bt, grid, s);
+    }
     static int occupancy(bool cigar, int bt) {
+        // (the forms that pack ASCII as they stage hold the same LDS and wavefronts)
         int blocks = 0;
         const int lds = lds_bytes(cigar, bt / 64);
         const hipError_t e =
             cigar ? hipOccupancyMaxActiveBlocksPerMultiprocessor(
-                        &blocks, (const void*)k_lane<X, OE, E, CAP, LMAX, true>, bt, lds)
+                        &blocks, (const void*)k_lane<X, OE, E, CAP, LMAX, true, false>, bt, lds)
                   : hipOccupancyMaxActiveBlocksPerMultiprocessor(
-                        &blocks, (const void*)k_lane<X, OE, E, CAP, LMAX, false>, bt, lds);
+                        &blocks, (const void*)k_lane<X, OE, E, CAP, LMAX, false, false>, bt, lds);
         return e == hipSuccess ? blocks : 0;
     }
     static int kmax() { return LaneKernel<X, OE, E, CAP, LMAX, false>::reach.kmax; }

@@ -108,6 +108,8 @@ struct LaneArgs {
     uint32_t* hist;             // CIGAR: one history and run-stage region per launched wavefront
     uint32_t* ovf_list;         // pairs the kernel could not hold
     uint32_t* ovf_count;
+    int ascii;                  // pw, tw are ASCII bytes, starts and lengths bytes
+    unsigned long long* err_pair;  // ascii: lowest staged pair with a byte outside ACGTacgt
 };
 
 // Arguments of the band kernel (all device pointers).
@@ -134,6 +136,8 @@ struct BandArgs {
     uint32_t* slots;            // [pairs * slot_cap] reversed runs, packed per wave
     uint32_t* ovf_list;         // pairs the kernel could not hold
     uint32_t* ovf_count;
+    int ascii;                  // pw, tw are ASCII bytes, starts and lengths bytes
+    unsigned long long* err_pair;  // ascii: lowest staged pair with a byte outside ACGTacgt
 };
 
 // Launch shape of the band kernel.
@@ -354,6 +358,14 @@ constexpr uint64_t SLOTS2_BIT = 1ULL << 62;
 hipError_t launch_compact(const uint64_t* run_src, const uint32_t* slots, const uint32_t* slots2,
                           const uint32_t* gen_runs, const uint64_t* offsets, size_t n,
                           uint32_t* out, uint64_t capacity, uint64_t* total_out, hipStream_t s);
+
+// The same for at most FINISH_SMALL_PAIRS pairs with the offsets' scan in one
+// launch: offsets[0..n] from nruns, then the runs.
+constexpr size_t FINISH_SMALL_PAIRS = 256;
+hipError_t launch_finish_small(const uint32_t* nruns, const uint64_t* run_src, const uint32_t* slots,
+                               const uint32_t* slots2, const uint32_t* gen_runs, size_t n,
+                               uint64_t* offsets, uint32_t* out, uint64_t capacity,
+                               uint64_t* total_out, hipStream_t s);
 
 // Counting sort of pairs by expected work: keys + histogram, then the
 // scatter into `order` (each block takes the exclusive scan of the histogram

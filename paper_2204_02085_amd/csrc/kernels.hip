@@ -26,6 +26,7 @@
 #include <stdint.h>
 
 #include "kernels.h"
+#include "pack.h"
 
 namespace wfa {
 
@@ -302,52 +303,6 @@ __global__ __launch_bounds__(SCAN_T) void k_scan_single(ScanKind kind, const voi
 // ---------------------------------------------------------------------------
 // ASCII -> 2-bit packing.  One thread per output word (32 bases).
 // ---------------------------------------------------------------------------
-// Codes of the 4 bytes of x (A/a=0, C/c=1, G/g=2, T/t=3) in 8 bits; `bad`
-// collects the bits of bytes (among the low `keep` mask) that are not one of
-// those letters.  The code of an ASCII letter is bits 1-2 of the byte folded
-// ((c >> 1) ^ (c >> 2)) & 3; a byte is valid when the lowercase letter of its
-// code (looked up bytewise with v_perm_b32) equals the byte in lowercase.
-__device__ __forceinline__ uint32_t pack4(uint32_t x, uint32_t keep, uint32_t& bad) {
-    const uint32_t c = ((x >> 1) ^ (x >> 2)) & 0x03030303u;
-    // bytes 'a' 'c' 'g' 't' selected by c (selector values 0..3 pick bytes of src1)
-    const uint32_t letters = __builtin_amdgcn_perm(0u, 0x74676361u, c);
-    bad |= (letters ^ (x | 0x20202020u)) & keep;
-    uint32_t v = c & keep;
-    v = (v | (v >> 6)) & 0x000F000Fu;
-    return (v | (v >> 12)) & 0xFFu;
-}
-
-// 32 bases starting at byte b0 of `ascii` (cnt of them valid, 1..32) as one
-// 2-bit word.  Reads the aligned dwords covering the bases; near the end of
-// the sequence the dword index is clamped to the last one holding a base,
-// so no byte past the sequence is read.
-__device__ __forceinline__ uint64_t pack_word(const uint8_t* __restrict__ ascii, uint64_t b0,
-                                              int cnt, bool& ok) {
-    const uint8_t* first = ascii + b0;
-    const uint32_t sh = (uint32_t)((uintptr_t)first & 3u);
-    const uint32_t* src = (const uint32_t*)(first - sh);
-    const int lastd = (int)((sh + cnt - 1) >> 2);  // last dword holding a base
-    uint32_t raw[9];
-    if (lastd == 8) {
-#pragma unroll
-        for (int d = 0; d < 9; d++) raw[d] = src[d];
-    } else {
-#pragma unroll
-        for (int d = 0; d < 9; d++) raw[d] = src[min(d, lastd)];
-    }
-    uint64_t word = 0;
-    uint32_t bad = 0;
-#pragma unroll
-    for (int d = 0; d < 8; d++) {
-        const uint32_t x = __builtin_amdgcn_alignbyte(raw[d + 1], raw[d], sh);
-        const int c = min(max(cnt - 4 * d, 0), 4);
-        const uint32_t keep = c >= 4 ? 0xFFFFFFFFu : ((1u << (8 * c)) - 1u);
-        word |= (uint64_t)pack4(x, keep, bad) << (8 * d);
-    }
-    ok = bad == 0;
-    return word;
-}
-
 // blockIdx.y selects the side: 0 patterns, 1 texts
 __global__ void k_pack_pairs(const PairDesc* __restrict__ pairs, size_t n,
                              const uint8_t* __restrict__ pascii, const uint8_t* __restrict__ tascii,
@@ -1969,6 +1924,40 @@ __global__ __launch_bounds__(COMPACT_PAIRS) void k_compact(const uint64_t* __res
     }
 }
 
+// Offsets and compaction of a small batch by one block (a scan and a compaction
+// kernel are 9 us of a 64-pair call, this one about half of that).
+__global__ __launch_bounds__(SCAN_T) void k_finish_small(
+    const uint32_t* __restrict__ nruns, const uint64_t* __restrict__ run_src,
+    const uint32_t* __restrict__ slots, const uint32_t* __restrict__ slots2,
+    const uint32_t* __restrict__ gen_runs, uint32_t n, uint64_t* __restrict__ offsets,
+    uint32_t* __restrict__ out, uint64_t capacity, uint64_t* __restrict__ total_out) {
+    __shared__ uint64_t end[SCAN_T];
+    __shared__ const uint32_t* src_of[SCAN_T];
+    const uint32_t t = threadIdx.x;
+    const uint64_t cnt = t < n ? nruns[t] : 0;
+    uint64_t incl = cnt;
+    const uint64_t total = block_inclusive_scan(incl);
+    end[t] = incl;
+    if (t < n) {
+        offsets[t] = incl - cnt;
+        const uint64_t src = run_src[t], off = src & ~(GEN_BIT | SLOTS2_BIT);
+        src_of[t] = (src & GEN_BIT) ? gen_runs + off : ((src & SLOTS2_BIT) ? slots2 : slots) + off;
+    }
+    if (t == 0) {
+        offsets[n] = total;
+        *total_out = total;
+    }
+    if (total > capacity) return;
+    __syncthreads();
+    for (uint64_t q = t; q < total; q += SCAN_T) {
+        uint32_t p = 0;  // pairs whose runs end at or before q
+#pragma unroll
+        for (uint32_t step = SCAN_T / 2; step; step >>= 1)
+            if (end[p + step - 1] <= q) p += step;
+        out[q] = src_of[p][end[p] - 1 - q];
+    }
+}
+
 // Bucket key: longer pairs and larger length differences (more expected
 // work) first, so a persistent grid starts the long jobs early and lane
 // groups sharing a wave hold pairs of similar cost.
@@ -2071,6 +2060,10 @@ hipError_t launch_batch_stats(const PairDesc* pairs, size_t n, BatchStats* out, 
                               hipStream_t s) {
     // out[1 .. STATS_BLOCKS] hold the per-block partials
     const int nb = n ? grid_for(n, 256 * 8, STATS_BLOCKS) : 1;
+    if (nb == 1) {  // one block: its partial is the result
+        hipLaunchKernelGGL(k_batch_stats, dim3(1), dim3(256), 0, s, pairs, n, out, max_len);
+        return hipGetLastError();
+    }
     hipLaunchKernelGGL(k_batch_stats, dim3(nb), dim3(256), 0, s, pairs, n, out + 1, max_len);
     hipLaunchKernelGGL(k_batch_stats_final, dim3(1), dim3(256), 0, s, out + 1, nb, out);
     return hipGetLastError();
@@ -2298,6 +2291,18 @@ hipError_t launch_compact(const uint64_t* run_src, const uint32_t* slots, const 
         hipLaunchKernelGGL(k_compact, dim3(grid_for(n, COMPACT_PAIRS, 1 << 20)), dim3(COMPACT_PAIRS),
                            0, s, run_src, slots, slots2, gen_runs, offsets, n, out, capacity,
                            total_out);
+    return hipGetLastError();
+}
+
+hipError_t launch_finish_small(const uint32_t* nruns, const uint64_t* run_src, const uint32_t* slots,
+                               const uint32_t* slots2, const uint32_t* gen_runs, size_t n,
+                               uint64_t* offsets, uint32_t* out, uint64_t capacity,
+                               uint64_t* total_out, hipStream_t s) {
+    static_assert(FINISH_SMALL_PAIRS == SCAN_T, "one pair per thread");
+    if (n > FINISH_SMALL_PAIRS) return hipErrorInvalidValue;
+    if (n)
+        hipLaunchKernelGGL(k_finish_small, dim3(1), dim3(SCAN_T), 0, s, nruns, run_src, slots, slots2,
+                           gen_runs, (uint32_t)n, offsets, out, capacity, total_out);
     return hipGetLastError();
 }
 
