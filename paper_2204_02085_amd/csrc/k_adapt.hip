@@ -37,8 +37,6 @@ namespace {
 
 using namespace rows;
 
-constexpr int WALK_DW = 1024;  // dwords of the walk's record window in LDS
-
 // smallest of the lanes' values, in every lane
 __device__ __forceinline__ int wave_min(int v) { return -wave_max(-v); }
 
@@ -278,37 +276,25 @@ __global__ __launch_bounds__(64) void k_adapt(FrontArgs a) {
         }
         return;
     }
-    // the walk, WQ quads of steps of the records in LDS at a time (what a quad
-    // left unwritten of its second block is never on the way)
-    constexpr int QW = 64 * NB, WQ = WALK_DW / QW;
+    // the walk (what a quad left unwritten of its second block is never on the
+    // way; the windows of all quads start at an even diagonal)
+    constexpr int QW = 64 * NB;
     __threadfence_block();
     uint32_t* evs = hist + job.hist_words;
     uint32_t* runs_end = evs + job.ev_words + job.run_words;
-    int qtop = -1;
-    uint32_t bases = 0;  // lane i: the window's base at quad qtop - i
-    auto record = [&](int s, int k, bool& bad) -> uint32_t {
-        const int q = s >> 2;
-        if (q > qtop || q <= qtop - WQ) {
-            qtop = q;
-            wave_fence();
-#pragma unroll 4
-            for (int i = 0; i < WQ * NB; i++) {
-                const int r = i / NB, w = (i % NB) * 64 + lane;
-                win[i * 64 + lane] = q - r >= 0 ? hist[(uint64_t)(q - r) * ADAPT_QUAD_WORDS + w] : 0u;
-            }
-            bases = lane < WQ && q - lane >= 0 ? hist[(uint64_t)(q - lane) * ADAPT_QUAD_WORDS + QW] : 0u;
-            wave_fence();
+    auto load = [&](int q, int k) {
+        const int kf = (k & ~1) - WALK_COLS / 2;
+        if (q - lane >= 0) {
+            const uint32_t* from = hist + (uint64_t)(q - lane) * ADAPT_QUAD_WORDS;
+            const int c0 = (kf - (int)from[QW]) >> 1;
+#pragma unroll
+            for (int i = 0; i < WALK_COLS / 2; i++)
+                win[lane * (WALK_COLS / 2) + i] = c0 + i >= 0 && c0 + i < QW ? from[c0 + i] : 0u;
         }
-        const int col = k - __builtin_amdgcn_readlane((int)bases, qtop - q);
-        if (col < 0 || col >= AW) {
-            bad = true;
-            return 0;
-        }
-        const uint32_t word = (uint32_t)__builtin_amdgcn_readfirstlane((int)win[(qtop - q) * QW + (col >> 1)]);
-        return record_of(word, s, col);
+        return kf;
     };
-    const int nr = walk<X, OE, E, true>(record, S, n, m, lane, evs, job.ev_words, runs_end, job.run_words,
-                                        tb, pb);
+    const int nr = walk<X, OE, E, true>(load, S, n, m, lane, win, evs, job.ev_words, runs_end,
+                                        job.run_words, tb, pb);
     walk_done(a, job, S, nr, runs_end, lane);
 }
 

@@ -120,41 +120,27 @@ __global__ __launch_bounds__(64) void k_bound(FrontArgs a) {
     if (lane == 0) a.bounds[blockIdx.x] = U;
 }
 
-constexpr int WALK_QUADS = 64;  // quads of steps of the record window in LDS
-constexpr int WALK_DW = 8;      // its dwords (16 diagonals) per quad
-
-// The walk over a pair's records, 256 steps of them in LDS (`win`) at a time.
+// The walk over a pair's records.
 template <int X, int OE, int E>
 __device__ void walk_job(const FrontArgs& a, const FrontJob& job, int S, int n, int m, int lane,
                          lds_p<uint32_t> win, uint32_t tb, uint32_t pb) {
     typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+    constexpr int ROW = WALK_COLS / 2;
     const int rowdw = job.nw * 32 * job.cols;  // dwords per quad of steps
     const uint32_t* hist = a.arena + job.hist;
     uint32_t* evs = a.arena + job.hist + job.hist_words;
     uint32_t* runs_end = evs + job.ev_words + job.run_words;
-    int qtop = -1, c0 = 0;
-    auto record = [&](int s, int k, bool& bad) -> uint32_t {
-        const int q = s >> 2, col = k - job.kbase, dw = col >> 1;
-        if (col < 0 || dw >= rowdw) {
-            bad = true;
-            return 0;
-        }
-        if (q > qtop || q <= qtop - WALK_QUADS || dw < c0 || dw >= c0 + WALK_DW) {
-            qtop = q;
-            c0 = min(max((dw - WALK_DW / 2) & ~3, 0), rowdw - WALK_DW);
-            wave_fence();
-            if (q - lane >= 0) {
-                const u32x4* from = (const u32x4*)(hist + (uint64_t)(q - lane) * rowdw + c0);
-                lds_p<u32x4> to = (lds_p<u32x4>)(win + lane * WALK_DW);
+    auto load = [&](int q, int k) {
+        const int c0 = min(max((((k - job.kbase) >> 1) - ROW / 2) & ~3, 0), rowdw - ROW);
+        if (q - lane >= 0) {
+            const u32x4* from = (const u32x4*)(hist + (uint64_t)(q - lane) * rowdw + c0);
+            lds_p<u32x4> to = (lds_p<u32x4>)(win + lane * ROW);
 #pragma unroll
-                for (int i = 0; i < WALK_DW / 4; i++) to[i] = from[i];
-            }
-            wave_fence();
+            for (int i = 0; i < ROW / 4; i++) to[i] = from[i];
         }
-        const uint32_t word = (uint32_t)__builtin_amdgcn_readfirstlane((int)win[(qtop - q) * WALK_DW + dw - c0]);
-        return record_of(word, s, col);
+        return job.kbase + 2 * c0;
     };
-    const int nr = walk<X, OE, E, false>(record, S, n, m, lane, evs, job.ev_words, runs_end,
+    const int nr = walk<X, OE, E, false>(load, S, n, m, lane, win, evs, job.ev_words, runs_end,
                                          job.run_words, tb, pb);
     walk_done(a, job, S, nr, runs_end, lane);
 }
@@ -193,7 +179,7 @@ void k_front(FrontArgs a) {
     lds_p<uint32_t> xch = (lds_p<uint32_t>)(done + 4);
     const int xb = 2 * (nbb + 2);  // words per buffer: {up, down} per block
     lds_p<uint32_t> win = xch + 2 * xb;
-    lds_p<uint64_t> seq = (lds_p<uint64_t>)(win + (CIGAR ? WALK_QUADS * WALK_DW : 0));
+    lds_p<uint64_t> seq = (lds_p<uint64_t>)(win + (CIGAR ? WALK_DW : 0));
     stage(seq, a.pw, a.tw, d, threadIdx.x, blockDim.x);
     for (int i = threadIdx.x; i < 2 * xb; i += blockDim.x) xch[i] = NUL16P;
     if (threadIdx.x == 0) *done = -1;
@@ -252,6 +238,9 @@ void k_front(FrontArgs a) {
         }
     };
     __syncthreads();
+    // wavefronts past the pair's own (a launch's workgroups have one size) make
+    // room for other workgroups: barriers count the wavefronts that are left
+    if (w >= nwv) return;
     for (int s = 0;; s += 4) {
         if (__builtin_amdgcn_readfirstlane(*done) >= 0 || s > U) break;
         // diagonals of these four steps' cells, with one to spare on each side
@@ -262,7 +251,7 @@ void k_front(FrontArgs a) {
 #pragma unroll
         for (int i = 0; i < NB; i++) {
             const int b = w + i * nwv, lo = kbase + b * WC;
-            act[i] = w < nwv && b < job.nw && lo + WC - 1 >= dlo && lo <= dhi;
+            act[i] = b < job.nw && lo + WC - 1 >= dlo && lo <= dhi;
             own[i] = b == eb;
         }
         auto quad = [&](bool first, bool second) {
@@ -392,7 +381,7 @@ hipError_t launch_front(const FrontArgs& a, const Pen& pen, bool cigar, const Fr
                         int waves, uint32_t n, uint32_t m, hipStream_t s) {
     if (!jobs) return hipSuccess;
     if (waves < 1 || waves > 16) return hipErrorInvalidValue;
-    const int lds = 16 + 16 * (waves * f.blocks + 2) + (cigar ? WALK_QUADS * WALK_DW * 4 : 0) +
+    const int lds = 16 + 16 * (waves * f.blocks + 2) + (cigar ? WALK_DW * 4 : 0) +
                     seq_lds_bytes(n, m);
 #define WFA_CASE(PX, POE, PE)                       \
     if (pen.x == PX && pen.oe == POE && pen.e == PE) \
