@@ -210,12 +210,11 @@ bool grow_arena(Workspace& ws, uint64_t want, uint64_t most) {
     return ws.arena.bytes >= most;
 }
 
-// The buffers and counters of one launch of the front or adaptive kernels over
-// `fj` (their pairs: `ids`), and its read-back: pairs that failed go to `rest`.
-int begin_jobs(Engine* e, const std::vector<FrontJob>& fj, const std::vector<uint32_t>& ids, bool cigar,
-               FrontArgs* a, hipStream_t s) {
+// The buffers and counters of launches of the front or adaptive kernels over up
+// to `nj` pairs, the pairs of a launch (`fj`, ids `ids`) to places `at` on of
+// the buffers, and the read-back: pairs that failed go to `rest`.
+int begin_jobs(Engine* e, size_t nj, FrontArgs* a, hipStream_t s) {
     Workspace& ws = e->ws;
-    const size_t nj = fj.size();
     RCCHK(ws.ensure(ws.jobs, nj * 4));
     RCCHK(ws.ensure(ws.gen_slices, nj * sizeof(FrontJob)));
     RCCHK(ws.ensure(ws.job_nruns, nj * 4));
@@ -223,17 +222,23 @@ int begin_jobs(Engine* e, const std::vector<FrontJob>& fj, const std::vector<uin
     RCCHK(ws.ensure(ws.fail_list, nj * 4));
     RCCHK(ws.ensure(ws.scan_tmp, scan_temp_bytes(nj) + 64));
     DevFlags* flags = ws.flags.as<DevFlags>();
-    HIPCHK(hipMemcpyAsync(ws.jobs.ptr, ids.data(), nj * 4, hipMemcpyHostToDevice, s));
-    HIPCHK(hipMemcpyAsync(ws.gen_slices.ptr, fj.data(), nj * sizeof(FrontJob), hipMemcpyHostToDevice, s));
     FillOps fill{};
     fill.add(ws.job_nruns.as<uint32_t>(), nj, 0u);
     fill.add(&flags->fail_count, 1, 0u);
     HIPCHK(launch_fill_multi(fill, s));
-    a->jobs = ws.gen_slices.as<FrontJob>();
-    a->job_nruns = ws.job_nruns.as<uint32_t>();
-    a->arena = cigar ? ws.arena.as<uint32_t>() : nullptr;
     a->fail_list = ws.fail_list.as<uint32_t>();
     a->fail_count = &flags->fail_count;
+    return WFA_OK;
+}
+int put_jobs(Engine* e, const FrontJob* fj, const uint32_t* ids, size_t at, size_t nj, FrontArgs* a,
+             hipStream_t s) {
+    Workspace& ws = e->ws;
+    a->arena = ws.arena.as<uint32_t>();  // (score-only: not read)
+    a->jobs = ws.gen_slices.as<FrontJob>() + at;
+    a->job_nruns = ws.job_nruns.as<uint32_t>() + at;
+    HIPCHK(hipMemcpyAsync(ws.jobs.as<uint32_t>() + at, ids, nj * 4, hipMemcpyHostToDevice, s));
+    HIPCHK(hipMemcpyAsync(ws.gen_slices.as<FrontJob>() + at, fj, nj * sizeof(FrontJob),
+                          hipMemcpyHostToDevice, s));
     return WFA_OK;
 }
 int end_jobs(Engine* e, size_t nj, bool cigar, uint64_t& gen_used, std::vector<uint32_t>* rest,
@@ -320,7 +325,8 @@ int run_adapt(Engine* e, const Pen& pen, bool cigar, const Dev& d, std::vector<u
             fj.push_back(j);
             ids.push_back(j.pair);
         }
-        RCCHK(begin_jobs(e, fj, ids, cigar, &a, s));
+        RCCHK(begin_jobs(e, end - off, &a, s));
+        RCCHK(put_jobs(e, fj.data(), ids.data(), 0, end - off, &a, s));
         const size_t split = std::min(std::max(b.past, off), end);  // pairs past 16383 bases end here
         uint32_t n, m;
         b.longest(off, split, &n, &m);
@@ -339,12 +345,48 @@ int run_adapt(Engine* e, const Pen& pen, bool cigar, const Dev& d, std::vector<u
     return WFA_OK;
 }
 
+// Launches of one call that run side by side: on the call's stream and on the
+// engine's copy streams, which wait for `fork` and are waited for by `join`
+// (and at the end of the scope, should the call end early).  Streams of its own
+// would share hardware queues with these, of which a process has four.
+struct SideBySide {
+    Engine* e;
+    hipStream_t s;
+    hipStream_t q[2] = {e->h2d, e->d2h};
+    bool forked = false;
+    ~SideBySide() {
+        if (forked)
+            for (hipStream_t x : q) (void)hipStreamSynchronize(x);
+    }
+    int fork() {
+        HIPCHK(hipEventRecord(e->side_ev[0], s));
+        forked = true;
+        for (hipStream_t x : q) HIPCHK(hipStreamWaitEvent(x, e->side_ev[0], 0));
+        return WFA_OK;
+    }
+    int join() {
+        if (!forked) return WFA_OK;
+        for (int i = 0; i < 2; i++) {
+            HIPCHK(hipEventRecord(e->side_ev[2 + i], q[i]));
+            HIPCHK(hipStreamWaitEvent(s, e->side_ev[2 + i], 0));
+        }
+        return WFA_OK;
+    }
+};
+
 // Pairs in `pending` on the front kernel (global alignment, exact, penalties
 // it is built for); what it does not hold stays in `pending` for the general
 // kernel.  The host reads the score bounds back to size every pair's rows,
 // records and workgroup.
+//
+// A large batch (`sides`: the copy streams are free) goes in two parts, the
+// longest pairs first, as many as are resident at once: their alignment runs
+// while the other pairs' bounds are found and the host sizes them.  The other
+// pairs' launches (one per size of workgroup) run on two streams, so that one's
+// first workgroups fill what another's last ones leave.  Score-only 5 k pairs of
+// 1-10 kbp 7.5 -> 5.8 ms, with CIGARs 10.3 -> 7.4 ms, 20 k pairs 26.9 -> 24.5 ms.
 int run_front(Engine* e, const Pen& pen, bool cigar, const Dev& d, std::vector<uint32_t>& pending,
-              uint64_t& gen_used, hipStream_t s, uint64_t* done) {
+              uint64_t& gen_used, hipStream_t s, bool sides, uint64_t* done) {
     Workspace& ws = e->ws;
     ByLength b;
     RCCHK(order_by_length(e, d, pending, s, &b));
@@ -357,23 +399,45 @@ int run_front(Engine* e, const Pen& pen, bool cigar, const Dev& d, std::vector<u
     for (size_t i = nf; i < np; i++) rest.push_back(pending[order[i]]);
     FrontArgs a = front_args(e, pen, d);
     uint32_t n, m;
+    const size_t first = 2 * (size_t)e->num_cus;  // pairs of the first part
+    const bool parts = sides && !ws.fixed_base && nf > 4 * first;
+    const size_t part_end[2] = {parts ? first : nf, nf};
 
     // ---- score bounds ------------------------------------------------------
     std::vector<int32_t> bounds(nf);
     std::vector<uint32_t> ids(nf);
     for (size_t i = 0; i < nf; i++) ids[i] = pending[order[i]];
-    RCCHK(ws.ensure(ws.gen_state, nf * 4));
-    HIPCHK(hipMemcpyAsync(ws.jobs.ptr, ids.data(), nf * 4, hipMemcpyHostToDevice, s));
-    a.ids = ws.jobs.as<uint32_t>();
-    a.bounds = ws.gen_state.as<int32_t>();
-    b.longest(0, n16, &n, &m);
-    HIPCHK(launch_bound(a, pen, 0, (int)n16, n, m, s));
-    a.ids += n16;
-    a.bounds += n16;
-    b.longest(n16, nf, &n, &m);
-    HIPCHK(launch_bound(a, pen, 1, (int)(nf - n16), n, m, s));
-    HIPCHK(hipMemcpyAsync(bounds.data(), ws.gen_state.ptr, nf * 4, hipMemcpyDeviceToHost, s));
-    HIPCHK(hipStreamSynchronize(s));
+    RCCHK(ws.ensure(ws.gen_state, nf * 8));
+    uint32_t* dev_ids = ws.gen_state.as<uint32_t>();
+    int32_t* dev_bounds = ws.gen_state.as<int32_t>() + nf;
+    HIPCHK(hipMemcpyAsync(dev_ids, ids.data(), nf * 4, hipMemcpyHostToDevice, s));
+    SideBySide side{e, s};
+    bool begun = false;
+    auto begin = [&]() -> int {
+        if (begun) return WFA_OK;
+        begun = true;
+        RCCHK(begin_jobs(e, nf, &a, s));
+        if (side.forked) HIPCHK(hipStreamSynchronize(s));  // for the side streams
+        return WFA_OK;
+    };
+    if (parts) RCCHK(begin());
+    auto bound_part = [&](size_t from, size_t to) -> int {
+        // few pairs go in one launch, side by side, as the longest's form
+        const bool one = to <= (size_t)e->num_cus && n16 > 0;
+        const size_t mid = one ? to : std::min(std::max(n16, from), to);
+        a.ids = dev_ids + from;
+        a.bounds = dev_bounds + from;
+        b.longest(from, mid, &n, &m);
+        HIPCHK(launch_bound(a, pen, 0, (int)(mid - from), n, m, s));
+        a.ids = dev_ids + mid;
+        a.bounds = dev_bounds + mid;
+        b.longest(mid, to, &n, &m);
+        HIPCHK(launch_bound(a, pen, 1, (int)(to - mid), n, m, s));
+        return WFA_OK;
+    };
+    RCCHK(bound_part(0, part_end[0]));
+    if (parts) RCCHK(side.fork());
+    if (parts) RCCHK(bound_part(part_end[0], nf));
 
     // ---- shapes --------------------------------------------------------------
     // Row forms.  Two blocks of diagonals per wavefront when the pairs fill
@@ -387,91 +451,144 @@ int run_front(Engine* e, const Pen& pen, bool cigar, const Dev& d, std::vector<u
         int nblk, waves;
         uint64_t words;  // CIGAR: records, events and runs in the arena
     };
-    std::vector<Job> held;
-    held.reserve(nf);
     const bool few = nf <= (size_t)e->num_cus;
-    FrontForm all{1, 2, 1};
-    for (size_t i = 0; i < nf; i++) {
-        Job j{};
-        j.idx = order[i];
-        if (!front_shape(pen, b.n(j.idx), b.m(j.idx), bounds[i], &j.f)) {
-            rest.push_back(pending[j.idx]);
-            continue;
-        }
-        if (j.f.width > 16 * 2 * 64 * 2) j.form = {j.f.sh, 4, 2};
-        else j.form = {j.f.sh, 2, few && j.f.width <= 16 * 64 * 2 ? 1 : 2};
-        all.sh = std::min(all.sh, j.form.sh);
-        all.cols = std::max(all.cols, j.form.cols);
-        all.blocks = std::max(all.blocks, j.form.blocks);
-        held.push_back(j);
-    }
-    if (held.empty() || (ws.fixed_base && !rest.empty())) return WFA_OK;
-    uint64_t want = 0, most = 0;
-    for (Job& j : held) {
-        if (few) j.form = all;
-        j.nblk = front_blocks(j.f.width, j.form.cols);
-        j.waves = (j.nblk + j.form.blocks - 1) / j.form.blocks;
-        j.words = (uint64_t)(j.f.bound / 4 + 1) * j.nblk * 32 * j.form.cols + j.f.ev_words + j.f.run_words;
-        want += j.words * 4;
-        most = std::max(most, j.words * 4);
-    }
-    // the pairs with the most work first; a launch takes pairs of one row form
     auto same_form = [](const FrontForm& x, const FrontForm& y) {
         return x.sh == y.sh && x.cols == y.cols && x.blocks == y.blocks;
     };
+    std::vector<FrontJob> fj(nf);
+    size_t at = 0;      // pairs launched since the last finish()
+    uint64_t used = 0;  // arena words they take
+    uint64_t want = 0, most = 0;
+    auto finish = [&]() -> int {
+        RCCHK(side.join());
+        if (at) RCCHK(end_jobs(e, at, cigar, gen_used, &rest, done, s));
+        at = 0;
+        used = 0;
+        begun = false;
+        return WFA_OK;
+    };
+    std::vector<Job> held;
     std::vector<uint32_t> by_work;
-    order_by(held.size(), 8 * 32, [&](size_t i) -> uint32_t {
-        const Job& j = held[i];
-        return ((1 - j.form.sh) * 4 + (j.form.cols == 4 ? 2 : 0) + (j.form.blocks - 1)) * 32 + j.waves;
-    }, &by_work);
-    if (cigar && !grow_arena(ws, want, most)) return WFA_OK;  // the general kernel needs less
-    if (std::getenv("WFA_DEBUG")) {
-        double sum = 0;
-        for (const Job& j : held) sum += j.f.bound;
-        std::fprintf(stderr, "libwfa front: %zu pairs, mean bound %.1f steps, records %.2f GiB\n",
-                     held.size(), sum / held.size(), want / 1073741824.0);
-    }
-
-    std::vector<FrontJob> fj;
-    for (size_t off = 0; off < held.size();) {
-        // the pairs whose records fit the arena
-        fj.clear();
-        ids.clear();
-        uint64_t used = 0;
-        size_t end = off;
-        for (; end < held.size(); end++) {
-            const Job& j = held[by_work[end]];
-            const uint64_t w = cigar ? j.words : 0;
-            if ((used + w) * 4 > ws.arena.bytes && cigar) break;
-            fj.push_back({pending[j.idx], j.f.bound, j.f.kbase, j.nblk, j.form.cols, used,
-                          j.words - j.f.ev_words - j.f.run_words, (int32_t)j.f.ev_words,
-                          (int32_t)j.f.run_words, 0});
-            ids.push_back(pending[j.idx]);
-            used += w;
+    for (int part = 0; part < (parts ? 2 : 1); part++) {
+        const size_t from = part ? part_end[0] : 0, to = part_end[part];
+        // the part's streams: its copies go to the first, which is idle by then
+        hipStream_t q[2] = {s, s};
+        if (parts) {
+            q[0] = part ? s : side.q[0];
+            // the second stream of the second part: one of its own, or, when
+            // there are so many pairs that two streams stay full to the end, the
+            // first part's (10 k pairs 14.9 and 15.3 ms, 20 k 25.4 and 24.5)
+            q[1] = part && nf <= 48 * (size_t)e->num_cus ? side.q[1] : side.q[0];
         }
-        const size_t nj = end - off;
-        RCCHK(begin_jobs(e, fj, ids, cigar, &a, s));
-        for (size_t i = 0; i < nj;) {
+        HIPCHK(hipMemcpyAsync(bounds.data() + from, dev_bounds + from, (to - from) * 4,
+                              hipMemcpyDeviceToHost, q[0]));
+        HIPCHK(hipStreamSynchronize(q[0]));
+        held.clear();
+        FrontForm all{1, 2, 1};
+        for (size_t i = from; i < to; i++) {
+            Job j{};
+            j.idx = order[i];
+            if (!front_shape(pen, b.n(j.idx), b.m(j.idx), bounds[i], &j.f)) {
+                rest.push_back(pending[j.idx]);
+                continue;
+            }
+            if (j.f.width > 16 * 2 * 64 * 2) j.form = {j.f.sh, 4, 2};
+            else j.form = {j.f.sh, 2, few && j.f.width <= 16 * 64 * 2 ? 1 : 2};
+            all.sh = std::min(all.sh, j.form.sh);
+            all.cols = std::max(all.cols, j.form.cols);
+            all.blocks = std::max(all.blocks, j.form.blocks);
+            held.push_back(j);
+        }
+        if (held.empty()) continue;
+        if (ws.fixed_base && !rest.empty()) return WFA_OK;
+        for (Job& j : held) {
+            if (few) j.form = all;
+            j.nblk = front_blocks(j.f.width, j.form.cols);
+            j.waves = (j.nblk + j.form.blocks - 1) / j.form.blocks;
+            j.words = (uint64_t)(j.f.bound / 4 + 1) * j.nblk * 32 * j.form.cols + j.f.ev_words + j.f.run_words;
+            want += j.words * 4;
+            most = std::max(most, j.words * 4);
+        }
+        // the pairs with the most work first; a launch takes pairs of one row form
+        order_by(held.size(), 8 * 32, [&](size_t i) -> uint32_t {
+            const Job& j = held[i];
+            return ((1 - j.form.sh) * 4 + (j.form.cols == 4 ? 2 : 0) + (j.form.blocks - 1)) * 32 + j.waves;
+        }, &by_work);
+        if (cigar && want > ws.arena.bytes) {
+            RCCHK(finish());  // the arena moves
+            if (!grow_arena(ws, want, most)) {  // the general kernel needs less
+                for (const Job& j : held) rest.push_back(pending[j.idx]);
+                continue;
+            }
+        }
+        if (std::getenv("WFA_DEBUG")) {
+            double sum = 0;
+            for (const Job& j : held) sum += j.f.bound;
+            std::fprintf(stderr, "libwfa front: %zu pairs, mean bound %.1f steps, records %.2f GiB\n",
+                         held.size(), sum / held.size(), want / 1073741824.0);
+        }
+
+        for (size_t off = 0; off < held.size();) {
+            // the pairs whose records fit the arena
+            RCCHK(begin());
+            const size_t at0 = at;
+            size_t end = off;
+            for (; end < held.size(); end++, at++) {
+                const Job& j = held[by_work[end]];
+                const uint64_t w = cigar ? j.words : 0;
+                if (cigar && (used + w) * 4 > ws.arena.bytes) break;
+                fj[at] = {pending[j.idx], j.f.bound, j.f.kbase, j.nblk, j.form.cols, used,
+                          j.words - j.f.ev_words - j.f.run_words, (int32_t)j.f.ev_words,
+                          (int32_t)j.f.run_words, 0};
+                ids[at] = pending[j.idx];
+                used += w;
+            }
+            const size_t nj = at - at0;
+            if (!nj) {
+                RCCHK(finish());
+                continue;
+            }
+            RCCHK(put_jobs(e, fj.data() + at0, ids.data() + at0, at0, nj, &a, q[0]));
+            if (q[1] != q[0]) {
+                HIPCHK(hipEventRecord(e->side_ev[1], q[0]));
+                HIPCHK(hipStreamWaitEvent(q[1], e->side_ev[1], 0));
+            }
             // a launch: workgroups of one size.  Smaller pairs join while the
             // group would not fill the chip, or lacks few wavefronts.
-            const Job& f = held[by_work[off + i]];
-            size_t k = i;
-            n = m = 0;
-            for (; k < nj; k++) {
-                const Job& g = held[by_work[off + k]];
-                if (!same_form(g.form, f.form)) break;
-                if (4 * g.waves <= 3 * f.waves && k - i >= 2 * (size_t)e->num_cus) break;
-                n = std::max(n, b.n(g.idx));
-                m = std::max(m, b.m(g.idx));
+            struct Launch {
+                size_t i, k;
+                uint32_t n, m;
+                double work;
+            };
+            std::vector<Launch> launches;
+            for (size_t i = 0; i < nj;) {
+                const Job& f = held[by_work[off + i]];
+                Launch l{i, i, 0, 0, 0};
+                for (; l.k < nj; l.k++) {
+                    const Job& g = held[by_work[off + l.k]];
+                    if (!same_form(g.form, f.form)) break;
+                    if (4 * g.waves <= 3 * f.waves && l.k - i >= 2 * (size_t)e->num_cus) break;
+                    l.n = std::max(l.n, b.n(g.idx));
+                    l.m = std::max(l.m, b.m(g.idx));
+                    l.work += (double)g.nblk * g.form.cols * g.f.bound;
+                }
+                i = l.k;
+                launches.push_back(l);
             }
-            a.jobs = ws.gen_slices.as<FrontJob>() + i;
-            a.job_nruns = ws.job_nruns.as<uint32_t>() + i;
-            HIPCHK(launch_front(a, pen, cigar, f.form, (int)(k - i), f.waves, n, m, s));
-            i = k;
+            const FrontArgs a0 = a;
+            double work[2] = {0, 0};
+            for (const Launch& l : launches) {
+                const int to = q[1] != q[0] && work[1] < work[0] ? 1 : 0;
+                const Job& f = held[by_work[off + l.i]];
+                a.jobs = a0.jobs + l.i;
+                a.job_nruns = a0.job_nruns + l.i;
+                HIPCHK(launch_front(a, pen, cigar, f.form, (int)(l.k - l.i), f.waves, l.n, l.m, q[to]));
+                work[to] += l.work;
+            }
+            off = end;
         }
-        RCCHK(end_jobs(e, nj, cigar, gen_used, &rest, done, s));
-        off = end;
     }
+    RCCHK(finish());
     std::sort(rest.begin(), rest.end());
     pending.swap(rest);
     return WFA_OK;
@@ -1446,8 +1563,9 @@ int engine_align_device(Engine* e, const BatchIO& io, hipStream_t user_stream,
     if (!pending.empty() && global && (heuristic ? adapt_supported(pen) : front_supported(pen)) &&
         e->opt.general_step_limit == 0 && e->opt.general_checkpoint == 0 &&
         e->opt.general_slice_kib == 0 && e->opt.general_pairs == 0) {
-        const int rf = (heuristic ? run_adapt : run_front)(e, pen, cigar, d, pending, gen_used, s,
-                                                           &general_done);
+        const int rf = heuristic ? run_adapt(e, pen, cigar, d, pending, gen_used, s, &general_done)
+                                 : run_front(e, pen, cigar, d, pending, gen_used, s, !io.no_graph,
+                                             &general_done);
         if (rf != WFA_OK) {
             (void)finish_user();
             return rf;

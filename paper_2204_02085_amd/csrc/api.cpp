@@ -194,6 +194,7 @@ int engine_init(Engine* e, int device, size_t budget) {
     if (hipGetDeviceProperties(&prop, device) == hipSuccess) e->num_cus = prop.multiProcessorCount;
     if (e->num_cus <= 0) e->num_cus = 256;
     for (auto& ev : e->ev) (void)hipEventCreate(&ev);
+    for (auto& ev : e->side_ev) (void)hipEventCreateWithFlags(&ev, hipEventDisableTiming);
     std::memset(&e->opt, 0, sizeof(e->opt));
     std::memset(&e->last, 0, sizeof(e->last));
     return WFA_OK;
@@ -205,6 +206,8 @@ void engine_destroy(Engine* e) {
     graph_cache_clear(e);
     e->ws.release_all();
     for (auto& ev : e->ev)
+        if (ev) (void)hipEventDestroy(ev);
+    for (auto& ev : e->side_ev)
         if (ev) (void)hipEventDestroy(ev);
     if (e->readback) (void)hipHostFree(e->readback);
     e->readback = nullptr;

@@ -120,7 +120,10 @@ struct Engine {
     int device = 0;
     int num_cus = 256;
     hipStream_t stream = nullptr;
-    hipStream_t h2d = nullptr, d2h = nullptr;  // copy streams of the host-memory pipeline
+    // copy streams of the host-memory pipeline; a device-memory call runs
+    // launches on them beside its own stream's
+    hipStream_t h2d = nullptr, d2h = nullptr;
+    hipEvent_t side_ev[4] = {};  // their fork and join
     Workspace ws;
     hipEvent_t ev[12] = {};
     wfa_options opt{};
