@@ -240,7 +240,9 @@ __global__ __launch_bounds__(64) void k_adapt(FrontArgs a) {
         if (s > job.bound || ul > uh || width + 2 > AW) break;
         const int room = width + 2 <= BW ? BW : AW;
         if (ul - 4 < kmin || uh + 4 > kmin + room - 1) {
-            int shift = (((ul + uh) >> 1) - room / 2 - kmin) / 2;  // lanes
+            // in the middle, rounded down to a lane: of the columns to spare
+            // there are at least two, so both margins hold
+            int shift = (ul - 4 - (room - width) / 2 - kmin) >> 1;  // lanes
             kmin += 2 * shift;
             for (; shift > 0; shift--) {
 #pragma unroll

@@ -62,3 +62,20 @@ def test_windows(aligner, oracle_lib, synth_lib, pen, heur):
     sc, _, _ = aligner.align(b, pen, cigar=False)
     assert np.array_equal(sc, ref.scores)
     assert aligner.stats()["general_pairs"] == len(b)
+
+
+@pytest.mark.parametrize("heur", [(10, 50), (10, 80)])
+def test_every_width(aligner, oracle_lib, synth_lib, heur):
+    """Gaps of every length about one block: the kept ranges take every width up
+    to it, at both parities, so the window is placed with nothing to spare."""
+    rng = np.random.default_rng(29)
+    pairs = []
+    for gap in range(90, 150):
+        p = _seq(rng, 1600)
+        t = np.concatenate([p[:700], _seq(rng, gap), p[700:]])
+        pairs += [(p, t), (t, p), (_noisy(rng, p, 0.02), t)]
+    b = synth_lib.from_pairs([(bytes(p), bytes(t)) for p, t in pairs])
+    say(f"case: adaptive windows of every width, heuristic {heur}, {len(b)} pairs")
+    ref = oracle_lib.align_batch(b, (4, 6, 2), cigar=True, threads=8, adaptive=heur)
+    aligner.set_heuristic(*heur)
+    assert_same(aligner.align(b, (4, 6, 2), capacity=int(ref.offsets[-1]) + 8), ref, b, f"{heur}")
