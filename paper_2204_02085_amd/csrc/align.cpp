@@ -294,7 +294,7 @@ int run_adapt(Engine* e, const Pen& pen, bool cigar, const Dev& d, std::vector<u
             return j;
         }
         j.bound = (int32_t)(std::max(n, m) / 4 * 3 + 64);
-        j.hist_words = ((uint64_t)(j.bound / 4 + 2) * ADAPT_QUAD_WORDS + 63) & ~63ull;
+        j.hist_words = adapt_hist_words(j.bound);
         j.ev_words = (j.bound / std::min(pen.x, pen.oe) + 64) & ~63;
         j.run_words = 2 * j.ev_words + 64;
         return j;
@@ -505,7 +505,7 @@ int run_front(Engine* e, const Pen& pen, bool cigar, const Dev& d, std::vector<u
             if (few) j.form = all;
             j.nblk = front_blocks(j.f.width, j.form.cols);
             j.waves = (j.nblk + j.form.blocks - 1) / j.form.blocks;
-            j.words = (uint64_t)(j.f.bound / 4 + 1) * j.nblk * 32 * j.form.cols + j.f.ev_words + j.f.run_words;
+            j.words = front_hist_words(j.f.bound, j.nblk, j.form.cols) + j.f.ev_words + j.f.run_words;
             want += j.words * 4;
             most = std::max(most, j.words * 4);
         }

@@ -223,6 +223,11 @@ __global__ __launch_bounds__(64) void k_adapt(FrontArgs a) {
 #pragma unroll
                 for (int b = 0; b < nb; b++) q[64 * b + lane] = acc[b] << (4 * (3 - u));
                 if (lane == 0) q[64 * NB] = (uint32_t)kmin;
+                if (u == 3 && (s & 15) == 0) {
+                    uint32_t* r = hist + adapt_rec_words(job.bound) + (uint64_t)(s >> 4) * (64 * NB);
+#pragma unroll
+                    for (int b = 0; b < nb; b++) r[64 * b + lane] = cm[b];
+                }
             }
         }
     };
@@ -295,7 +300,14 @@ __global__ __launch_bounds__(64) void k_adapt(FrontArgs a) {
         }
         return kf;
     };
-    const int nr = walk<X, OE, E, true>(load, S, n, m, lane, win, evs, job.ev_words, runs_end,
+    auto offset = [&](int s, int k) {
+        const int col = k - (int)hist[(uint64_t)(s >> 2) * ADAPT_QUAD_WORDS + QW];
+        const uint32_t w = col >= 0 && col < AW
+                               ? hist[adapt_rec_words(job.bound) + (uint64_t)(s >> 4) * QW + (col >> 1)]
+                               : NUL16P;
+        return (int)(short)(w >> (16 * (col & 1))) >> SH;
+    };
+    const int nr = walk<X, OE, E, true>(load, offset, S, n, m, lane, win, evs, job.ev_words, runs_end,
                                         job.run_words, tb, pb);
     walk_done(a, job, S, nr, runs_end, lane);
 }

@@ -121,26 +121,31 @@ __global__ __launch_bounds__(64) void k_bound(FrontArgs a) {
 }
 
 // The walk over a pair's records.
-template <int X, int OE, int E>
+template <int X, int OE, int E, int SH>
 __device__ void walk_job(const FrontArgs& a, const FrontJob& job, int S, int n, int m, int lane,
                          lds_p<uint32_t> win, uint32_t tb, uint32_t pb) {
     typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
     constexpr int ROW = WALK_COLS / 2;
-    const int rowdw = job.nw * 32 * job.cols;  // dwords per quad of steps
+    const int rowdw = front_row_words(job.nw, job.cols);
     const uint32_t* hist = a.arena + job.hist;
     uint32_t* evs = a.arena + job.hist + job.hist_words;
     uint32_t* runs_end = evs + job.ev_words + job.run_words;
     auto load = [&](int q, int k) {
         const int c0 = min(max((((k - job.kbase) >> 1) - ROW / 2) & ~3, 0), rowdw - ROW);
         if (q - lane >= 0) {
-            const u32x4* from = (const u32x4*)(hist + (uint64_t)(q - lane) * rowdw + c0);
+            const u32x4* from = (const u32x4*)(hist + (uint64_t)front_row(4 * (q - lane)) * rowdw + c0);
             lds_p<u32x4> to = (lds_p<u32x4>)(win + lane * ROW);
 #pragma unroll
             for (int i = 0; i < ROW / 4; i++) to[i] = from[i];
         }
         return job.kbase + 2 * c0;
     };
-    const int nr = walk<X, OE, E, false>(load, S, n, m, lane, win, evs, job.ev_words, runs_end,
+    auto offset = [&](int s, int k) {
+        const int col = k - job.kbase;
+        const uint32_t w = col >= 0 && (col >> 1) < rowdw ? hist[(uint64_t)(front_row(s) + 4) * rowdw + (col >> 1)] : NUL16P;
+        return (int)(short)(w >> (16 * (col & 1))) >> SH;
+    };
+    const int nr = walk<X, OE, E, false>(load, offset, S, n, m, lane, win, evs, job.ev_words, runs_end,
                                          job.run_words, tb, pb);
     walk_done(a, job, S, nr, runs_end, lane);
 }
@@ -232,9 +237,14 @@ void k_front(FrontArgs a) {
     };
     auto flush = [&](B& q, int s, int b) {
         if (CIGAR) {
-            uint32_t* h = a.arena + job.hist + ((uint64_t)(s >> 2) * job.nw + b) * (64 * P) + lane * P;
+            uint32_t* h = a.arena + job.hist + ((uint64_t)front_row(s) * job.nw + b) * (64 * P) + lane * P;
 #pragma unroll
             for (int p = 0; p < P; p++) h[p] = q.row.acc[p];
+            if ((s & 15) == 0) {
+                uint32_t* r = h + (uint64_t)(4 * job.nw) * (64 * P);
+#pragma unroll
+                for (int p = 0; p < P; p++) r[p] = q.row.M[0][p];
+            }
         }
     };
     __syncthreads();
@@ -298,7 +308,7 @@ void k_front(FrontArgs a) {
     // the others' slots go to the next workgroup
     __threadfence_block();
     __syncthreads();
-    if (w == 0) walk_job<X, OE, E>(a, job, S2, n, m, lane, win, tb, pb);
+    if (w == 0) walk_job<X, OE, E, SH>(a, job, S2, n, m, lane, win, tb, pb);
 }
 
 // Scaled penalties (x, o + e, e) the rows are built for.

@@ -147,14 +147,22 @@ struct BandPlan {
 };
 
 // One pair of a front-kernel launch.
+// A pair's records: every 16 steps five rows of its blocks, the records of four
+// steps in each of the first four, then the M row of the group's fourth step
+// (see walk.h).  Words of a row, and the row of step s's records.
+constexpr int front_row_words(int nblk, int cols) { return nblk * 32 * cols; }
+constexpr int front_row(int s) { return (s >> 4) * 5 + ((s >> 2) & 3); }
+constexpr uint64_t front_hist_words(int bound, int nblk, int cols) {
+    return (uint64_t)front_row((bound | 15) + 1) * front_row_words(nblk, cols);
+}
 struct FrontJob {
     uint32_t pair;
     int32_t bound;        // no optimal alignment needs more score steps
     int32_t kbase;        // diagonal of column 0
     int32_t nw;           // blocks of 64 * cols diagonals
     int32_t cols;         // diagonals per lane (2 or 4)
-    uint64_t hist;        // CIGAR: the pair's words in the arena: records,
-    uint64_t hist_words;  // events, runs
+    uint64_t hist;        // CIGAR: the pair's words in the arena: records and
+    uint64_t hist_words;  // rows, events, runs
     int32_t ev_words, run_words, pad;
 };
 
@@ -339,6 +347,11 @@ hipError_t launch_front(const FrontArgs& a, const Pen& pen, bool cigar, const Fr
 // hold (ADAPT_QUAD_WORDS words per four steps), pairs it does not hold go to
 // the fail list.  A launch takes pairs of one `sh` (1: up to 16383 bases).
 constexpr int ADAPT_QUAD_WORDS = 2 * 64 + 1;  // both blocks' records, the window's base
+// a pair's record words, then with its M rows of every 16th step (see walk.h)
+constexpr uint64_t adapt_rec_words(int bound) { return (uint64_t)(bound / 4 + 2) * ADAPT_QUAD_WORDS; }
+constexpr uint64_t adapt_hist_words(int bound) {
+    return (adapt_rec_words(bound) + (uint64_t)(bound / 16 + 1) * 128 + 63) & ~(uint64_t)63;
+}
 bool adapt_supported(const Pen& pen);
 hipError_t launch_adapt(const FrontArgs& a, const Pen& pen, bool cigar, int sh, int jobs, uint32_t n,
                         uint32_t m, hipStream_t s);
