@@ -242,27 +242,24 @@ __device__ __forceinline__ uint32_t win16(uint32_t base, int b) {
 }
 
 // Extend the cells m of one step along matches (sequences in LDS at byte
-// addresses tb, pb) and drop those past the matrix.  Sixteen bases first;
-// a wavefront goes on only while one of its lanes still matches.
+// addresses tb, pb) and drop those past the matrix.  Fifteen bases first (a stop
+// bit in place of the sixteenth bounds the count); a wavefront goes on only while
+// one of its lanes still matches.  What runs past the matrix is cut off by one
+// packed minimum at the end.
 template <int C, int SH>
 __device__ __forceinline__ void extend(uint32_t (&m)[C / 2], const Place<C>& pl, uint32_t tb,
                                        uint32_t pb) {
     constexpr int P = C / 2;
-    uint32_t bad[P], hv[P], rm[P], x[C], r[C];
+    constexpr uint32_t STOP = 0x80000000u;
+    uint32_t bad[P], hv[P], x[C], r[C];
 #pragma unroll
     for (int p = 0; p < P; p++) {
-        const uint32_t u = pk_sub(pl.lim[p], m[p]);
-        bad[p] = pk_sign(m[p] | u);
+        bad[p] = pk_sign(m[p] | pk_sub(pl.lim[p], m[p]));
         hv[p] = bit_select(bad[p], pl.safe[p], m[p]);
-        rm[p] = u & ~bad[p];  // what is left before the matrix ends
-        asm("" : "+v"(rm[p]));
     }
-    // bit position of column c in the text, bits left
+    // bit position of column c in the text
     auto pos = [&](int c) -> uint32_t {
         return ((c & 1) ? hv[c / 2] >> 16 : hv[c / 2] & 0xffffu) << (1 - SH);
-    };
-    auto left = [&](int c) -> uint32_t {
-        return ((c & 1) ? rm[c / 2] >> 16 : rm[c / 2] & 0xffffu) << (1 - SH);
     };
     // every column's loads go out before the first is used (left to itself the
     // compiler waits for each pair in turn)
@@ -281,25 +278,26 @@ __device__ __forceinline__ void extend(uint32_t (&m)[C / 2], const Place<C>& pl,
     uint32_t lo = ~0u;
 #pragma unroll
     for (int c = 0; c < C; c++) {
-        x[c] = __builtin_amdgcn_alignbit(t1[c], t0[c], pos(c)) ^
-               __builtin_amdgcn_alignbit(p1[c], p0[c], (uint32_t)v[c]);
-        uint32_t z;
-        asm("v_ffbl_b32 %0, %1" : "=v"(z) : "v"(x[c]));  // ~0 for a zero word
-        r[c] = min(z, left(c));  // bits; an odd one rounds down below
+        x[c] = (__builtin_amdgcn_alignbit(t1[c], t0[c], pos(c)) ^
+                __builtin_amdgcn_alignbit(p1[c], p0[c], (uint32_t)v[c])) | STOP;
+        // bits; an odd one rounds down below
+        asm("v_ffbl_b32 %0, %1" : "=v"(r[c]) : "v"(x[c]));
         lo = min(lo, x[c]);
     }
-    if (lanes_where(lo == 0)) {
+    if (lanes_where(lo == STOP)) {
 #pragma unroll
         for (int c = 0; c < C; c++) {
-            if (x[c] == 0 && left(c) > 32) {
+            const uint32_t left = pk_sub(pl.lim[c / 2], hv[c / 2]) & ~bad[c / 2];
+            const uint32_t end = ((c & 1) ? left >> 16 : left & 0xffffu) << (1 - SH);
+            if (x[c] == STOP && end > 30) {
                 const int h = (int)pos(c);
-                uint32_t done = 32, z;
+                uint32_t done = 30, z;
                 do {
                     const uint32_t y = win16(tb, h + (int)done) ^ win16(pb, v[c] + (int)done);
-                    asm("v_ffbl_b32 %0, %1" : "=v"(z) : "v"(y));
+                    asm("v_ffbl_b32 %0, %1" : "=v"(z) : "v"(y));  // ~0 for a zero word
                     done += min(z, 32u);
-                } while (z >= 32 && done < left(c));
-                r[c] = min(done, left(c));
+                } while (z >= 32 && done < end);
+                r[c] = done;
             }
         }
     }
@@ -307,7 +305,7 @@ __device__ __forceinline__ void extend(uint32_t (&m)[C / 2], const Place<C>& pl,
     for (int p = 0; p < P; p++) {
         const uint32_t rr = SH ? (r[2 * p] | (r[2 * p + 1] << 16)) & 0xFFFEFFFEu
                                : (r[2 * p] >> 1) | ((r[2 * p + 1] >> 1) << 16);
-        m[p] = bit_select(bad[p], NUL16P, hv[p] + rr);
+        m[p] = bit_select(bad[p], NUL16P, pk_minu(hv[p] + rr, pl.lim[p]));
     }
 }
 
