@@ -272,55 +272,58 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5))) void k
                 ne++;
             }
             // replay: from the start along matches, edit by edit; runs go to
-            // the front of the records, in alignment order
+            // the front of the records, in alignment order.  Only an eighth of
+            // the lanes is here, so every instruction counts: 32 bases a compare,
+            // stores without branches (a store past the last run is overwritten).
             int h = max(k, 0), v = h - k;
-            int nr = 0, cop = -1, clen = 0;
-            auto emit = [&](int op, int len) {
-                if (len <= 0) return;
-                if (op == cop) {
-                    clen += len;
-                } else {
-                    if (cop >= 0) HI[nr++] = ((uint32_t)clen << 4) | (uint32_t)cop;
-                    cop = op;
-                    clen = len;
-                }
+            int nr = 0, last_op = -1;  // -1: a match run, or none
+            uint32_t cur = 0;          // the last edit run
+            auto edit = [&](int op, int len) {
+                const bool same = op == last_op;
+                cur = same ? cur + ((uint32_t)len << 4) : ((uint32_t)len << 4) | (uint32_t)op;
+                nr += same ? 0 : 1;
+                HI[nr - 1] = cur;
+                last_op = op;
             };
             if (!bad) {
                 if (ENDS) {
-                    emit(2, k);
-                    emit(3, -k);
+                    if (k > 0) edit(2, k);
+                    if (k < 0) edit(3, -k);
                 }
                 for (int e2 = ne;; e2--) {
                     // matches from (v, h) on
-                    int left = min(n - v, m - h), mm = 0;
-                    while (left > 0) {
-                        const uint32_t y = win16(tb, 2 * (h + mm)) ^ win16(pb, 2 * (v + mm));
-                        const int z = min(y ? (int)(__builtin_ctz(y) >> 1) : 16, left);
-                        mm += z;
-                        left -= z;
-                        if (z < 16) break;
+                    const int left = min(n - v, m - h);
+                    int mm = 0;
+                    for (;;) {
+                        const uint32_t x0 = win16(tb, 2 * (h + mm)) ^ win16(pb, 2 * (v + mm));
+                        const uint32_t x1 = win16(tb, 2 * (h + mm) + 32) ^ win16(pb, 2 * (v + mm) + 32);
+                        const uint64_t x = ((uint64_t)x1 << 32) | x0;
+                        mm += x ? (int)(__builtin_ctzll(x) >> 1) : 32;
+                        if (x || mm >= left) break;
                     }
-                    emit(0, mm);
+                    mm = min(mm, left);
+                    HI[nr] = (uint32_t)mm << 4;
+                    nr += mm > 0 ? 1 : 0;
+                    last_op = mm > 0 ? -1 : last_op;
                     h += mm;
                     v += mm;
                     if (e2 == 0) break;
                     const uint32_t ev = HI[top - e2];
                     const int len = (int)(ev >> 2), kind = (int)(ev & 3);
-                    emit(1 + kind, len);
-                    if (kind != EV_D) h += len;
-                    if (kind != EV_I) v += len;
+                    edit(1 + kind, len);
+                    h += kind != EV_D ? len : 0;
+                    v += kind != EV_I ? len : 0;
                     if (h > m || v > n) {
                         bad = true;
                         break;
                     }
                 }
                 if (!ENDS && (h != m || v != n)) bad = true;
-                if (ENDS) {
+                if (ENDS && !bad) {
                     if (h < m && v < n) bad = true;
-                    emit(3, n - v);
-                    emit(2, m - h);
+                    if (v < n) edit(3, n - v);
+                    if (h < m) edit(2, m - h);
                 }
-                if (cop >= 0) HI[nr++] = ((uint32_t)clen << 4) | (uint32_t)cop;
             }
             if (bad || nr > a.slot_cap) overflow = true;
             cnt = nr;
