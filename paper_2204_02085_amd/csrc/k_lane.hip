@@ -1,487 +1,354 @@
-// One lane per pair: the wavefront algorithm with every wavefront row of a
-// pair in registers, for short reads under a fixed penalty set.
+// One lane per pair: short reads under a fixed penalty set, every wavefront row
+// of a pair in the registers of one lane, 64 pairs stepping together.
 //
 // The paper runs one pair per DPU thread (Introduction and Methods); on a
-// GPU the same independence puts one pair on each lane of a wavefront, 64
-// pairs stepping through the score steps together.  What makes this pay on
-// CDNA is that, for fixed scaled penalties (x', o'+e', e'), which (s, k)
-// cells of the WFA recurrences can hold an offset at all does not depend on
-// the sequences:
+// GPU the same independence puts one pair on each lane.  What makes this pay on
+// CDNA is that, for fixed scaled penalties (x', o'+e', e'), which (s, k) cells can
+// matter does not depend on the sequences:
 //
 //   M_0[0] exists; I_s[k] exists if M_{s-o'-e'}[k-1] or I_{s-e'}[k-1] does;
 //   D_s[k] exists if M_{s-o'-e'}[k+1] or D_{s-e'}[k+1] does; M_s[k] exists
-//   if M_{s-x'}[k], I_s[k] or D_s[k] does.
+//   if M_{s-x'}[k], I_s[k] or D_s[k] does;
+//   and a pair that ends by step CAP on a diagonal kt of at most LANE_KT has no
+//   cell of an optimal alignment with s + e' |k - kt| > CAP.
 //
-// So the kernel is unrolled at compile time over exactly those cells (167
-// M cells for steps 0..16 under (4, 6, 2), against 289 in the full
-// triangle), every source index is a constant, the rows are plain
-// registers, and a cell whose source cannot exist drops that candidate at
-// compile time.  All lanes compute the same cells; each lane's own values
-// differ.  The recurrences, the admissibility rule (a candidate offset c on
-// diagonal k counts only if 0 <= c <= min(m, n + k), dropped before the
-// maximum), the extension along matches, the termination test
-// (M_s[m - n] == m) and the tie-break of the decision records are those of
-// the short-pair kernel, so the results are bit-identical to it and to the
-// oracle.
+// So the kernel is unrolled at compile time over a diamond of registers, two
+// neighbouring diagonals to each as 16-bit offsets (rows.h): 81 register-steps
+// for steps 0..16 under (4, 6, 2), every source a constant register, the
+// neighbour's column one funnel shift away, no data exchange between lanes.
+// Offsets past the matrix are dropped from M after the maximum (rows.h has the
+// argument), so scores and tie-breaks are those of the full wavefronts.
 //
-// LDS per wavefront, lane-interleaved (dword q of lane l at q * 64 + l, so
-// 64 lanes reading "their" dword q hit 64 different banks): the pattern and
-// the text in 2-bit little-endian words, and the bytes of one step's cells
-// on their way to the history.  Per block: the (s, k) -> compact cell table
-// and the (s, k) -> history byte table (the target test, the walk); the
-// diagonal of each compact cell is a constant table read with scalar loads.
-// Global memory per wavefront, lane-interleaved the same way (CIGAR mode):
-// the history of every reachable M cell, its offset after extension (one
-// byte, 0x80 for NULL; each step's staged dwords as they stand) and its
-// 4-bit decision record (source of M: mismatch / end of insertion / end of
-// deletion; whether I and D opened from M, packed in the cells' compile-time
-// order), then a stage for the runs.  Keeping it out of LDS leaves room for four wavefronts per SIMD.
-// The backtrace is the short kernel's walk, run by every lane on its own
-// pair.
+// What bounds it: VALU issue (0.9 of the slots with CIGARs, all of them without).
+// About 50 instructions per register and step with CIGARs, 15 bases of each
+// cell's matches among them; a wavefront follows longer matches, 32 bases at a
+// time, while one of its lanes has some.  5 M pairs of 100 bp at E = 4 % in the
+// kernel: 1.01 ms with CIGARs, 0.74 without, where a form with a byte per
+// diagonal and a cell at a time, over all 167 cells that can hold an offset, took
+// 1.48 and 1.03.
 //
-// A pair leaves through the overflow list (to the wider short-kernel passes
-// and the general kernel) when a sequence is longer than LMAX bases, when
-// its target diagonal lies outside the cells the kernel holds, when it needs
-// more than CAP steps, or when its walk or runs do not fit.
+// LDS per wavefront, lane-interleaved (dword q of lane l at q * 64 + l, so 64
+// lanes reading "their" dword q hit 64 different banks): both sequences in 2-bit
+// words, and (CIGAR) the runs.  Global memory per wavefront, interleaved the same
+// way: the decision records, four bits a cell, four steps of a register to a
+// dword.  Every lane walks its own pair's records back to at most eight edits, kept
+// in a register pair, and replays these from the start along matches.
+//
+// A pair leaves through the overflow list (to the band kernel's passes) when a
+// sequence is longer than LMAX bases, when its end diagonal lies beyond LANE_KT,
+// or when it needs more than CAP steps.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <algorithm>
 #include <utility>
 
 #include "kernels.h"
 #include "pack.h"
+#include "rows.h"
 
 namespace wfa {
 
 namespace {
 
-// NULL offset: far below every offset, and its low byte is 0x80, the NULL
-// byte of the packed rows, the staging and the history
-constexpr int LNUL = -(1 << 20) + 0x80;
-
-// Which cells of steps 0..CAP can hold an offset (see above), and the
-// compact history index of each reachable M cell.
-template <int X, int OE, int E, int CAP, int KM>
-struct LaneReach {
-    static constexpr int W = 2 * KM + 1;
-    bool m[CAP + 1][W] = {};
-    bool i[CAP + 1][W] = {};
-    bool d[CAP + 1][W] = {};
-    short cidx[CAP + 1][W] = {};
-    int ncells = 0;
-    int kmax = 0;
-    constexpr LaneReach() {
-        for (int s = 0; s <= CAP; s++)
-            for (int j = 0; j < W; j++) cidx[s][j] = -1;
-        m[0][KM] = true;
-        for (int s = 1; s <= CAP; s++) {
-            for (int j = 0; j < W; j++) {
-                bool iv = false, dv = false, mv = false;
-                if (s >= OE && j >= 1 && m[s - OE][j - 1]) iv = true;
-                if (s >= E && j >= 1 && i[s - E][j - 1]) iv = true;
-                if (s >= OE && j + 1 < W && m[s - OE][j + 1]) dv = true;
-                if (s >= E && j + 1 < W && d[s - E][j + 1]) dv = true;
-                if (s >= X && m[s - X][j]) mv = true;
-                i[s][j] = iv;
-                d[s][j] = dv;
-                m[s][j] = mv || iv || dv;
-            }
-        }
-        int c = 0;
-        for (int s = 0; s <= CAP; s++)
-            for (int j = 0; j < W; j++)
-                if (m[s][j]) {
-                    cidx[s][j] = (short)c++;
-                    const int k = j - KM;
-                    kmax = (k > kmax) ? k : ((-k > kmax) ? -k : kmax);
-                }
-        ncells = c;
-    }
-};
-
-template <class P>
-__device__ __forceinline__ uint32_t lds_u32(P base, int dw) {
-    return base[dw];
-}
-
-// 16 bases from base `pos` of a lane's sequence column (dword q at q * 64).
-template <class P>
-__device__ __forceinline__ uint32_t col_window16(P col, int pos) {
-    const int q = pos >> 4;
-    const uint32_t b = (uint32_t)(pos & 15) << 1;
-    return __builtin_amdgcn_alignbit(col[q * 64 + 64], col[q * 64], b);
-}
-
-// 32 bases from base `pos` of a lane's sequence column (dword q at q * 64).
-template <class P>
-__device__ __forceinline__ uint64_t col_window32(P col, int pos) {
-    const int q = pos >> 4;
-    const uint32_t b = (uint32_t)(pos & 15) << 1;
-    const uint32_t w0 = col[q * 64], w1 = col[q * 64 + 64], w2 = col[q * 64 + 128];
-    const uint32_t lo = __builtin_amdgcn_alignbit(w1, w0, b);
-    const uint32_t hi = __builtin_amdgcn_alignbit(w2, w1, b);
-    return ((uint64_t)hi << 32) | lo;
-}
+using namespace rows;
 
 template <class T>
-using lptr = __attribute__((address_space(3))) T*;
+using lptr = lds_p<T>;
 template <class T>
 using gptr_t = __attribute__((address_space(1))) T*;
 
-template <int X, int OE, int E, int CAP, int LMAX, bool CIGAR>
-struct LaneKernel {
-    static constexpr int KM = CAP;  // array half-width; reachable |k| stays below it
-    static constexpr int CAP1 = CAP + 1;
-    using R = LaneReach<X, OE, E, CAP, KM>;
-    static constexpr R reach{};
-    static constexpr int W = R::W;
-    static_assert(reach.kmax < KM, "reachable cells must stay inside the arrays");
-    static constexpr int NC = reach.ncells;
-    static constexpr int RM = (X > OE ? X : OE) + 1;  // ring of M rows (registers)
-    static constexpr int RID = E + 1;                 // rings of I and D rows (registers)
-    static constexpr int SQ = (LMAX >> 4) + 3;        // dwords per sequence column
+constexpr int LANE_KT = 4;  // end diagonals held: reads of a few edits
 
-    // the diagonal of each compact cell, as a constant table the extension
-    // loop reads with scalar loads (its cell index is wave-uniform)
-    struct Kof {
-        int k[NC > 0 ? NC : 1] = {};
-        constexpr Kof() {
-            for (int s = 0; s <= CAP; s++)
-                for (int j = 0; j < W; j++)
-                    if (reach.cidx[s][j] >= 0) k[reach.cidx[s][j]] = j - KM;
+// Which registers (diagonals 2p and 2p + 1, p = index - PR) hold cells at each
+// step, which have records, and where these go.
+template <int X, int OE, int E, int CAP>
+struct LanePlan {
+    static constexpr int reach(int s) {  // largest |k| of the diamond at step s
+        if (s < OE) return 0;
+        const int out = 1 + (s - OE) / E, back = (CAP - s) / E + LANE_KT;
+        return out < back ? out : back;
+    }
+    static constexpr int most() {
+        int r = 0;
+        for (int s = 0; s <= CAP; s++) r = reach(s) > r ? reach(s) : r;
+        return r;
+    }
+    static constexpr int PR = (most() + 2) / 2;
+    static constexpr int NP = 2 * PR, Q = CAP / 4;
+    bool m[CAP + 1][NP] = {}, i[CAP + 1][NP] = {}, d[CAP + 1][NP] = {}, rec[CAP + 1][NP] = {};
+    bool a[CAP + 1][NP] = {}, b[CAP + 1][NP] = {};  // sources of insertions, deletions
+    // a record word of this quad of steps (4 q + 1 to 4 q + 4: so many single
+    // edits end with a quad)
+    bool acc[Q][NP] = {};
+    int lo[Q] = {}, off[Q] = {};                    // its row: off + index
+    int rows = 0;
+    constexpr bool inside(int s, int p) const {
+        const int k0 = 2 * (p - PR), k1 = k0 + 1;
+        const int least = k0 >= 0 ? k0 : -k1;
+        return least <= reach(s);
+    }
+    constexpr LanePlan() {
+        m[0][PR] = true;
+        for (int s = 1; s <= CAP; s++) {
+            for (int p = 0; p < NP; p++) {
+                a[s][p] = (s >= OE && m[s - OE][p]) || (s >= E && i[s - E][p]);
+                b[s][p] = (s >= OE && m[s - OE][p]) || (s >= E && d[s - E][p]);
+            }
+            for (int p = 0; p < NP; p++) {
+                if (!inside(s, p)) continue;
+                i[s][p] = a[s][p] || (p > 0 && a[s][p - 1]);
+                d[s][p] = b[s][p] || (p + 1 < NP && b[s][p + 1]);
+                m[s][p] = (s >= X && m[s - X][p]) || i[s][p] || d[s][p];
+            }
+            for (int p = 0; p < NP; p++)
+                rec[s][p] = s >= OE && (m[s][p] || (a[s][p] && p + 1 < NP && m[s][p + 1]) ||
+                                        (b[s][p] && p > 0 && m[s][p - 1]));
         }
-    };
-    static constexpr Kof kof_tab{};
-
-    static constexpr int first_cell(int s) {
-        for (int j = 0; j < W; j++)
-            if (reach.m[s][j]) return reach.cidx[s][j];
-        return -1;
-    }
-    static constexpr int cells_of(int s) {
-        int c = 0;
-        for (int j = 0; j < W; j++) c += reach.m[s][j] ? 1 : 0;
-        return c;
-    }
-    static constexpr int max_cells() {
-        int mx = 0;
-        for (int s = 0; s <= CAP; s++) mx = cells_of(s) > mx ? cells_of(s) : mx;
-        return mx;
-    }
-    // A step's staged offsets, its M row words and its history words share
-    // one layout: diagonal index J of step s at byte J - jbase(s), jbase(s)
-    // the lowest reachable J rounded down to a multiple of four, so each
-    // staged dword is a row word as it stands (bytes of unreachable diagonals
-    // are never read).
-    static constexpr int jlo(int s) {
-        for (int j = 0; j < W; j++)
-            if (reach.m[s][j]) return j;
-        return -1;
-    }
-    static constexpr int jhi(int s) {
-        for (int j = W - 1; j >= 0; j--)
-            if (reach.m[s][j]) return j;
-        return -1;
-    }
-    static constexpr int jbase(int s) { return jlo(s) < 0 ? 0 : (jlo(s) & ~3); }
-    static constexpr int nwords(int s) { return jlo(s) < 0 ? 0 : (jhi(s) - jbase(s)) / 4 + 1; }
-    static constexpr int hword(int s) {  // the history word of step s's first word
-        int t = 0;
-        for (int u = 0; u < s; u++) t += nwords(u);
-        return t;
-    }
-    static constexpr int max_words() {
-        int mx = 0;
-        for (int s = 0; s <= CAP; s++) mx = nwords(s) > mx ? nwords(s) : mx;
-        return mx;
-    }
-    // the history byte of each (s, k) cell (-1 where none), copied to LDS
-    struct HistByte {
-        short b[(CAP + 1) * W] = {};
-        constexpr HistByte() {
-            for (int s = 0; s <= CAP; s++)
-                for (int j = 0; j < W; j++)
-                    b[s * W + j] = reach.m[s][j] ? (short)(4 * hword(s) + j - jbase(s)) : (short)-1;
-        }
-    };
-    static constexpr HistByte hist_byte{};
-    // LDS per lane: both sequences and the staging bytes of one step's cells
-    static constexpr int STW = max_words();
-    static constexpr int LANE_DW = 2 * SQ + STW;
-    static constexpr int WAVE_BYTES = LANE_DW * 64 * 4;
-    // per block: the (s, k) -> compact cell table and the (s, k) -> history
-    // byte table (int16 each), rounded to 256 bytes, so the lane columns that
-    // follow sit at whole multiples of 64 dwords and paired column reads need
-    // no base add
-    static constexpr int TABLE_BYTES = (2 * (CAP + 1) * W * 2 + 255) & ~255;
-    // CIGAR history per lane in global memory: the offset after extension of
-    // every reachable cell (a byte; 0x80 NULL) in the staging layout, step
-    // after step, then the cells' 4-bit decision records in compact order
-    static constexpr int HMW = hword(CAP + 1);
-    static constexpr int HRW = (NC + 7) / 8;
-    static constexpr int HIST_DW = CIGAR ? HMW + HRW : 0;
-
-    // Register rows hold one byte per diagonal, four diagonals to a word
-    // (diagonal index J in byte J % 4 of word J / 4): every offset is at most
-    // LMAX < 0x80, and 0x80 stands for NULL.  A row word is rebuilt at each
-    // step from its reachable bytes only; bytes of unreachable diagonals are
-    // never read.  A finished word passes through an empty asm, so the
-    // compiler extracts each byte where a cell reads it instead of keeping
-    // the unpacked bytes in registers.
-    static constexpr int WP = (W + 3) / 4;
-    struct St {
-        uint32_t M[RM][WP];  // offsets after extension
-        uint32_t I[RID][WP];
-        uint32_t D[RID][WP];
-        uint32_t pr;  // the record word being packed
-    };
-    template <int J>
-    static __device__ __forceinline__ uint32_t byte_of(uint32_t w) {
-        return (w >> (8 * (J & 3))) & 0xffu;
-    }
-    static constexpr bool reaches(int T, int S, int j) {
-        return T == 0 ? reach.m[S][j] : (T == 1 ? reach.i[S][j] : reach.d[S][j]);
-    }
-    // whether J is the lowest / highest diagonal of its word that row type T
-    // (0: M, 1: I, 2: D) reaches at step S
-    static constexpr bool first_in_word(int T, int S, int J) {
-        for (int j = J & ~3; j < J; j++)
-            if (reaches(T, S, j)) return false;
-        return true;
-    }
-    static constexpr bool last_in_word(int T, int S, int J) {
-        for (int j = J + 1; j < ((J | 3) + 1) && j < W; j++)
-            if (reaches(T, S, j)) return false;
-        return true;
-    }
-    // byte J % 4 of w = the low byte of v (its other bytes are ignored): the
-    // lowest reachable byte of a word starts it (bytes above it are left as
-    // they come, and are either written next or never read), the others go
-    // in by a byte permute that keeps the rest of the word
-    template <int T, int S, int J>
-    static __device__ __forceinline__ void put_byte(uint32_t& w, uint32_t v) {
-        constexpr int p = J & 3;
-        if constexpr (first_in_word(T, S, J)) {
-            w = v << (8 * p);
-        } else {
-            constexpr uint32_t sel = (p == 0 ? 0x03020104u
-                                      : p == 1 ? 0x03020400u : p == 2 ? 0x03040100u : 0x04020100u);
-            w = __builtin_amdgcn_perm(v, w, sel);
-        }
-        if constexpr (last_in_word(T, S, J)) asm volatile("" : "+v"(w));
-    }
-
-    struct Lane {
-        int n, m, kt;
-        bool run;  // holds a pair that has not finished
-        int S;
-        lptr<uint32_t> P, T, G;  // sequence columns, staging column
-        gptr_t<uint32_t> H;      // history column (global), dword d at H[d * 64]
-    };
-
-    static __device__ __forceinline__ lptr<uint8_t> gptr(const Lane& ln, int b) {
-        return (lptr<uint8_t>)(ln.G + (b >> 2) * 64) + (b & 3);
-    }
-
-    // Phase 1 of a step, one cell: the recurrences from the register rows,
-    // the decision record, and the offset before extension staged in LDS.
-    template <int S, int J>
-    static __device__ __forceinline__ void cell(St& st, Lane& ln) {
-        if constexpr (reach.m[S][J]) {
-            constexpr int k = J - KM;
-            constexpr int g = J - jbase(S);  // staging byte
-            const int L = min(ln.m, ln.n + k);  // largest admissible offset
-            int Mv, Iv = LNUL, Dv = LNUL;
-            [[maybe_unused]] uint32_t rec = 0;
-            if constexpr (S == 0) {
-                Mv = 0;
-            } else {
-                // candidates as unsigned distances t = L - c below the limit:
-                // admissible offsets 0 <= t <= L, offsets past L negative
-                // (huge); the largest admissible candidate is the smallest t,
-                // floored at tn = L - NULL.  A source byte of 0x80 (NULL) is
-                // past every limit, so it drops out.
-                constexpr bool hA = S >= OE && J >= 1 && reach.m[S >= OE ? S - OE : 0][J >= 1 ? J - 1 : 0];
-                constexpr bool hB = S >= E && J >= 1 && reach.i[S >= E ? S - E : 0][J >= 1 ? J - 1 : 0];
-                constexpr bool hC = S >= OE && J + 1 < W && reach.m[S >= OE ? S - OE : 0][J + 1 < W ? J + 1 : 0];
-                constexpr bool hE = S >= E && J + 1 < W && reach.d[S >= E ? S - E : 0][J + 1 < W ? J + 1 : 0];
-                constexpr bool hX = S >= X && reach.m[S >= X ? S - X : 0][J];
-                const uint32_t tn = (uint32_t)(L - LNUL);
-                uint32_t ta = tn, tb = tn, tc = tn, te = tn, tx = tn;
-                if constexpr (hA) ta = (uint32_t)(L - 1) - byte_of<J - 1>(st.M[(S - OE) % RM][(J - 1) / 4]);
-                if constexpr (hB) tb = (uint32_t)(L - 1) - byte_of<J - 1>(st.I[(S - E) % RID][(J - 1) / 4]);
-                if constexpr (hC) tc = (uint32_t)L - byte_of<J + 1>(st.M[(S - OE) % RM][(J + 1) / 4]);
-                if constexpr (hE) te = (uint32_t)L - byte_of<J + 1>(st.D[(S - E) % RID][(J + 1) / 4]);
-                if constexpr (hX) tx = (uint32_t)(L - 1) - byte_of<J>(st.M[(S - X) % RM][J / 4]);
-                const uint32_t ti = min(min(ta, tb), tn);
-                const uint32_t td = min(min(tc, te), tn);
-                const uint32_t tm = min(min(tx, ti), td);
-                Mv = L - (int)tm;
-                Iv = L - (int)ti;
-                Dv = L - (int)td;
-                if constexpr (CIGAR) {
-                    // tie-break: mismatch, then insertion, then deletion;
-                    // gap open before gap extension
-                    const uint32_t msrc = tx == tm ? 0u : (ti == tm ? 1u : 2u);
-                    rec = msrc | (ta == ti ? 4u : 0u) | (tc == td ? 8u : 0u);
-                    // materialise the record here: left to itself the compiler
-                    // sinks these compares to the record word's store, keeping
-                    // every candidate distance of eight cells live
-                    asm volatile("" : "+v"(rec));
+        for (int q = 0; q < Q; q++) {
+            int first = NP, last = -1;
+            for (int p = 0; p < NP; p++) {
+                for (int s = 4 * q + 1; s <= 4 * q + 4; s++) acc[q][p] = acc[q][p] || rec[s][p];
+                if (acc[q][p]) {
+                    first = p < first ? p : first;
+                    last = p;
                 }
             }
-            // an offset is in [0, L] or exactly NULL (the minimum is floored
-            // at tn), so its low byte is the offset or 0x80
-            if constexpr (reach.i[S][J]) put_byte<1, S, J>(st.I[S % RID][J / 4], (uint32_t)Iv);
-            if constexpr (reach.d[S][J]) put_byte<2, S, J>(st.D[S % RID][J / 4], (uint32_t)Dv);
-            if constexpr (CIGAR) {
-                constexpr int c = reach.cidx[S][J];
-                if constexpr ((c & 7) == 0) st.pr = rec;
-                else st.pr |= rec << (4 * (c & 7));
-                if constexpr ((c & 7) == 7 || c == NC - 1) ln.H[(HMW + (c >> 3)) * 64] = st.pr;
-            }
-            // the low byte: the offset, or 0x80 for NULL
-            *gptr(ln, g) = (uint8_t)Mv;
+            lo[q] = first;
+            off[q] = last < 0 ? 0 : rows - first;
+            if (last >= 0) rows += last - first + 1;
         }
     }
-
-    // Phase 3 of a step, one staged dword (four diagonals): the offsets after
-    // extension as they stand into the register row and (CIGAR) the history.
-    template <int S, int Wi>
-    static __device__ __forceinline__ void word_back(St& st, Lane& ln) {
-        constexpr int rw = jbase(S) / 4 + Wi, hw = hword(S) + Wi;  // row word, history word
-        const uint32_t w = ln.G[Wi * 64];
-        st.M[S % RM][rw] = w;
-        if constexpr (CIGAR) ln.H[hw * 64] = w;
-    }
-
-    template <int S, int... Js>
-    static __device__ __forceinline__ void step_cells(St& st, Lane& ln,
-                                                      std::integer_sequence<int, Js...>) {
-        (cell<S, Js>(st, ln), ...);
-    }
-    template <int S, int... Ws>
-    static __device__ __forceinline__ void step_back(St& st, Lane& ln,
-                                                     std::integer_sequence<int, Ws...>) {
-        (word_back<S, Ws>(st, ln), ...);
-    }
-
-    // Phase 2 of a step: extend every staged cell along matches, 32 bases
-    // per compare (a wave-uniform loop; lanes with nothing to extend compare
-    // at offset 0 and add nothing), stage the offset after extension, and
-    // test the target cell.  One loop over the step's cells, unrolled by four
-    // so the LDS reads of neighbouring cells overlap (5 M pairs at E = 4 %:
-    // 1.79 against 1.84 ms per call rolled, with the packed rows); the target
-    // test afterwards reads the one staged byte of the lane's target diagonal
-    // through the (s, k) -> cell table.
-    template <int S>
-    static __device__ __forceinline__ bool extend_step(Lane& ln, lptr<const short> table) {
-        constexpr int c0 = first_cell(S), ns = cells_of(S);
-        bool term = false;
-        if constexpr (ns > 0) {
-#pragma unroll 4
-            for (int j = 0; j < ns; j++) {
-                const int k = kof_tab.k[c0 + j];
-                constexpr int jb = jbase(S);
-                lptr<uint8_t> bp = gptr(ln, k + KM - jb);
-                const int Mv = *bp;  // 0x80 for NULL
-                const int L = min(ln.m, ln.n + k);
-                const bool go = ln.run && Mv < L;  // L <= LMAX < 0x80
-                // a lane that does not extend keeps rem = 0, so it adds nothing
-                // and its compares read its own or a neighbouring column of
-                // this block's LDS (Mv - k within -16 .. 144), never stored
-                int hp = Mv;
-                int vp = Mv - k;
-                int rem = go ? L - Mv : 0;
-                // a 16-base compare first, for every cell (some lane of the
-                // wave almost always extends, and testing for none costs more
-                // than it saves); most cells stop within it, and the wave
-                // runs on to 32-base compares only while a lane still matches
-                uint32_t z16;
-                asm("v_ffbl_b32 %0, %1" : "=v"(z16) : "v"(col_window16(ln.P, vp) ^ col_window16(ln.T, hp)));
-                const int r16 = min((int)(min(z16, 32u) >> 1), rem);
-                hp += r16;
-                vp += r16;
-                rem -= r16;
-                bool more = __ballot(r16 == 16 && rem > 0) != 0;
-                while (more) {
-                    const uint64_t a = col_window32(ln.P, vp), bb = col_window32(ln.T, hp);
-                    const uint64_t dx = a ^ bb;
-                    // matching bases before the first mismatch: trailing zero
-                    // bits of dx / 2, 32 when dx is 0 (v_ffbl gives ~0 for a zero
-                    // word; the saturating add keeps it ~0 for the high word)
-                    const uint32_t lo = (uint32_t)dx, hi = (uint32_t)(dx >> 32);
-                    uint32_t zl, zh;
-                    asm("v_ffbl_b32 %0, %1" : "=v"(zl) : "v"(lo));
-                    asm("v_ffbl_b32 %0, %1" : "=v"(zh) : "v"(hi));
-                    const int cp = (int)(min(min(zl, __builtin_elementwise_add_sat(zh, 32u)), 64u) >> 1);
-                    const int r = min(cp, rem);
-                    hp += r;
-                    vp += r;
-                    rem -= r;
-                    // a lane that stopped short (a mismatch, or the end) compares
-                    // at the same place again and adds 0 while others go on
-                    more = __ballot(r == 32 && rem > 0) != 0;
-                }
-                if (go) *bp = (uint8_t)hp;
-            }
-            const int jt = ln.kt + KM;
-            if (ln.run && jt >= 0 && jt < W) {
-                const int c = table[S * W + jt];
-                constexpr int jb = jbase(S);
-                if (c >= 0) term = *gptr(ln, jt - jb) == ln.m;  // 0x80 (NULL) never equals m
-            }
-        }
-        return term;
-    }
-
-    // The record word being packed when the forward pass stops after step
-    // S (every lane finished): store it, so the walk never reads a stale word.
-    template <int S>
-    static __device__ __forceinline__ void flush(St& st, Lane& ln) {
-        if constexpr (CIGAR && cells_of(S) > 0) {
-            constexpr int last = first_cell(S) + cells_of(S) - 1;
-            if constexpr ((last & 7) != 7 && last != NC - 1) ln.H[(HMW + (last >> 3)) * 64] = st.pr;
-        }
-    }
-
-    // One score step; false once no lane of the wavefront is still running.
-    template <int S>
-    static __device__ __forceinline__ bool step(St& st, Lane& ln, lptr<const short> table) {
-        // The lengths pass through an empty asm each step, so the per-diagonal
-        // limits min(m, n + k) are recomputed (two instructions per cell)
-        // instead of being kept in registers across the whole pass.
-        // The history column's address passes through one too: otherwise the
-        // compiler hoists the address of every history word out of the pair
-        // loop and keeps them all in registers.
-        asm volatile("" : "+v"(ln.n), "+v"(ln.m), "+v"(ln.H));
-        step_cells<S>(st, ln, std::make_integer_sequence<int, W>{});
-        const bool term = extend_step<S>(ln, table);
-        step_back<S>(st, ln, std::make_integer_sequence<int, nwords(S)>{});
-        const bool fin = ln.run && term;
-        ln.S = fin ? S : ln.S;
-        ln.run = ln.run && !term;
-        if (__ballot(ln.run) == 0) {
-            flush<S>(st, ln);
-            return false;
-        }
-        return true;
-    }
-
-    template <int... Ss>
-    static __device__ __forceinline__ void forward(St& st, Lane& ln, lptr<const short> table,
-                                                   std::integer_sequence<int, Ss...>) {
-        (step<Ss>(st, ln, table) && ...);  // stops after the step where every lane finished
+    // off of every quad, a byte each (they are above -NP)
+    constexpr uint64_t offs() const {
+        uint64_t w = 0;
+        for (int q = 0; q < Q; q++) w |= (uint64_t)(off[q] + NP) << (8 * q);
+        return w;
     }
 };
 
-// At most 128 VGPRs (four wavefronts per SIMD).  With the register rows as
-// packed bytes the 16-step CIGAR form needs 125 and no scratch (with the
-// extension loop unrolled by four and the row words taken from the staged
-// dwords as they stand): a 5 M-pair call
-// at E = 4 % took 1.87 ms (rolled) against 2.02 ms with one register per
-// diagonal (128 VGPRs and 48 dwords per lane in scratch), and 1.88 ms at five
-// wavefronts (96 VGPRs, 30 spilled), in alternating runs on one device.
+template <int X, int OE, int E, int CAP, int LMAX, bool CIGAR>
+struct LaneKernel {
+    static_assert(E == 1 && CAP % 4 == 0 && CAP <= 16 && LMAX <= 127, "see the walk and the records");
+    using Plan = LanePlan<X, OE, E, CAP>;
+    static constexpr Plan plan{};
+    static constexpr int NP = Plan::NP, PR = Plan::PR;
+    static constexpr int RM = X > OE ? X : OE;
+    static constexpr int SQ = (LMAX >> 4) + 3;  // dwords per sequence column
+    static_assert(SQ % 2 == 0, "staged by words");
+    static constexpr int EDITS = CAP / (X < OE ? X : OE);
+    static_assert(6 * EDITS <= 64, "the edits of a pair fill a register pair");
+    // Rows of the runs, one to spare.  Until the runs are made they hold the
+    // first record rows; the other records go to global memory.
+    static constexpr int RUNS = CIGAR ? 2 * EDITS + 2 : 0;
+    static constexpr int WAVE_BYTES = (2 * SQ + RUNS) * 256;
+    static constexpr int HIST_DW = CIGAR && plan.rows > RUNS ? plan.rows - RUNS : 0;
+    static constexpr uint32_t ONE = 0x00020002u;  // offsets are doubled
+    static constexpr uint32_t STOP = 0x80000000u;
+    static constexpr int TLO = PR - (LANE_KT + 1) / 2, THI = PR + LANE_KT / 2;  // registers of end diagonals
+
+    struct St {
+        uint32_t M[RM][NP], I[NP], D[NP];  // M of step s in row s % RM
+        uint32_t acc[NP];
+        uint32_t n2, m2;  // the lengths doubled, in both halves
+        uint32_t tb, pb;  // LDS addresses of the lane's columns
+        int tsh, tp;      // the end diagonal's half (a shift) and register
+        int S;
+        lptr<uint32_t> R;    // record row r at R[r * 64], from RUNS on
+        gptr_t<uint32_t> H;  // at H[(r - RUNS) * 64]
+    };
+
+    // dwords q and q + 1 (and q + 2) of a lane's column
+    static __device__ __forceinline__ lptr<const uint32_t> at(uint32_t col, uint32_t q) {
+        return (lptr<const uint32_t>)(uintptr_t)(col + (q << 8));
+    }
+    static __device__ __forceinline__ uint32_t ffbl(uint32_t x) {
+        uint32_t z;
+        asm("v_ffbl_b32 %0, %1" : "=v"(z) : "v"(x));
+        return z;
+    }
+
+    // Extension of one register's two cells (see rows.h).
+    template <int PI>
+    static __device__ __forceinline__ uint32_t extend(const St& st, uint32_t m) {
+        constexpr int k0 = 2 * (PI - PR);
+        constexpr uint32_t SAFE = k0 >= 0 ? (uint32_t)(2 * k0) | ((uint32_t)(2 * k0 + 2) << 16) : 0u;
+        // the largest offset, min(m, n + k): below every offset on the diagonals
+        // left of the matrix, and an offset on one to the right of it is past m
+        constexpr uint32_t K2 = (uint32_t)(2 * k0 & 0xffff) | ((uint32_t)(2 * k0 + 2) << 16);
+        const uint32_t lim = bits(__builtin_elementwise_min(as_s(st.m2), as_s(pk_add(st.n2, K2))));
+        const uint32_t bad = pk_sign(m | pk_sub(lim, m));
+        const uint32_t hv = (bad & SAFE) | (~bad & m);
+        uint32_t t0[2], t1[2], p0[2], p1[2], h[2], v[2], x[2], r[2];
+#pragma unroll
+        for (int c = 0; c < 2; c++) {
+            h[c] = c ? hv >> 16 : hv & 0xffffu;
+            v[c] = h[c] - (uint32_t)(2 * (k0 + c));
+            const lptr<const uint32_t> t = at(st.tb, c ? hv >> 21 : __builtin_amdgcn_ubfe(hv, 5, 11));
+            const lptr<const uint32_t> p = at(st.pb, v[c] >> 5);
+            t0[c] = t[0];
+            t1[c] = t[64];
+            p0[c] = p[0];
+            p1[c] = p[64];
+        }
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int c = 0; c < 2; c++) {
+            x[c] = (__builtin_amdgcn_alignbit(t1[c], t0[c], h[c]) ^
+                    __builtin_amdgcn_alignbit(p1[c], p0[c], v[c])) | STOP;
+            r[c] = ffbl(x[c]);
+        }
+        if (lanes_where(min(x[0], x[1]) == STOP)) {
+            const uint32_t left = pk_sub(lim, hv) & ~bad;
+#pragma unroll
+            for (int c = 0; c < 2; c++) {
+                const uint32_t end = c ? left >> 16 : left & 0xffffu;
+                if (x[c] == STOP && end > 30) {
+                    uint32_t done = 30, z;
+                    do {
+                        const uint32_t hd = h[c] + done, vd = v[c] + done;
+                        const lptr<const uint32_t> t = at(st.tb, hd >> 5), p = at(st.pb, vd >> 5);
+                        const uint32_t ta = t[0], tm = t[64], tz = t[128];
+                        const uint32_t pa = p[0], pm = p[64], pz = p[128];
+                        const uint32_t y0 = __builtin_amdgcn_alignbit(tm, ta, hd) ^ __builtin_amdgcn_alignbit(pm, pa, vd);
+                        const uint32_t y1 = __builtin_amdgcn_alignbit(tz, tm, hd) ^ __builtin_amdgcn_alignbit(pz, pm, vd);
+                        // ~0 for a zero word: the sum saturates
+                        z = min(min(ffbl(y0), __builtin_elementwise_add_sat(ffbl(y1), 32u)), 64u);
+                        done += z;
+                    } while (z >= 64 && done < end);
+                    r[c] = done;
+                }
+            }
+        }
+        const uint32_t rr = (r[0] | (r[1] << 16)) & 0xFFFEFFFEu;
+        const uint32_t e = pk_minu(hv + rr, lim);
+        return (bad & NUL16P) | (~bad & e);
+    }
+
+    // The best sources of step S of gaps into the next diagonals, and the M cells
+    // they open from.
+    template <int S, int PI>
+    static __device__ __forceinline__ uint32_t opens(const St& st) {
+        if constexpr (PI < NP && S >= OE && plan.m[S >= OE ? S - OE : 0][PI < NP ? PI : 0])
+            return st.M[(S + RM - OE) % RM][PI];
+        return NUL16P;
+    }
+    template <int S, int PI, bool INS>
+    static __device__ __forceinline__ uint32_t source(const St& st) {
+        if constexpr (PI < NP && S >= E) {
+            constexpr bool gap = INS ? plan.i[S - E][PI] : plan.d[S - E][PI];
+            constexpr bool open = S >= OE && plan.m[S >= OE ? S - OE : 0][PI];
+            if constexpr (gap && open) return pk_max(opens<S, PI>(st), INS ? st.I[PI] : st.D[PI]);
+            if constexpr (gap) return INS ? st.I[PI] : st.D[PI];
+        }
+        return opens<S, PI>(st);
+    }
+
+    // One register of step S: its cells from the rows, extended, in place.  The
+    // registers go upwards; `ap` and `b` carry the insertion source of the one
+    // before and the deletion source of this one.
+    template <int S, int PI>
+    static __device__ __forceinline__ void cells(St& st, uint32_t& ap, uint32_t& b, uint32_t& z) {
+        const uint32_t open = opens<S, PI>(st), a = source<S, PI, true>(st);
+        const uint32_t bn = source<S, PI + 1, false>(st);
+        [[maybe_unused]] uint32_t nx = 0, ni = 0, ai = 0, ad = 0;
+        if constexpr (CIGAR && plan.rec[S][PI]) {
+            // gaps into the next diagonals up and down: extended (ties: opened)
+            constexpr bool ho = S >= OE && plan.m[S >= OE ? S - OE : 0][PI];
+            if constexpr (plan.a[S][PI]) ai = ho ? pk_ne(a, open) : 0x00010001u;
+            if constexpr (plan.b[S][PI]) ad = ho ? pk_ne(b, open) : 0x00010001u;
+        }
+        uint32_t m = NUL16P, i = NUL16P, d = NUL16P;
+        if constexpr (plan.m[S][PI]) {
+            constexpr bool hx = S >= X && plan.m[S >= X ? S - X : 0][PI];
+            constexpr bool hi = plan.i[S][PI], hd = plan.d[S][PI];
+            uint32_t x = NUL16P;
+            if constexpr (hx) m = x = pk_add(st.M[(S + RM - X) % RM][PI], ONE);
+            if constexpr (hi) {
+                i = pk_add(__builtin_amdgcn_alignbit(a, ap, 16), ONE);
+                m = hx ? pk_max(m, i) : i;
+            }
+            if constexpr (hd) {
+                d = __builtin_amdgcn_alignbit(bn, b, 16);
+                m = hx || hi ? pk_max(m, d) : d;
+            }
+            if constexpr (CIGAR && plan.rec[S][PI]) {
+                if constexpr (!hx) nx = 0x00010001u;
+                else if constexpr (hi || hd) nx = pk_ne(m, x);
+                if constexpr (!hi) ni = 0x00010001u;
+                else if constexpr (hx || hd) ni = pk_ne(m, i);
+            }
+        }
+        if constexpr (CIGAR && plan.rec[S][PI]) {
+            const uint32_t rec = shl_or<1>(shl_or<1>(shl_or<1>(ad, ai), ni), nx);
+            constexpr int sh = 4 * (3 - ((S - 1) & 3));
+            if constexpr (fresh(S, PI)) st.acc[PI] = rec << sh;
+            else st.acc[PI] = shl_or<sh>(rec, st.acc[PI]);
+        }
+        if constexpr (plan.m[S][PI]) {
+            m = extend<PI>(st, m);
+            st.M[S % RM][PI] = m;
+            if constexpr (PI >= TLO && PI <= THI) z = st.tp == PI ? m : z;
+        }
+        if constexpr (plan.i[S][PI]) st.I[PI] = i;
+        if constexpr (plan.d[S][PI]) st.D[PI] = d;
+        ap = a;
+        b = bn;
+    }
+    // no earlier step of S's quad has a record of this register
+    static constexpr bool fresh(int S, int p) {
+        for (int s = ((S - 1) & ~3) + 1; s < S; s++)
+            if (plan.rec[s][p]) return false;
+        return true;
+    }
+
+    template <int S, int... Ps>
+    static __device__ __forceinline__ bool step(St& st, std::integer_sequence<int, Ps...>) {
+        // (through an empty asm each step: else the compiler hoists the address of
+        // every record row out of the pair loop and keeps them all in registers)
+        asm volatile("" : "+v"(st.H));
+        uint32_t z = ~0u;
+        if constexpr (S == 0) {
+            st.M[0][PR] = extend<PR>(st, 0xC0000000u);  // M_0[0] = 0
+            z = st.tp == PR ? st.M[0][PR] : z;
+        } else {
+            uint32_t ap = NUL16P, b = source<S, 0, false>(st);
+            (cells<S, Ps>(st, ap, b, z), ...);
+        }
+        const bool hit = ((z >> st.tsh) & 0xffffu) == (st.m2 & 0xffffu);
+        st.S = st.S < 0 && hit ? S : st.S;
+        // a quad's end: its record words, and whether any lane goes on (exits
+        // within a quad, with record words to store, cost 50 spilled registers)
+        if constexpr (S == 0 || S % 4 != 0) return true;
+        if constexpr (CIGAR && S > 0) {
+#pragma unroll
+            for (int p = 0; p < NP; p++) {
+                const int row = plan.off[(S - 1) >> 2] + p;
+                if (!plan.acc[(S - 1) >> 2][p]) continue;
+                if (row < RUNS) st.R[row * 64] = st.acc[p];
+                else st.H[(row - RUNS) * 64] = st.acc[p];
+            }
+        }
+        return lanes_where(st.S < 0) != 0;
+    }
+    template <int S>
+    static __device__ __forceinline__ bool step_if(St& st) {
+        if constexpr (has_step(S)) return step<S>(st, std::make_integer_sequence<int, NP>{});
+        return true;
+    }
+    static constexpr bool has_step(int s) {
+        for (int p = 0; p < NP; p++)
+            if (plan.m[s][p]) return true;
+        return false;
+    }
+    template <int... Ss>
+    static __device__ __forceinline__ void forward(St& st, std::integer_sequence<int, Ss...>) {
+        (step_if<Ss>(st) && ...);  // stops after the step where every lane finished
+    }
+};
+
+// At most 128 VGPRs (four wavefronts per SIMD; the limits of the diagonals are
+// made again where they are used, two instructions, to stay below).
 template <int X, int OE, int E, int CAP, int LMAX, bool CIGAR, bool ASCII>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k_lane(LaneArgs a,
                                                                                     int persistent) {
@@ -490,26 +357,15 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
     const int lane = threadIdx.x & 63;
     const int wave = threadIdx.x >> 6;
     const int wpb = blockDim.x >> 6;
-    lptr<unsigned char> ldsb = (lptr<unsigned char>)lds;
-    // per block: the (s, k) -> compact cell table, the (s, k) -> history byte
-    // table, then one region per wavefront
-    lptr<short> table = (lptr<short>)ldsb;
-    lptr<short> hbt = table + K::CAP1 * K::W;
-    for (int i = threadIdx.x; i < (K::CAP1) * K::W; i += blockDim.x) {
-        const int s = i / K::W, j = i % K::W;
-        table[i] = (short)K::reach.cidx[s][j];
-        hbt[i] = K::hist_byte.b[i];
-    }
-    __syncthreads();
-    lptr<uint32_t> wbase = (lptr<uint32_t>)(ldsb + K::TABLE_BYTES + wave * K::WAVE_BYTES) + lane;
-    typename K::Lane ln;
-    ln.P = wbase;
-    ln.T = wbase + K::SQ * 64;
-    ln.G = wbase + 2 * K::SQ * 64;
-    // this wavefront's history and run-stage region (HIST_DW + slot_cap rows
-    // of 64 dwords; one region per launched wavefront)
-    ln.H = (gptr_t<uint32_t>)a.hist +
-           ((uint64_t)(blockIdx.x * wpb + wave) * (CIGAR ? K::HIST_DW + a.slot_cap : 0)) * 64 + lane;
+    lptr<uint32_t> wbase = (lptr<uint32_t>)((lptr<unsigned char>)lds + wave * K::WAVE_BYTES) + lane;
+    const lptr<uint32_t> colP = wbase, colT = wbase + K::SQ * 64, stage = wbase + 2 * K::SQ * 64;
+    typename K::St st;
+    st.pb = (uint32_t)(uintptr_t)colP;
+    st.tb = (uint32_t)(uintptr_t)colT;
+    st.R = stage;
+    // this wavefront's records (HIST_DW rows of 64 dwords; one region per
+    // launched wavefront)
+    st.H = (gptr_t<uint32_t>)a.hist + (uint64_t)(blockIdx.x * wpb + wave) * K::HIST_DW * 64 + lane;
     // persistent: LANE_QUEUES counters (one per 128-byte line), wavefront w
     // drawing from counter w % LANE_QUEUES; the i-th claim from counter q is
     // the group of 64 queue entries number i * LANE_QUEUES + q, so every
@@ -548,13 +404,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
             ps = d.p_start;
             ts = d.t_start;
         }
-        ln.n = n;
-        ln.m = m;
-        ln.kt = m - n;
+        const int kt = m - n;
         // pairs this kernel cannot hold leave at once
-        bool fits = n <= LMAX && m <= LMAX && ln.kt >= -K::reach.kmax && ln.kt <= K::reach.kmax;
-        ln.run = active && fits;
-        ln.S = -1;
+        const bool run = active && n <= LMAX && m <= LMAX && kt >= -LANE_KT && kt <= LANE_KT;
         // stage both sequences in the lane's columns (zero past their ends)
         if constexpr (ASCII) {
             // ASCII: packed on the way in, the words of the 64 pairs spread
@@ -563,7 +415,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
             // task i * NW + w
             constexpr int NW = (K::SQ + 1) / 2;
             const uint32_t start[4] = {(uint32_t)ps, (uint32_t)(ps >> 32), (uint32_t)ts, (uint32_t)(ts >> 32)};
-            const int lens = ln.run ? n | (m << 8) : 0;  // at most LMAX < 256 each
+            const int lens = run ? n | (m << 8) : 0;  // at most LMAX < 256 each
             for (int t0 = 0; t0 < 64 * NW; t0 += 64) {
                 const int own = (t0 + lane) / NW, w = (t0 + lane) % NW;
                 const uint64_t p0 = (uint32_t)__shfl((int)start[0], own) | ((uint64_t)(uint32_t)__shfl((int)start[1], own) << 32);
@@ -583,18 +435,18 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
                 if (!(okp && okt)) atomicMin(a.err_pair, (unsigned long long)(uint32_t)(a.order ? a.order[qbase + own] : qbase + own));
             }
         } else {
-            const int nwp = ln.run ? (n + 31) >> 5 : 0, nwt = ln.run ? (m + 31) >> 5 : 0;
+            const int nwp = run ? (n + 31) >> 5 : 0, nwt = run ? (m + 31) >> 5 : 0;
 #pragma unroll
             for (int w = 0; w < (K::SQ + 1) / 2; w++) {
                 const uint64_t pv = w < nwp ? a.pw[ps + w] : 0ull;
                 const uint64_t tv = w < nwt ? a.tw[ts + w] : 0ull;
                 if (2 * w < K::SQ) {
-                    ln.P[(2 * w) * 64] = (uint32_t)pv;
-                    ln.T[(2 * w) * 64] = (uint32_t)tv;
+                    colP[(2 * w) * 64] = (uint32_t)pv;
+                    colT[(2 * w) * 64] = (uint32_t)tv;
                 }
                 if (2 * w + 1 < K::SQ) {
-                    ln.P[(2 * w + 1) * 64] = (uint32_t)(pv >> 32);
-                    ln.T[(2 * w + 1) * 64] = (uint32_t)(tv >> 32);
+                    colP[(2 * w + 1) * 64] = (uint32_t)(pv >> 32);
+                    colT[(2 * w + 1) * 64] = (uint32_t)(tv >> 32);
                 }
             }
         }
@@ -602,115 +454,101 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
         __builtin_amdgcn_wave_barrier();
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 
-        typename K::St st;
-        if (__ballot(ln.run) != 0)
-            K::forward(st, ln, (lptr<const short>)table, std::make_integer_sequence<int, CAP + 1>{});
+        // (lengths of an idle lane: two empty sequences)
+        const int ln = run ? n : 0, lm = run ? m : 0;
+        st.n2 = pk_pair(2 * ln, 2 * ln);
+        st.m2 = pk_pair(2 * lm, 2 * lm);
+        st.tsh = 16 * (kt & 1);
+        st.tp = run ? (kt >> 1) + K::PR : -1;
+        st.S = run ? -1 : CAP + 1;  // idle lanes hold up no other
+        if (lanes_where(run)) K::forward(st, std::make_integer_sequence<int, CAP + 1>{});
         // lanes still running after CAP steps leave through the overflow list
-        bool overflow = active && ln.S < 0;
+        bool overflow = active && !(run && st.S >= 0 && st.S <= CAP);
         int nr = 0;
         if (CIGAR && active && !overflow) {
-            // The short kernel's walk, on this lane's pair: one event per
-            // iteration -- at M cell (s, k) the record names the source (a
-            // mismatch from M at s - x, or the end of a gap whose chain of I
-            // or D cells is followed back to the M cell it opened from); the
-            // iteration emits the cell's match run and the event's edit run
-            // (extending the open run when nothing matched in between and
-            // the op is the same) and moves to the source M cell.  Runs go
-            // to the pair's slot last to first.
-            const int cap_runs = a.slot_cap;
-            // runs are staged lane-interleaved after the wavefront's history
-            // (run r of this lane at stage[r * 64]), so every store of the
-            // walk writes one contiguous 256-byte row
-            gptr_t<uint32_t> slot = ln.H + K::HIST_DW * 64;
-            auto cidx = [&](int s, int k) -> int {
-                if (s < 0 || s > CAP || k < -K::KM || k > K::KM) return -1;
-                return table[s * K::W + k + K::KM];
-            };
-            // the offset of a reachable cell (s, k): byte hbt of the history
-            auto hm = [&](int s, int k) -> int {
-                const int hb = hbt[s * K::W + k + K::KM];
-                const uint32_t w = ln.H[(hb >> 2) * 64];
-                const int b = (int)((w >> (8 * (hb & 3))) & 0xFFu);
-                return b & 0x80 ? -1 : b;
-            };
-            auto hr = [&](int c) -> int {
-                const uint32_t w = ln.H[(K::HMW + (c >> 3)) * 64];
-                return (int)((w >> (4 * (c & 7))) & 15u);
-            };
-            int cop = -1, clen = 0;
-            int s = ln.S, k = ln.kt, h = m;
+            // walk: the edits from the end back to step 0, the last one walked
+            // (the first of the alignment) in the low six bits
+            uint64_t edits = 0;
+            int s = st.S, k = kt, ne = 0;
             bool bad = false;
-            for (;;) {
-                const int c = cidx(s, k);
-                if (c < 0) {
-                    bad = true;
-                    break;
-                }
-                int h0 = 0, hn = 0, L = 1, op = 0, s2 = 0, dk = 0;
-                if (s > 0) {
-                    const int f = hr(c);
-                    const int ms = f & 3;
-                    if (ms == 0) {
-                        const int cs = cidx(s - X, k);
-                        if (cs < 0) {
+            auto word = [&](int s2, int k2) -> uint32_t {
+                constexpr uint64_t OFFS = K::plan.offs();
+                const int row = (int)((OFFS >> (8 * ((s2 - 1) >> 2))) & 0xff) - K::NP + ((k2 + 2 * K::PR) >> 1);
+                const int last = K::plan.rows - 1;
+                const int r = min(max(row, 0), last);
+                uint32_t w;
+                if (r < K::RUNS) w = stage[r * 64];
+                else w = st.H[(r - K::RUNS) * 64];
+                return record_of(w, s2 - 1, k2);
+            };
+            while (s > 0 && !bad) {
+                int kind = EV_X, len = 1;
+                const uint32_t f = s >= OE ? word(s, k) : 0u;  // before OE: mismatches only
+                if (!(f & 1)) {
+                    s -= X;
+                } else {
+                    const bool ins = !(f & 2);
+                    const uint32_t more = ins ? 4u : 8u;
+                    kind = ins ? EV_I : EV_D;
+                    len = 0;
+                    for (;;) {
+                        len++;
+                        k += ins ? -1 : 1;
+                        if (s < OE || k < -2 * K::PR || k >= 2 * K::PR) {
                             bad = true;
                             break;
                         }
-                        hn = hm(s - X, k);
-                        h0 = hn + 1;
-                        s2 = s - X;
-                    } else {
-                        const int bit = ms == 1 ? 4 : 8;
-                        const int dj = ms == 1 ? -1 : 1;
-                        int sc = s, kc = k, fc = f;
-                        while (!(fc & bit)) {  // still extending: one step back
-                            sc -= E;
-                            kc += dj;
-                            const int cc = cidx(sc, kc);
-                            if (sc <= 0 || cc < 0) break;
-                            L++;
-                            fc = hr(cc);
-                        }
-                        const int co = cidx(sc - OE, kc + dj);
-                        if (!(fc & bit) || co < 0) {
-                            bad = true;  // a gap with no opening: inconsistent
-                            break;
-                        }
-                        hn = hm(sc - OE, kc + dj);
-                        h0 = ms == 1 ? hn + L : hn;  // insertions consume text
-                        s2 = sc - OE;
-                        dk = dj * L;
+                        const uint32_t g = word(s, k);
+                        s -= (g & more) ? E : OE;
+                        if (!(g & more)) break;
                     }
-                    op = ms + 1;  // op codes: X=1 I=2 D=3
                 }
-                const bool last = s == 0;
-                const int mlen = h - h0;
-                if (mlen < 0 || hn < 0) {
-                    bad = true;
-                    break;
-                }
-                const bool hasM = mlen > 0;
-                const bool flushr = cop >= 0 && (hasM || last || cop != op);
-                if (flushr) {
-                    if (nr < cap_runs) slot[nr * 64] = ((uint32_t)clen << 4) | (uint32_t)cop;
-                    nr++;
-                }
-                if (hasM) {
-                    if (nr < cap_runs) slot[nr * 64] = ((uint32_t)mlen << 4);
-                    nr++;
-                }
-                if (last) break;
-                clen = (flushr || hasM) ? L : clen + L;
-                cop = op;
-                s = s2;
-                k += dk;
-                h = hn;
+                edits = edits << 6 | (uint32_t)((len & 15) << 2 | kind);
+                ne++;
             }
-            if (bad || nr > cap_runs) overflow = true;
+            if (s != 0 || k != 0 || ne > K::EDITS) bad = true;
+            // replay: from the start along matches, edit by edit (as in the band
+            // kernel); runs in alignment order
+            int h = 0, v = 0, last_op = -1;
+            uint32_t cur = 0;
+            while (!bad) {
+                const int left = min(n - v, m - h);
+                int mm = 0;
+                for (;;) {
+                    const uint32_t hd = 2 * (h + mm), vd = 2 * (v + mm);
+                    const lptr<const uint32_t> t = K::at(st.tb, hd >> 5), p = K::at(st.pb, vd >> 5);
+                    const uint32_t ta = t[0], tm = t[64], tz = t[128];
+                    const uint32_t pa = p[0], pm = p[64], pz = p[128];
+                    const uint32_t y0 = __builtin_amdgcn_alignbit(tm, ta, hd) ^ __builtin_amdgcn_alignbit(pm, pa, vd);
+                    const uint32_t y1 = __builtin_amdgcn_alignbit(tz, tm, hd) ^ __builtin_amdgcn_alignbit(pz, pm, vd);
+                    const uint32_t z = min(min(K::ffbl(y0), __builtin_elementwise_add_sat(K::ffbl(y1), 32u)), 64u);
+                    mm += (int)(z >> 1);
+                    if (z < 64 || mm >= left) break;
+                }
+                mm = min(mm, left);
+                stage[nr * 64] = (uint32_t)mm << 4;
+                nr += mm > 0 ? 1 : 0;
+                last_op = mm > 0 ? -1 : last_op;
+                h += mm;
+                v += mm;
+                if (ne == 0) break;
+                const int len = (int)(edits >> 2) & 15, kind = (int)(edits & 3);
+                edits >>= 6;
+                ne--;
+                const bool same = last_op == kind;
+                cur = same ? cur + ((uint32_t)len << 4) : ((uint32_t)len << 4) | (uint32_t)(1 + kind);
+                nr += same ? 0 : 1;
+                stage[(nr - 1) * 64] = cur;
+                last_op = kind;
+                h += kind != EV_D ? len : 0;
+                v += kind != EV_I ? len : 0;
+                if (h > m || v > n) bad = true;
+            }
+            if (bad || h != m || v != n || nr > a.slot_cap) overflow = true;
         }
-        // CIGAR: the 64 pairs' runs packed one after another at the start of
-        // the group's slot area (64 * slot_cap words from queue position
-        // qbase on), so the compaction reads dense data
+        // CIGAR: the 64 pairs' runs, last to first, packed one after another at
+        // the start of the group's slot area (64 * slot_cap words from queue
+        // position qbase on), so the compaction reads dense data
         uint64_t src = 0;
         if (CIGAR) {
             const int cnt = (active && !overflow) ? nr : 0;
@@ -721,15 +559,14 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
                 incl += lane >= off ? t : 0;
             }
             src = (uint64_t)qbase * a.slot_cap + (uint64_t)(incl - cnt);
-            const gptr_t<uint32_t> stage = ln.H + K::HIST_DW * 64;
-            for (int r = 0; r < cnt; r++) a.slots[src + r] = stage[r * 64];
+            for (int r = 0; r < cnt; r++) a.slots[src + r] = stage[(cnt - 1 - r) * 64];
         }
         if (active) {
             if (overflow) {
                 const uint32_t at = atomicAdd(a.ovf_count, 1u);
                 a.ovf_list[at] = pair;
             } else {
-                a.scores[pair] = ln.S * a.pen.g;
+                a.scores[pair] = st.S * a.pen.g;
                 a.nruns[pair] = CIGAR ? (uint32_t)nr : 0u;
                 if (CIGAR) a.run_src[pair] = src;
             }
@@ -743,14 +580,12 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
 template <int X, int OE, int E, int CAP, int LMAX>
 struct LaneShape {
     static int lds_bytes(bool cigar, int waves) {
-        return cigar ? LaneKernel<X, OE, E, CAP, LMAX, true>::TABLE_BYTES +
-                           waves * LaneKernel<X, OE, E, CAP, LMAX, true>::WAVE_BYTES
-                     : LaneKernel<X, OE, E, CAP, LMAX, false>::TABLE_BYTES +
-                           waves * LaneKernel<X, OE, E, CAP, LMAX, false>::WAVE_BYTES;
+        return waves * (cigar ? LaneKernel<X, OE, E, CAP, LMAX, true>::WAVE_BYTES
+                              : LaneKernel<X, OE, E, CAP, LMAX, false>::WAVE_BYTES);
     }
-    // history and run stage of one wavefront (slot_cap runs per lane)
-    static int hist_dwords(bool cigar, int slot_cap) {
-        return cigar ? (LaneKernel<X, OE, E, CAP, LMAX, true>::HIST_DW + slot_cap) * 64 : 0;
+    // records of one wavefront
+    static int hist_dwords(bool cigar) {
+        return cigar ? LaneKernel<X, OE, E, CAP, LMAX, true>::HIST_DW * 64 : 0;
     }
     template <bool CIGAR, bool ASCII>
     static hipError_t launch_t(const LaneArgs& a, bool persistent, int bt, int grid, hipStream_t s) {
@@ -777,7 +612,6 @@ struct LaneShape {
                         &blocks, (const void*)k_lane<X, OE, E, CAP, LMAX, false, false>, bt, lds);
         return e == hipSuccess ? blocks : 0;
     }
-    static int kmax() { return LaneKernel<X, OE, E, CAP, LMAX, false>::reach.kmax; }
 };
 
 // Shapes built: scaled penalties (2, 4, 1) -- x = 4, o = 6, e = 2 and their
@@ -796,14 +630,6 @@ bool lane_supported(const Pen& pen, int cap, uint32_t max_len) {
     return false;
 }
 
-int lane_kmax(const Pen& pen, int cap) {
-#define WFA_LANE_CASE(PX, POE, PE, PC, PLM) \
-    if (pen.x == PX && pen.oe == POE && pen.e == PE && cap == PC) return LaneShape<PX, POE, PE, PC, PLM>::kmax();
-    WFA_LANE_SHAPES(WFA_LANE_CASE)
-#undef WFA_LANE_CASE
-    return -1;
-}
-
 int lane_lds_bytes(const Pen& pen, int cap, bool cigar, int block_threads) {
 #define WFA_LANE_CASE(PX, POE, PE, PC, PLM) \
     if (pen.x == PX && pen.oe == POE && pen.e == PE && cap == PC) \
@@ -813,10 +639,10 @@ int lane_lds_bytes(const Pen& pen, int cap, bool cigar, int block_threads) {
     return -1;
 }
 
-size_t lane_hist_bytes_per_wave(const Pen& pen, int cap, bool cigar, int slot_cap) {
+size_t lane_hist_bytes_per_wave(const Pen& pen, int cap, bool cigar) {
 #define WFA_LANE_CASE(PX, POE, PE, PC, PLM) \
     if (pen.x == PX && pen.oe == POE && pen.e == PE && cap == PC) \
-        return (size_t)LaneShape<PX, POE, PE, PC, PLM>::hist_dwords(cigar, slot_cap) * 4;
+        return (size_t)LaneShape<PX, POE, PE, PC, PLM>::hist_dwords(cigar) * 4;
     WFA_LANE_SHAPES(WFA_LANE_CASE)
 #undef WFA_LANE_CASE
     return 0;

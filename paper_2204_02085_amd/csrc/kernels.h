@@ -105,7 +105,7 @@ struct LaneArgs {
     uint32_t* nruns;            // [pairs] runs written
     uint64_t* run_src;          // [pairs] where the reversed runs live (packed per group of 64)
     uint32_t* slots;            // [pairs * slot_cap] reversed runs
-    uint32_t* hist;             // CIGAR: one history and run-stage region per launched wavefront
+    uint32_t* hist;             // CIGAR: one region of records per launched wavefront
     uint32_t* ovf_list;         // pairs the kernel could not hold
     uint32_t* ovf_count;
     int ascii;                  // pw, tw are ASCII bytes, starts and lengths bytes
@@ -317,14 +317,13 @@ hipError_t launch_band(const BandArgs& a, const Pen& pen, const BandPlan& bp, bo
 constexpr int LANE_QUEUES = 64;
 
 // One-lane-per-pair kernel: built for some scaled penalty sets and step caps
-// (lane_supported); kmax is the largest |target diagonal| it can end on.
+// (lane_supported).
 bool lane_supported(const Pen& pen, int cap, uint32_t max_len);
-int lane_kmax(const Pen& pen, int cap);
 int lane_lds_bytes(const Pen& pen, int cap, bool cigar, int block_threads);
 int lane_max_blocks_per_cu(const Pen& pen, int cap, bool cigar, int block_threads);
-// CIGAR history and run stage bytes of one wavefront (global memory, one
-// region per wavefront of the launch)
-size_t lane_hist_bytes_per_wave(const Pen& pen, int cap, bool cigar, int slot_cap);
+// CIGAR record bytes of one wavefront (global memory, one region per wavefront
+// of the launch)
+size_t lane_hist_bytes_per_wave(const Pen& pen, int cap, bool cigar);
 hipError_t launch_lane(const LaneArgs& a, int cap, bool cigar, bool persistent, int block_threads,
                        int grid, hipStream_t s);
 
