@@ -409,31 +409,33 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
         const bool run = active && n <= LMAX && m <= LMAX && kt >= -LANE_KT && kt <= LANE_KT;
         // stage both sequences in the lane's columns (zero past their ends)
         if constexpr (ASCII) {
-            // ASCII: packed on the way in, the words of the 64 pairs spread
-            // over the lanes (consecutive lanes on a pair's consecutive words,
-            // so their loads fall together): word w of each side of pair i is
-            // task i * NW + w
-            constexpr int NW = (K::SQ + 1) / 2;
-            const uint32_t start[4] = {(uint32_t)ps, (uint32_t)(ps >> 32), (uint32_t)ts, (uint32_t)(ts >> 32)};
-            const int lens = run ? n | (m << 8) : 0;  // at most LMAX < 256 each
-            for (int t0 = 0; t0 < 64 * NW; t0 += 64) {
-                const int own = (t0 + lane) / NW, w = (t0 + lane) % NW;
-                const uint64_t p0 = (uint32_t)__shfl((int)start[0], own) | ((uint64_t)(uint32_t)__shfl((int)start[1], own) << 32);
-                const uint64_t q0 = (uint32_t)__shfl((int)start[2], own) | ((uint64_t)(uint32_t)__shfl((int)start[3], own) << 32);
-                const int nm = __shfl(lens, own);
-                const int pn = (nm & 255) - 32 * w, tn = (nm >> 8) - 32 * w;
-                bool okp = true, okt = true;
-                const uint64_t pv = pn > 0 ? pack_word((const uint8_t*)a.pw, p0 + 32 * w, min(pn, 32), okp) : 0ull;
-                const uint64_t tv = tn > 0 ? pack_word((const uint8_t*)a.tw, q0 + 32 * w, min(tn, 32), okt) : 0ull;
-                lptr<uint32_t> col = wbase - lane + own;
-                col[2 * w * 64] = (uint32_t)pv;
-                col[(K::SQ + 2 * w) * 64] = (uint32_t)tv;
-                if (2 * w + 1 < K::SQ) {
-                    col[(2 * w + 1) * 64] = (uint32_t)(pv >> 32);
-                    col[(K::SQ + 2 * w + 1) * 64] = (uint32_t)(tv >> 32);
-                }
-                if (!(okp && okt)) atomicMin(a.err_pair, (unsigned long long)(uint32_t)(a.order ? a.order[qbase + own] : qbase + own));
+            // ASCII: packed on the way in, a word at a time by the pair's own
+            // lane, so that all lanes are at the same word and whole words, most
+            // of them, go without masks (the words spread over the lanes instead
+            // took 57 % of a score-only call of 1 M pairs)
+            bool ok = true;
+#pragma unroll
+            for (int w = 0; w < K::SQ / 2; w++) {
+                auto word = [&](const uint64_t* base, uint64_t start, int len) -> uint64_t {
+                    const int left = run ? len - 32 * w : 0;
+                    uint64_t v = 0;
+                    bool good = true;
+                    if (lanes_where(left > 0 && left < 32)) {
+                        if (left > 0) v = pack_word((const uint8_t*)base, start + 32 * w, min(left, 32), good);
+                    } else if (left > 0) {
+                        v = pack_full_word((const uint8_t*)base, start + 32 * w, good);
+                    }
+                    ok = ok && good;
+                    return v;
+                };
+                const uint64_t pv = 32 * w < LMAX ? word(a.pw, ps, n) : 0ull;
+                const uint64_t tv = 32 * w < LMAX ? word(a.tw, ts, m) : 0ull;
+                colP[(2 * w) * 64] = (uint32_t)pv;
+                colT[(2 * w) * 64] = (uint32_t)tv;
+                colP[(2 * w + 1) * 64] = (uint32_t)(pv >> 32);
+                colT[(2 * w + 1) * 64] = (uint32_t)(tv >> 32);
             }
+            if (!ok) atomicMin(a.err_pair, (unsigned long long)pair);
         } else {
             const int nwp = run ? (n + 31) >> 5 : 0, nwt = run ? (m + 31) >> 5 : 0;
 #pragma unroll

@@ -16,9 +16,7 @@ __device__ __forceinline__ uint32_t pack4(uint32_t x, uint32_t keep, uint32_t& b
     // bytes 'a' 'c' 'g' 't' selected by c (selector values 0..3 pick bytes of src1)
     const uint32_t letters = __builtin_amdgcn_perm(0u, 0x74676361u, c);
     bad |= (letters ^ (x | 0x20202020u)) & keep;
-    uint32_t v = c & keep;
-    v = (v | (v >> 6)) & 0x000F000Fu;
-    return (v | (v >> 12)) & 0xFFu;
+    return __builtin_amdgcn_udot4(c & keep, 0x40100401u, 0u, false);  // a base's code times 4 to its place
 }
 
 // 32 bases starting at byte b0 of `ascii` (cnt of them valid, 1..32) as one
@@ -50,6 +48,24 @@ __device__ __forceinline__ uint64_t pack_word(const uint8_t* __restrict__ ascii,
     }
     ok = bad == 0;
     return word;
+}
+
+// The same for a whole word (32 bases).
+__device__ __forceinline__ uint64_t pack_full_word(const uint8_t* __restrict__ ascii, uint64_t b0, bool& ok) {
+    typedef uint32_t u32x4 __attribute__((ext_vector_type(4), aligned(4)));
+    const uint8_t* first = ascii + b0;
+    const uint32_t sh = (uint32_t)((uintptr_t)first & 3u);
+    const uint32_t* src = (const uint32_t*)(first - sh);
+    const u32x4 lo = *(const u32x4*)src, hi = *(const u32x4*)(src + 4);
+    const uint32_t raw[9] = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3], src[sh ? 8 : 7]};
+    uint32_t half[2] = {0, 0}, bad = 0;
+#pragma unroll
+    for (int d = 7; d >= 0; d--) {
+        const uint32_t x = __builtin_amdgcn_alignbyte(raw[d + 1], raw[d], sh);
+        half[d >> 2] = half[d >> 2] << 8 | pack4(x, ~0u, bad);
+    }
+    ok = bad == 0;
+    return (uint64_t)half[1] << 32 | half[0];
 }
 
 }  // namespace wfa
