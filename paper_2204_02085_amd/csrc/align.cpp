@@ -1008,13 +1008,13 @@ int engine_align_device(Engine* e, const BatchIO& io, hipStream_t user_stream,
     // asks for at most 8 steps, else 16), alignment is global, and no
     // short-kernel shape was asked for.  Pairs it cannot hold go to the
     // cascade from window 64 on, as from a 32-wide first pass.
-    // A batch of at most 64 pairs per CU takes the band kernel instead, unless the
-    // lane kernel is asked for: it would leave most SIMDs without a wavefront
-    // and take the latency of its unrolled steps, 47 us (64 pairs: 98 us a call
-    // against 116; 10 k: 112 against 127; 100 k: 185 against 154, before the
-    // launches around it were cut for both).
+    // With CIGARs a batch of at most 64 pairs per CU takes the band kernel
+    // instead, unless the lane kernel is asked for: that would leave most SIMDs
+    // without a wavefront, and one lane's walk and replay take longer than the
+    // band's (64 pairs 71 us a call against 79, 4 k 79 against 90, 16 k 98 against
+    // 104, 30 k 102 against 95; score only 60 against 56 at 64 pairs).
     bool lane = false;
-    const bool tiny = N <= 64 * (size_t)e->num_cus && e->opt.lane_kernel == 0 &&
+    const bool tiny = cigar && N <= 64 * (size_t)e->num_cus && e->opt.lane_kernel == 0 &&
                       e->opt.step_cap == 0 && band_supported(pen, 32);
     if (use_short && global && !tiny && e->opt.lane_kernel >= 0 && !e->opt.window && !e->opt.lanes_per_pair &&
         e->opt.step_cap <= 16) {
