@@ -71,9 +71,11 @@
  * kernels, which may already have written scores, offsets and runs; their
  * contents are then unspecified.
  *
- * Plan reuse.  A call whose buffers (pointers), pair count, run capacity,
- * 2-bit packed input and settings equal the previous call's on the context
- * starts that call's launch before its batch facts are read back, and keeps
+ * Plan reuse.  A call whose buffers (pointers), pair count, run capacity and
+ * settings equal the previous call's on the context, and whose input needs no
+ * packing ahead of the first pass (2-bit words, or ASCII that the lane or band
+ * kernel packs on the way in), starts that call's launch before its batch facts
+ * are read back, and keeps
  * the results if the facts lead to the same plan; otherwise it runs again as
  * planned.  Results never depend on it.
  */
@@ -109,11 +111,11 @@ typedef enum { WFA_ASCII = 0, WFA_PACKED2 = 1 } wfa_encoding;
 typedef enum { WFA_HOST = 0, WFA_DEVICE = 1 } wfa_memspace;
 
 /* Schedules (all give identical results):
- *   AUTO:       persistent, bucketed, graph-replayed short-pair kernel, with
- *               the general kernel for pairs it cannot hold;
+ *   AUTO:       persistent, graph-replayed short-pair kernel, with further
+ *               kernels for the pairs it cannot hold;
  *   PLAIN:      one launch, pair i on lane group i, no bucketing;
  *   PERSISTENT: grid sized to the GPU, lane groups pull pairs from a device
- *               queue in bucketed order;
+ *               queue (in bucketed order, see `bucket`);
  *   GENERAL:    every pair on the workgroup-per-pair kernel whose
  *               wavefronts live in the HBM arena (any length, any score). */
 typedef enum {
@@ -139,7 +141,8 @@ typedef struct {
                                (wfa_stats.ms_align then times the kernel alone);
                                -1: never; 0: form 1 for the persistent and
                                automatic schedules */
-    int32_t bucket;         /* 1: sort pairs by (length, length difference); -1: off */
+    int32_t bucket;         /* 1: sort pairs by (length, length difference); -1: off;
+                               0: batches of uneven length past 256 pairs per CU */
     int32_t general_pairs;  /* concurrent pairs of the general kernel; 0: by budget */
     int32_t block_threads;  /* threads per workgroup of the short kernel: 64..256 */
     int32_t lanes_per_pair; /* lanes of a wavefront per pair in the short kernel
@@ -159,7 +162,7 @@ typedef struct {
                                  whose history outgrows its slice is re-run
                                  with a 4x slice.  0: estimated from the
                                  lengths and the history seen so far */
-    int32_t lane_kernel;      /* 0 or 1: the first pass runs on the
+    int32_t lane_kernel;      /* 1: the first pass runs on the
                                  one-pair-per-lane kernel, whose wavefront rows
                                  live in registers, whenever it is built for the
                                  penalties (x, o, e = 4, 6, 2 and multiples),
@@ -167,6 +170,8 @@ typedef struct {
                                  alignment is global, no window or lanes per
                                  pair are asked for and step_cap is at most 16
                                  (it holds 8 steps if step_cap <= 8, else 16);
+                                 0: the same, but batches of at most 64 pairs per
+                                 CU with CIGARs go to lane groups;
                                  -1: never */
     int32_t general_step_limit; /* diagnostic: score steps (in units of
                                  gcd(x,o,e)) after which the general kernel

@@ -3,13 +3,14 @@
 // The reduction keeps a wavefront to the diagonals near its furthest points,
 // usually a few dozen, so a pair's rows fit the registers of one wavefront: a
 // window of 128 diagonals, two per lane, that moves along with the reduced
-// ranges, and a second block of 128 beside it while they are wider.  Where k_general spent a workgroup, several barriers and row traffic
-// on every step, a step here is about 130 instructions of one wavefront, the
-// least distance by DPP and the kept range by two ballots.
+// ranges, and a second block of 128 beside it while they are wider.  Where
+// k_general spent a workgroup, several barriers and row traffic on every step, a
+// step here is about 130 instructions of one wavefront, the least distance by DPP
+// and the kept range by two ballots.
 //
 // What bounds it: VALU issue, 0.75 of it over 10 k pairs of 1-10 kbp at 5-10 %
-// under the thresholds (10, 50), 4.3 ms with CIGARs (whole call 4.8 ms; 32.5 ms on
-// the general kernel).  The second block inside the same kernel: 22 of those
+// under the thresholds (10, 50), whole call with CIGARs 3.7 ms (32.0 ms on the
+// general kernel).  The second block inside the same kernel: 22 of those
 // pairs outgrow 128 diagonals for a stretch, and aligning them again in a wider
 // window took another 4.7 ms, the latency of their chains.
 //

@@ -10,18 +10,18 @@
 // A band is exact up to a score its width gives: an alignment that leaves the
 // band pays a gap to the first diagonal outside it and a gap back, so while
 // the score stays below the cheaper of the two ways out, cells outside the
-// band lie on no optimal alignment (w.r.t. score and tie-breaks).  For (4, 6, 2)
+// band lie on no optimal alignment, and score and tie-breaks are unchanged.  For (4, 6, 2)
 // and equal lengths W diagonals hold W + 5 steps; a rule that gives a pair up
 // once the wavefront touches the window's edge stops near W / 2.  Pairs that
 // need more leave through the overflow list.
 //
-// What bounds it: VALU issue (0.83 of the issue slots on 1 M pairs of 100 bp
-// with 10 free bases at each end; about 105 instructions per step and wavefront
-// plus the longer compares).  Measured, kernel alone: those pairs with CIGARs
-// 0.85 ms, where the lane groups with rows in LDS (k_short, window 64) took
-// 2.50 ms; 2 M pairs of 50-300 bp at 0-5 % 3.06 + 0.64 + 0.08 ms over windows
+// What bounds it: VALU issue (all of the issue slots on 1 M pairs of 100 bp with 10
+// free bases at each end; about 100 instructions per step and wavefront plus the
+// longer compares).  Measured, kernel alone: those pairs with CIGARs
+// 0.81 ms, where the lane groups with rows in LDS (k_short, window 64) took
+// 2.50 ms; 2 M pairs of 50-300 bp at 0-5 % 2.83 + 0.57 + 0.07 ms over windows
 // 32, 64 and 128 against 8.62 + 3.77 ms over 64 and 128; 300 k pairs of 150 bp
-// under (1, 0, 1) 0.18 ms against 0.47.  Five wavefronts per SIMD (96 VGPRs,
+// under (1, 0, 1) 0.19 ms against 0.47.  Five wavefronts per SIMD (96 VGPRs,
 // some spills outside the steps) beat four (118) by 2 to 3 %.  One loop for
 // every lane's longer compares instead of one per column: 25 % slower.
 //

@@ -20,13 +20,16 @@
 // What bounds it: VALU issue and the chain of a step (the neighbour's column
 // from LDS, the recurrences, two windows of each sequence from LDS, the barrier),
 // hidden by the other workgroups of a CU: about 60 instructions per step and
-// 128 diagonals, 0.6 to 0.85 of the issue slots by the workgroups' size.
+// 128 diagonals, 0.65 to 0.76 of the issue slots in launches that fill the chip.
 // Measured on whole calls against the general kernel, whose rows cross L2 and
 // HBM and fill the whole triangle: 20 k pairs of 1-10 kbp at 5-10 % with CIGARs
-// 29.4 ms (108.3), 5 k of them score-only 7.3 ms (25.5), 24 pairs of 10-20 kbp
-// 11.3 ms (66.5).  Of the 20 k pairs' time k_bound takes 2.1 ms; its bound was
-// the score itself for every pair looked at.  The record walk in a kernel of its
-// own took 2.8 ms more.
+// 24.3 ms (107.5), 5 k of them score-only 5.7 ms (25.0), 24 pairs of 10-20 kbp
+// 9.1 ms (66.4).  k_bound takes 2.1 ms alone for the 20 k pairs, most of it beside
+// the first alignments; its bound was the score itself for every pair looked at.
+// Columns exchanged every four steps instead, with four columns computed twice on
+// either side, saved three of four barriers and cost 7 % more cells: no gain; four
+// diagonals per lane: 20 % slower.  The record walk in a kernel of its own took
+// 2.8 ms more.
 //
 // Cells a pruned cell would have fed never beat those of an optimal
 // alignment: a missing candidate only lowers offsets off the optimal paths,

@@ -22,6 +22,9 @@
 //   k_general       any pair: one workgroup per pair, wavefront rows in a
 //                   per-pair slice of the HBM arena
 //   k_compact       reversed per-pair runs -> caller's CIGAR buffer
+//   k_finish_small  offsets and that buffer in one launch for small batches
+// Kernels with rows in registers have files of their own (rows.h is theirs):
+// k_lane.hip, k_band.hip, k_front.hip, k_adapt.hip.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
