@@ -3,9 +3,10 @@
 //
 // Two kernels per batch of pairs:
 //
-//   k_bound       one wavefront per pair aligns greedily in a band of 128
-//                 diagonals that follows the furthest point.  Its score U is
-//                 that of an alignment, so no optimal one costs more.
+//   k_bound       two wavefronts per pair align greedily, from either end, in
+//                 bands of 128 diagonals that follow the furthest points.  Where
+//                 they meet there is an alignment of the sum U of their scores,
+//                 so no optimal one costs more.
 //   k_front       one workgroup per pair.  A cell on diagonal k at step s lies
 //                 on an optimal alignment only if a gap back to the end
 //                 diagonal still fits, s + e |k - kt| <= U, and only if a gap
@@ -23,9 +24,10 @@
 // 128 diagonals, 0.65 to 0.76 of the issue slots in launches that fill the chip.
 // Measured on whole calls against the general kernel, whose rows cross L2 and
 // HBM and fill the whole triangle: 20 k pairs of 1-10 kbp at 5-10 % with CIGARs
-// 24.3 ms (107.5), 5 k of them score-only 5.7 ms (25.0), 24 pairs of 10-20 kbp
-// 9.1 ms (66.4).  k_bound takes 2.1 ms alone for the 20 k pairs, most of it beside
-// the first alignments; its bound was the score itself for every pair looked at.
+// 24.1 ms (107.5), 5 k of them score-only 5.4 ms (25.0), 24 pairs of 10-20 kbp
+// 8.4 ms (66.4).  k_bound takes 2 ms for the 20 k pairs, most of it beside the
+// first alignments (from one end only, by one wavefront, the chain of a pair took
+// twice as long: 5 k pairs score-only 5.8 ms, the 24 pairs 9.1 ms).
 // Columns exchanged every four steps instead, with four columns computed twice on
 // either side, saved three of four barriers and cost 7 % more cells: no gain; four
 // diagonals per lane: 20 % slower.  The record walk in a kernel of its own took
@@ -50,30 +52,66 @@ namespace {
 
 using namespace rows;
 
+// A sequence of `len` bases from its last to its first, into LDS.
+__device__ __forceinline__ void stage_reversed(lds_p<uint64_t> dst, const uint64_t* words, int len, int count,
+                                               int tid, int bt) {
+    for (int w = tid; w < count; w += bt) {
+        const int q = len - 32 * (w + 1);  // the first of the word's bases (below 0: as many fewer)
+        uint64_t x = 0;
+        if (q > -32) {
+            const int from = max(q, 0), i = from >> 5, sh = 2 * (from & 31);
+            x = words[i] >> sh;
+            if (sh && from + 31 < len && ((from + 31) >> 5) > i) x |= words[i + 1] << (64 - sh);
+            if (q < 0) x <<= -2 * q;
+            x = __builtin_bitreverse64(x);  // bases and the two bits of each; these back
+            x = ((x >> 1) & 0x5555555555555555ull) | ((x & 0x5555555555555555ull) << 1);
+        }
+        dst[w] = x;
+    }
+}
+
+constexpr int BOUND_ROWS = 5;  // M of four steps, and their maximum
+
+// Two wavefronts per pair, one from either end: a pair's chain of steps is what
+// this kernel costs where few pairs are in flight, and each goes half of it.  They
+// meet where on one diagonal the offsets from both ends cover the text: an
+// alignment of the sum of their scores exists then.
 template <int X, int OE, int E, int SH>
-__global__ __launch_bounds__(64) void k_bound(FrontArgs a) {
+__global__ __launch_bounds__(128) void k_bound(FrontArgs a) {
     constexpr int C = 2;
     extern __shared__ __align__(16) unsigned char lds[];
     const uint32_t pair = a.ids[blockIdx.x];
     const PairDesc d = a.pairs[pair];
     const int n = (int)d.p_len, m = (int)d.t_len, kt = m - n;
-    const int lane = threadIdx.x;
-    stage((lds_p<uint64_t>)lds, a.pw, a.tw, d, lane, 64);
-    wave_fence();
-    const uint32_t tb = (uint32_t)(uintptr_t)(lds_p<unsigned char>)lds;
-    const uint32_t pb = tb + 8 * text_words(m);
+    const int lane = threadIdx.x & 63;
+    const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    // LDS: the quad they met in and the reverse window's base per buffer, two
+    // buffers of the reverse rows, the sequences, the sequences reversed
+    lds_p<int> met = (lds_p<int>)lds;
+    lds_p<int> base = met + 2;
+    lds_p<uint32_t> rows = (lds_p<uint32_t>)(met + 4);
+    lds_p<uint64_t> seq = (lds_p<uint64_t>)(rows + 2 * BOUND_ROWS * 64);
+    const int tws = text_words(m), nwp = (n + 31) >> 5;
+    lds_p<uint64_t> rev = seq + tws + nwp + 1;
+    stage(seq, a.pw, a.tw, d, threadIdx.x, 128);
+    stage_reversed(rev, a.tw + d.t_start, m, tws, threadIdx.x, 128);
+    stage_reversed(rev + tws, a.pw + d.p_start, n, nwp + 1, threadIdx.x, 128);
+    if (threadIdx.x == 0) *met = -1;
+    __syncthreads();
+    const uint32_t tb = (uint32_t)(uintptr_t)(w ? rev : seq);
+    const uint32_t pb = tb + 8 * tws;
     // every base mismatched and the length difference in one gap
     int U = X * min(n, m) + (kt ? (OE - E) + E * abs(kt) : 0);
+    const int last = min(U, SH ? 8000 : 16000);  // (the front kernel holds no more)
     int kmin = -64;
     Place<C> pl;
     pl.template set<SH>(n, m, kmin + C * lane);
     Rows<X, OE, E, C, SH, false> row;
     row.clear();
-    for (int s = 0; s < U; s += 4) {
-        bool end = false;
+    for (int s = 0;; s += 4) {
+        uint32_t mq[4];
 #pragma unroll
         for (int u = 0; u < 4; u++) {
-            if (end) break;
             uint32_t sa[1], sb[1], cm[1], ci[1], cd[1];
             row.sources(sa, sb);
             row.cells(sa, sb, wave_prev(NUL16P, sa[0]), wave_next(NUL16P, sb[0]), cm, ci, cd, false);
@@ -83,18 +121,43 @@ __global__ __launch_bounds__(64) void k_bound(FrontArgs a) {
             }
             extend<C, SH>(cm, pl, tb, pb);
             row.push(cm, ci, cd);
-            const int col = kt - kmin;
-            if (col >= 0 && col < 128 && half_at(cm[0], col >> 1, col & 1) == m << SH) {
-                U = min(U, s + u);
-                end = true;
+            mq[u] = cm[0];
+        }
+        const uint32_t far = pk_max(pk_max(mq[0], mq[1]), pk_max(mq[2], mq[3]));
+        lds_p<uint32_t> buf = rows + ((s >> 2) & 1) * (BOUND_ROWS * 64);
+        if (w) {
+#pragma unroll
+            for (int u = 0; u < 4; u++) buf[u * 64 + lane] = mq[u];
+            buf[4 * 64 + lane] = far;
+            if (lane == 0) base[(s >> 2) & 1] = kmin;
+        }
+        __syncthreads();
+        // (set by the forward wavefront after this quad's barrier at the earliest)
+        const int at = __builtin_amdgcn_readfirstlane(*met);
+        if ((at >= 0 && at < s) || 2 * s >= last) break;
+        if (!w && at < 0) {
+            // the reverse columns of this lane's diagonals k and k + 1: kt - k and
+            // the one before it
+            const int c = kt - (kmin + C * lane) - __builtin_amdgcn_readfirstlane(base[(s >> 2) & 1]);
+            auto meets = [&](uint32_t mine, int r) -> bool {
+                lds_p<const short> other = (lds_p<const short>)(buf + r * 64);
+                const int o0 = c >= 0 && c < 128 ? other[c] : -1, o1 = c >= 1 && c <= 128 ? other[c - 1] : -1;
+                const int m0 = (int)(short)mine, m1 = (int)(short)(mine >> 16);
+                return (o0 >= 0 && m0 >= 0 && o0 + m0 >= m << SH) || (o1 >= 0 && m1 >= 0 && o1 + m1 >= m << SH);
+            };
+            if (lanes_where(meets(far, 4))) {
+#pragma unroll
+                for (int u = 0; u < 4; u++)
+                    for (int r = 0; r < 4; r++)
+                        if (2 * s + u + r < U && lanes_where(meets(mq[u], r))) U = 2 * s + u + r;
+                if (lane == 0) *met = s;
             }
         }
-        if (end) break;
         // follow the furthest point (2 h - k), a lane or two at a time
         const int k0 = kmin + C * lane;
-        const int h0 = (int)(short)row.M[0][0] << (1 - SH), h1 = (int)(short)(row.M[0][0] >> 16) << (1 - SH);
+        const int h0 = (int)(short)far << (1 - SH), h1 = (int)(short)(far >> 16) << (1 - SH);
         const int top = wave_max((max(h0 - k0, h1 - k0 - 1) << 6) | lane);
-        int shift = top < 0 ? 0 : (top & 63) - 32;  // (below 0: no cell at this step)
+        int shift = top < 0 ? 0 : (top & 63) - 32;  // (below 0: no cell at these steps)
         shift = shift > 8 ? 2 : shift > 2 ? 1 : shift < -8 ? -2 : shift < -2 ? -1 : 0;
         if (shift) {
             for (; shift > 0; shift--, kmin += C) {
@@ -120,7 +183,7 @@ __global__ __launch_bounds__(64) void k_bound(FrontArgs a) {
             pl.template set<SH>(n, m, kmin + C * lane);
         }
     }
-    if (lane == 0) a.bounds[blockIdx.x] = U;
+    if (threadIdx.x == 0) a.bounds[blockIdx.x] = U;
 }
 
 // The walk over a pair's records.
@@ -378,11 +441,12 @@ int front_blocks(int width, int cols) { return (width + 64 * cols - 1) / (64 * c
 hipError_t launch_bound(const FrontArgs& a, const Pen& pen, int sh, int jobs, uint32_t n, uint32_t m,
                         hipStream_t s) {
     if (!jobs) return hipSuccess;
-    const int lds = seq_lds_bytes(n, m);
+    // (the rows; both sequences each way; compares read on past the last)
+    const int lds = 16 + 2 * BOUND_ROWS * 256 + 2 * seq_lds_bytes(n, m);
 #define WFA_CASE(PX, POE, PE)                                                                        \
     if (pen.x == PX && pen.oe == POE && pen.e == PE) {                                               \
-        if (sh) hipLaunchKernelGGL((k_bound<PX, POE, PE, 1>), dim3(jobs), dim3(64), lds, s, a);      \
-        else hipLaunchKernelGGL((k_bound<PX, POE, PE, 0>), dim3(jobs), dim3(64), lds, s, a);         \
+        if (sh) hipLaunchKernelGGL((k_bound<PX, POE, PE, 1>), dim3(jobs), dim3(128), lds, s, a);      \
+        else hipLaunchKernelGGL((k_bound<PX, POE, PE, 0>), dim3(jobs), dim3(128), lds, s, a);         \
         return hipGetLastError();                                                                    \
     }
     WFA_FRONT_PENS(WFA_CASE)

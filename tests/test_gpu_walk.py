@@ -66,3 +66,33 @@ def test_walk_edges(oracle_lib, synth_lib, pen, heur):
     finally:
         al.close()
     assert_same(got, ref, b, f"{pen} {heur}")
+
+
+@pytest.mark.parametrize("pen", [(4, 6, 2), (1, 0, 1), (2, 3, 1)])
+def test_bound_from_both_ends(oracle_lib, synth_lib, pen):
+    """The score bound is found from both ends: lengths around the words of the
+    reversed sequences, length differences of both parities, edits at either end or
+    in the middle, where the two meet, and none."""
+    import paper_2204_02085_amd as wfa
+
+    rng = np.random.default_rng(23)
+    pairs = [(_seq(rng, 2500), _seq(rng, 2500)[:100])]  # the batch is the long kernels'
+    for n in (1, 2, 31, 32, 33, 63, 64, 65, 95, 96, 97, 1000, 2401):
+        p = _seq(rng, n)
+        pairs += [(p, p), (p, p[:0]), (p[:0], p), (p, _other(p[:1])), (p, _seq(rng, max(1, n - 1)))]
+        for at in (0, n // 2, n - 1):
+            t = p.copy()
+            t[at] = _other(t[at:at + 1])[0]
+            pairs += [(p, t), (p, np.delete(p, at)), (np.delete(t, at), p)]
+            for gap in (1, 2, 7, 64, 131):
+                pairs.append((p, np.concatenate([t[:at], _seq(rng, gap), t[at:]])))
+    b = synth_lib.from_pairs([(bytes(p), bytes(t)) for p, t in pairs])
+    say(f"case: bounds from both ends, penalties {pen}, {len(b)} pairs")
+    ref = oracle_lib.align_batch(b, pen, cigar=True, threads=8)
+    al = wfa.Aligner(0)
+    try:
+        got = al.align(b, pen, capacity=int(ref.offsets[-1]) + 8)
+        assert al.stats()["general_pairs"] == len(b)
+    finally:
+        al.close()
+    assert_same(got, ref, b, f"{pen}")
