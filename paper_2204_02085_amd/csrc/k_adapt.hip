@@ -9,7 +9,7 @@
 // and the kept range by two ballots.
 //
 // What bounds it: VALU issue, 0.75 of it over 10 k pairs of 1-10 kbp at 5-10 %
-// under the thresholds (10, 50), whole call with CIGARs 3.7 ms (32.0 ms on the
+// under the thresholds (10, 50), whole call with CIGARs 3.6 ms (32.0 ms on the
 // general kernel).  The second block inside the same kernel: 22 of those
 // pairs outgrow 128 diagonals for a stretch, and aligning them again in a wider
 // window took another 4.7 ms, the latency of their chains.
@@ -39,7 +39,16 @@ namespace {
 using namespace rows;
 
 // smallest of the lanes' values, in every lane
-__device__ __forceinline__ int wave_min(int v) { return -wave_max(-v); }
+__device__ __forceinline__ uint32_t wave_min(uint32_t v) {
+    auto step = [&](int other) { v = min(v, (uint32_t)other); };
+    step(__builtin_amdgcn_update_dpp((int)v, (int)v, 0x111, 0xF, 0xF, false));  // row_shr:1
+    step(__builtin_amdgcn_update_dpp((int)v, (int)v, 0x112, 0xF, 0xF, false));
+    step(__builtin_amdgcn_update_dpp((int)v, (int)v, 0x114, 0xF, 0xF, false));
+    step(__builtin_amdgcn_update_dpp((int)v, (int)v, 0x118, 0xF, 0xF, false));
+    step(__builtin_amdgcn_update_dpp((int)v, (int)v, 0x142, 0xA, 0xF, false));  // row_bcast:15
+    step(__builtin_amdgcn_update_dpp((int)v, (int)v, 0x143, 0xC, 0xF, false));  // row_bcast:31
+    return (uint32_t)__builtin_amdgcn_readlane((int)v, 63);
+}
 
 // The window is two blocks of 128 diagonals, two per lane and block; the second
 // is computed only while the ranges do not fit the first.
@@ -64,11 +73,14 @@ __global__ __launch_bounds__(64) void k_adapt(FrontArgs a) {
     int kmin = -BW / 2;
     Place<2> pl[NB];
     uint32_t inside[NB];  // 0xffff in the halves whose diagonal is in the matrix
+    uint32_t whole[NB];   // max(n + k, m), in the offsets' units: 16 bits without sign
     auto place = [&]() {
 #pragma unroll
         for (int b = 0; b < NB; b++) {
             pl[b].template set<SH>(n, m, kmin + BW * b + 2 * lane);
             inside[b] = ~pk_sign(pl[b].lim[0]);
+            const int k = kmin + BW * b + 2 * lane;
+            whole[b] = pk_pair(max(n + k, m) << SH, max(n + k + 1, m) << SH);
         }
     };
     place();
@@ -164,23 +176,22 @@ __global__ __launch_bounds__(64) void k_adapt(FrontArgs a) {
             if (tc >= 0 && tc < nb * BW && half_at(treg, (tc & (BW - 1)) >> 1, tc & 1) == m << SH) {
                 S = s + u;  // the step that reaches the end is not reduced
             } else if (present && h - l + 1 >= MWL) {
-                // distances to the end: max(n + k, m) - M, in the offsets' units
-                constexpr int FAR = 1 << 28;
-                int dist[2 * NB], least = FAR;
+                // distances to the end: max(n + k, m) - M, two to a register;
+                // all ones where there is no offset
+                constexpr uint32_t FAR = 0xFFFF;
+                uint32_t dist[NB], least = FAR;
 #pragma unroll
-                for (int c = 0; c < 2 * nb; c++) {
-                    const int v = (int)(short)(cm[c / 2] >> (16 * (c & 1)));
-                    const int k = kmin + BW * (c / 2) + 2 * lane + (c & 1);
-                    dist[c] = v >= 0 ? (max(n + k, m) << SH) - v : FAR;
-                    least = min(least, dist[c]);
+                for (int b = 0; b < nb; b++) {
+                    dist[b] = pk_sub(whole[b], cm[b]) | pk_sign(cm[b]);
+                    least = min(least, min(dist[b] & 0xffffu, dist[b] >> 16));
                 }
                 least = wave_min(least);
                 if (least != FAR) {
-                    const int lim = min(least + (int)min((long long)MDT << SH, (long long)FAR), FAR - 1);
+                    const uint32_t lim = (uint32_t)min((long long)least + ((long long)MDT << SH), (long long)FAR - 1);
                     int rl = AW, rh = -1;  // kept columns
 #pragma unroll
                     for (int c = 0; c < 2 * nb; c++) {
-                        const uint64_t in = lanes_where(dist[c] <= lim);
+                        const uint64_t in = lanes_where(((c & 1) ? dist[c / 2] >> 16 : dist[c / 2] & 0xffffu) <= lim);
                         if (in) {
                             rl = min(rl, BW * (c / 2) + 2 * (int)__builtin_ctzll(in) + (c & 1));
                             rh = max(rh, BW * (c / 2) + 2 * (63 - (int)__builtin_clzll(in)) + (c & 1));
