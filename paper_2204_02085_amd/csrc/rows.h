@@ -1,5 +1,6 @@
-// Wavefront rows in registers, shared by the band kernel (k_band.hip) and the
-// front kernel (k_front.hip).
+// Wavefront rows in registers, shared by the band kernel (k_band.hip), the front
+// kernel (k_front.hip) and, for the packed operations and the extension, the
+// adaptive kernel (k_adapt.hip) and the lane kernel (k_lane.hip).
 //
 // A lane owns C neighbouring diagonals; a row of offsets is C / 2 registers of
 // two 16-bit offsets each, so the recurrences run two cells per instruction
@@ -22,8 +23,8 @@
 // this diagonal; D past the last pattern row and a mismatch past either are
 // the same argument.  So the cells such a candidate hides lie on no optimal
 // alignment, and every cell on one keeps its offset and its tie-break.
-// (The WF-adaptive reduction measures cells off the optimal paths too and
-// keeps to the general kernel.)
+// (The WF-adaptive reduction measures cells off the optimal paths too, so the
+// adaptive kernel drops candidates before the maximum.)
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
