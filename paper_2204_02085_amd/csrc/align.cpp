@@ -65,6 +65,7 @@ int auto_window(uint32_t max_len) {
 }
 
 constexpr int KEY_STAGED = 64;  // GraphKey: ASCII packed by the first pass itself
+constexpr int KEY_WIDE = 128;   // the lane kernel's wide form
 
 // Band kernel: the first window tried for a batch's longest sequence.  A
 // window of W diagonals is exact for about W score steps, and a pair that
@@ -1013,7 +1014,7 @@ int engine_align_device(Engine* e, const BatchIO& io, hipStream_t user_stream,
     // without a wavefront, and one lane's walk and replay take longer than the
     // band's (64 pairs 71 us a call against 79, 4 k 79 against 90, 16 k 98 against
     // 104, 30 k 102 against 95; score only 60 against 56 at 64 pairs).
-    bool lane = false;
+    bool lane = false, lane_wide = false;
     const bool tiny = cigar && N <= 64 * (size_t)e->num_cus && e->opt.lane_kernel == 0 &&
                       e->opt.step_cap == 0 && band_supported(pen, 32);
     if (use_short && global && !tiny && e->opt.lane_kernel >= 0 && !e->opt.window && !e->opt.lanes_per_pair &&
@@ -1025,6 +1026,17 @@ int engine_align_device(Engine* e, const BatchIO& io, hipStream_t user_stream,
         while (lbt > 64 && lane_lds_bytes(pen, lcap, cigar, lbt) > 64 * 1024) lbt -= 64;
         if (lane_supported(pen, lcap, max_len) && lane_lds_bytes(pen, lcap, cigar, lbt) <= 64 * 1024) {
             lane = true;
+            // The wide form where pairs end on diagonals that the narrow one
+            // does not hold, and there are at least an eighth as many of them
+            // as pairs a few bases apart: then most are a read with one gap,
+            // which 16 steps hold.  Among reads of several edits such a pair
+            // needs more than 16 steps, and the wide form's late steps are
+            // paid for nothing.  Wide against narrow: 1 M pairs of few edits,
+            // one in 100 with a gap of 5 bases 130 us against 277, every one
+            // 201 against 1356 (with no such pair 100 and 100); 5 M pairs at
+            // 4 % with a length difference of 6 in one of 100 1.68 ms against
+            // 1.40, so narrow there.
+            lane_wide = lcap == 16 && st.diff_wide > 0 && 8ull * st.diff_wide >= st.diff_few;
             window = 32;
             lanes = 1;
             sp = ShortPlan{};
@@ -1132,7 +1144,7 @@ int engine_align_device(Engine* e, const BatchIO& io, hipStream_t user_stream,
         // pairs per workgroup: lane groups of the short kernel, or one per lane
         const int gpb = lane ? sp.block_threads : short_groups_per_block(lanes, sp.block_threads);
         if (persistent) {
-            int bpc = lane   ? lane_max_blocks_per_cu(pen, sp.cap, cigar, sp.block_threads)
+            int bpc = lane   ? lane_max_blocks_per_cu(pen, sp.cap, lane_wide, cigar, sp.block_threads)
                       : band ? band_max_blocks_per_cu(pen, bp, cigar, !global)
                              : short_max_blocks_per_cu(window, lanes, cigar, sp.block_threads,
                                                      sp.lds_per_block, sp.row_bytes);
@@ -1156,7 +1168,7 @@ int engine_align_device(Engine* e, const BatchIO& io, hipStream_t user_stream,
 
     if (lane && cigar)  // one region of records per wavefront of the launch
         RCCHK(ws.ensure(ws.lane_hist, (size_t)grid * (sp.block_threads / 64) *
-                                          lane_hist_bytes_per_wave(pen, sp.cap, true)));
+                                          lane_hist_bytes_per_wave(pen, sp.cap, lane_wide, true)));
     if ((lane || band) && persistent) RCCHK(ws.ensure(ws.lane_queues, LANE_QUEUES * 32 * 4));
     flags = ws.flags.as<DevFlags>();
 
@@ -1242,7 +1254,7 @@ int engine_align_device(Engine* e, const BatchIO& io, hipStream_t user_stream,
             a.err_pair = &flags->err_pair;
             a.ovf_list = ws.ovf_list.as<uint32_t>();
             a.ovf_count = &flags->ovf_count;
-            HIPCHK(launch_lane(a, sp.cap, cigar, persistent, sp.block_threads, grid, q));
+            HIPCHK(launch_lane(a, sp.cap, lane_wide, cigar, persistent, sp.block_threads, grid, q));
         } else if (band) {
             BandArgs a = band_args(bp);
             a.order = bucket ? ws.order.as<uint32_t>() : nullptr;
@@ -1326,7 +1338,7 @@ int engine_align_device(Engine* e, const BatchIO& io, hipStream_t user_stream,
                               (int)(bucket ? 1 : 0) | (stride_p && !staged ? 4 : 0) |
                                   (stride_t && !staged ? 8 : 0) |
                                   (persistent ? 16 : 0) | (band ? 32 : 0) | (staged ? KEY_STAGED : 0) |
-                                  (sp.block_threads << 8),
+                                  (lane_wide ? KEY_WIDE : 0) | (sp.block_threads << 8),
                               e->ends.pb, e->ends.pe, e->ends.tb, e->ends.te, queue_chunk,
                               sp.slot_cap};
         for (int i = 0; i < 18; i++) key.ints[i] = ints[i];

@@ -9,7 +9,7 @@
 //   M_0[0] exists; I_s[k] exists if M_{s-o'-e'}[k-1] or I_{s-e'}[k-1] does;
 //   D_s[k] exists if M_{s-o'-e'}[k+1] or D_{s-e'}[k+1] does; M_s[k] exists
 //   if M_{s-x'}[k], I_s[k] or D_s[k] does;
-//   and a pair that ends by step CAP on a diagonal kt of at most LANE_KT has no
+//   and a pair that ends by step CAP on a diagonal kt of at most KT has no
 //   cell of an optimal alignment with s + e' |k - kt| > CAP.
 //
 // So the kernel is unrolled at compile time over a diamond of registers, two
@@ -27,6 +27,15 @@
 // diagonal and a cell at a time, over all 167 cells that can hold an offset, took
 // 1.48 and 1.03.
 //
+// With 16 steps there are two forms: KT = 4 as above, for reads of a few edits,
+// and KT = 13, every diagonal 16 steps can reach, 106 register-steps, for reads
+// with longer gaps (the rule between them stands where the batch is planned).
+// The wide form's steps grow to the end, so it looks before each step whether any
+// lane goes on, not at a quad's end only; that also keeps the steps apart and the
+// registers below 128.  1 M pairs with a gap of 6 bases each 0.18 ms with CIGARs,
+// 0.23 with quads run to their end, 0.18 by the form with a byte per diagonal;
+// handed over by the narrow form 1.36.
+//
 // LDS per wavefront, lane-interleaved (dword q of lane l at q * 64 + l, so 64
 // lanes reading "their" dword q hit 64 different banks): both sequences in 2-bit
 // words, and (CIGAR) the runs.  Global memory per wavefront, interleaved the same
@@ -35,7 +44,7 @@
 // in a register pair, and replays these from the start along matches.
 //
 // A pair leaves through the overflow list (to the band kernel's passes) when a
-// sequence is longer than LMAX bases, when its end diagonal lies beyond LANE_KT,
+// sequence is longer than LMAX bases, when its end diagonal lies beyond KT,
 // or when it needs more than CAP steps.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
@@ -58,15 +67,13 @@ using lptr = lds_p<T>;
 template <class T>
 using gptr_t = __attribute__((address_space(1))) T*;
 
-constexpr int LANE_KT = 4;  // end diagonals held: reads of a few edits
-
 // Which registers (diagonals 2p and 2p + 1, p = index - PR) hold cells at each
 // step, which have records, and where these go.
-template <int X, int OE, int E, int CAP>
+template <int X, int OE, int E, int CAP, int KT>
 struct LanePlan {
     static constexpr int reach(int s) {  // largest |k| of the diamond at step s
         if (s < OE) return 0;
-        const int out = 1 + (s - OE) / E, back = (CAP - s) / E + LANE_KT;
+        const int out = 1 + (s - OE) / E, back = (CAP - s) / E + KT;
         return out < back ? out : back;
     }
     static constexpr int most() {
@@ -127,10 +134,10 @@ struct LanePlan {
     }
 };
 
-template <int X, int OE, int E, int CAP, int LMAX, bool CIGAR>
+template <int X, int OE, int E, int CAP, int KT, int LMAX, bool CIGAR>
 struct LaneKernel {
     static_assert(E == 1 && CAP % 4 == 0 && CAP <= 16 && LMAX <= 127, "see the walk and the records");
-    using Plan = LanePlan<X, OE, E, CAP>;
+    using Plan = LanePlan<X, OE, E, CAP, KT>;
     static constexpr Plan plan{};
     static constexpr int NP = Plan::NP, PR = Plan::PR;
     static constexpr int RM = X > OE ? X : OE;
@@ -144,8 +151,10 @@ struct LaneKernel {
     static constexpr int WAVE_BYTES = (2 * SQ + RUNS) * 256;
     static constexpr int HIST_DW = CIGAR && plan.rows > RUNS ? plan.rows - RUNS : 0;
     static constexpr uint32_t ONE = 0x00020002u;  // offsets are doubled
+    // the diamond grows to its last steps: those past the last lane's end are skipped
+    static constexpr bool WIDE = KT > CAP / 2;
     static constexpr uint32_t STOP = 0x80000000u;
-    static constexpr int TLO = PR - (LANE_KT + 1) / 2, THI = PR + LANE_KT / 2;  // registers of end diagonals
+    static constexpr int TLO = PR - (KT + 1) / 2, THI = PR + KT / 2;  // registers of end diagonals
 
     struct St {
         uint32_t M[RM][NP], I[NP], D[NP];  // M of step s in row s % RM
@@ -311,7 +320,7 @@ struct LaneKernel {
         if constexpr (S == 0) {
             st.M[0][PR] = extend<PR>(st, 0xC0000000u);  // M_0[0] = 0
             z = st.tp == PR ? st.M[0][PR] : z;
-        } else {
+        } else if (!WIDE || S % 4 == 1 || lanes_where(st.S < 0)) {
             uint32_t ap = NUL16P, b = source<S, 0, false>(st);
             (cells<S, Ps>(st, ap, b, z), ...);
         }
@@ -349,10 +358,10 @@ struct LaneKernel {
 
 // At most 128 VGPRs (four wavefronts per SIMD; the limits of the diagonals are
 // made again where they are used, two instructions, to stay below).
-template <int X, int OE, int E, int CAP, int LMAX, bool CIGAR, bool ASCII>
+template <int X, int OE, int E, int CAP, int KT, int LMAX, bool CIGAR, bool ASCII>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k_lane(LaneArgs a,
                                                                                     int persistent) {
-    using K = LaneKernel<X, OE, E, CAP, LMAX, CIGAR>;
+    using K = LaneKernel<X, OE, E, CAP, KT, LMAX, CIGAR>;
     extern __shared__ __align__(16) unsigned char lds[];
     const int lane = threadIdx.x & 63;
     const int wave = threadIdx.x >> 6;
@@ -406,7 +415,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
         }
         const int kt = m - n;
         // pairs this kernel cannot hold leave at once
-        const bool run = active && n <= LMAX && m <= LMAX && kt >= -LANE_KT && kt <= LANE_KT;
+        const bool run = active && n <= LMAX && m <= LMAX && kt >= -KT && kt <= KT;
         // stage both sequences in the lane's columns (zero past their ends)
         if constexpr (ASCII) {
             // ASCII: packed on the way in, a word at a time by the pair's own
@@ -579,19 +588,19 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
     }
 }
 
-template <int X, int OE, int E, int CAP, int LMAX>
+template <int X, int OE, int E, int CAP, int KT, int LMAX>
 struct LaneShape {
     static int lds_bytes(bool cigar, int waves) {
-        return waves * (cigar ? LaneKernel<X, OE, E, CAP, LMAX, true>::WAVE_BYTES
-                              : LaneKernel<X, OE, E, CAP, LMAX, false>::WAVE_BYTES);
+        return waves * (cigar ? LaneKernel<X, OE, E, CAP, KT, LMAX, true>::WAVE_BYTES
+                              : LaneKernel<X, OE, E, CAP, KT, LMAX, false>::WAVE_BYTES);
     }
     // records of one wavefront
     static int hist_dwords(bool cigar) {
-        return cigar ? LaneKernel<X, OE, E, CAP, LMAX, true>::HIST_DW * 64 : 0;
+        return cigar ? LaneKernel<X, OE, E, CAP, KT, LMAX, true>::HIST_DW * 64 : 0;
     }
     template <bool CIGAR, bool ASCII>
     static hipError_t launch_t(const LaneArgs& a, bool persistent, int bt, int grid, hipStream_t s) {
-        hipLaunchKernelGGL((k_lane<X, OE, E, CAP, LMAX, CIGAR, ASCII>), dim3(grid), dim3(bt),
+        hipLaunchKernelGGL((k_lane<X, OE, E, CAP, KT, LMAX, CIGAR, ASCII>), dim3(grid), dim3(bt),
                            lds_bytes(CIGAR, bt / 64), s, a, persistent ? 1 : 0);
         return hipGetLastError();
     }
@@ -609,23 +618,24 @@ struct LaneShape {
         const int lds = lds_bytes(cigar, bt / 64);
         const hipError_t e =
             cigar ? hipOccupancyMaxActiveBlocksPerMultiprocessor(
-                        &blocks, (const void*)k_lane<X, OE, E, CAP, LMAX, true, false>, bt, lds)
+                        &blocks, (const void*)k_lane<X, OE, E, CAP, KT, LMAX, true, false>, bt, lds)
                   : hipOccupancyMaxActiveBlocksPerMultiprocessor(
-                        &blocks, (const void*)k_lane<X, OE, E, CAP, LMAX, false, false>, bt, lds);
+                        &blocks, (const void*)k_lane<X, OE, E, CAP, KT, LMAX, false, false>, bt, lds);
         return e == hipSuccess ? blocks : 0;
     }
 };
 
 // Shapes built: scaled penalties (2, 4, 1) -- x = 4, o = 6, e = 2 and their
 // multiples -- with 8 or 16 score steps, sequences up to 127 bases.
-#define WFA_LANE_SHAPES(F) \
-    F(2, 4, 1, 8, 127)     \
-    F(2, 4, 1, 16, 127)
+#define WFA_LANE_SHAPES(F)                     \
+    F(2, 4, 1, 8, LANE_KT_CAP8, false, 127)    \
+    F(2, 4, 1, 16, LANE_KT, false, 127)        \
+    F(2, 4, 1, 16, LANE_KT_WIDE, true, 127)
 
 }  // namespace
 
 bool lane_supported(const Pen& pen, int cap, uint32_t max_len) {
-#define WFA_LANE_CASE(PX, POE, PE, PC, PLM) \
+#define WFA_LANE_CASE(PX, POE, PE, PC, PKT, PW, PLM) \
     if (pen.x == PX && pen.oe == POE && pen.e == PE && cap == PC && max_len <= (uint32_t)PLM) return true;
     WFA_LANE_SHAPES(WFA_LANE_CASE)
 #undef WFA_LANE_CASE
@@ -633,37 +643,38 @@ bool lane_supported(const Pen& pen, int cap, uint32_t max_len) {
 }
 
 int lane_lds_bytes(const Pen& pen, int cap, bool cigar, int block_threads) {
-#define WFA_LANE_CASE(PX, POE, PE, PC, PLM) \
+    // (either form)
+#define WFA_LANE_CASE(PX, POE, PE, PC, PKT, PW, PLM) \
     if (pen.x == PX && pen.oe == POE && pen.e == PE && cap == PC) \
-        return LaneShape<PX, POE, PE, PC, PLM>::lds_bytes(cigar, block_threads / 64);
+        return LaneShape<PX, POE, PE, PC, PKT, PLM>::lds_bytes(cigar, block_threads / 64);
     WFA_LANE_SHAPES(WFA_LANE_CASE)
 #undef WFA_LANE_CASE
     return -1;
 }
 
-size_t lane_hist_bytes_per_wave(const Pen& pen, int cap, bool cigar) {
-#define WFA_LANE_CASE(PX, POE, PE, PC, PLM) \
-    if (pen.x == PX && pen.oe == POE && pen.e == PE && cap == PC) \
-        return (size_t)LaneShape<PX, POE, PE, PC, PLM>::hist_dwords(cigar) * 4;
+size_t lane_hist_bytes_per_wave(const Pen& pen, int cap, bool wide, bool cigar) {
+#define WFA_LANE_CASE(PX, POE, PE, PC, PKT, PW, PLM) \
+    if (pen.x == PX && pen.oe == POE && pen.e == PE && cap == PC && wide == PW) \
+        return (size_t)LaneShape<PX, POE, PE, PC, PKT, PLM>::hist_dwords(cigar) * 4;
     WFA_LANE_SHAPES(WFA_LANE_CASE)
 #undef WFA_LANE_CASE
     return 0;
 }
 
-int lane_max_blocks_per_cu(const Pen& pen, int cap, bool cigar, int block_threads) {
-#define WFA_LANE_CASE(PX, POE, PE, PC, PLM) \
-    if (pen.x == PX && pen.oe == POE && pen.e == PE && cap == PC) \
-        return LaneShape<PX, POE, PE, PC, PLM>::occupancy(cigar, block_threads);
+int lane_max_blocks_per_cu(const Pen& pen, int cap, bool wide, bool cigar, int block_threads) {
+#define WFA_LANE_CASE(PX, POE, PE, PC, PKT, PW, PLM) \
+    if (pen.x == PX && pen.oe == POE && pen.e == PE && cap == PC && wide == PW) \
+        return LaneShape<PX, POE, PE, PC, PKT, PLM>::occupancy(cigar, block_threads);
     WFA_LANE_SHAPES(WFA_LANE_CASE)
 #undef WFA_LANE_CASE
     return 0;
 }
 
-hipError_t launch_lane(const LaneArgs& a, int cap, bool cigar, bool persistent, int block_threads,
-                       int grid, hipStream_t s) {
-#define WFA_LANE_CASE(PX, POE, PE, PC, PLM) \
-    if (a.pen.x == PX && a.pen.oe == POE && a.pen.e == PE && cap == PC) \
-        return LaneShape<PX, POE, PE, PC, PLM>::launch(a, cigar, persistent, block_threads, grid, s);
+hipError_t launch_lane(const LaneArgs& a, int cap, bool wide, bool cigar, bool persistent,
+                       int block_threads, int grid, hipStream_t s) {
+#define WFA_LANE_CASE(PX, POE, PE, PC, PKT, PW, PLM) \
+    if (a.pen.x == PX && a.pen.oe == POE && a.pen.e == PE && cap == PC && wide == PW) \
+        return LaneShape<PX, POE, PE, PC, PKT, PLM>::launch(a, cigar, persistent, block_threads, grid, s);
     WFA_LANE_SHAPES(WFA_LANE_CASE)
 #undef WFA_LANE_CASE
     return hipErrorInvalidValue;

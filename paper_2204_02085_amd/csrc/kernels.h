@@ -22,7 +22,14 @@ struct BatchStats {
     uint64_t words_p;  // sum of ceil(p_len / 32)
     uint64_t words_t;
     uint64_t first_too_long;  // lowest pair index over the length limit, or ~0
+    uint32_t diff_few;   // pairs whose lengths differ by 2 or 3 bases,
+    uint32_t diff_wide;  // by LANE_KT + 1 to LANE_KT_WIDE
 };
+
+// Largest end diagonals (length differences) the lane kernel holds: with 16
+// score steps narrow and wide, with 8 steps in its one form (both what that
+// many steps can reach under x, o, e = 4, 6, 2).
+constexpr uint32_t LANE_KT = 4, LANE_KT_WIDE = 13, LANE_KT_CAP8 = 5;
 
 // Blocks of the first batch-statistics pass; the statistics buffer holds
 // 1 + STATS_BLOCKS records (result, then the partials).
@@ -320,12 +327,12 @@ constexpr int LANE_QUEUES = 64;
 // (lane_supported).
 bool lane_supported(const Pen& pen, int cap, uint32_t max_len);
 int lane_lds_bytes(const Pen& pen, int cap, bool cigar, int block_threads);
-int lane_max_blocks_per_cu(const Pen& pen, int cap, bool cigar, int block_threads);
+int lane_max_blocks_per_cu(const Pen& pen, int cap, bool wide, bool cigar, int block_threads);
 // CIGAR record bytes of one wavefront (global memory, one region per wavefront
 // of the launch)
-size_t lane_hist_bytes_per_wave(const Pen& pen, int cap, bool cigar);
-hipError_t launch_lane(const LaneArgs& a, int cap, bool cigar, bool persistent, int block_threads,
-                       int grid, hipStream_t s);
+size_t lane_hist_bytes_per_wave(const Pen& pen, int cap, bool wide, bool cigar);
+hipError_t launch_lane(const LaneArgs& a, int cap, bool wide, bool cigar, bool persistent,
+                       int block_threads, int grid, hipStream_t s);
 
 // Front kernel (global, exact): built for some scaled penalties.  launch_bound
 // writes an upper bound of every pair's score steps; front_shape turns it into

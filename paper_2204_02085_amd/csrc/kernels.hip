@@ -87,6 +87,8 @@ __device__ __forceinline__ void stats_reduce_block(BatchStats& v, BatchStats* ou
         v.words_p += __shfl_xor(v.words_p, off);
         v.words_t += __shfl_xor(v.words_t, off);
         v.first_too_long = min(v.first_too_long, (uint64_t)__shfl_xor(v.first_too_long, off));
+        v.diff_few += __shfl_xor(v.diff_few, off);
+        v.diff_wide += __shfl_xor(v.diff_wide, off);
     }
     __shared__ BatchStats sh[4];
     const int wave = threadIdx.x >> 6;
@@ -101,6 +103,8 @@ __device__ __forceinline__ void stats_reduce_block(BatchStats& v, BatchStats* ou
             v.words_p += sh[w].words_p;
             v.words_t += sh[w].words_t;
             v.first_too_long = min(v.first_too_long, sh[w].first_too_long);
+            v.diff_few += sh[w].diff_few;
+            v.diff_wide += sh[w].diff_wide;
         }
         *out = v;
     }
@@ -109,14 +113,17 @@ __device__ __forceinline__ void stats_reduce_block(BatchStats& v, BatchStats* ou
 __global__ __launch_bounds__(256) void k_batch_stats(const PairDesc* __restrict__ pairs, size_t n,
                                                      BatchStats* __restrict__ partial,
                                                      uint32_t max_len) {
-    BatchStats v{0u, 0u, 0u, 0u, 0ull, 0ull, ~0ull};
+    BatchStats v{0u, 0u, 0u, 0u, 0ull, 0ull, ~0ull, 0u, 0u};
     const size_t stride = (size_t)gridDim.x * blockDim.x;
 #pragma unroll 4
     for (size_t i = blockIdx.x * (size_t)blockDim.x + threadIdx.x; i < n; i += stride) {
         const uint32_t p = pairs[i].p_len, t = pairs[i].t_len;
         v.max_p = max(v.max_p, p);
         v.max_t = max(v.max_t, t);
-        v.max_absdiff = max(v.max_absdiff, p > t ? p - t : t - p);
+        const uint32_t diff = p > t ? p - t : t - p;
+        v.max_absdiff = max(v.max_absdiff, diff);
+        v.diff_few += diff == 2 || diff == 3 ? 1u : 0u;
+        v.diff_wide += diff > LANE_KT && diff <= LANE_KT_WIDE ? 1u : 0u;
         const bool tl = p > max_len || t > max_len;
         v.too_long |= tl ? 1u : 0u;
         v.first_too_long = tl ? min(v.first_too_long, (uint64_t)i) : v.first_too_long;
@@ -128,7 +135,7 @@ __global__ __launch_bounds__(256) void k_batch_stats(const PairDesc* __restrict_
 
 __global__ __launch_bounds__(256) void k_batch_stats_final(const BatchStats* __restrict__ partial,
                                                            int nb, BatchStats* __restrict__ out) {
-    BatchStats v{0u, 0u, 0u, 0u, 0ull, 0ull, ~0ull};
+    BatchStats v{0u, 0u, 0u, 0u, 0ull, 0ull, ~0ull, 0u, 0u};
     for (int b = threadIdx.x; b < nb; b += blockDim.x) {
         const BatchStats q = partial[b];
         v.max_p = max(v.max_p, q.max_p);
@@ -138,6 +145,8 @@ __global__ __launch_bounds__(256) void k_batch_stats_final(const BatchStats* __r
         v.words_p += q.words_p;
         v.words_t += q.words_t;
         v.first_too_long = min(v.first_too_long, q.first_too_long);
+        v.diff_few += q.diff_few;
+        v.diff_wide += q.diff_wide;
     }
     stats_reduce_block(v, out);
 }
