@@ -142,7 +142,8 @@ typedef struct {
                                -1: never; 0: form 1 for the persistent and
                                automatic schedules */
     int32_t bucket;         /* 1: sort pairs by (length, length difference); -1: off;
-                               0: batches of uneven length past 256 pairs per CU */
+                               0: where it pays, by the batch's size and lengths
+                               and the kernel of the first pass */
     int32_t general_pairs;  /* concurrent pairs of the general kernel; 0: by budget */
     int32_t block_threads;  /* threads per workgroup of the short kernel: 64..256 */
     int32_t lanes_per_pair; /* lanes of a wavefront per pair in the short kernel

@@ -1078,17 +1078,24 @@ int engine_align_device(Engine* e, const BatchIO& io, hipStream_t user_stream,
         }
     }
     const bool persistent = use_short && schedule != WFA_SCHED_PLAIN;
-    // Bucketing pays when lengths vary and a wavefront works through several
-    // rounds: it costs two passes over the descriptors (35 us at 1 M pairs), and
-    // on reads of one length it saves the lane kernel nothing (5 M pairs with
-    // CIGARs 1.55 ms either way; 1 M score-only 0.247 ms with, 0.197 without).
-    // Pairs of 50-300 bp: 50 k 0.454 ms with, 0.443 without; 100 k 0.525 and
-    // 0.551; 300 k 0.845 and 0.922; 2 M 3.72 and 4.19.
+    // Bucketing costs two passes over the descriptors (12 us, 35 at 1 M pairs) and
+    // puts pairs of similar length and length difference side by side.
+    // Lane groups with rows in LDS: past 8 pairs per CU, as a group holds up its
+    // wavefront's others whatever the lengths.  Under (3, 1, 4): 1 M pairs of
+    // 100 bp, one in ten with a gap of 6 bases, 0.91 ms with, 2.41 without; 60 k
+    // 0.19 and 0.22; 20 k of 50-300 bp 0.38 and 0.41; 2 k pairs within 1 % or
+    // better without, 3 k of one length 0.086 and 0.074.
+    // Lane and band kernels: uneven batches that a wavefront takes several rounds
+    // of.  Pairs of 50-300 bp (band): 50 k 0.454 ms with, 0.443 without; 100 k
+    // 0.525 and 0.551; 300 k 0.845 and 0.922; 2 M 3.72 and 4.19.  Reads of one
+    // length with four edits gain nothing (lane, 5 M pairs with CIGARs 1.19 ms with,
+    // 1.10 without).
     const uint64_t mw_p = std::max<uint64_t>((st.max_p + 31) / 32, 1);
     const uint64_t mw_t = std::max<uint64_t>((st.max_t + 31) / 32, 1);
     const bool even = N * (mw_p + mw_t) <= st.words_p + st.words_t + (st.words_p + st.words_t) / 16;
-    const bool bucket = persistent && (e->opt.bucket > 0 || (e->opt.bucket == 0 && !even &&
-                                                             N > 256 * (size_t)e->num_cus));
+    const size_t cus = (size_t)e->num_cus;
+    const bool bucket_auto = lane || band ? !even && N > 256 * cus : N >= 8 * cus;
+    const bool bucket = persistent && (e->opt.bucket > 0 || (e->opt.bucket == 0 && bucket_auto));
     // graphs: by default for the persistent schedule; the plain one only on request
     const bool graph = use_short && !io.no_graph && e->opt.use_graph >= 0 &&
                        (e->opt.use_graph > 0 || schedule == WFA_SCHED_AUTO ||
@@ -1152,9 +1159,9 @@ int engine_align_device(Engine* e, const BatchIO& io, hipStream_t user_stream,
             grid = e->num_cus * bpc;
             if (std::getenv("WFA_DEBUG"))
                 std::fprintf(stderr, "libwfa plan: %s, %d threads per block, %d blocks per CU, "
-                                     "%d B LDS per block\n",
+                                     "%d B LDS per block%s\n",
                              lane ? "lane kernel" : band ? "band kernel" : "short kernel",
-                             sp.block_threads, bpc, sp.lds_per_block);
+                             sp.block_threads, bpc, sp.lds_per_block, bucket ? ", bucketed" : "");
             const size_t needed = (N + gpb - 1) / gpb;
             if ((size_t)grid > needed) grid = (int)needed;
             // claims of several rounds keep the queue atomic off the critical
