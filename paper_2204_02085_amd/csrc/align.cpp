@@ -1090,11 +1090,19 @@ int engine_align_device(Engine* e, const BatchIO& io, hipStream_t user_stream,
     // 0.525 and 0.551; 300 k 0.845 and 0.922; 2 M 3.72 and 4.19.  Reads of one
     // length with four edits gain nothing (lane, 5 M pairs with CIGARs 1.19 ms with,
     // 1.10 without).
+    // Lane kernel: also reads of which some have one gap of four bases or more
+    // among others of few edits, as such a read keeps its wavefront going for twice
+    // the steps.  At least one in 128, a quarter as many as pairs two or three
+    // bases apart (reads of several edits: one in 14), and more than two rounds of
+    // the lanes a chip holds.  Gaps of 6 bases, two substitutions: one read in 50,
+    // 5 M pairs 0.46 ms with, 0.67 without, 1 M 0.150 and 0.192, 400 k 0.135 and
+    // 0.128; one in 167, 1 M 0.148 and 0.155.
     const uint64_t mw_p = std::max<uint64_t>((st.max_p + 31) / 32, 1);
     const uint64_t mw_t = std::max<uint64_t>((st.max_t + 31) / 32, 1);
     const bool even = N * (mw_p + mw_t) <= st.words_p + st.words_t + (st.words_p + st.words_t) / 16;
     const size_t cus = (size_t)e->num_cus;
-    const bool bucket_auto = lane || band ? !even && N > 256 * cus : N >= 8 * cus;
+    const bool gaps = N > 2048 * cus && 128ull * st.diff_many >= N && 4ull * st.diff_many >= st.diff_few;
+    const bool bucket_auto = lane || band ? (!even && N > 256 * cus) || (lane && gaps) : N >= 8 * cus;
     const bool bucket = persistent && (e->opt.bucket > 0 || (e->opt.bucket == 0 && bucket_auto));
     // graphs: by default for the persistent schedule; the plain one only on request
     const bool graph = use_short && !io.no_graph && e->opt.use_graph >= 0 &&

@@ -23,6 +23,7 @@ struct BatchStats {
     uint64_t words_t;
     uint64_t first_too_long;  // lowest pair index over the length limit, or ~0
     uint32_t diff_few;   // pairs whose lengths differ by 2 or 3 bases,
+    uint32_t diff_many;  // by 4 to LANE_KT_WIDE,
     uint32_t diff_wide;  // by LANE_KT + 1 to LANE_KT_WIDE
 };
 

@@ -88,6 +88,7 @@ __device__ __forceinline__ void stats_reduce_block(BatchStats& v, BatchStats* ou
         v.words_t += __shfl_xor(v.words_t, off);
         v.first_too_long = min(v.first_too_long, (uint64_t)__shfl_xor(v.first_too_long, off));
         v.diff_few += __shfl_xor(v.diff_few, off);
+        v.diff_many += __shfl_xor(v.diff_many, off);
         v.diff_wide += __shfl_xor(v.diff_wide, off);
     }
     __shared__ BatchStats sh[4];
@@ -104,6 +105,7 @@ __device__ __forceinline__ void stats_reduce_block(BatchStats& v, BatchStats* ou
             v.words_t += sh[w].words_t;
             v.first_too_long = min(v.first_too_long, sh[w].first_too_long);
             v.diff_few += sh[w].diff_few;
+            v.diff_many += sh[w].diff_many;
             v.diff_wide += sh[w].diff_wide;
         }
         *out = v;
@@ -113,7 +115,7 @@ __device__ __forceinline__ void stats_reduce_block(BatchStats& v, BatchStats* ou
 __global__ __launch_bounds__(256) void k_batch_stats(const PairDesc* __restrict__ pairs, size_t n,
                                                      BatchStats* __restrict__ partial,
                                                      uint32_t max_len) {
-    BatchStats v{0u, 0u, 0u, 0u, 0ull, 0ull, ~0ull, 0u, 0u};
+    BatchStats v{0u, 0u, 0u, 0u, 0ull, 0ull, ~0ull, 0u, 0u, 0u};
     const size_t stride = (size_t)gridDim.x * blockDim.x;
 #pragma unroll 4
     for (size_t i = blockIdx.x * (size_t)blockDim.x + threadIdx.x; i < n; i += stride) {
@@ -123,6 +125,7 @@ __global__ __launch_bounds__(256) void k_batch_stats(const PairDesc* __restrict_
         const uint32_t diff = p > t ? p - t : t - p;
         v.max_absdiff = max(v.max_absdiff, diff);
         v.diff_few += diff == 2 || diff == 3 ? 1u : 0u;
+        v.diff_many += diff >= 4 && diff <= LANE_KT_WIDE ? 1u : 0u;
         v.diff_wide += diff > LANE_KT && diff <= LANE_KT_WIDE ? 1u : 0u;
         const bool tl = p > max_len || t > max_len;
         v.too_long |= tl ? 1u : 0u;
@@ -135,7 +138,7 @@ __global__ __launch_bounds__(256) void k_batch_stats(const PairDesc* __restrict_
 
 __global__ __launch_bounds__(256) void k_batch_stats_final(const BatchStats* __restrict__ partial,
                                                            int nb, BatchStats* __restrict__ out) {
-    BatchStats v{0u, 0u, 0u, 0u, 0ull, 0ull, ~0ull, 0u, 0u};
+    BatchStats v{0u, 0u, 0u, 0u, 0ull, 0ull, ~0ull, 0u, 0u, 0u};
     for (int b = threadIdx.x; b < nb; b += blockDim.x) {
         const BatchStats q = partial[b];
         v.max_p = max(v.max_p, q.max_p);
@@ -146,6 +149,7 @@ __global__ __launch_bounds__(256) void k_batch_stats_final(const BatchStats* __r
         v.words_t += q.words_t;
         v.first_too_long = min(v.first_too_long, q.first_too_long);
         v.diff_few += q.diff_few;
+        v.diff_many += q.diff_many;
         v.diff_wide += q.diff_wide;
     }
     stats_reduce_block(v, out);

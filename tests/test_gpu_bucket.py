@@ -1,6 +1,7 @@
 """Which batches are sorted by length and length difference before the first pass
 (the plan as the library reports it on stderr), with results byte-identical to the
 oracle either way."""
+import numpy as np
 import pytest
 
 from gpu_util import assert_same, say
@@ -35,3 +36,22 @@ def test_short_kernel(aligner, oracle_lib, synth_lib, capfd, monkeypatch, count,
     say(f"case: bucketing of the short kernel, {count} pairs")
     b = synth_lib.workload("pairs100_e4_5m", count, first=5)
     _check(aligner, oracle_lib, b, (5, 7, 1), capfd, monkeypatch, "short kernel", bucketed)
+
+
+# 256 compute units: the lane kernel past 2048 pairs per CU, from one read in 128
+# with a gap of four bases on
+@pytest.mark.parametrize("count,gapped,bucketed", [(524_289, 4097, True), (524_289, 4096, False),
+                                                   (524_288, 8000, False)])
+def test_lane_kernel_gaps(aligner, oracle_lib, synth_lib, capfd, monkeypatch, count, gapped, bucketed):
+    say(f"case: bucketing of the lane kernel, {count} pairs, {gapped} with a gap")
+    rng = np.random.default_rng(9)
+    L = 40
+    pat = rng.choice(np.frombuffer(b"ACGT", np.uint8), (count, L))
+    txt = pat.copy()
+    txt[:, 7] = pat[:, 8]  # a substitution in three of four reads
+    lens = np.full(count, L, np.uint32)
+    lens[rng.permutation(count)[:gapped]] = L - 4  # four bases at the end
+    off = np.arange(count, dtype=np.uint64) * L
+    b = synth_lib.Batch(np.ascontiguousarray(pat).reshape(-1), np.ascontiguousarray(txt).reshape(-1), off,
+                        np.full(count, L, np.uint32), off, lens)
+    _check(aligner, oracle_lib, b, (4, 6, 2), capfd, monkeypatch, "lane kernel", bucketed)
