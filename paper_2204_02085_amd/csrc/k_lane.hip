@@ -30,11 +30,11 @@
 // With 16 steps there are two forms: KT = 4 as above, for reads of a few edits,
 // and KT = 13, every diagonal 16 steps can reach, 106 register-steps, for reads
 // with longer gaps (the rule between them stands where the batch is planned).
-// The wide form's steps grow to the end, so it looks before each step whether any
-// lane goes on, not at a quad's end only; that also keeps the steps apart and the
-// registers below 128.  1 M pairs with a gap of 6 bases each 0.18 ms with CIGARs,
-// 0.23 with quads run to their end, 0.18 by the form with a byte per diagonal;
-// handed over by the narrow form 1.36.
+// 1 M pairs with a gap of 6 bases each 0.18 ms with CIGARs, by the form with a byte
+// per diagonal 0.18, handed over by the narrow form 1.36.
+// Steps past the last lane's end are skipped within a quad as well, by a branch
+// around a step's cells, which also keeps the compiler from mixing two steps: no
+// spills in the narrow form (20 bytes without), and those pairs 0.23 ms without.
 //
 // LDS per wavefront, lane-interleaved (dword q of lane l at q * 64 + l, so 64
 // lanes reading "their" dword q hit 64 different banks): both sequences in 2-bit
@@ -151,8 +151,6 @@ struct LaneKernel {
     static constexpr int WAVE_BYTES = (2 * SQ + RUNS) * 256;
     static constexpr int HIST_DW = CIGAR && plan.rows > RUNS ? plan.rows - RUNS : 0;
     static constexpr uint32_t ONE = 0x00020002u;  // offsets are doubled
-    // the diamond grows to its last steps: those past the last lane's end are skipped
-    static constexpr bool WIDE = KT > CAP / 2;
     static constexpr uint32_t STOP = 0x80000000u;
     static constexpr int TLO = PR - (KT + 1) / 2, THI = PR + KT / 2;  // registers of end diagonals
 
@@ -320,7 +318,7 @@ struct LaneKernel {
         if constexpr (S == 0) {
             st.M[0][PR] = extend<PR>(st, 0xC0000000u);  // M_0[0] = 0
             z = st.tp == PR ? st.M[0][PR] : z;
-        } else if (!WIDE || S % 4 == 1 || lanes_where(st.S < 0)) {
+        } else if (S % 4 == 1 || lanes_where(st.S < 0)) {  // (a quad begins with lanes that go on)
             uint32_t ap = NUL16P, b = source<S, 0, false>(st);
             (cells<S, Ps>(st, ap, b, z), ...);
         }
