@@ -1055,6 +1055,13 @@ int engine_align_device(Engine* e, const BatchIO& io, hipStream_t user_stream,
     BandPlan bp;
     if (use_short && !lane && !e->opt.window && !e->opt.lanes_per_pair) {
         int bw = band_window(max_len);
+        // A batch that leaves the chip idle (at most one wavefront per SIMD with
+        // the wider window) takes the window that saves it further passes, each
+        // a launch and a wait.  Pairs of 154-323 bp at 0-5 %: 64 pairs 104 us a
+        // call from 128 diagonals on, 250 from 32; 2 k of 100 bp at 4 % 73 and
+        // 77, 4 k 75 from 64 diagonals on, 87 from 128, 78 from 32, 8 k 84, 107
+        // and 82.
+        while (bw < 128 && N * (size_t)(2 * bw / 4) <= 256 * (size_t)e->num_cus) bw *= 2;
         if (!global) {
             const uint32_t reach = std::max(
                 std::max(std::min<uint32_t>((uint32_t)e->ends.pb, st.max_p),
