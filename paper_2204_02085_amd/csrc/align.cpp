@@ -1079,6 +1079,7 @@ int engine_align_device(Engine* e, const BatchIO& io, hipStream_t user_stream,
             sp.window = bp.window;
             sp.lanes = bp.lanes;
             sp.cap = bp.cap;
+            sp.seq_words = bp.seq_words;
             sp.slot_cap = bp.slot_cap;
             sp.block_threads = bp.block_threads;
             sp.lds_per_block = bp.lds_per_block;
@@ -1352,13 +1353,15 @@ int engine_align_device(Engine* e, const BatchIO& io, hipStream_t user_stream,
         key.form = form;
         // every value the captured launches bake in besides the pointers:
         // penalties, plan, lengths, grid, forms, free ends, queue claims
+        const bool packs = ascii && !staged;
         const int ints[18] = {(int)io.enc, (int)io.mode, pen.x, pen.oe, pen.e, pen.g,
                               window * 256 + lanes, sp.cap,
-                              // the packing's word counts (packed input: none)
-                              ascii && !staged ? (int)st.max_p : 0, ascii && !staged ? (int)st.max_t : 0,
+                              // the packing's longest sequences, which the plan follows
+                              // from; without it the LDS per sequence and offset
+                              packs ? (int)st.max_p : sp.seq_words, packs ? (int)st.max_t : sp.row_bytes,
                               grid,
-                              (int)(bucket ? 1 : 0) | (stride_p && !staged ? 4 : 0) |
-                                  (stride_t && !staged ? 8 : 0) |
+                              (int)(bucket ? 1 : 0) | (stride_p && packs ? 4 : 0) |
+                                  (stride_t && packs ? 8 : 0) |
                                   (persistent ? 16 : 0) | (band ? 32 : 0) | (staged ? KEY_STAGED : 0) |
                                   (lane_wide ? KEY_WIDE : 0) | (sp.block_threads << 8),
                               e->ends.pb, e->ends.pe, e->ends.tb, e->ends.te, queue_chunk,
