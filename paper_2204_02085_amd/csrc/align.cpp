@@ -213,7 +213,8 @@ bool grow_arena(Workspace& ws, uint64_t want, uint64_t most) {
 
 // The buffers and counters of launches of the front or adaptive kernels over up
 // to `nj` pairs, the pairs of a launch (`fj`, ids `ids`) to places `at` on of
-// the buffers, and the read-back: pairs that failed go to `rest`.
+// the buffers, and the read-back: pairs that failed go to `rest`, those whose
+// records were too short (adaptive kernel) to `more`.
 int begin_jobs(Engine* e, size_t nj, FrontArgs* a, hipStream_t s) {
     Workspace& ws = e->ws;
     RCCHK(ws.ensure(ws.jobs, nj * 4));
@@ -226,9 +227,12 @@ int begin_jobs(Engine* e, size_t nj, FrontArgs* a, hipStream_t s) {
     FillOps fill{};
     fill.add(ws.job_nruns.as<uint32_t>(), nj, 0u);
     fill.add(&flags->fail_count, 1, 0u);
+    fill.add(&flags->more_count, 1, 0u);
     HIPCHK(launch_fill_multi(fill, s));
     a->fail_list = ws.fail_list.as<uint32_t>();
     a->fail_count = &flags->fail_count;
+    a->more_count = &flags->more_count;
+    a->fail_cap = (uint32_t)nj;
     return WFA_OK;
 }
 int put_jobs(Engine* e, const FrontJob* fj, const uint32_t* ids, size_t at, size_t nj, FrontArgs* a,
@@ -242,19 +246,22 @@ int put_jobs(Engine* e, const FrontJob* fj, const uint32_t* ids, size_t at, size
                           hipMemcpyHostToDevice, s));
     return WFA_OK;
 }
-int end_jobs(Engine* e, size_t nj, bool cigar, uint64_t& gen_used, std::vector<uint32_t>* rest,
-             uint64_t* done, hipStream_t s) {
+int end_jobs(Engine* e, const FrontArgs& a, size_t nj, bool cigar, uint64_t& gen_used,
+             std::vector<uint32_t>* rest, std::vector<uint32_t>* more, uint64_t* done, hipStream_t s) {
     Workspace& ws = e->ws;
-    uint32_t nfail = 0;
-    HIPCHK(hipMemcpyAsync(&nfail, &ws.flags.as<DevFlags>()->fail_count, 4, hipMemcpyDeviceToHost, s));
+    DevFlags now;
+    HIPCHK(hipMemcpyAsync(&now, ws.flags.ptr, sizeof(now), hipMemcpyDeviceToHost, s));
     if (cigar) RCCHK(gather_runs(e, nj, gen_used, s));
     HIPCHK(hipStreamSynchronize(s));
-    if (nfail) {
-        std::vector<uint32_t> f(nfail);
-        HIPCHK(hipMemcpy(f.data(), ws.fail_list.ptr, nfail * 4ull, hipMemcpyDeviceToHost));
-        rest->insert(rest->end(), f.begin(), f.end());
-    }
-    *done += nj - nfail;
+    auto take = [&](size_t from, size_t n, std::vector<uint32_t>* to) -> int {
+        if (!n) return WFA_OK;
+        to->resize(to->size() + n);
+        HIPCHK(hipMemcpy(to->data() + to->size() - n, a.fail_list + from, n * 4, hipMemcpyDeviceToHost));
+        return WFA_OK;
+    };
+    RCCHK(take(0, now.fail_count, rest));
+    RCCHK(take(a.fail_cap - now.more_count, now.more_count, more));
+    *done += nj - now.fail_count - now.more_count;
     return WFA_OK;
 }
 
@@ -271,30 +278,24 @@ FrontArgs front_args(Engine* e, const Pen& pen, const Dev& d) {
     return a;
 }
 
-// Pairs in `pending` on the adaptive kernel; what it does not hold stays for
-// the general kernel.
-int run_adapt(Engine* e, const Pen& pen, bool cigar, const Dev& d, std::vector<uint32_t>& pending,
-              uint64_t& gen_used, hipStream_t s, uint64_t* done) {
+// One round of the adaptive kernel over `pending`: its records hold `steps` of a
+// pair; the pairs left go to `rest` (the general kernel's) and `more` (those that
+// need more steps).  False in *ran: not for this kernel, nothing was done.
+template <class Steps>
+int adapt_round(Engine* e, const Pen& pen, bool cigar, const Dev& d, const std::vector<uint32_t>& pending,
+                Steps&& steps, uint64_t& gen_used, hipStream_t s, std::vector<uint32_t>* rest,
+                std::vector<uint32_t>* more, bool* ran, uint64_t* done) {
     Workspace& ws = e->ws;
+    *ran = false;
     ByLength b;
     RCCHK(order_by_length(e, d, pending, s, &b));
     if (!b.held || (ws.fixed_base && b.held < pending.size())) return WFA_OK;
-    std::vector<uint32_t> rest, ids;
-    for (size_t i = b.held; i < pending.size(); i++) rest.push_back(pending[b.order[i]]);
-    // records for three quarters of a step per base: reads at 10 % with
-    // gaps take half of that, and a pair past it goes to the general
-    // kernel.  Score-only runs have none to hold: any score is below n + m
-    // bases at the dearest price each.
     auto job_of = [&](size_t i, uint64_t at) -> FrontJob {
-        const uint32_t n = b.n(i), m = b.m(i);
         FrontJob j{};
         j.pair = pending[i];
         j.hist = at;
-        if (!cigar) {
-            j.bound = (int32_t)((n + m) * (uint64_t)std::max(pen.x, pen.oe) + 2);
-            return j;
-        }
-        j.bound = (int32_t)(std::max(n, m) / 4 * 3 + 64);
+        j.bound = steps(b.n(i), b.m(i));
+        if (!cigar) return j;  // no records
         j.hist_words = adapt_hist_words(j.bound);
         j.ev_words = (j.bound / std::min(pen.x, pen.oe) + 64) & ~63;
         j.run_words = 2 * j.ev_words + 64;
@@ -312,8 +313,11 @@ int run_adapt(Engine* e, const Pen& pen, bool cigar, const Dev& d, std::vector<u
         }
         if (!grow_arena(ws, want, most)) return WFA_OK;
     }
+    *ran = true;
+    for (size_t i = b.held; i < pending.size(); i++) rest->push_back(pending[b.order[i]]);
     FrontArgs a = front_args(e, pen, d);
     std::vector<FrontJob> fj;
+    std::vector<uint32_t> ids;
     for (size_t off = 0; off < b.held;) {
         fj.clear();
         ids.clear();
@@ -336,9 +340,49 @@ int run_adapt(Engine* e, const Pen& pen, bool cigar, const Dev& d, std::vector<u
         a.job_nruns += split - off;
         b.longest(split, end, &n, &m);
         HIPCHK(launch_adapt(a, pen, cigar, 1, (int)(end - split), n, m, s));
-        RCCHK(end_jobs(e, end - off, cigar, gen_used, &rest, done, s));
+        RCCHK(end_jobs(e, a, end - off, cigar, gen_used, rest, more, done, s));
         off = end;
     }
+    return WFA_OK;
+}
+
+// Pairs in `pending` on the adaptive kernel; what it does not hold stays for
+// the general kernel.
+//
+// CIGARs: the records first hold three quarters of a step per base (reads at 10 %
+// with gaps take half of that), then, for the pairs that need more, every step up
+// to all bases of both sequences in gaps.  One round with these would take four
+// times the memory; on the general kernel the second lot took longer than both
+// rounds (1-3 kbp at 40 %: 50 pairs 9.9 ms a call, now 3.5; 1000 pairs 17.2 and 4.4).  Score-only runs
+// have no records.
+int run_adapt(Engine* e, const Pen& pen, bool cigar, const Dev& d, std::vector<uint32_t>& pending,
+              uint64_t& gen_used, hipStream_t s, uint64_t* done) {
+    std::vector<uint32_t> rest, more;
+    bool ran = false;
+    RCCHK(adapt_round(
+        e, pen, cigar, d, pending,
+        [&](uint32_t n, uint32_t m) -> int32_t {
+            if (!cigar)  // any score: all bases at the dearest price each
+                return (int32_t)((n + m) * (uint64_t)std::max(pen.x, pen.oe) + 2);
+            return (int32_t)(std::max(n, m) / 4 * 3 + 64);
+        },
+        gen_used, s, &rest, &more, &ran, done));
+    if (!ran) return WFA_OK;
+    // (the fixed region of the allocation-free entry point has no room for a
+    // second arena beside what the first round left)
+    if (!more.empty() && !e->ws.fixed_base) {
+        std::vector<uint32_t> again;
+        again.swap(more);
+        std::sort(again.begin(), again.end());
+        RCCHK(adapt_round(
+            e, pen, cigar, d, again,
+            [&](uint32_t n, uint32_t m) -> int32_t {
+                return (int32_t)((n + m) * (uint32_t)pen.e + 2u * (uint32_t)pen.oe + 64);
+            },
+            gen_used, s, &rest, &more, &ran, done));
+        if (!ran) more.swap(again);
+    }
+    rest.insert(rest.end(), more.begin(), more.end());
     std::sort(rest.begin(), rest.end());
     pending.swap(rest);
     if (std::getenv("WFA_DEBUG"))
@@ -462,7 +506,7 @@ int run_front(Engine* e, const Pen& pen, bool cigar, const Dev& d, std::vector<u
     uint64_t want = 0, most = 0;
     auto finish = [&]() -> int {
         RCCHK(side.join());
-        if (at) RCCHK(end_jobs(e, at, cigar, gen_used, &rest, done, s));
+        if (at) RCCHK(end_jobs(e, a, at, cigar, gen_used, &rest, &rest, done, s));
         at = 0;
         used = 0;
         begun = false;

@@ -20,8 +20,8 @@
 // limit, like the general kernel's), in I and D too, and the ranges of steps
 // are those of the sources widened by one and clipped to the matrix.
 //
-// A pair whose ranges outgrow the window, or that needs more steps than its
-// records hold, goes to the general kernel.
+// A pair whose ranges outgrow the window goes to the general kernel; one that needs
+// more steps than its records hold is aligned again with longer ones.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -243,6 +243,7 @@ __global__ __launch_bounds__(64) void k_adapt(FrontArgs a) {
             }
         }
     };
+    bool more = false;  // the records are too short
     for (int s = 0; S < 0; s += 4) {
         // the rows' ranges, four steps on, inside the first block or, if they
         // are wider, inside both
@@ -254,7 +255,8 @@ __global__ __launch_bounds__(64) void k_adapt(FrontArgs a) {
         }
         if (s == 0) ul = uh = 0;
         const int width = uh - ul + 1 + 8;
-        if (s > job.bound || ul > uh || width + 2 > AW) break;
+        more = s > job.bound;
+        if (more || ul > uh || width + 2 > AW) break;
         const int room = width + 2 <= BW ? BW : AW;
         if (ul - 4 < kmin || uh + 4 > kmin + room - 1) {
             // in the middle, rounded down to a lane: of the columns to spare
@@ -284,8 +286,11 @@ __global__ __launch_bounds__(64) void k_adapt(FrontArgs a) {
         if (room == BW) quad(s, std::integral_constant<int, 1>{});
         else quad(s, std::integral_constant<int, 2>{});
     }
-    if (S < 0) {  // outgrew the window, or its records
-        if (lane == 0) a.fail_list[atomicAdd(a.fail_count, 1u)] = job.pair;
+    if (S < 0) {  // outgrew its records, or the window
+        if (lane == 0) {
+            if (more) a.fail_list[a.fail_cap - 1 - atomicAdd(a.more_count, 1u)] = job.pair;
+            else a.fail_list[atomicAdd(a.fail_count, 1u)] = job.pair;
+        }
         return;
     }
     if (!CIGAR) {

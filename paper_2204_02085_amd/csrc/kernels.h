@@ -190,6 +190,9 @@ struct FrontArgs {
     uint32_t* job_nruns;        // [jobs] runs (zeroed before the launch)
     uint32_t* fail_list;        // pairs handed to the general kernel
     uint32_t* fail_count;
+    // k_adapt: pairs that need longer records, from entry fail_cap - 1 of the list down
+    uint32_t* more_count;
+    uint32_t fail_cap;          // entries of the list, at least the launches' pairs
     Heuristic heur;             // k_adapt: the reduction
 };
 
