@@ -156,7 +156,7 @@ void order_by(size_t n, uint32_t keys, Key&& key, std::vector<uint32_t>* order) 
     for (size_t i = 0; i < n; i++) (*order)[first[keys - key(i)]++] = (uint32_t)i;
 }
 
-// The pairs of `pending` the 16-bit kernels can hold, longest first (by classes
+// The pairs of `pending` that `fits` says a 16-bit kernel can hold, longest first (by classes
 // of 64 bases of n + m), those past 16383 bases (`past` of them) before all
 // others; positions in `pending`.  The rest follow at the end.
 struct ByLength {
@@ -172,12 +172,13 @@ struct ByLength {
         }
     }
 };
-int order_by_length(Engine* e, const Dev& d, const std::vector<uint32_t>& pending, hipStream_t s,
-                    ByLength* b) {
+template <class Fits>
+int order_by_length(Engine* e, const Dev& d, const std::vector<uint32_t>& pending, Fits&& fits,
+                    hipStream_t s, ByLength* b) {
     RCCHK(pair_lengths(e, d, pending, s, &b->lens));
     constexpr uint32_t CLASSES = 1024;
     auto len_class = [&](size_t i) -> uint32_t {
-        if (!front_fits(b->n(i), b->m(i))) return 0;
+        if (!fits(b->n(i), b->m(i))) return 0;
         const uint32_t c = 1 + std::min((b->n(i) + b->m(i)) / 64, CLASSES - 2);
         return std::max(b->n(i), b->m(i)) > 16383 ? c + CLASSES : c;
     };
@@ -213,8 +214,7 @@ bool grow_arena(Workspace& ws, uint64_t want, uint64_t most) {
 
 // The buffers and counters of launches of the front or adaptive kernels over up
 // to `nj` pairs, the pairs of a launch (`fj`, ids `ids`) to places `at` on of
-// the buffers, and the read-back: pairs that failed go to `rest`, those whose
-// records were too short (adaptive kernel) to `more`.
+// the buffers, and the read-back: pairs that failed go to `rest`.
 int begin_jobs(Engine* e, size_t nj, FrontArgs* a, hipStream_t s) {
     Workspace& ws = e->ws;
     RCCHK(ws.ensure(ws.jobs, nj * 4));
@@ -227,12 +227,9 @@ int begin_jobs(Engine* e, size_t nj, FrontArgs* a, hipStream_t s) {
     FillOps fill{};
     fill.add(ws.job_nruns.as<uint32_t>(), nj, 0u);
     fill.add(&flags->fail_count, 1, 0u);
-    fill.add(&flags->more_count, 1, 0u);
     HIPCHK(launch_fill_multi(fill, s));
     a->fail_list = ws.fail_list.as<uint32_t>();
     a->fail_count = &flags->fail_count;
-    a->more_count = &flags->more_count;
-    a->fail_cap = (uint32_t)nj;
     return WFA_OK;
 }
 int put_jobs(Engine* e, const FrontJob* fj, const uint32_t* ids, size_t at, size_t nj, FrontArgs* a,
@@ -246,22 +243,19 @@ int put_jobs(Engine* e, const FrontJob* fj, const uint32_t* ids, size_t at, size
                           hipMemcpyHostToDevice, s));
     return WFA_OK;
 }
-int end_jobs(Engine* e, const FrontArgs& a, size_t nj, bool cigar, uint64_t& gen_used,
-             std::vector<uint32_t>* rest, std::vector<uint32_t>* more, uint64_t* done, hipStream_t s) {
+int end_jobs(Engine* e, size_t nj, bool cigar, uint64_t& gen_used, std::vector<uint32_t>* rest,
+             uint64_t* done, hipStream_t s) {
     Workspace& ws = e->ws;
-    DevFlags now;
-    HIPCHK(hipMemcpyAsync(&now, ws.flags.ptr, sizeof(now), hipMemcpyDeviceToHost, s));
+    uint32_t nfail = 0;
+    HIPCHK(hipMemcpyAsync(&nfail, &ws.flags.as<DevFlags>()->fail_count, 4, hipMemcpyDeviceToHost, s));
     if (cigar) RCCHK(gather_runs(e, nj, gen_used, s));
     HIPCHK(hipStreamSynchronize(s));
-    auto take = [&](size_t from, size_t n, std::vector<uint32_t>* to) -> int {
-        if (!n) return WFA_OK;
-        to->resize(to->size() + n);
-        HIPCHK(hipMemcpy(to->data() + to->size() - n, a.fail_list + from, n * 4, hipMemcpyDeviceToHost));
-        return WFA_OK;
-    };
-    RCCHK(take(0, now.fail_count, rest));
-    RCCHK(take(a.fail_cap - now.more_count, now.more_count, more));
-    *done += nj - now.fail_count - now.more_count;
+    if (nfail) {
+        std::vector<uint32_t> f(nfail);
+        HIPCHK(hipMemcpy(f.data(), ws.fail_list.ptr, nfail * 4ull, hipMemcpyDeviceToHost));
+        rest->insert(rest->end(), f.begin(), f.end());
+    }
+    *done += nj - nfail;
     return WFA_OK;
 }
 
@@ -278,17 +272,25 @@ FrontArgs front_args(Engine* e, const Pen& pen, const Dev& d) {
     return a;
 }
 
-// One round of the adaptive kernel over `pending`: its records hold `steps` of a
-// pair; the pairs left go to `rest` (the general kernel's) and `more` (those that
-// need more steps).  False in *ran: not for this kernel, nothing was done.
+// One round of the adaptive kernel over `pending`, in windows of `blocks` blocks,
+// with records for `steps` of a pair; the pairs left go to `rest`.  False in *ran:
+// not for this kernel, nothing was done.
 template <class Steps>
 int adapt_round(Engine* e, const Pen& pen, bool cigar, const Dev& d, const std::vector<uint32_t>& pending,
-                Steps&& steps, uint64_t& gen_used, hipStream_t s, std::vector<uint32_t>* rest,
-                std::vector<uint32_t>* more, bool* ran, uint64_t* done) {
+                int blocks, Steps&& steps, uint64_t& gen_used, hipStream_t s,
+                std::vector<uint32_t>* rest, bool* ran, uint64_t* done) {
     Workspace& ws = e->ws;
     *ran = false;
     ByLength b;
-    RCCHK(order_by_length(e, d, pending, s, &b));
+    // A pair comes to the wide window when it has outgrown the narrow one.  A
+    // length difference past one and a half times its diagonals is then a gap
+    // that outgrows this one as well (10 kbp with 3 kbp missing: 27.9 ms with a
+    // try, 22.9 on the general kernel alone).
+    const uint32_t most_gap = blocks > ADAPT_BLOCKS ? 3 * 64 * (uint32_t)blocks : FRONT_MAX_LEN;
+    auto fits = [&](uint32_t n, uint32_t m) -> bool {
+        return front_fits(n, m) && std::max(n, m) - std::min(n, m) <= most_gap;
+    };
+    RCCHK(order_by_length(e, d, pending, fits, s, &b));
     if (!b.held || (ws.fixed_base && b.held < pending.size())) return WFA_OK;
     auto job_of = [&](size_t i, uint64_t at) -> FrontJob {
         FrontJob j{};
@@ -296,7 +298,7 @@ int adapt_round(Engine* e, const Pen& pen, bool cigar, const Dev& d, const std::
         j.hist = at;
         j.bound = steps(b.n(i), b.m(i));
         if (!cigar) return j;  // no records
-        j.hist_words = adapt_hist_words(j.bound);
+        j.hist_words = adapt_hist_words(j.bound, blocks);
         j.ev_words = (j.bound / std::min(pen.x, pen.oe) + 64) & ~63;
         j.run_words = 2 * j.ev_words + 64;
         return j;
@@ -335,12 +337,12 @@ int adapt_round(Engine* e, const Pen& pen, bool cigar, const Dev& d, const std::
         const size_t split = std::min(std::max(b.past, off), end);  // pairs past 16383 bases end here
         uint32_t n, m;
         b.longest(off, split, &n, &m);
-        HIPCHK(launch_adapt(a, pen, cigar, 0, (int)(split - off), n, m, s));
+        HIPCHK(launch_adapt(a, pen, cigar, 0, blocks, (int)(split - off), n, m, s));
         a.jobs += split - off;
         a.job_nruns += split - off;
         b.longest(split, end, &n, &m);
-        HIPCHK(launch_adapt(a, pen, cigar, 1, (int)(end - split), n, m, s));
-        RCCHK(end_jobs(e, a, end - off, cigar, gen_used, rest, more, done, s));
+        HIPCHK(launch_adapt(a, pen, cigar, 1, blocks, (int)(end - split), n, m, s));
+        RCCHK(end_jobs(e, end - off, cigar, gen_used, rest, done, s));
         off = end;
     }
     return WFA_OK;
@@ -349,40 +351,42 @@ int adapt_round(Engine* e, const Pen& pen, bool cigar, const Dev& d, const std::
 // Pairs in `pending` on the adaptive kernel; what it does not hold stays for
 // the general kernel.
 //
-// CIGARs: the records first hold three quarters of a step per base (reads at 10 %
-// with gaps take half of that), then, for the pairs that need more, every step up
-// to all bases of both sequences in gaps.  One round with these would take four
-// times the memory; on the general kernel the second lot took longer than both
-// rounds (1-3 kbp at 40 %: 50 pairs 9.9 ms a call, now 3.5; 1000 pairs 17.2 and 4.4).  Score-only runs
-// have no records.
+// Two rounds.  Nearly all pairs stay in the narrow window, with records (CIGARs)
+// for three quarters of a step per base: reads at 10 % with gaps take half of
+// that.  The others are aligned again in the wide one, with records for every step
+// up to all bases of both sequences in gaps.  On the general kernel they cost more
+// than both rounds.  Calls under (10, 50) with CIGARs, the second lot on the general
+// kernel against now: 50 pairs of 1-3 kbp at 40 % 9.9 and 3.7 ms, with 30 % of the
+// text's bases missing 10.0 and 5.3, with a third of it missing in one piece 4.8
+// and 2.5, unrelated 13.8 and 5.5; the general kernel alone 8.3, 7.8, 4.3 and 11.9.
+//
+// A wide threshold drops so little that divergent pairs outgrow both windows: 50
+// pairs of 2-6 kbp at 20 % 10.4 ms at a threshold of 400 and 31.2 at 800, on the
+// general kernel alone 14.3 and 24.3.  The line lies between.
 int run_adapt(Engine* e, const Pen& pen, bool cigar, const Dev& d, std::vector<uint32_t>& pending,
               uint64_t& gen_used, hipStream_t s, uint64_t* done) {
-    std::vector<uint32_t> rest, more;
+    auto any_score = [&](uint32_t n, uint32_t m) -> int32_t {  // all bases at the dearest price each
+        return (int32_t)((n + m) * (uint64_t)std::max(pen.x, pen.oe) + 2);
+    };
+    auto usual = [&](uint32_t n, uint32_t m) -> int32_t {
+        return cigar ? (int32_t)(std::max(n, m) / 4 * 3 + 64) : any_score(n, m);
+    };
+    auto all_gaps = [&](uint32_t n, uint32_t m) -> int32_t {
+        return cigar ? (int32_t)((n + m) * (uint32_t)pen.e + 2u * (uint32_t)pen.oe + 64) : any_score(n, m);
+    };
+    std::vector<uint32_t> rest, again;
     bool ran = false;
-    RCCHK(adapt_round(
-        e, pen, cigar, d, pending,
-        [&](uint32_t n, uint32_t m) -> int32_t {
-            if (!cigar)  // any score: all bases at the dearest price each
-                return (int32_t)((n + m) * (uint64_t)std::max(pen.x, pen.oe) + 2);
-            return (int32_t)(std::max(n, m) / 4 * 3 + 64);
-        },
-        gen_used, s, &rest, &more, &ran, done));
+    if (e->heur.mdt > 512) return WFA_OK;
+    RCCHK(adapt_round(e, pen, cigar, d, pending, ADAPT_BLOCKS, usual, gen_used, s, &rest, &ran, done));
     if (!ran) return WFA_OK;
     // (the fixed region of the allocation-free entry point has no room for a
     // second arena beside what the first round left)
-    if (!more.empty() && !e->ws.fixed_base) {
-        std::vector<uint32_t> again;
-        again.swap(more);
-        std::sort(again.begin(), again.end());
-        RCCHK(adapt_round(
-            e, pen, cigar, d, again,
-            [&](uint32_t n, uint32_t m) -> int32_t {
-                return (int32_t)((n + m) * (uint32_t)pen.e + 2u * (uint32_t)pen.oe + 64);
-            },
-            gen_used, s, &rest, &more, &ran, done));
-        if (!ran) more.swap(again);
+    if (!rest.empty() && !(cigar && e->ws.fixed_base)) {
+        std::sort(rest.begin(), rest.end());
+        again.swap(rest);
+        RCCHK(adapt_round(e, pen, cigar, d, again, ADAPT_BLOCKS_WIDE, all_gaps, gen_used, s, &rest, &ran, done));
+        if (!ran) rest.swap(again);
     }
-    rest.insert(rest.end(), more.begin(), more.end());
     std::sort(rest.begin(), rest.end());
     pending.swap(rest);
     if (std::getenv("WFA_DEBUG"))
@@ -434,7 +438,7 @@ int run_front(Engine* e, const Pen& pen, bool cigar, const Dev& d, std::vector<u
               uint64_t& gen_used, hipStream_t s, bool sides, uint64_t* done) {
     Workspace& ws = e->ws;
     ByLength b;
-    RCCHK(order_by_length(e, d, pending, s, &b));
+    RCCHK(order_by_length(e, d, pending, front_fits, s, &b));
     const std::vector<uint32_t>& order = b.order;
     const size_t np = pending.size(), nf = b.held, n16 = b.past;
     // the fixed region of the allocation-free entry point cannot hold an arena
@@ -506,7 +510,7 @@ int run_front(Engine* e, const Pen& pen, bool cigar, const Dev& d, std::vector<u
     uint64_t want = 0, most = 0;
     auto finish = [&]() -> int {
         RCCHK(side.join());
-        if (at) RCCHK(end_jobs(e, a, at, cigar, gen_used, &rest, &rest, done, s));
+        if (at) RCCHK(end_jobs(e, at, cigar, gen_used, &rest, done, s));
         at = 0;
         used = 0;
         begun = false;

@@ -80,7 +80,7 @@ struct DevFlags {
     uint32_t fail_count;          // general jobs whose slice was too small
     uint32_t ovf_count2;          // pairs a cascade pass (a wider short pass) handed over
     uint32_t queue2;              // queue head of a cascade pass
-    uint32_t more_count;          // pairs the adaptive kernel's records were too short for
+    uint32_t pad;
     uint64_t total_runs;          // run total of the first pass (written by the compaction)
     unsigned long long gave_up;   // first pair the general kernel gave up on (~0: none)
 };

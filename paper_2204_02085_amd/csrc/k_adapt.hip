@@ -3,7 +3,7 @@
 // The reduction keeps a wavefront to the diagonals near its furthest points,
 // usually a few dozen, so a pair's rows fit the registers of one wavefront: a
 // window of 128 diagonals, two per lane, that moves along with the reduced
-// ranges, and a second block of 128 beside it while they are wider.  Where
+// ranges, and further blocks of 128 beside it while they are wider.  Where
 // k_general spent a workgroup, several barriers and row traffic on every step, a
 // step here is about 130 instructions of one wavefront, the least distance by DPP
 // and the kept range by two ballots.
@@ -20,8 +20,10 @@
 // limit, like the general kernel's), in I and D too, and the ranges of steps
 // are those of the sources widened by one and clipped to the matrix.
 //
-// A pair whose ranges outgrow the window goes to the general kernel; one that needs
-// more steps than its records hold is aligned again with longer ones.
+// Two blocks first.  A pair whose ranges outgrow them (gaps of hundreds of bases,
+// unrelated sequences), or that needs more steps than its records hold, is aligned
+// again in a window of eight blocks, at one wavefront per SIMD instead of four, with
+// records for every step it can need; what outgrows that goes to the general kernel.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -50,11 +52,16 @@ __device__ __forceinline__ uint32_t wave_min(uint32_t v) {
     return (uint32_t)__builtin_amdgcn_readlane((int)v, 63);
 }
 
-// The window is two blocks of 128 diagonals, two per lane and block; the second
-// is computed only while the ranges do not fit the first.
-template <int X, int OE, int E, int SH, bool CIGAR>
+// The window is NB blocks of 128 diagonals, two per lane and block; the second, the
+// third and fourth, and the last four are computed only while the ranges do not fit
+// those before.
+template <int X, int OE, int E, int SH, int NB, bool CIGAR>
 __global__ __launch_bounds__(64) void k_adapt(FrontArgs a) {
-    constexpr int NB = 2, BW = 128, AW = NB * BW;
+    constexpr int BW = 128, AW = NB * BW, QUAD = adapt_quad_words(NB);
+    // the walk's window; columns of a wide window past the last diagonal compare from
+    // up to AW bases before the pattern, which stays behind it
+    constexpr bool HEAD = CIGAR || AW / 4 > 64;
+    static_assert(AW / 4 <= 64 + 4 * WALK_DW, "compares stay in the workgroup's LDS");
     constexpr int RM = X > OE ? X : OE;
     constexpr uint32_t ONE = SH ? 0x00020002u : 0x00010001u;
     extern __shared__ __align__(16) unsigned char lds[];
@@ -63,7 +70,7 @@ __global__ __launch_bounds__(64) void k_adapt(FrontArgs a) {
     const int n = (int)d.p_len, m = (int)d.t_len, kt = m - n;
     const int lane = threadIdx.x;
     lds_p<uint32_t> win = (lds_p<uint32_t>)lds;
-    lds_p<uint64_t> seq = (lds_p<uint64_t>)(win + (CIGAR ? WALK_DW : 0));
+    lds_p<uint64_t> seq = (lds_p<uint64_t>)(win + (HEAD ? WALK_DW : 0));
     stage(seq, a.pw, a.tw, d, lane, 64);
     wave_fence();
     const uint32_t tb = (uint32_t)(uintptr_t)seq, pb = tb + 8 * text_words(m);
@@ -94,12 +101,15 @@ __global__ __launch_bounds__(64) void k_adapt(FrontArgs a) {
         for (int j = 0; j < E; j++) I[j][b] = D[j][b] = NUL16P;
     }
     auto shift_up = [&](uint32_t (&r)[NB]) {  // one lane: the window moves two diagonals up
-        r[0] = wave_next((uint32_t)__builtin_amdgcn_readlane((int)r[1], 0), r[0]);
-        r[1] = wave_next(NUL16P, r[1]);
+#pragma unroll
+        for (int b = 0; b < NB; b++)
+            r[b] = wave_next(b + 1 < NB ? (uint32_t)__builtin_amdgcn_readlane((int)r[b + 1 < NB ? b + 1 : b], 0) : NUL16P,
+                             r[b]);
     };
     auto shift_down = [&](uint32_t (&r)[NB]) {
-        r[1] = wave_prev((uint32_t)__builtin_amdgcn_readlane((int)r[0], 63), r[1]);
-        r[0] = wave_prev(NUL16P, r[0]);
+#pragma unroll
+        for (int b = NB - 1; b >= 0; b--)
+            r[b] = wave_prev(b ? (uint32_t)__builtin_amdgcn_readlane((int)r[b ? b - 1 : 0], 63) : NUL16P, r[b]);
     };
     // ranges of the last RM steps; lo > hi: no wavefront
     constexpr int NONE = 1 << 29;
@@ -172,7 +182,9 @@ __global__ __launch_bounds__(64) void k_adapt(FrontArgs a) {
                 for (int b = 0; b < nb; b++) acc[b] = u ? shl_or<4>(acc[b], rec[b]) : rec[b];
             }
             const int tc = kt - kmin;
-            const uint32_t treg = nb > 1 && tc >= BW ? cm[NB - 1] : cm[0];
+            uint32_t treg = cm[0];
+#pragma unroll
+            for (int b = 1; b < nb; b++) treg = tc >= BW * b ? cm[b] : treg;
             if (tc >= 0 && tc < nb * BW && half_at(treg, (tc & (BW - 1)) >> 1, tc & 1) == m << SH) {
                 S = s + u;  // the step that reaches the end is not reduced
             } else if (present && h - l + 1 >= MWL) {
@@ -231,22 +243,21 @@ __global__ __launch_bounds__(64) void k_adapt(FrontArgs a) {
                 D[0][b] = cd[b];
             }
             if (CIGAR && (u == 3 || S >= 0)) {
-                uint32_t* q = hist + (uint64_t)(s >> 2) * ADAPT_QUAD_WORDS;
+                uint32_t* q = hist + (uint64_t)(s >> 2) * QUAD;
 #pragma unroll
                 for (int b = 0; b < nb; b++) q[64 * b + lane] = acc[b] << (4 * (3 - u));
                 if (lane == 0) q[64 * NB] = (uint32_t)kmin;
                 if (u == 3 && (s & 15) == 0) {
-                    uint32_t* r = hist + adapt_rec_words(job.bound) + (uint64_t)(s >> 4) * (64 * NB);
+                    uint32_t* r = hist + adapt_rec_words(job.bound, NB) + (uint64_t)(s >> 4) * (64 * NB);
 #pragma unroll
                     for (int b = 0; b < nb; b++) r[64 * b + lane] = cm[b];
                 }
             }
         }
     };
-    bool more = false;  // the records are too short
     for (int s = 0; S < 0; s += 4) {
         // the rows' ranges, four steps on, inside the first block or, if they
-        // are wider, inside both
+        // are wider, inside the first two, four or all
         int ul = NONE, uh = -NONE;
 #pragma unroll
         for (int j = 0; j < RM; j++) {
@@ -255,9 +266,9 @@ __global__ __launch_bounds__(64) void k_adapt(FrontArgs a) {
         }
         if (s == 0) ul = uh = 0;
         const int width = uh - ul + 1 + 8;
-        more = s > job.bound;
-        if (more || ul > uh || width + 2 > AW) break;
-        const int room = width + 2 <= BW ? BW : AW;
+        if (s > job.bound || ul > uh || width + 2 > AW) break;
+        int room = BW;
+        while (room < width + 2) room *= 2;
         if (ul - 4 < kmin || uh + 4 > kmin + room - 1) {
             // in the middle, rounded down to a lane: of the columns to spare
             // there are at least two, so both margins hold
@@ -284,13 +295,12 @@ __global__ __launch_bounds__(64) void k_adapt(FrontArgs a) {
             place();
         }
         if (room == BW) quad(s, std::integral_constant<int, 1>{});
-        else quad(s, std::integral_constant<int, 2>{});
+        else if (NB == 2 || room == 2 * BW) quad(s, std::integral_constant<int, 2>{});
+        else if (room == 4 * BW) quad(s, std::integral_constant<int, NB < 4 ? NB : 4>{});
+        else quad(s, std::integral_constant<int, NB>{});
     }
     if (S < 0) {  // outgrew its records, or the window
-        if (lane == 0) {
-            if (more) a.fail_list[a.fail_cap - 1 - atomicAdd(a.more_count, 1u)] = job.pair;
-            else a.fail_list[atomicAdd(a.fail_count, 1u)] = job.pair;
-        }
+        if (lane == 0) a.fail_list[atomicAdd(a.fail_count, 1u)] = job.pair;
         return;
     }
     if (!CIGAR) {
@@ -300,7 +310,7 @@ __global__ __launch_bounds__(64) void k_adapt(FrontArgs a) {
         }
         return;
     }
-    // the walk (what a quad left unwritten of its second block is never on the
+    // the walk (what a quad left unwritten of its later blocks is never on the
     // way; the windows of all quads start at an even diagonal)
     constexpr int QW = 64 * NB;
     __threadfence_block();
@@ -309,7 +319,7 @@ __global__ __launch_bounds__(64) void k_adapt(FrontArgs a) {
     auto load = [&](int q, int k) {
         const int kf = (k & ~1) - WALK_COLS / 2;
         if (q - lane >= 0) {
-            const uint32_t* from = hist + (uint64_t)(q - lane) * ADAPT_QUAD_WORDS;
+            const uint32_t* from = hist + (uint64_t)(q - lane) * QUAD;
             const int c0 = (kf - (int)from[QW]) >> 1;
 #pragma unroll
             for (int i = 0; i < WALK_COLS / 2; i++)
@@ -318,9 +328,9 @@ __global__ __launch_bounds__(64) void k_adapt(FrontArgs a) {
         return kf;
     };
     auto offset = [&](int s, int k) {
-        const int col = k - (int)hist[(uint64_t)(s >> 2) * ADAPT_QUAD_WORDS + QW];
+        const int col = k - (int)hist[(uint64_t)(s >> 2) * QUAD + QW];
         const uint32_t w = col >= 0 && col < AW
-                               ? hist[adapt_rec_words(job.bound) + (uint64_t)(s >> 4) * QW + (col >> 1)]
+                               ? hist[adapt_rec_words(job.bound, NB) + (uint64_t)(s >> 4) * QW + (col >> 1)]
                                : NUL16P;
         return (int)(short)(w >> (16 * (col & 1))) >> SH;
     };
@@ -345,20 +355,22 @@ bool adapt_supported(const Pen& pen) {
     return false;
 }
 
-hipError_t launch_adapt(const FrontArgs& a, const Pen& pen, bool cigar, int sh, int jobs, uint32_t n,
-                        uint32_t m, hipStream_t s) {
+hipError_t launch_adapt(const FrontArgs& a, const Pen& pen, bool cigar, int sh, int blocks, int jobs,
+                        uint32_t n, uint32_t m, hipStream_t s) {
     if (!jobs) return hipSuccess;
-    const int lds = (cigar ? WALK_DW * 4 : 0) + seq_lds_bytes(n, m);
-#define WFA_GO(PX, POE, PE, SHF, CG) \
-    hipLaunchKernelGGL((k_adapt<PX, POE, PE, SHF, CG>), dim3(jobs), dim3(64), lds, s, a)
-#define WFA_CASE(PX, POE, PE)                                                                    \
-    if (pen.x == PX && pen.oe == POE && pen.e == PE) {                                           \
-        if (cigar) { if (sh) WFA_GO(PX, POE, PE, 1, true); else WFA_GO(PX, POE, PE, 0, true); }  \
-        else { if (sh) WFA_GO(PX, POE, PE, 1, false); else WFA_GO(PX, POE, PE, 0, false); }      \
-        return hipGetLastError();                                                                \
+    const int lds = (cigar || blocks > ADAPT_BLOCKS ? WALK_DW * 4 : 0) + seq_lds_bytes(n, m);
+#define WFA_GO(PX, POE, PE, SHF, NB, CG) \
+    hipLaunchKernelGGL((k_adapt<PX, POE, PE, SHF, NB, CG>), dim3(jobs), dim3(64), lds, s, a)
+#define WFA_FORM(PX, POE, PE, NB)                                                                       \
+    if (pen.x == PX && pen.oe == POE && pen.e == PE && blocks == NB) {                                  \
+        if (cigar) { if (sh) WFA_GO(PX, POE, PE, 1, NB, true); else WFA_GO(PX, POE, PE, 0, NB, true); } \
+        else { if (sh) WFA_GO(PX, POE, PE, 1, NB, false); else WFA_GO(PX, POE, PE, 0, NB, false); }     \
+        return hipGetLastError();                                                                       \
     }
+#define WFA_CASE(PX, POE, PE) WFA_FORM(PX, POE, PE, ADAPT_BLOCKS) WFA_FORM(PX, POE, PE, ADAPT_BLOCKS_WIDE)
     WFA_ADAPT_PENS(WFA_CASE)
 #undef WFA_CASE
+#undef WFA_FORM
 #undef WFA_GO
     return hipErrorInvalidValue;
 }

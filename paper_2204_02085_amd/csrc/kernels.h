@@ -190,9 +190,6 @@ struct FrontArgs {
     uint32_t* job_nruns;        // [jobs] runs (zeroed before the launch)
     uint32_t* fail_list;        // pairs handed to the general kernel
     uint32_t* fail_count;
-    // k_adapt: pairs that need longer records, from entry fail_cap - 1 of the list down
-    uint32_t* more_count;
-    uint32_t fail_cap;          // entries of the list, at least the launches' pairs
     Heuristic heur;             // k_adapt: the reduction
 };
 
@@ -353,18 +350,22 @@ hipError_t launch_front(const FrontArgs& a, const Pen& pen, bool cigar, const Fr
                         int waves, uint32_t n, uint32_t m, hipStream_t s);
 
 // Adaptive kernel (the WF-adaptive heuristic, global): one wavefront per pair,
-// built for some scaled penalties; a job's `bound` is the last step its records
-// hold (ADAPT_QUAD_WORDS words per four steps), pairs it does not hold go to
-// the fail list.  A launch takes pairs of one `sh` (1: up to 16383 bases).
-constexpr int ADAPT_QUAD_WORDS = 2 * 64 + 1;  // both blocks' records, the window's base
+// built for some scaled penalties and windows of ADAPT_BLOCKS or ADAPT_BLOCKS_WIDE
+// blocks of 128 diagonals; a job's `bound` is the last step its records hold
+// (adapt_quad_words words per four steps), pairs it does not hold go to the fail
+// list.  A launch takes pairs of one `sh` (1: up to 16383 bases).
+constexpr int ADAPT_BLOCKS = 2, ADAPT_BLOCKS_WIDE = 8;
+constexpr int adapt_quad_words(int blocks) { return blocks * 64 + 1; }  // the records, the window's base
 // a pair's record words, then with its M rows of every 16th step (see walk.h)
-constexpr uint64_t adapt_rec_words(int bound) { return (uint64_t)(bound / 4 + 2) * ADAPT_QUAD_WORDS; }
-constexpr uint64_t adapt_hist_words(int bound) {
-    return (adapt_rec_words(bound) + (uint64_t)(bound / 16 + 1) * 128 + 63) & ~(uint64_t)63;
+constexpr uint64_t adapt_rec_words(int bound, int blocks) {
+    return (uint64_t)(bound / 4 + 2) * adapt_quad_words(blocks);
+}
+constexpr uint64_t adapt_hist_words(int bound, int blocks) {
+    return (adapt_rec_words(bound, blocks) + (uint64_t)(bound / 16 + 1) * (64 * blocks) + 63) & ~(uint64_t)63;
 }
 bool adapt_supported(const Pen& pen);
-hipError_t launch_adapt(const FrontArgs& a, const Pen& pen, bool cigar, int sh, int jobs, uint32_t n,
-                        uint32_t m, hipStream_t s);
+hipError_t launch_adapt(const FrontArgs& a, const Pen& pen, bool cigar, int sh, int blocks, int jobs,
+                        uint32_t n, uint32_t m, hipStream_t s);
 
 // rows16: 16-bit ring rows (every text of the launch shorter than 32767 bases)
 hipError_t launch_general(const GeneralArgs& a, int block_threads, bool seq_in_lds,
