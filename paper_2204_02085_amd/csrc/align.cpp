@@ -462,10 +462,11 @@ int run_front(Engine* e, const Pen& pen, bool cigar, const Dev& d, std::vector<u
     HIPCHK(hipMemcpyAsync(dev_ids, ids.data(), nf * 4, hipMemcpyHostToDevice, s));
     SideBySide side{e, s};
     bool begun = false;
+    size_t places = nf;  // pairs launched between two calls of finish(), at most
     auto begin = [&]() -> int {
         if (begun) return WFA_OK;
         begun = true;
-        RCCHK(begin_jobs(e, nf, &a, s));
+        RCCHK(begin_jobs(e, places, &a, s));
         if (side.forked) HIPCHK(hipStreamSynchronize(s));  // for the side streams
         return WFA_OK;
     };
@@ -568,6 +569,16 @@ int run_front(Engine* e, const Pen& pen, bool cigar, const Dev& d, std::vector<u
             if (!grow_arena(ws, want, most)) {  // the general kernel needs less
                 for (const Job& j : held) rest.push_back(pending[j.idx]);
                 continue;
+            }
+        }
+        if (cigar && !parts) {  // (one part: what a full arena holds)
+            uint64_t words = 0;
+            size_t n_in = 0;
+            places = 0;
+            for (uint32_t i : by_work) {
+                if ((words + held[i].words) * 4 > ws.arena.bytes) words = n_in = 0;
+                words += held[i].words;
+                places = std::max(places, ++n_in);
             }
         }
         if (std::getenv("WFA_DEBUG")) {
@@ -1648,13 +1659,32 @@ int engine_align_device(Engine* e, const BatchIO& io, hipStream_t user_stream,
     if (!pending.empty() && global && (heuristic ? adapt_supported(pen) : front_supported(pen)) &&
         e->opt.general_step_limit == 0 && e->opt.general_checkpoint == 0 &&
         e->opt.general_slice_kib == 0 && e->opt.general_pairs == 0) {
+        // These kernels want more memory beside their arena than the general kernel
+        // does (a launch holds more pairs, a second round more records), so where
+        // they run out of it, all pairs are that kernel's, with what it had before.
+        const Workspace before = ws;
         const int rf = heuristic ? run_adapt(e, pen, cigar, d, pending, gen_used, s, &general_done)
                                  : run_front(e, pen, cigar, d, pending, gen_used, s, !io.no_graph,
                                              &general_done);
-        if (rf != WFA_OK) {
+        if (rf == WFA_E_NOMEM) {
+            HIPCHK(hipStreamSynchronize(s));
+            if (ws.fixed_base) {
+                const uint64_t generation = ws.generation;
+                ws = before;
+                ws.generation = generation + 1;
+            } else {
+                for (Buf* b : {&ws.arena, &ws.gen_runs, &ws.gen_slices, &ws.gen_state, &ws.gen_tmp, &ws.jobs,
+                               &ws.job_nruns, &ws.job_offsets, &ws.fail_list})
+                    ws.release(*b);
+            }
+            gen_used = general_done = 0;
+            if (std::getenv("WFA_DEBUG"))
+                std::fprintf(stderr, "libwfa: out of memory, %zu pairs to the general kernel\n", pending.size());
+        } else if (rf != WFA_OK) {
             (void)finish_user();
             return rf;
         }
+        flags = ws.flags.as<DevFlags>();
     }
     if (!pending.empty()) {
         int64_t gave_up = -1;
