@@ -108,9 +108,12 @@ size_t pair_bytes(const wfa_server_cfg& cfg, uint32_t n, uint32_t m) {
     return io + (size_t)wf;
 }
 
-// A worker's host buffer, kept from batch to batch and grown by doubling:
-// page-locked where the worker has an engine, so the batch's copies run by DMA
-// without staging.
+// A worker's host buffer, kept from batch to batch and grown by doubling up to
+// KEPT_BYTES: page-locked where the worker has an engine, so the batch's copies run
+// by DMA without staging.  A batch that needs more gets ordinary memory, which
+// trim() gives back once its results are handed over, so one large request pins
+// nothing for the server's life (six buffers: at most 384 MiB per worker).
+constexpr size_t KEPT_BYTES = (size_t)64 << 20;
 struct HostBuf {
     void* ptr = nullptr;
     size_t bytes = 0;
@@ -121,13 +124,16 @@ struct HostBuf {
         else std::free(ptr);
         ptr = nullptr;
         bytes = 0;
+        locked = false;
     }
     // at least `want` bytes, contents lost when it grows; false: out of memory
     bool ensure(size_t want, bool lock) {
         if (bytes >= want && ptr) return true;
+        const bool keep = want <= KEPT_BYTES;
         // from 2 MiB on: pinning memory stalls the device's other streams
-        const size_t size = std::max({want, 2 * bytes, (size_t)2 << 20});
+        const size_t size = keep ? std::min(std::max({want, 2 * bytes, (size_t)2 << 20}), KEPT_BYTES) : want;
         drop();
+        lock = lock && keep;
         locked = lock && hipHostMalloc(&ptr, size, hipHostMallocDefault) == hipSuccess;
         if (!locked) {
             if (lock) (void)hipGetLastError();
@@ -135,6 +141,9 @@ struct HostBuf {
         }
         bytes = ptr ? size : 0;
         return ptr != nullptr;
+    }
+    void trim() {
+        if (bytes > KEPT_BYTES) drop();
     }
     template <class T>
     T* as() const {
@@ -144,6 +153,9 @@ struct HostBuf {
 
 struct WorkerBufs {
     HostBuf pat, txt, pairs, scores, runs, offsets;
+    void trim() {
+        for (HostBuf* b : {&pat, &txt, &pairs, &scores, &runs, &offsets}) b->trim();
+    }
 };
 
 // Run one merged batch on an engine (or the user's executor); the results land
@@ -353,6 +365,7 @@ void worker_main(wfa_server* srv, Engine* eng) {
         }
         srv->cv_done.notify_all();
         srv->cv_work.notify_all();
+        w.trim();
     }
 }
 
