@@ -116,8 +116,17 @@ typedef enum { WFA_HOST = 0, WFA_DEVICE = 1 } wfa_memspace;
  *   PLAIN:      one launch, pair i on lane group i, no bucketing;
  *   PERSISTENT: grid sized to the GPU, lane groups pull pairs from a device
  *               queue (in bucketed order, see `bucket`);
- *   GENERAL:    every pair on the workgroup-per-pair kernel whose
- *               wavefronts live in the HBM arena (any length, any score). */
+ *   GENERAL:    every pair on the kernels for long pairs (any length, any
+ *               score).  Global alignment under the penalties they are built
+ *               for (x, o, e = 4, 6, 2; 1, 0, 1; 2, 3, 1 and multiples) has
+ *               kernels with the wavefronts in registers; all else, and what
+ *               these hand over, goes to the workgroup-per-pair kernel whose
+ *               wavefronts live in the HBM arena, the "general kernel".  The
+ *               same kernels take what the short-pair kernels hand over under
+ *               the other schedules.  Setting general_pairs,
+ *               general_slice_kib, general_step_limit or general_checkpoint
+ *               (to -1 for full histories) sends these pairs to the general
+ *               kernel alone, which is several times slower. */
 typedef enum {
     WFA_SCHED_AUTO = 0,
     WFA_SCHED_PLAIN = 1,
@@ -130,7 +139,9 @@ typedef enum {
 typedef struct {
     int32_t schedule;       /* wfa_schedule                                      */
     int32_t window;         /* diagonals held per pair by the short kernel:
-                               16, 24, 32, 48, 64, 128, 256 */
+                               16, 24, 32, 48, 64, 128, 256; this or
+                               lanes_per_pair asks for the kernel with rows
+                               in LDS */
     int32_t step_cap;       /* score steps (in units of gcd(x,o,e)) held in LDS  */
     int32_t use_graph;      /* 1: the whole first pass (counters, packing,
                                bucketing, the short kernel, CIGAR offsets and
@@ -144,7 +155,9 @@ typedef struct {
     int32_t bucket;         /* 1: sort pairs by (length, length difference); -1: off;
                                0: where it pays, by the batch's size and lengths
                                and the kernel of the first pass */
-    int32_t general_pairs;  /* concurrent pairs of the general kernel; 0: by budget */
+    int32_t general_pairs;  /* concurrent pairs of the general kernel; 0: by budget
+                               (this and the other general_* options: long pairs
+                               on that kernel alone, see WFA_SCHED_GENERAL) */
     int32_t block_threads;  /* threads per workgroup of the short kernel: 64..256 */
     int32_t lanes_per_pair; /* lanes of a wavefront per pair in the short kernel
                                (8, 16, 32 or 64, at most the window): 64 / lanes
@@ -156,7 +169,8 @@ typedef struct {
                                  short-kernel passes, each over the pairs the
                                  previous pass handed over, with windows 64,
                                  128, 256 above the first; only what the last
-                                 pass hands over goes to the general kernel.
+                                 pass hands over goes to the kernels for long
+                                 pairs.
                                  0: up to 256; -1: no cascade */
     int32_t general_slice_kib; /* CIGAR mode: first guess of the history bytes
                                  (KiB) per pair of the general kernel; a pair
@@ -234,7 +248,7 @@ typedef struct {
 typedef struct {
     uint64_t pairs;              /* pairs aligned                                    */
     uint64_t short_pairs;        /* pairs finished by the short-pair kernel          */
-    uint64_t general_pairs;      /* pairs finished by the general kernel             */
+    uint64_t general_pairs;      /* pairs finished by the kernels for long pairs     */
     uint64_t requeued;           /* pairs re-run after exceeding a window, step or
                                     memory limit (results are unaffected)            */
     uint64_t cigar_runs;         /* total runs written                               */
@@ -315,7 +329,8 @@ int wfa_set_ends_free(wfa_ctx *ctx, const wfa_ends_free *ends);
  * Select the heuristic (wfa_heuristic) for later wfa_align_batch,
  * wfa_align_batch_noalloc and wfa_autotune calls on the context, and for
  * servers opened on it later; NULL or min_wavefront_length 0 selects exact
- * alignment.  Every pair then runs on the general kernel.  The heuristic
+ * alignment.  Every pair then runs on the kernels for long pairs (see
+ * WFA_SCHED_GENERAL).  The heuristic
  * applies to global alignment only: selecting it while free ends are set
  * (or free ends while it is selected), or a negative field, is
  * WFA_E_INVAL and changes nothing. */

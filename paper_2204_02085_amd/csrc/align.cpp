@@ -1,7 +1,8 @@
-// One batch in device memory: plan, pack, short-pair kernel (plain or
-// persistent, with optional bucketing and graph replay), general kernel for
-// whatever the short kernel hands over, CIGAR offsets and compaction.  Host
-// memory batches go through the chunk pipeline, which calls this per chunk.
+// One batch in device memory: plan, pack, a kernel for short pairs (lane, band or
+// short kernel; plain or persistent, with optional bucketing and graph replay),
+// wider passes over what it hands over, the kernels for long pairs (front,
+// adaptive, general) for the rest, CIGAR offsets and compaction.  Host memory
+// batches go through the chunk pipeline, which calls this per chunk.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -1052,8 +1053,8 @@ int engine_align_device(Engine* e, const BatchIO& io, hipStream_t user_stream,
         if ((uint32_t)window < 2 * reach + 16) window = 0;
     }
     ShortPlan sp;
-    // the WF-adaptive heuristic runs on the general kernel alone (the
-    // short-pair kernels are exact)
+    // the WF-adaptive heuristic: the kernels for long pairs alone (the short-pair
+    // kernels are exact)
     bool use_short = schedule != WFA_SCHED_GENERAL && window != 0 && max_len <= SHORT_MAX_LEN &&
                      e->heur.mwl == 0;
     int lanes = 0;
