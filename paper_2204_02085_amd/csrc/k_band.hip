@@ -1,7 +1,7 @@
 // Band kernel: short and middling pairs, a lane group per pair, wavefront rows
 // in registers (rows.h).
 //
-// A group of G = 8, 16, 32 or 64 lanes holds a band of W = 4 G diagonals, four
+// A group of G = 8, 16 or 32 lanes holds a band of W = 4 G diagonals, four
 // to a lane; 64 / G pairs share a wavefront and step through the scores
 // together.  Recurrences run on 16-bit pairs in registers, neighbours exchange
 // columns by DPP, only the sequences and (CIGAR) the decision records live in
@@ -62,7 +62,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5))) void k
     const int wpb = blockDim.x >> 6;
     const int grp = lane / G, gl = lane % G;
     const bool first = gl == 0, last = gl == G - 1;
-    const uint64_t gmask = (G == 64 ? ~0ull : ((1ull << (G & 63)) - 1)) << (grp * G);
+    const uint64_t gmask = ((1ull << G) - 1) << (grp * G);
 
     // per group: the text, the pattern, (CIGAR) the records
     lds_p<unsigned char> gb = (lds_p<unsigned char>)lds + (wave * GPW + grp) * a.group_bytes;
@@ -360,10 +360,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5))) void k
 // LDS bytes of one group: both sequences, the records of `cap` + 1 steps and a
 // spare quad of steps; an odd multiple of eight dwords, so that the groups of
 // a wavefront start at different banks
-int group_words(int G, int seq_words, int hist_words) {
+int group_words(int seq_words, int hist_words) {
     int w = 4 * seq_words + hist_words;
     w = (w + 7) & ~7;
-    if (G < 64 && !((w >> 3) & 1)) w += 8;
+    if (!((w >> 3) & 1)) w += 8;
     return w;
 }
 
@@ -423,7 +423,7 @@ bool band_plan(const Pen& pen, bool cigar, int window, int step_cap, uint32_t ma
     // an edit run and a match run per event, the match run and the free run at
     // either end
     bp->slot_cap = 2 * (bp->cap / (pen.x < pen.oe ? pen.x : pen.oe) + 1) + 2 + (ends ? 2 : 0);
-    bp->group_bytes = 4 * group_words(G, bp->seq_words, bp->hist_words);
+    bp->group_bytes = 4 * group_words(bp->seq_words, bp->hist_words);
     int bt = block_threads ? block_threads : 256;
     const int gpw = 64 / G;
     while (bt > 64 && (bt / 64) * gpw * bp->group_bytes + BAND_TAIL > 64 * 1024) bt -= 64;

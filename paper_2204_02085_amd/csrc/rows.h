@@ -95,13 +95,11 @@ __device__ __forceinline__ uint32_t wave_prev(uint32_t end, uint32_t x) {
 __device__ __forceinline__ uint32_t wave_next(uint32_t end, uint32_t x) {
     return (uint32_t)__builtin_amdgcn_update_dpp((int)end, (int)x, 0x130, 0xF, 0xF, false);
 }
-// the same within groups of G lanes (`first` / `last`: this lane is at the
+// the same within groups of G = 8, 16 or 32 lanes (`first` / `last`: this lane is at the
 // group's end); the group's end lane reads NULL
 template <int G>
 __device__ __forceinline__ uint32_t group_prev(uint32_t x, bool first) {
-    if constexpr (G == 64) {
-        return wave_prev(NUL16P, x);
-    } else if constexpr (G == 16) {
+    if constexpr (G == 16) {
         return (uint32_t)__builtin_amdgcn_update_dpp((int)NUL16P, (int)x, 0x111, 0xF, 0xF, false);
     } else if constexpr (G < 16) {
         const uint32_t y = (uint32_t)__builtin_amdgcn_update_dpp((int)NUL16P, (int)x, 0x111, 0xF, 0xF, false);
@@ -113,9 +111,7 @@ __device__ __forceinline__ uint32_t group_prev(uint32_t x, bool first) {
 }
 template <int G>
 __device__ __forceinline__ uint32_t group_next(uint32_t x, bool last) {
-    if constexpr (G == 64) {
-        return wave_next(NUL16P, x);
-    } else if constexpr (G == 16) {
+    if constexpr (G == 16) {
         return (uint32_t)__builtin_amdgcn_update_dpp((int)NUL16P, (int)x, 0x101, 0xF, 0xF, false);
     } else if constexpr (G < 16) {
         const uint32_t y = (uint32_t)__builtin_amdgcn_update_dpp((int)NUL16P, (int)x, 0x101, 0xF, 0xF, false);

@@ -89,6 +89,9 @@ namespace {
 // ring of (pre + 1) rows of n + m + 1 offsets (score only).  d = 6 %, the
 // middle of the 1-10 % the server is sized for; a pair that needs more is
 // still aligned exactly (the engine re-runs it with a larger arena slice).
+// That is the general kernel's need.  Short pairs and those of the kernels with
+// rows in registers take less (a 10 kbp pair at 6 % 2.5 MB of the 10 estimated),
+// so admission errs on the side of fewer pairs at once.
 size_t pair_bytes(const wfa_server_cfg& cfg, uint32_t n, uint32_t m) {
     const double x = cfg.pen.mismatch, o = cfg.pen.gap_open, e = cfg.pen.gap_extend;
     const double g = std::gcd(std::gcd(cfg.pen.mismatch, cfg.pen.gap_open), cfg.pen.gap_extend);
