@@ -526,10 +526,10 @@ int run_front(Engine* e, const Pen& pen, bool cigar, const Dev& d, std::vector<u
         hipStream_t q[2] = {s, s};
         if (parts) {
             q[0] = part ? s : side.q[0];
-            // the second stream of the second part: one of its own, or, when
-            // there are so many pairs that two streams stay full to the end, the
-            // first part's (10 k pairs 14.9 and 15.3 ms, 20 k 25.4 and 24.5)
-            q[1] = part && nf <= 48 * (size_t)e->num_cus ? side.q[1] : side.q[0];
+            // the second part's second stream is one of its own: behind the first
+            // part on that one's, 5 k pairs of 1-10 kbp took 8.6 ms against 7.1, 16 k
+            // 21.2 and 20.5, 20 k 24.4 and 24.4, 30 k 35.8 and 36.5
+            q[1] = part ? side.q[1] : side.q[0];
         }
         HIPCHK(hipMemcpyAsync(bounds.data() + from, dev_bounds + from, (to - from) * 4,
                               hipMemcpyDeviceToHost, q[0]));
