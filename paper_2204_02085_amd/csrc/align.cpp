@@ -526,10 +526,12 @@ int run_front(Engine* e, const Pen& pen, bool cigar, const Dev& d, std::vector<u
         hipStream_t q[2] = {s, s};
         if (parts) {
             q[0] = part ? s : side.q[0];
-            // the second part's second stream is one of its own: behind the first
-            // part on that one's, 5 k pairs of 1-10 kbp took 8.6 ms against 7.1, 16 k
-            // 21.2 and 20.5, 20 k 24.4 and 24.4, 30 k 35.8 and 36.5
-            q[1] = part ? side.q[1] : side.q[0];
+            // The second part's second stream: one of its own, or behind the first
+            // part, which overlaps less and ends with fewer launches side by side.
+            // Pairs of 1-10 kbp with CIGARs, own against shared: 2.5 k 4.2 and 5.1 ms,
+            // 5 k 7.1 and 8.6, 10 k 13.9 and 14.4, 16 k 20.5 and 21.2, 20 k 25.1 and
+            // 24.4, 30 k 36.5 and 35.8; of 2.5-4 kbp own is never slower.
+            q[1] = part && nf <= 64 * (size_t)e->num_cus ? side.q[1] : side.q[0];
         }
         HIPCHK(hipMemcpyAsync(bounds.data() + from, dev_bounds + from, (to - from) * 4,
                               hipMemcpyDeviceToHost, q[0]));
