@@ -1117,13 +1117,15 @@ int engine_align_device(Engine* e, const BatchIO& io, hipStream_t user_stream,
     BandPlan bp;
     if (use_short && !lane && !e->opt.window && !e->opt.lanes_per_pair) {
         int bw = band_window(max_len);
-        // A batch that leaves the chip idle (at most one wavefront per SIMD with
-        // the wider window) takes the window that saves it further passes, each
-        // a launch and a wait.  Pairs of 154-323 bp at 0-5 %: 64 pairs 104 us a
-        // call from 128 diagonals on, 250 from 32; 2 k of 100 bp at 4 % 73 and
-        // 77, 4 k 75 from 64 diagonals on, 87 from 128, 78 from 32, 8 k 84, 107
-        // and 82.
-        while (bw < 128 && N * (size_t)(2 * bw / 4) <= 256 * (size_t)e->num_cus) bw *= 2;
+        // A batch that leaves the chip idle takes the window that saves it further
+        // passes, each a launch and a wait: up to 400 bases the widest of which
+        // there is at most one wavefront per SIMD, beyond, where more pairs need
+        // it, two.  154-323 bp at 0-5 %: 64 pairs 104 us a call from 128 diagonals
+        // on, 250 from 32; 2 k of 100 bp at 4 % 73 and 77, 4 k 75 from 64 diagonals
+        // on, 87 from 128, 78 from 32, 8 k 84, 107 and 82.  1200-2400 bp at 0-1 %,
+        // score only: 100 pairs 91 us from 256 on, 253 from 128, 2 k 107 and 208.
+        const int widest = max_len <= 400 ? 128 : 256, waves = max_len <= 400 ? 4 : 8;
+        while (bw < widest && N * (size_t)(2 * bw / 4) <= 64 * waves * (size_t)e->num_cus) bw *= 2;
         if (!global) {
             const uint32_t reach = std::max(
                 std::max(std::min<uint32_t>((uint32_t)e->ends.pb, st.max_p),

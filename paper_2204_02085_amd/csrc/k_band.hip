@@ -1,7 +1,7 @@
 // Band kernel: short and middling pairs, a lane group per pair, wavefront rows
 // in registers (rows.h).
 //
-// A group of G = 8, 16 or 32 lanes holds a band of W = 4 G diagonals, four
+// A group of G = 8, 16, 32 or 64 lanes holds a band of W = 4 G diagonals, four
 // to a lane; 64 / G pairs share a wavefront and step through the scores
 // together.  Recurrences run on 16-bit pairs in registers, neighbours exchange
 // columns by DPP, only the sequences and (CIGAR) the decision records live in
@@ -25,10 +25,16 @@
 // some spills outside the steps) beat four (118) by 2 to 3 %.  One loop for
 // every lane's longer compares instead of one per column: 25 % slower.
 //
-// CIGAR: the forward pass keeps four record bits per cell.  The group's first
-// lane walks them back to the list of edits, then replays the edits from the
-// start: after each edit the alignment runs along matches exactly as the
-// forward pass extended, so no offset is stored.
+// Where few pairs are in flight, the chain of a pair sets the time, for long matches
+// that of their compares: forward 32 bases a trip after the first 31, in the replay
+// the whole group's lanes, 32 bases each.  100 pairs of 600-1200 bp at 0-1 % took
+// 105 us in the kernel with 16 bases a trip and the replay by one lane, now 40; 1 M
+// pairs with 10 free bases 0.81 ms either way, the uneven pairs 3.47 ms a call (3.65).
+//
+// CIGAR: the forward pass keeps four record bits per cell.  The group walks them
+// back to the list of edits, then replays the edits from the start: after each edit
+// the alignment runs along matches exactly as the forward pass extended, so no
+// offset is stored.
 #include <hip/hip_runtime.h>
 #include <limits.h>
 #include <stdint.h>
@@ -62,7 +68,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5))) void k
     const int wpb = blockDim.x >> 6;
     const int grp = lane / G, gl = lane % G;
     const bool first = gl == 0, last = gl == G - 1;
-    const uint64_t gmask = ((1ull << G) - 1) << (grp * G);
+    const uint64_t gmask = (~0ull >> (64 - G)) << (grp * G);
 
     // per group: the text, the pattern, (CIGAR) the records
     lds_p<unsigned char> gb = (lds_p<unsigned char>)lds + (wave * GPW + grp) * a.group_bytes;
@@ -193,7 +199,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5))) void k
                         ci[p] = cd[p] = NUL16P;
                     }
                 }
-                extend<C, 1>(cm, pl, tb, pb);
+                extend<C, 1, true>(cm, pl, tb, pb);
                 row.push(cm, ci, cd);
                 // a cell at its end diagonal's limit ends its pair
                 uint32_t z = cm[0] ^ tg[0];
@@ -235,10 +241,11 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5))) void k
 
         bool overflow = active && S < 0;
         int cnt = 0;
-        if (CIGAR && active && !overflow && first) {
+        if (CIGAR && active && !overflow) {
             // walk: the edits from the end back to step 0, from the top of the
             // group's records down (the walk has consumed at least as many
-            // steps as it has written words, and reads only below)
+            // steps as it has written words, and reads only below); every lane of
+            // the group takes it alike, and stores the same words
             const int top = a.hist_words;
             int ws = S, k = kmin + ecol, ne = 0;
             bool bad = ecol >= W;
@@ -271,10 +278,11 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5))) void k
                 if (!bad) HI[top - 1 - ne] = (uint32_t)(len << 2 | kind);
                 ne++;
             }
+            wave_fence();
             // replay: from the start along matches, edit by edit; runs go to
-            // the front of the records, in alignment order.  Only an eighth of
-            // the lanes is here, so every instruction counts: 32 bases a compare,
-            // stores without branches (a store past the last run is overwritten).
+            // the front of the records, in alignment order.  32 bases a compare,
+            // stores without branches (a store past the last run is overwritten);
+            // a longer match is followed by the group, 32 bases to a lane.
             int h = max(k, 0), v = h - k;
             int nr = 0, last_op = -1;  // -1: a match run, or none
             uint32_t cur = 0;          // the last edit run
@@ -285,6 +293,13 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5))) void k
                 HI[nr - 1] = cur;
                 last_op = op;
             };
+            // matching bases from o on, at most 32
+            auto match32 = [&](int o) -> int {
+                const uint32_t x0 = win16(tb, 2 * (h + o)) ^ win16(pb, 2 * (v + o));
+                const uint32_t x1 = win16(tb, 2 * (h + o) + 32) ^ win16(pb, 2 * (v + o) + 32);
+                const uint64_t x = ((uint64_t)x1 << 32) | x0;
+                return x ? (int)(__builtin_ctzll(x) >> 1) : 32;
+            };
             if (!bad) {
                 if (ENDS) {
                     if (k > 0) edit(2, k);
@@ -293,13 +308,13 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5))) void k
                 for (int e2 = ne;; e2--) {
                     // matches from (v, h) on
                     const int left = min(n - v, m - h);
-                    int mm = 0;
-                    for (;;) {
-                        const uint32_t x0 = win16(tb, 2 * (h + mm)) ^ win16(pb, 2 * (v + mm));
-                        const uint32_t x1 = win16(tb, 2 * (h + mm) + 32) ^ win16(pb, 2 * (v + mm) + 32);
-                        const uint64_t x = ((uint64_t)x1 << 32) | x0;
-                        mm += x ? (int)(__builtin_ctzll(x) >> 1) : 32;
-                        if (x || mm >= left) break;
+                    int mm = match32(0);
+                    for (bool on = mm == 32 && left > 32; on;) {
+                        const int z = mm + 32 * gl < left ? match32(mm + 32 * gl) : 0;
+                        const uint64_t stop = lanes_where(z < 32) & gmask;
+                        on = stop == 0;
+                        const int l = on ? lane : (int)__builtin_ctzll(stop);
+                        mm += on ? 32 * G : 32 * (l - grp * G) + __shfl(z, l);
                     }
                     mm = min(mm, left);
                     HI[nr] = (uint32_t)mm << 4;
@@ -328,11 +343,11 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5))) void k
             if (bad || nr > a.slot_cap) overflow = true;
             cnt = nr;
         }
+        if (overflow) cnt = 0;
         if (active && first) {
             if (overflow) {
                 const uint32_t at = atomicAdd(a.ovf_count, 1u);
                 a.ovf_list[at] = pair;
-                cnt = 0;
             } else {
                 a.scores[pair] = S * a.g;
                 a.nruns[pair] = (uint32_t)cnt;
@@ -397,7 +412,8 @@ struct BandShape {
     F(2, 4, 1, G)           \
     F(1, 1, 1, G)           \
     F(2, 5, 1, G)
-#define WFA_BAND_SHAPES(F) WFA_BAND_PENS(F, 8) WFA_BAND_PENS(F, 16) WFA_BAND_PENS(F, 32)
+#define WFA_BAND_SHAPES(F) \
+    WFA_BAND_PENS(F, 8) WFA_BAND_PENS(F, 16) WFA_BAND_PENS(F, 32) WFA_BAND_PENS(F, 64)
 
 }  // namespace
 

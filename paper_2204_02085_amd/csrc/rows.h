@@ -95,11 +95,13 @@ __device__ __forceinline__ uint32_t wave_prev(uint32_t end, uint32_t x) {
 __device__ __forceinline__ uint32_t wave_next(uint32_t end, uint32_t x) {
     return (uint32_t)__builtin_amdgcn_update_dpp((int)end, (int)x, 0x130, 0xF, 0xF, false);
 }
-// the same within groups of G = 8, 16 or 32 lanes (`first` / `last`: this lane is at the
+// the same within groups of G = 8, 16, 32 or 64 lanes (`first` / `last`: this lane is at the
 // group's end); the group's end lane reads NULL
 template <int G>
 __device__ __forceinline__ uint32_t group_prev(uint32_t x, bool first) {
-    if constexpr (G == 16) {
+    if constexpr (G == 64) {
+        return wave_prev(NUL16P, x);
+    } else if constexpr (G == 16) {
         return (uint32_t)__builtin_amdgcn_update_dpp((int)NUL16P, (int)x, 0x111, 0xF, 0xF, false);
     } else if constexpr (G < 16) {
         const uint32_t y = (uint32_t)__builtin_amdgcn_update_dpp((int)NUL16P, (int)x, 0x111, 0xF, 0xF, false);
@@ -111,7 +113,9 @@ __device__ __forceinline__ uint32_t group_prev(uint32_t x, bool first) {
 }
 template <int G>
 __device__ __forceinline__ uint32_t group_next(uint32_t x, bool last) {
-    if constexpr (G == 16) {
+    if constexpr (G == 64) {
+        return wave_next(NUL16P, x);
+    } else if constexpr (G == 16) {
         return (uint32_t)__builtin_amdgcn_update_dpp((int)NUL16P, (int)x, 0x101, 0xF, 0xF, false);
     } else if constexpr (G < 16) {
         const uint32_t y = (uint32_t)__builtin_amdgcn_update_dpp((int)NUL16P, (int)x, 0x101, 0xF, 0xF, false);
@@ -238,12 +242,35 @@ __device__ __forceinline__ uint32_t win16(uint32_t base, int b) {
     return __builtin_amdgcn_alignbit(w1, w0, (uint32_t)b);
 }
 
+// Bits (two a base; an odd count: with one of a mismatch) that match from bit positions
+// h and v on, at most 64.
+__device__ __forceinline__ uint32_t match_bits(uint32_t tb, uint32_t pb, uint32_t h, uint32_t v) {
+    lds_p<const uint32_t> t = (lds_p<const uint32_t>)(uintptr_t)(tb + ((h >> 5) << 2));
+    lds_p<const uint32_t> p = (lds_p<const uint32_t>)(uintptr_t)(pb + ((v >> 5) << 2));
+    uint32_t a[3], b[3], n = 64;
+#pragma unroll
+    for (int i = 0; i < 3; i++) {
+        a[i] = t[i];
+        b[i] = p[i];
+    }
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int i = 0; i < 2; i++) {
+        const uint32_t y = __builtin_amdgcn_alignbit(a[i + 1], a[i], h) ^ __builtin_amdgcn_alignbit(b[i + 1], b[i], v);
+        uint32_t z;
+        asm("v_ffbl_b32 %0, %1" : "=v"(z) : "v"(y));  // ~0 for a zero word: the sum saturates
+        n = min(n, __builtin_elementwise_add_sat(z, 32u * i));
+    }
+    return n;
+}
+
 // Extend the cells m of one step along matches (sequences in LDS at byte
 // addresses tb, pb) and drop those past the matrix.  Fifteen bases first (a stop
 // bit in place of the sixteenth bounds the count); a wavefront goes on only while
 // one of its lanes still matches.  What runs past the matrix is cut off by one
-// packed minimum at the end.
-template <int C, int SH>
+// packed minimum at the end.  LONG: after 31 bases 32 at a time, for kernels in
+// which few wavefronts hide the chain of a long match.
+template <int C, int SH, bool LONG = false>
 __device__ __forceinline__ void extend(uint32_t (&m)[C / 2], const Place<C>& pl, uint32_t tb,
                                        uint32_t pb) {
     constexpr int P = C / 2;
@@ -293,7 +320,15 @@ __device__ __forceinline__ void extend(uint32_t (&m)[C / 2], const Place<C>& pl,
                     const uint32_t y = win16(tb, h + (int)done) ^ win16(pb, v[c] + (int)done);
                     asm("v_ffbl_b32 %0, %1" : "=v"(z) : "v"(y));  // ~0 for a zero word
                     done += min(z, 32u);
-                } while (z >= 32 && done < end);
+                } while (!LONG && z >= 32 && done < end);
+                if constexpr (LONG) {
+                    bool on = z >= 32 && done < end;
+                    while (on) {
+                        z = match_bits(tb, pb, (uint32_t)h + done, (uint32_t)v[c] + done);
+                        done += z;
+                        on = z >= 64 && done < end;
+                    }
+                }
                 r[c] = done;
             }
         }
