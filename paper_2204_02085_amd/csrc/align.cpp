@@ -1124,7 +1124,7 @@ int engine_align_device(Engine* e, const BatchIO& io, hipStream_t user_stream,
         // on, 250 from 32; 2 k of 100 bp at 4 % 73 and 77, 4 k 75 from 64 diagonals
         // on, 87 from 128, 78 from 32, 8 k 84, 107 and 82.  1200-2400 bp at 0-1 %,
         // score only: 100 pairs 91 us from 256 on, 253 from 128, 2 k 107 and 208.
-        const int widest = max_len <= 400 ? 128 : 256, waves = max_len <= 400 ? 4 : 8;
+        const int widest = max_len <= 400 || e->opt.step_cap ? 128 : 256, waves = max_len <= 400 ? 4 : 8;
         while (bw < widest && N * (size_t)(2 * bw / 4) <= 64 * waves * (size_t)e->num_cus) bw *= 2;
         if (!global) {
             const uint32_t reach = std::max(
@@ -1556,9 +1556,11 @@ int engine_align_device(Engine* e, const BatchIO& io, hipStream_t user_stream,
             requeued += n_out;
             return WFA_OK;
         };
-        // the cascade's windows: 64, 128, 256 above the first window
+        // the cascade's windows: 64, 128, 256 above the first window (from it on
+        // where the caller's step cap, not the band, ended a pair)
+        const bool capped = band && bp.cap == e->opt.step_cap;
         for (int w2 = 64; w2 <= wmax && ovf_final > 0; w2 *= 2) {
-            if (w2 <= window) continue;
+            if (w2 < window || (w2 == window && !capped)) continue;
             const uint32_t n2 = ovf_final;
             BandPlan bp2;
             const bool shaped = e->opt.window || e->opt.lanes_per_pair;

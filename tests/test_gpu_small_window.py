@@ -47,3 +47,18 @@ def test_ends_free(aligner, oracle_lib, synth_lib):
     got = aligner.align(b, (4, 6, 2), capacity=int(ref.offsets[-1]) + 8)
     assert aligner.stats()["window"] == 128
     assert_same(got, ref, b, "free ends")
+
+
+@pytest.mark.parametrize("cap", [8, 30, 90])
+def test_step_cap(aligner, oracle_lib, synth_lib, cap):
+    """What a step cap hands over is held by the same window without it: no pair goes
+    on to the kernels for long pairs."""
+    b = synth_lib.generate(synth_lib.uneven(154, 323, 0.0, 0.05), 78, 1000)
+    say(f"case: small batch, step cap {cap}")
+    ref = oracle_lib.align_batch(b, (4, 6, 2), cigar=True, threads=8)
+    aligner.set_options(step_cap=cap)
+    got = aligner.align(b, (4, 6, 2), capacity=int(ref.offsets[-1]) + 8)
+    st = aligner.stats()
+    assert st["window"] == 128 and st["step_cap"] == cap and st["general_pairs"] == 0
+    assert (st["requeued"] > 0) == (cap <= 30)
+    assert_same(got, ref, b, f"cap {cap}")
