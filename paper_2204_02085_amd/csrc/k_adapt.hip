@@ -63,6 +63,7 @@ __global__ __launch_bounds__(64) void k_adapt(FrontArgs a) {
     constexpr bool HEAD = CIGAR || AW / 4 > 64;
     static_assert(AW / 4 <= 64 + 4 * WALK_DW, "compares stay in the workgroup's LDS");
     constexpr int RM = X > OE ? X : OE;
+    constexpr int LONG = NB > ADAPT_BLOCKS ? LONG_LANE : LONG_WAVE;  // (no registers left for the other)
     constexpr uint32_t ONE = SH ? 0x00020002u : 0x00010001u;
     extern __shared__ __align__(16) unsigned char lds[];
     const FrontJob job = a.jobs[blockIdx.x];
@@ -143,7 +144,7 @@ __global__ __launch_bounds__(64) void k_adapt(FrontArgs a) {
                 l = h = 0;
                 if (lane == 32) cm[0] = 0xC0000000u;  // M_0[0] = 0
                 uint32_t c1[1] = {cm[0]};
-                extend<2, SH>(c1, pl[0], tb, pb);
+                extend<2, SH, LONG>(c1, pl[0], tb, pb);
                 cm[0] = c1[0];
             } else if (present) {
 #pragma unroll
@@ -173,7 +174,7 @@ __global__ __launch_bounds__(64) void k_adapt(FrontArgs a) {
                     ci[b] = bit_select(pk_sign(ci[b] | ti | ~inside[b]), NUL16P, ci[b]);
                     cd[b] = bit_select(pk_sign(cd[b] | td | ~inside[b]), NUL16P, cd[b]);
                     uint32_t c1[1] = {bit_select(inside[b], pk_sub(L, tm), NUL16P)};
-                    extend<2, SH>(c1, pl[b], tb, pb);
+                    extend<2, SH, LONG>(c1, pl[b], tb, pb);
                     cm[b] = c1[0];
                 }
             }

@@ -199,7 +199,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5))) void k
                         ci[p] = cd[p] = NUL16P;
                     }
                 }
-                extend<C, 1, true>(cm, pl, tb, pb);
+                extend<C, 1, LONG_LANE>(cm, pl, tb, pb);
                 row.push(cm, ci, cd);
                 // a cell at its end diagonal's limit ends its pair
                 uint32_t z = cm[0] ^ tg[0];

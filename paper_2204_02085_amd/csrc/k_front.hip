@@ -119,7 +119,7 @@ __global__ __launch_bounds__(128) void k_bound(FrontArgs a) {
                 cm[0] = lane == 32 ? 0xC0000000u : NUL16P;  // M_0[0] = 0
                 ci[0] = cd[0] = NUL16P;
             }
-            extend<C, SH>(cm, pl, tb, pb);
+            extend<C, SH, LONG_WAVE>(cm, pl, tb, pb);
             row.push(cm, ci, cd);
             mq[u] = cm[0];
         }
@@ -290,7 +290,8 @@ void k_front(FrontArgs a) {
                 ci[p] = cd[p] = NUL16P;
             }
         }
-        extend<C, SH>(cm, q.pl, tb, pb);
+        // (two blocks with events, or of four columns a lane, have no registers for the other)
+        extend<C, SH, NB == 1 || (C == 2 && !CIGAR) ? LONG_WAVE : LONG_LANE>(cm, q.pl, tb, pb);
         q.row.push(cm, ci, cd);
         q.row.sources(q.sa, q.sb);
         if (edge) q.xout[((u + 1) & 1) * xb] = lane == 63 ? q.sa[P - 1] : q.sb[0];

@@ -268,9 +268,14 @@ __device__ __forceinline__ uint32_t match_bits(uint32_t tb, uint32_t pb, uint32_
 // addresses tb, pb) and drop those past the matrix.  Fifteen bases first (a stop
 // bit in place of the sixteenth bounds the count); a wavefront goes on only while
 // one of its lanes still matches.  What runs past the matrix is cut off by one
-// packed minimum at the end.  LONG: after 31 bases 32 at a time, for kernels in
-// which few wavefronts hide the chain of a long match.
-template <int C, int SH, bool LONG = false>
+// packed minimum at the end.  Past 31 bases a lane takes 32 at a time, some 400
+// cycles of LDS latency and a short chain.  With LONG_WAVE a match of 255 bases or
+// more (one or two lanes a step have one) is handed to the wavefront, which takes
+// 1024 in that time: 600 reads of 8 to 20 kbp at up to 0.05 % divergence, score
+// only, 345 us (899 without it, 1325 at 16 bases a trip).  It pays where a pair has
+// the wavefront to itself; from 64 bases on it cost 1 % of 5 % divergent reads.
+enum { LONG_LANE, LONG_WAVE };
+template <int C, int SH, int LONG>
 __device__ __forceinline__ void extend(uint32_t (&m)[C / 2], const Place<C>& pl, uint32_t tb,
                                        uint32_t pb) {
     constexpr int P = C / 2;
@@ -309,27 +314,57 @@ __device__ __forceinline__ void extend(uint32_t (&m)[C / 2], const Place<C>& pl,
         lo = min(lo, x[c]);
     }
     if (lanes_where(lo == STOP)) {
+        auto to_end = [&](int c) -> uint32_t {  // bits from column c to the matrix' edge
+            const uint32_t left = pk_sub(pl.lim[c / 2], hv[c / 2]) & ~bad[c / 2];
+            return ((c & 1) ? left >> 16 : left & 0xffffu) << (1 - SH);
+        };
+        constexpr int TRIPS = 7;
+        constexpr uint32_t FAR = 62 + 64 * TRIPS;
+        uint32_t longest = 0;
 #pragma unroll
         for (int c = 0; c < C; c++) {
-            const uint32_t left = pk_sub(pl.lim[c / 2], hv[c / 2]) & ~bad[c / 2];
-            const uint32_t end = ((c & 1) ? left >> 16 : left & 0xffffu) << (1 - SH);
+            const uint32_t end = to_end(c);
             if (x[c] == STOP && end > 30) {
                 const int h = (int)pos(c);
                 uint32_t done = 30, z;
-                do {
-                    const uint32_t y = win16(tb, h + (int)done) ^ win16(pb, v[c] + (int)done);
-                    asm("v_ffbl_b32 %0, %1" : "=v"(z) : "v"(y));  // ~0 for a zero word
-                    done += min(z, 32u);
-                } while (!LONG && z >= 32 && done < end);
-                if constexpr (LONG) {
-                    bool on = z >= 32 && done < end;
-                    while (on) {
-                        z = match_bits(tb, pb, (uint32_t)h + done, (uint32_t)v[c] + done);
-                        done += z;
-                        on = z >= 64 && done < end;
-                    }
+                const uint32_t y = win16(tb, h + (int)done) ^ win16(pb, v[c] + (int)done);
+                asm("v_ffbl_b32 %0, %1" : "=v"(z) : "v"(y));  // ~0 for a zero word
+                done += min(z, 32u);
+                int trips = TRIPS;
+                for (bool on = z >= 32 && done < end; on; on = z >= 64 && done < end) {
+                    if (LONG == LONG_WAVE && !trips--) break;
+                    z = match_bits(tb, pb, (uint32_t)h + done, (uint32_t)v[c] + done);
+                    done += z;
                 }
                 r[c] = done;
+            }
+            longest = max(longest, r[c]);
+        }
+        if (LONG == LONG_WAVE && lanes_where(longest >= FAR)) {
+            const uint32_t lane = __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));
+#pragma unroll
+            for (int c = 0; c < C; c++) {
+                const uint32_t end = to_end(c);
+                for (uint64_t far = lanes_where(x[c] == STOP && r[c] >= FAR && r[c] < end); far; far &= far - 1) {
+                    const int l = __builtin_ctzll(far);
+                    const int hl = __builtin_amdgcn_readlane((int)pos(c) + (int)r[c], l);
+                    const int vl = __builtin_amdgcn_readlane(v[c] + (int)r[c], l);
+                    const uint32_t el = (uint32_t)__builtin_amdgcn_readlane((int)(end - r[c]), l);
+                    uint32_t sum = 0;
+                    for (;;) {
+                        const uint32_t o = sum + 32 * lane;
+                        uint32_t y = 1;
+                        if (o < el) y = win16(tb, hl + (int)o) ^ win16(pb, vl + (int)o);
+                        const uint64_t stop = lanes_where(y != 0);
+                        if (stop) {
+                            const int f = __builtin_ctzll(stop);
+                            sum += 32 * f + __builtin_ctz((uint32_t)__builtin_amdgcn_readlane((int)y, f));
+                            break;
+                        }
+                        sum += 64 * 32;
+                    }
+                    if (lane == (uint32_t)l) r[c] += sum;
+                }
             }
         }
     }
