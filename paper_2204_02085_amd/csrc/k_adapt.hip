@@ -8,7 +8,7 @@
 // step here is about 130 instructions of one wavefront, the least distance by DPP
 // and the kept range by two ballots.
 //
-// What bounds it: VALU issue, 0.75 of it over 10 k pairs of 1-10 kbp at 5-10 %
+// What bounds it: VALU issue, 0.91 of it over 10 k pairs of 1-10 kbp at 5-10 %
 // under the thresholds (10, 50), whole call with CIGARs 3.6 ms (32.0 ms on the
 // general kernel).  The second block inside the same kernel: 22 of those
 // pairs outgrow 128 diagonals for a stretch, and aligning them again in a wider

@@ -18,8 +18,8 @@
 // What bounds it: VALU issue (all of the issue slots on 1 M pairs of 100 bp with 10
 // free bases at each end; about 100 instructions per step and wavefront plus the
 // longer compares).  Measured, kernel alone: those pairs with CIGARs
-// 0.81 ms, where the lane groups with rows in LDS (k_short, window 64) took
-// 2.50 ms; 2 M pairs of 50-300 bp at 0-5 % 2.83 + 0.57 + 0.07 ms over windows
+// 0.82 ms, where the lane groups with rows in LDS (k_short, window 64) took
+// 2.50 ms; 2 M pairs of 50-300 bp at 0-5 % 2.67 + 0.56 + 0.06 ms over windows
 // 32, 64 and 128 against 8.62 + 3.77 ms over 64 and 128; 300 k pairs of 150 bp
 // under (1, 0, 1) 0.19 ms against 0.47.  Five wavefronts per SIMD (96 VGPRs,
 // some spills outside the steps) beat four (118) by 2 to 3 %.  One loop for
@@ -29,7 +29,7 @@
 // that of their compares: forward 32 bases a trip after the first 31, in the replay
 // the whole group's lanes, 32 bases each.  100 pairs of 600-1200 bp at 0-1 % took
 // 105 us in the kernel with 16 bases a trip and the replay by one lane, now 40; 1 M
-// pairs with 10 free bases 0.81 ms either way, the uneven pairs 3.47 ms a call (3.65).
+// pairs with 10 free bases 0.82 ms either way, the uneven pairs 3.47 ms a call (3.65).
 //
 // CIGAR: the forward pass keeps four record bits per cell.  The group walks them
 // back to the list of edits, then replays the edits from the start: after each edit

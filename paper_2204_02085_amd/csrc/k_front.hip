@@ -24,8 +24,8 @@
 // 128 diagonals, 0.65 to 0.76 of the issue slots in launches that fill the chip.
 // Measured on whole calls against the general kernel, whose rows cross L2 and
 // HBM and fill the whole triangle: 20 k pairs of 1-10 kbp at 5-10 % with CIGARs
-// 24.1 ms (107.5), 5 k of them score-only 5.4 ms (25.0), 24 pairs of 10-20 kbp
-// 8.4 ms (66.4).  k_bound takes 2 ms for the 20 k pairs, most of it beside the
+// 24.4 ms (107.5), 5 k of them score-only 5.4 ms (25.0), 24 pairs of 10-20 kbp
+// 7.9 to 8.3 ms (66.4).  k_bound takes 2 ms for the 20 k pairs, most of it beside the
 // first alignments (from one end only, by one wavefront, the chain of a pair took
 // twice as long: 5 k pairs score-only 5.8 ms, the 24 pairs 9.1 ms).
 // Columns exchanged every four steps instead, with four columns computed twice on
